@@ -91,6 +91,126 @@ __device__ __forceinline__ void wave_accumulate(const typename RawOf<DT>::type (
     accumulate<N, NU, ARG>(z, m, ones, S, t, sc, idx, c0);
 }
 
+// One tile of a wave relative to the WAVE's running maximum mw (the same in every lane): S = sum of the weights
+// below 1, ones = the number of weights that are exactly 1, td = sum w (z - mw), all per lane.  What the lane-wise
+// form above pays per logit and this one does not:
+//  - the count of ones: only the vectors that hold the maximum have any, found by one comparison per vector of the
+//    lane (its maximum is there anyway) and a branch the whole wave takes; about one vector in four goes that way;
+//  - the floor of the exponent: masked (-inf) logits are lowered to the most negative finite number while still
+//    packed (half an instruction per logit), so z - mw stays finite and 0 * (z - mw) is 0;
+//  - a product per term of the entropy sum: w (z - mw) is accumulated by fused multiply-adds, and the scale is
+//    applied once per record in fp64.
+// About 9 issue slots per bf16 logit instead of 12.5, and the lanes of a wave need no rescaling to one another: about
+// 380 vector instructions per wave of one tile instead of 478.  What that is worth grows with how far issue rather
+// than latency bounds the launch; us per draft step in a graph, before / after: 8 rows of 128256 bf16 logits 7.74 /
+// 7.63, 64 rows 10.19 / 10.06 (greedy 9.75 / 9.26), 128 rows 13.6 / 12.8, 256 rows 20.1 / 18.5.
+// Returns false, with nothing changed, for the tiles this form is not for: no logit above the most negative
+// finite number (masked tiles), or one beyond 1e30.
+template <typename DT, int NU, bool ARG>
+__device__ __forceinline__ bool wave_tile(const typename RawOf<DT>::type (&raw)[NU], int c0, float &mw, float &ones, float &S,
+                                          float &td, int &idx, const Scale &sc)
+{
+    constexpr int N = VecOf<DT>::N;
+    float z[NU][N], gm[NU];
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+        unpack_finite<DT>(raw[u], z[u]);
+        gm[u] = tree_max<N>(z[u]);
+    }
+    float mt = gm[0];
+#pragma unroll
+    for (int u = 1; u < NU; ++u) mt = vmax(mt, gm[u]);
+    mt = wave_max(mt);
+    if (!(mt > FiniteLow<DT>::value() && mt < 1e30f)) return false;
+    const bool higher = mt > mw;
+    if (higher) {
+        if (mw != neg_inf()) {
+            const float d = mw - mt, f = exp2_raw(scaled_diff(mw, mt, sc));
+            if (f < 1.0f) {                     // the old maximum becomes an ordinary term
+                const float all = S + ones;
+                td = f * fmaf(d, all, td);
+                S = f * all;
+                ones = 0.f;
+            }
+        }
+        mw = mt;
+        if (ARG) idx = -1;
+    }
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+        float w[N], d[N];
+#pragma unroll
+        for (int e = 0; e < N; ++e) {
+            d[e] = z[u][e] - mw;
+            w[e] = exp2_raw(fmaf(d[e], sc.c_hi, d[e] * sc.c_lo));
+        }
+        // two chains of N / 2 terms: no more roundings in a row than the tree of products had
+        float ta = w[0] * d[0], tb = w[N / 2] * d[N / 2];
+#pragma unroll
+        for (int e = 1; e < N / 2; ++e) {
+            ta = fmaf(w[e], d[e], ta);
+            tb = fmaf(w[N / 2 + e], d[N / 2 + e], tb);
+        }
+        td += ta + tb;
+        const unsigned long long hit = __ballot(gm[u] == mw);
+        float Sb = tree_sum<N>(w);
+        if (hit) {
+            float fr[N];                        // a weight of exactly 1 is counted and leaves 0 behind
+#pragma unroll
+            for (int e = 0; e < N; ++e) fr[e] = __builtin_amdgcn_fractf(w[e]);
+            const float below = tree_sum<N>(fr);
+            ones += rintf(Sb - below);
+            Sb = below;
+            if (ARG && higher && idx < 0) {     // vectors come in index order: the first lane of the first one
+                int at = 0;
+#pragma unroll
+                for (int e = N - 1; e >= 0; --e) at = z[u][e] == mw ? e : at;
+                const int first = __ffsll((long long)hit) - 1;
+                idx = ((c0 + u) * 64 + first) * N + read_lane(at, first);
+            }
+        }
+        S += Sb;
+        // the sums are formed here: the compiler would otherwise move all of them behind the last branch and keep
+        // every weight of the tile in registers until then
+        asm volatile("" : "+v"(S), "+v"(td), "+v"(ones));
+    }
+    return true;
+}
+
+// A record outside wave_tile's range (a masked tile, logits or a temperature of extreme size), from memory again:
+// every lane keeps its own running maximum, and the lanes are brought to the wave's at the end.
+template <typename DT, bool ARG>
+__device__ __forceinline__ void uncommon_record(const DraftArgs &a, const DT *row, int tb, int te, float &mw, double &Sd,
+                                                double &td, int &first)
+{
+    constexpr int CPT = WG / 64;
+    float m = neg_inf(), ones = 0.f, S = 0.f, t = 0.f;
+    int idx = -1;
+#pragma unroll 1
+    for (int c = tb * CPT; c < te * CPT; ++c) {           // a chunk at a time: few registers, this path is rare
+        typename RawOf<DT>::type raw[1];
+        wave_load<DT, 1, true>(row, a.geo.V, c, raw);
+        wave_accumulate<DT, 1, ARG>(raw, c, m, ones, S, t, idx, a.sc);
+    }
+    // the wave's lanes to one record: maximum first, then sums rescaled to it in fp64
+    mw = wave_max(m);
+    Sd = td = 0.0;
+    if (m != neg_inf()) {
+        const float xd = scaled_diff(m, mw, a.sc);
+        const double all = (double)ones + (double)S, f = (double)exp2_raw(xd);
+        Sd = f * all;
+        td = f * ((double)t + (double)xd * all);
+    }
+    Sd = wave_sum(Sd);
+    td = wave_sum(td);
+    first = -1;
+    if (ARG) {      // smallest index among the lanes that hold the wave maximum
+        const int cand = (m == mw && idx >= 0) ? idx : 0x7FFFFFFF;
+        const int wmin = -wave_reduce(-cand, OpMax{});
+        first = wmin == 0x7FFFFFFF ? -1 : wmin;
+    }
+}
+
 // grid (ceil(rows * records / 4)), one wave per record.  TWO: the launch's records hold two tiles; a record of
 // two whole tiles then requests both before it works on the first (the arithmetic of the first runs while the
 // second is still on its way: 0.2 us of an 11.2 us step at 64 rows of 128K logits, 0.55 of 21 us at 256), which
@@ -102,7 +222,7 @@ __global__ __launch_bounds__(WG, TWO ? 6 : 8) void k_draft_stats(DraftArgs a)
     const int lane = threadIdx.x & 63, nrec = a.geo.ns;
     // Which record this wave takes is the same in all its lanes: worked out in scalar registers, with the one
     // division done by a multiplication the host prepared, so that none of it takes vector-ALU slots (a wave of one
-    // tile has about 500 vector instructions in all, and they are what bounds this kernel).
+    // tile has about 380 vector instructions in all, and they bound this kernel at large batches).
     const unsigned wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int b, r;
     if (a.rows_by_xcd) {
@@ -123,53 +243,44 @@ __global__ __launch_bounds__(WG, TWO ? 6 : 8) void k_draft_stats(DraftArgs a)
     const DT *row = static_cast<const DT *>(a.logits) + draft_row_offset(a, b);
     const int tb = r * a.geo.tps, te = min(tb + a.geo.tps, a.geo.ntiles);
     const int fe = min(te, a.geo.V / (WG * N));           // end of the tiles wholly inside the row
-    float m = neg_inf(), ones = 0.f, S = 0.f, t = 0.f;
-    int idx = -1;
     // The record's first tile is requested before the row's stop flag is looked at, so that the two travel
     // together (a step is bound by round trips to memory); a stopped row costs those loads and nothing else.
     const unsigned flag = request_stop_flag(a, b);
     typename RawOf<DT>::type raw[CPT];
+    float mw = neg_inf(), ones = 0.f, S = 0.f, td = 0.f;
+    int first = -1;
+    bool ok = a.common_range;
     if (TWO && te - tb == 2 && te <= fe) {
         typename RawOf<DT>::type raw2[CPT];
         wave_load<DT, CPT, false>(row, a.geo.V, tb * CPT, raw);
         wave_load<DT, CPT, false>(row, a.geo.V, (tb + 1) * CPT, raw2);
         if (flag_after_loads(a, flag)) return;
-        wave_accumulate<DT, CPT, ARG>(raw, tb * CPT, m, ones, S, t, idx, a.sc);
-        wave_accumulate<DT, CPT, ARG>(raw2, (tb + 1) * CPT, m, ones, S, t, idx, a.sc);
+        ok = ok && wave_tile<DT, CPT, ARG>(raw, tb * CPT, mw, ones, S, td, first, a.sc) &&
+             wave_tile<DT, CPT, ARG>(raw2, (tb + 1) * CPT, mw, ones, S, td, first, a.sc);
     } else {
         if (tb < fe) wave_load<DT, CPT, false>(row, a.geo.V, tb * CPT, raw);
         else wave_load<DT, CPT, true>(row, a.geo.V, tb * CPT, raw);
         if (flag_after_loads(a, flag)) return;
-        wave_accumulate<DT, CPT, ARG>(raw, tb * CPT, m, ones, S, t, idx, a.sc);
-        for (int t0 = tb + 1; t0 < te; ++t0) {
+        ok = ok && wave_tile<DT, CPT, ARG>(raw, tb * CPT, mw, ones, S, td, first, a.sc);
+        for (int t0 = tb + 1; t0 < te && ok; ++t0) {
             if (t0 < fe) wave_load<DT, CPT, false>(row, a.geo.V, t0 * CPT, raw);
             else wave_load<DT, CPT, true>(row, a.geo.V, t0 * CPT, raw);
-            wave_accumulate<DT, CPT, ARG>(raw, t0 * CPT, m, ones, S, t, idx, a.sc);
+            ok = wave_tile<DT, CPT, ARG>(raw, t0 * CPT, mw, ones, S, td, first, a.sc);
         }
     }
-    // the wave's lanes to one record: maximum first, then sums rescaled to it in fp64
-    const float mw = wave_max(m);
-    double Sd = 0.0, td = 0.0;
-    if (m != neg_inf()) {
-        const float xd = scaled_diff(m, mw, a.sc);
-        const double all = (double)ones + (double)S, f = (double)exp2_raw(xd);
-        Sd = f * all;
-        td = f * ((double)t + (double)xd * all);
-    }
-    Sd = wave_sum(Sd);
-    td = wave_sum(td);
-    int first = -1;
-    if (ARG) {      // smallest index among the lanes that hold the wave maximum
-        const int cand = (m == mw && idx >= 0) ? idx : 0x7FFFFFFF;
-        const int wmin = -wave_reduce(-cand, OpMax{});
-        first = wmin == 0x7FFFFFFF ? -1 : wmin;
+    double Sd, tsum;
+    if (ok) {
+        Sd = wave_sum((double)ones + (double)S);
+        tsum = wave_sum((double)td) * a.sc.c;
+    } else {
+        uncommon_record<DT, ARG>(a, row, tb, te, mw, Sd, tsum, first);
     }
     if (lane == 0) {
         Partial p;
         p.m = mw;
         p.idx = first;
         p.S = Sd;
-        p.t = td;
+        p.t = tsum;
         a.part[(size_t)b * nrec + r] = p;
     }
 }

@@ -83,6 +83,7 @@ struct DraftArgs {
     int *draft_len;
     long long io_stride;
     Partial *part;          // [B][ns] records of the row's waves
+    int common_range;       // 1: the temperature is in the range of wave_tile (draft_kernels.h)
     int rows_by_xcd;        // k_draft_stats: workgroup -> (row, records) mapping, see there
     unsigned div, div_magic;  // its one division, by div: n / div = div == 1 ? n : umulhi(n, div_magic), exact for n * div < 2^32
 };

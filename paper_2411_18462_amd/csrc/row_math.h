@@ -170,6 +170,37 @@ __device__ __forceinline__ void unpack<f16>(const u32x4 &v, float (&z)[8])
     }
 }
 
+// The most negative finite value of a storage type, and the widening of a vector with everything below it (-inf)
+// raised to it.  As unsigned integers the 16-bit negatives sort by magnitude with -inf above all finite ones, so one
+// packed minimum does two logits.
+template <typename DT> struct FiniteLow;
+template <> struct FiniteLow<float> { static __device__ __forceinline__ float value() { return -3.402823466e38f; } };
+template <> struct FiniteLow<bf16> {
+    static constexpr unsigned short bits = 0xFF7F;
+    static __device__ __forceinline__ float value() { return __uint_as_float(0xFF7F0000u); }
+};
+template <> struct FiniteLow<f16> {
+    static constexpr unsigned short bits = 0xFBFF;
+    static __device__ __forceinline__ float value() { return -65504.f; }
+};
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+template <typename DT>
+__device__ __forceinline__ void unpack_finite(const typename RawOf<DT>::type &v, float (&z)[VecOf<DT>::N])
+{
+    if constexpr (VecOf<DT>::N == 4) {
+        unpack<DT>(v, z);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) z[e] = vmax(z[e], FiniteLow<DT>::value());
+    } else {
+        const u16x2 low = {FiniteLow<DT>::bits, FiniteLow<DT>::bits};
+        typename RawOf<DT>::type r;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            r[i] = __builtin_bit_cast(unsigned, __builtin_elementwise_min(__builtin_bit_cast(u16x2, (unsigned)v[i]), low));
+        unpack<DT>(r, z);
+    }
+}
+
 // One stored logit widened to fp32 (exact).  Kept apart from the load so that a caller can request a value and
 // only look at it later.
 __device__ __forceinline__ float widen(float v) { return v; }

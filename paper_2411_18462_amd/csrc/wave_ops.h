@@ -89,7 +89,21 @@ __device__ __forceinline__ T wave_reduce(T v, Op op)
     return op(op(r0, r1), op(r2, r3));
 }
 
-__device__ __forceinline__ float wave_max(float v) { return wave_reduce(v, OpMax{}); }
+// Wave-uniform fp32 maximum: one v_max_f32 with a DPP operand per step (the s_nop covers the two wait states a DPP
+// read needs after the write before it).  Going through fmaxf() takes five instructions per step, because the
+// compiler quiets both operands.
+#define SVIP_MAX_STEP(CTRL) asm("s_nop 1\n\tv_max_f32_dpp %0, %0, %0 " CTRL : "+v"(v))
+__device__ __forceinline__ float wave_max(float v)
+{
+    SVIP_MAX_STEP("quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf");
+    SVIP_MAX_STEP("quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf");
+    SVIP_MAX_STEP("row_ror:4 row_mask:0xf bank_mask:0xf");
+    SVIP_MAX_STEP("row_ror:8 row_mask:0xf bank_mask:0xf");
+    SVIP_MAX_STEP("row_bcast:15 row_mask:0xa bank_mask:0xf");
+    SVIP_MAX_STEP("row_bcast:31 row_mask:0xc bank_mask:0xf");
+    return read_lane(v, 63);
+}
+#undef SVIP_MAX_STEP
 
 // Wave-uniform fp64 sum of all 64 lanes' values by the DPP butterfly (about 30 vector-ALU slots).  The same
 // sum as two v_mfma_f64_16x16x4 against a matrix of ones is exact too and needs 6 slots, but its long
