@@ -155,13 +155,13 @@ svip_status svip_draft_step(
  * live in a fixed array of SVIP_STATIC_SCRATCH_BYTES inside the library's device code, one copy per
  * GPU, held until the process ends.  The call allocates nothing and frees nothing.
  *   - Sizes whose records do not fit that array (svip_workspace_needed(SVIP_CALL_DRAFT_STEP, ...) >
- *     SVIP_STATIC_SCRATCH_BYTES; about 1200 rows of a 128K vocabulary) return SVIP_ERR_WORKSPACE.
+ *     SVIP_STATIC_SCRATCH_BYTES; about 1800 rows of a 128K vocabulary) return SVIP_ERR_WORKSPACE.
  *   - All calls on one GPU share the array: calls that overlap on one GPU (different streams, or
  *     threads) race and must be serialised by the caller.  Device-data flags are not reported.
  *   - The first call on a GPU asks the runtime for the array's address on that GPU (no allocation,
  *     nothing enqueued); nothing in the array has to be cleared.
  */
-#define SVIP_STATIC_SCRATCH_BYTES (1 << 20)
+#define SVIP_STATIC_SCRATCH_BYTES (1 << 21)
 svip_status svip_draft_step_static(
     const void *draft_logits, int dtype, int B, int V, long long row_stride,
     float temperature, float h, int step_j, int k_max, const float *u_sample,

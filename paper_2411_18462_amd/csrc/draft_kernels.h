@@ -17,14 +17,6 @@ __device__ __forceinline__ bool at_cap(const DraftArgs &a, int b)
     return a.step_j + 1 >= cap;
 }
 
-struct FinishLds {
-    LocateLds loc;
-    double target, L, S, tt;
-    float m;
-    int slice, tile;
-    int use_resid;
-};
-
 // Entropy of weights e_i = exp2(x_i) with sum S and tt = sum e_i x_i:  H = ln S - ln2 tt / S, then the
 // stop test and the row's outputs that do not depend on the token (Section 2.2, Eq. stop_condition).
 __device__ __forceinline__ void write_row_outputs(const DraftArgs &a, int b, long long o, float m, double S, double tt)
@@ -42,17 +34,24 @@ __device__ __forceinline__ void write_row_outputs(const DraftArgs &a, int b, lon
 // The draft step is two launches ordered by the stream.
 //
 // k_draft_stats: the statistics of a row as one record per WAVE.  Record r of a row covers tiles
-// [r * tps, (r + 1) * tps), and a wave reads a tile (256 consecutive vectors) as four loads of 64
-// consecutive vectors.  Nothing is shared between the waves of a workgroup -- no LDS, no barrier, so
-// no wave waits for data that another wave's loads are still bringing in.
-// k_draft_finish: one workgroup per row; one wave merges the row's records (a record per lane), writes
-// entropy, logsumexp and stop flag, and picks the record that holds u * S -- for rows of up to 64 tiles
-// a single tile, which is all the inverse-CDF search has to read again; with greedy drafting (ARG) the
-// token is the first maximum the records already carry and nothing is read again.
+// [r * tps, (r + 1) * tps), and a wave reads a tile (256 consecutive vectors) as four chunks of 64
+// consecutive vectors, one load each.  Nothing is shared between the waves of a workgroup -- no LDS, no
+// barrier, so no wave waits for data that another wave's loads are still bringing in.
+// k_draft_finish_*: merges a row's records (one or two per lane), writes entropy, logsumexp and stop flag, and finds
+// the token.  What a record holds besides the statistics decides how:
+//   QUARTERS  (records of one tile, launches of at most DRAFT_QUARTER_WAVES waves) the mass of each of its four
+//             chunks: record and chunk are picked from the records alone, and one wave reads that chunk again,
+//             one vector per lane, one scan over the lanes -- no LDS, no barrier;
+//   TOTAL     (beyond) one sum: the chosen record's tiles are read and searched by a workgroup.  The statistics of a
+//             launch this large are bound by vector-ALU issue, and the quarters' sums cost them more than the
+//             shorter search gives back: us per step of 128256 bf16 logits, quarters / totals: 1 row 6.16 / 6.6, 8 rows
+//             6.9 / 7.5, 64 rows 9.85 / 10.0, 128 rows 12.6 / 12.6, but 192 rows 16.4 / 15.3, 256 rows 19.7 / 18.3;
+//   GREEDY    one sum and the first index of the maximum, which is the token: nothing is read again.
 //
 // A single launch in which the row's last workgroup does the second part (hand-over through
 // write-through stores and a ticket, as the residual pass of verification does) measured the same at 64
 // rows of 128K logits and slower beyond, and was dropped for this simpler form.
+enum RecordKind { QUARTERS, TOTAL, GREEDY };
 
 // A row's stop flag, requested without looking at it: with no flag array the load goes to the start of the
 // records (any valid address) and the value is ignored.  flag_after_loads() is where the value is first looked
@@ -76,38 +75,59 @@ template <typename DT, int NU, bool CHECKED>
 __device__ __forceinline__ void wave_load(const DT *row, int V, int c0, typename RawOf<DT>::type (&raw)[NU])
 {
     const int lane = threadIdx.x & 63;
+    if (CHECKED) {
+        load_raw_tail<DT, NU, 64>(row, c0 * 64 + lane, V, raw);
+    } else {
 #pragma unroll
-    for (int u = 0; u < NU; ++u)
-        raw[u] = CHECKED ? load_raw_checked<DT>(row, (c0 + u) * 64 + lane, V) : load_raw<DT>(row, (c0 + u) * 64 + lane);
+        for (int u = 0; u < NU; ++u) raw[u] = load_raw<DT>(row, (c0 + u) * 64 + lane);
+    }
 }
-template <typename DT, int NU, bool ARG>
-__device__ __forceinline__ void wave_accumulate(const typename RawOf<DT>::type (&raw)[NU], int c0, float &m, float &ones,
-                                                float &S, float &t, int &idx, const Scale &sc)
-{
-    constexpr int N = VecOf<DT>::N;
-    float z[NU][N];
-#pragma unroll
-    for (int u = 0; u < NU; ++u) unpack<DT>(raw[u], z[u]);
-    accumulate<N, NU, ARG>(z, m, ones, S, t, sc, idx, c0);
-}
+// Per lane, what a wave has summed so far.  QUARTERS: the sum of the weights of each chunk of its one tile.  Otherwise:
+// the sum of the weights below 1 and the number of weights that are exactly 1, which have to stay out of the fp32 sum
+// (next to a 1 the tail of a confident row, 1e-4 and less, would lose its low bits).
+template <RecordKind KIND> struct LaneSums {
+    float S = 0.f, ones = 0.f;
+    __device__ __forceinline__ void add(int, float below) { S += below; }
+    __device__ __forceinline__ void add(int, float below, float exact_ones)
+    {
+        S += below;
+        ones += exact_ones;
+    }
+    __device__ __forceinline__ void rescale(float f, float d, float &td)
+    {
+        if (f < 1.0f) {                     // the old maximum becomes an ordinary term
+            const float all = S + ones;
+            td = f * fmaf(d, all, td);
+            S = f * all;
+            ones = 0.f;
+        }
+    }
+    __device__ __forceinline__ double total() const { return (double)ones + (double)S; }
+};
+template <> struct LaneSums<QUARTERS> {
+    double S[4] = {};
+    __device__ __forceinline__ void add(int, float) {}
+    __device__ __forceinline__ void add(int chunk, float below, float exact_ones) { S[chunk] = (double)below + (double)exact_ones; }
+    __device__ __forceinline__ void rescale(float, float, float &) {}         // one tile: nothing before it
+};
 
-// One tile of a wave relative to the WAVE's running maximum mw (the same in every lane): S = sum of the weights
-// below 1, ones = the number of weights that are exactly 1, td = sum w (z - mw), all per lane.  What the lane-wise
-// form above pays per logit and this one does not:
-//  - the count of ones: only the vectors that hold the maximum have any, found by one comparison per vector of the
-//    lane (its maximum is there anyway) and a branch the whole wave takes; about one vector in four goes that way;
+// One tile of a wave relative to the WAVE's running maximum mw (the same in every lane): the sums of the weights and
+// td = sum w (z - mw), per lane.  One reference for the whole wave instead of one per lane saves per logit
+//  - the count of weights that are exactly 1 (the maximum, its ties): only vectors that hold the maximum have any;
+//    one comparison per vector (its own maximum is there anyway) and a branch the whole wave takes find them, about
+//    one vector in four.  There sum fract(w) (fract(1) = 0) is what goes into the fp32 sum;
 //  - the floor of the exponent: masked (-inf) logits are lowered to the most negative finite number while still
 //    packed (half an instruction per logit), so z - mw stays finite and 0 * (z - mw) is 0;
 //  - a product per term of the entropy sum: w (z - mw) is accumulated by fused multiply-adds, and the scale is
-//    applied once per record in fp64.
-// About 9 issue slots per bf16 logit instead of 12.5, and the lanes of a wave need no rescaling to one another: about
-// 380 vector instructions per wave of one tile instead of 478.  What that is worth grows with how far issue rather
-// than latency bounds the launch; us per draft step in a graph, before / after: 8 rows of 128256 bf16 logits 7.74 /
-// 7.63, 64 rows 10.19 / 10.06 (greedy 9.75 / 9.26), 128 rows 13.6 / 12.8, 256 rows 20.1 / 18.5.
-// Returns false, with nothing changed, for the tiles this form is not for: no logit above the most negative
-// finite number (masked tiles), or one beyond 1e30.
-template <typename DT, int NU, bool ARG>
-__device__ __forceinline__ bool wave_tile(const typename RawOf<DT>::type (&raw)[NU], int c0, float &mw, float &ones, float &S,
+//    applied once per record in fp64,
+// and per wave the rescaling of its lanes to one another: about 9 issue slots per bf16 logit instead of 12.5.  What
+// that is worth grows with how far issue rather than latency bounds the launch; us per draft step in a graph, before
+// / after: 8 rows of 128256 bf16 logits 7.74 / 7.63, 64 rows 10.19 / 10.06 (greedy 9.75 / 9.26), 128 rows 13.6 / 12.8,
+// 256 rows 20.1 / 18.5.
+// Returns false for the tiles this form is not for: no logit above the most negative finite number (masked tiles), or
+// one beyond 1e30.
+template <typename DT, int NU, RecordKind KIND>
+__device__ __forceinline__ bool wave_tile(const typename RawOf<DT>::type (&raw)[NU], int c0, float &mw, LaneSums<KIND> &sums,
                                           float &td, int &idx, const Scale &sc)
 {
     constexpr int N = VecOf<DT>::N;
@@ -124,17 +144,9 @@ __device__ __forceinline__ bool wave_tile(const typename RawOf<DT>::type (&raw)[
     if (!(mt > FiniteLow<DT>::value() && mt < 1e30f)) return false;
     const bool higher = mt > mw;
     if (higher) {
-        if (mw != neg_inf()) {
-            const float d = mw - mt, f = exp2_raw(scaled_diff(mw, mt, sc));
-            if (f < 1.0f) {                     // the old maximum becomes an ordinary term
-                const float all = S + ones;
-                td = f * fmaf(d, all, td);
-                S = f * all;
-                ones = 0.f;
-            }
-        }
+        if (mw != neg_inf()) sums.rescale(exp2_raw(scaled_diff(mw, mt, sc)), mw - mt, td);
         mw = mt;
-        if (ARG) idx = -1;
+        idx = -1;
     }
 #pragma unroll
     for (int u = 0; u < NU; ++u) {
@@ -153,82 +165,136 @@ __device__ __forceinline__ bool wave_tile(const typename RawOf<DT>::type (&raw)[
         }
         td += ta + tb;
         const unsigned long long hit = __ballot(gm[u] == mw);
-        float Sb = tree_sum<N>(w);
+        float Sb = tree_sum<N>(w), ones = 0.f;
         if (hit) {
-            float fr[N];                        // a weight of exactly 1 is counted and leaves 0 behind
+            float fr[N];
 #pragma unroll
             for (int e = 0; e < N; ++e) fr[e] = __builtin_amdgcn_fractf(w[e]);
             const float below = tree_sum<N>(fr);
-            ones += rintf(Sb - below);
+            ones = rintf(Sb - below);
             Sb = below;
-            if (ARG && higher && idx < 0) {     // vectors come in index order: the first lane of the first one
+            if (KIND != QUARTERS) sums.add(u, Sb, ones);
+            if (KIND == GREEDY && higher && idx < 0) {     // vectors come in index order: the first lane of the first one
                 int at = 0;
 #pragma unroll
                 for (int e = N - 1; e >= 0; --e) at = z[u][e] == mw ? e : at;
                 const int first = __ffsll((long long)hit) - 1;
                 idx = ((c0 + u) * 64 + first) * N + read_lane(at, first);
             }
+        } else if (KIND != QUARTERS) {
+            sums.add(u, Sb);
         }
-        S += Sb;
+        if (KIND == QUARTERS) sums.add(u, Sb, ones);
         // the sums are formed here: the compiler would otherwise move all of them behind the last branch and keep
         // every weight of the tile in registers until then
-        asm volatile("" : "+v"(S), "+v"(td), "+v"(ones));
+        if constexpr (KIND == QUARTERS) asm volatile("" : "+v"(td), "+v"(sums.S[u]));
+        else asm volatile("" : "+v"(td), "+v"(sums.S), "+v"(sums.ones));
     }
     return true;
 }
 
 // A record outside wave_tile's range (a masked tile, logits or a temperature of extreme size), from memory again:
-// every lane keeps its own running maximum, and the lanes are brought to the wave's at the end.
-template <typename DT, bool ARG>
-__device__ __forceinline__ void uncommon_record(const DraftArgs &a, const DT *row, int tb, int te, float &mw, double &Sd,
-                                                double &td, int &first)
+// maximum first, then sums chunk by chunk with a floor under every exponent -- few registers, this is rare.
+// S[q]: this lane's sum over the record's chunks q, q + 4, ..; td in units of log2 here.
+template <typename DT, RecordKind KIND>
+__device__ __forceinline__ void uncommon_record(const DraftArgs &a, const DT *row, int tb, int te, float &mw, double (&S)[4],
+                                                double &td, int &idx)
 {
-    constexpr int CPT = WG / 64;
-    float m = neg_inf(), ones = 0.f, S = 0.f, t = 0.f;
-    int idx = -1;
+    constexpr int N = VecOf<DT>::N, CPT = WG / 64;
+    float m = neg_inf(), z[N];
 #pragma unroll 1
-    for (int c = tb * CPT; c < te * CPT; ++c) {           // a chunk at a time: few registers, this path is rare
+    for (int t0 = tb; t0 < te; ++t0) {
+        typename RawOf<DT>::type tile[CPT];
+        if (t0 < a.geo.V / (WG * N)) wave_load<DT, CPT, false>(row, a.geo.V, t0 * CPT, tile);
+        else wave_load<DT, CPT, true>(row, a.geo.V, t0 * CPT, tile);
+#pragma unroll
+        for (int u = 0; u < CPT; ++u) {
+            unpack<DT>(tile[u], z);
+            m = vmax(m, tree_max<N>(z));
+        }
+    }
+    mw = wave_max(m);
+    idx = -1;
+    td = 0.0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) S[q] = 0.0;
+    if (mw == neg_inf()) return;
+#pragma unroll 1
+    for (int c = tb * CPT; c < te * CPT; ++c) {
         typename RawOf<DT>::type raw[1];
         wave_load<DT, 1, true>(row, a.geo.V, c, raw);
-        wave_accumulate<DT, 1, ARG>(raw, c, m, ones, S, t, idx, a.sc);
-    }
-    // the wave's lanes to one record: maximum first, then sums rescaled to it in fp64
-    mw = wave_max(m);
-    Sd = td = 0.0;
-    if (m != neg_inf()) {
-        const float xd = scaled_diff(m, mw, a.sc);
-        const double all = (double)ones + (double)S, f = (double)exp2_raw(xd);
-        Sd = f * all;
-        td = f * ((double)t + (double)xd * all);
-    }
-    Sd = wave_sum(Sd);
-    td = wave_sum(td);
-    first = -1;
-    if (ARG) {      // smallest index among the lanes that hold the wave maximum
-        const int cand = (m == mw && idx >= 0) ? idx : 0x7FFFFFFF;
-        const int wmin = -wave_reduce(-cand, OpMax{});
-        first = wmin == 0x7FFFFFFF ? -1 : wmin;
+        unpack<DT>(raw[0], z);
+        float w[N], fr[N], wx[N];
+#pragma unroll
+        for (int e = 0; e < N; ++e) {
+            const float x = scaled_diff(z[e], mw, a.sc);
+            w[e] = exp2_raw(x);
+            fr[e] = __builtin_amdgcn_fractf(w[e]);
+            wx[e] = w[e] * x;
+        }
+        const float below = tree_sum<N>(fr);
+        const double Su = (double)below + (double)rintf(tree_sum<N>(w) - below);
+        td += (double)tree_sum<N>(wx);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) S[q] += q == (c & (CPT - 1)) ? Su : 0.0;
+        if (KIND == GREEDY && idx < 0) {
+            const unsigned long long hit = __ballot(tree_max<N>(z) == mw);
+            if (hit) {
+                int at = 0;
+#pragma unroll
+                for (int e = N - 1; e >= 0; --e) at = z[e] == mw ? e : at;
+                const int first = __ffsll((long long)hit) - 1;
+                idx = (c * 64 + first) * N + read_lane(at, first);
+            }
+        }
     }
 }
 
-// grid (ceil(rows * records / 4)), one wave per record.  TWO: the launch's records hold two tiles; a record of
-// two whole tiles then requests both before it works on the first (the arithmetic of the first runs while the
-// second is still on its way: 0.2 us of an 11.2 us step at 64 rows of 128K logits, 0.55 of 21 us at 256), which
-// takes 65 registers; with one tile per record that form is 0.2 us slower, so those launches keep the other.
-template <typename DT, bool ARG, bool TWO>
-__global__ __launch_bounds__(WG, TWO ? 6 : 8) void k_draft_stats(DraftArgs a)
+// The wave's record from its lanes' sums.
+__device__ __forceinline__ void store_record(const DraftArgs &a, size_t at, float mw, int first, double lane_sum, double t)
+{
+    const double S = wave_sum(lane_sum);
+    if ((threadIdx.x & 63) == 0) {
+        Partial p;
+        p.m = mw;
+        p.idx = first;
+        p.S = S;
+        p.t = t;
+        static_cast<Partial *>(a.part)[at] = p;
+    }
+}
+__device__ __forceinline__ void store_record(const DraftArgs &a, size_t at, float mw, const double (&S)[4], double t)
+{
+    // one store of six lanes: the chunks' sums (lane q holds that of chunk q), t, and the maximum
+    const int lane = threadIdx.x & 63;
+    double x = wave_sum4(S);
+    x = lane == 4 ? t : x;
+    x = lane == 5 ? __hiloint2double(0, __float_as_int(mw)) : x;
+    if (lane < 6) reinterpret_cast<double *>(static_cast<QuarterRec *>(a.part) + at)[lane] = x;
+}
+
+// grid (ceil(rows * records / 4)), one wave per record.  TPS: tiles per record, 1, 2 or 0 for more.  A record of two
+// whole tiles requests both before it works on the first (the arithmetic of the first runs while the second is
+// still on its way), which takes more registers; launches with one tile per record keep the other form.
+template <typename DT, RecordKind KIND, int TPS>
+__global__ __launch_bounds__(WG, TPS == 1 ? 8 : 6) void k_draft_stats(DraftArgs a)
 {
     constexpr int N = VecOf<DT>::N, CPT = WG / 64;       // chunks of 64 vectors per tile
-    const int lane = threadIdx.x & 63, nrec = a.geo.ns;
+    static_assert(KIND != QUARTERS || TPS == 1, "a quarter is a chunk");
+    const int nrec = a.geo.ns;
+    // All arguments are requested at once: left to itself the compiler loads those behind the first branch only there,
+    // a second trip to the scalar cache before the first load of a logit.
+    asm volatile("" : : "s"(a.logits), "s"(a.row_stride), "s"(a.pos), "s"(a.stop_in), "s"(a.geo.V), "s"(a.part), "s"(a.sc.c_hi),
+                 "s"(a.sc.c_lo), "s"(a.sc.c), "s"(a.common_range), "s"(a.step_j));
     // Which record this wave takes is the same in all its lanes: worked out in scalar registers, with the one
-    // division done by a multiplication the host prepared, so that none of it takes vector-ALU slots (a wave of one
-    // tile has about 380 vector instructions in all, and they bound this kernel at large batches).
+    // division done by a multiplication the host prepared, so that none of it takes vector-ALU slots.
     const unsigned wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int b, r;
     if (a.rows_by_xcd) {
-        // Workgroups go to the chip's 8 XCDs in turn, and so do the rows' workgroups of k_draft_finish: keeping
-        // row b on XCD b % 8 lets that kernel find the row's records and the tile it reads again in the L2 of
-        // its own XCD.  The grid is ceil(B / 8) * 8 * ceil(nrec / 4) workgroups; those of rows past B exit.
+        // Workgroups go to the chip's 8 XCDs in turn, and so do the rows' workgroups of the finish: keeping row b on
+        // XCD b % 8 lets that kernel find the row's records (and what it reads again) in the L2 of its own XCD, and
+        // the lines of the records are written by one L2 each.  The grid is ceil(B / 8) * 8 * ceil(nrec / 4)
+        // workgroups; those of rows past B exit.
         const unsigned xcd = blockIdx.x & 7u, slot = blockIdx.x >> 3;           // div = workgroups per row
         const unsigned q = a.div == 1u ? slot : __umulhi(slot, a.div_magic);
         b = (int)(q * 8u + xcd);
@@ -241,116 +307,284 @@ __global__ __launch_bounds__(WG, TWO ? 6 : 8) void k_draft_stats(DraftArgs a)
         r = (int)(gw - (unsigned)b * (unsigned)nrec);
     }
     const DT *row = static_cast<const DT *>(a.logits) + draft_row_offset(a, b);
-    const int tb = r * a.geo.tps, te = min(tb + a.geo.tps, a.geo.ntiles);
+    const int tps = TPS ? TPS : a.geo.tps;
+    const int tb = r * tps, te = min(tb + tps, a.geo.ntiles);
     const int fe = min(te, a.geo.V / (WG * N));           // end of the tiles wholly inside the row
     // The record's first tile is requested before the row's stop flag is looked at, so that the two travel
     // together (a step is bound by round trips to memory); a stopped row costs those loads and nothing else.
     const unsigned flag = request_stop_flag(a, b);
     typename RawOf<DT>::type raw[CPT];
-    float mw = neg_inf(), ones = 0.f, S = 0.f, td = 0.f;
+    float mw = neg_inf(), td = 0.f;
+    LaneSums<KIND> sums;
     int first = -1;
     bool ok = a.common_range;
-    if (TWO && te - tb == 2 && te <= fe) {
+    if (TPS == 2 && te - tb == 2 && te <= fe) {
         typename RawOf<DT>::type raw2[CPT];
         wave_load<DT, CPT, false>(row, a.geo.V, tb * CPT, raw);
         wave_load<DT, CPT, false>(row, a.geo.V, (tb + 1) * CPT, raw2);
         if (flag_after_loads(a, flag)) return;
-        ok = ok && wave_tile<DT, CPT, ARG>(raw, tb * CPT, mw, ones, S, td, first, a.sc) &&
-             wave_tile<DT, CPT, ARG>(raw2, (tb + 1) * CPT, mw, ones, S, td, first, a.sc);
+        ok = ok && wave_tile<DT, CPT, KIND>(raw, tb * CPT, mw, sums, td, first, a.sc) &&
+             wave_tile<DT, CPT, KIND>(raw2, (tb + 1) * CPT, mw, sums, td, first, a.sc);
     } else {
         if (tb < fe) wave_load<DT, CPT, false>(row, a.geo.V, tb * CPT, raw);
         else wave_load<DT, CPT, true>(row, a.geo.V, tb * CPT, raw);
         if (flag_after_loads(a, flag)) return;
-        ok = ok && wave_tile<DT, CPT, ARG>(raw, tb * CPT, mw, ones, S, td, first, a.sc);
-        for (int t0 = tb + 1; t0 < te && ok; ++t0) {
-            if (t0 < fe) wave_load<DT, CPT, false>(row, a.geo.V, t0 * CPT, raw);
-            else wave_load<DT, CPT, true>(row, a.geo.V, t0 * CPT, raw);
-            ok = wave_tile<DT, CPT, ARG>(raw, t0 * CPT, mw, ones, S, td, first, a.sc);
+        ok = ok && wave_tile<DT, CPT, KIND>(raw, tb * CPT, mw, sums, td, first, a.sc);
+        if (TPS != 1) {
+            for (int t0 = tb + 1; t0 < te && ok; ++t0) {
+                if (t0 < fe) wave_load<DT, CPT, false>(row, a.geo.V, t0 * CPT, raw);
+                else wave_load<DT, CPT, true>(row, a.geo.V, t0 * CPT, raw);
+                ok = wave_tile<DT, CPT, KIND>(raw, t0 * CPT, mw, sums, td, first, a.sc);
+            }
         }
     }
-    double Sd, tsum;
+    const size_t at = (size_t)b * nrec + r;
     if (ok) {
-        Sd = wave_sum((double)ones + (double)S);
-        tsum = wave_sum((double)td) * a.sc.c;
+        const double t = wave_sum((double)td) * a.sc.c;
+        if constexpr (KIND == QUARTERS) store_record(a, at, mw, sums.S, t);
+        else store_record(a, at, mw, first, sums.total(), t);
     } else {
-        uncommon_record<DT, ARG>(a, row, tb, te, mw, Sd, tsum, first);
-    }
-    if (lane == 0) {
-        Partial p;
-        p.m = mw;
-        p.idx = first;
-        p.S = Sd;
-        p.t = tsum;
-        a.part[(size_t)b * nrec + r] = p;
+        double S[4], t2;
+        uncommon_record<DT, KIND>(a, row, tb, te, mw, S, t2, first);
+        const double t = wave_sum(t2);
+        if constexpr (KIND == QUARTERS) store_record(a, at, mw, S, t);
+        else store_record(a, at, mw, first, (S[0] + S[1]) + (S[2] + S[3]), t);
     }
 }
 
-// What the thread that finds the draft token does with it (see locate_batch's `report`).
+// The inverse CDF inside one chunk of a row by one wave: the smallest index whose inclusive prefix of weights
+// exp2((z - m) c), counted from the start of the chunk, exceeds `target`.  A lane holds one vector; fp32 sums per
+// vector, fp64 over the lanes.  The lane that holds the token reports it (see locate_batch).  If rounding leaves no
+// crossing, it is the last index with positive weight (-1 if there is none).
+template <typename DT, typename Report>
+__device__ __forceinline__ void search_chunk(const DT *row, int V, int chunk, float m, const Scale &sc, double target, Report report)
+{
+    constexpr int N = VecOf<DT>::N;
+    const int lane = threadIdx.x & 63;
+    float z[N], w[N];
+    typename RawOf<DT>::type raw[1];
+    wave_load<DT, 1, true>(row, V, chunk, raw);
+    unpack<DT>(raw[0], z);
+#pragma unroll
+    for (int e = 0; e < N; ++e) w[e] = exp2_raw(scaled_diff(z[e], m, sc));
+    const double g = (double)tree_sum<N>(w);
+    const double incl = wave_inclusive_sum(g);
+    const unsigned long long hit = __ballot(g > 0.0 && incl > target), mass = __ballot(g > 0.0);
+    double C = incl - g;
+    int pick = -1, lastpos = -1;
+    float wp = 0.f, wl = 0.f;
+#pragma unroll
+    for (int e = 0; e < N; ++e) {
+        C += (double)w[e];
+        if (w[e] > 0.f) {
+            lastpos = e;
+            wl = w[e];
+            if (pick < 0 && C > target) {
+                pick = e;
+                wp = w[e];
+            }
+        }
+    }
+    const int base = (chunk * 64 + lane) * N;
+    if (hit) {
+        if (lane == __ffsll((long long)hit) - 1) {
+            if (pick < 0) report(base + lastpos, wl);
+            else report(base + pick, wp);
+        }
+    } else if (mass) {
+        if (lane == 63 - __clzll((long long)mass)) report(base + lastpos, wl);
+    } else if (lane == 0) {
+        report(-1, 0.f);
+    }
+}
+
+// What the thread that finds the draft token does with it (see locate_batch's `report`); unit: the weight of 1 of the
+// search in units of the row's sum S.
 struct StoreDraftToken {
     static constexpr bool active = true;
     const DraftArgs &a;
     long long o;
-    double S;
+    double unit, S;
     __device__ __forceinline__ void operator()(int tok, float w) const
     {
         a.token[o] = tok;
-        if (a.q_tok) a.q_tok[o] = (float)((double)w / S);
+        if (a.q_tok) a.q_tok[o] = (float)((double)w * unit / S);
     }
 };
 
-// grid (rows): the rows' last step over the records of k_draft_stats.  Sampling: WG + 64 threads, greedy: 64.
+// A row already marked stopped: the two outputs every such row gets.
+__device__ __forceinline__ void stopped_row(const DraftArgs &a, int b, long long o)
+{
+    if (threadIdx.x == 0) {
+        a.token[o] = -1;
+        a.stop[b] = 1;
+    }
+}
+
+// Factor that brings a record with maximum m and sum S to the row maximum, and its log2 (0, 0 for an empty record).
+__device__ __forceinline__ double record_factor(float m, double S, float mrow, const Scale &sc, double *xd)
+{
+    double f = 0.0;
+    *xd = 0.0;
+    if (m != neg_inf() && S > 0.0) {
+        *xd = ((double)m - (double)mrow) * sc.c;
+        f = exp2(*xd);
+    }
+    return f;
+}
+
+// QUARTERS, grid (rows): two waves, neither waits for the other; each loads and merges the records for itself, RPL
+// consecutive records per lane.  Wave 1 writes entropy, logsumexp and stop flag (an fp64 logarithm and a square
+// root), wave 0 finds the token.
+constexpr int QUARTER_FINISH_THREADS = 128;
+template <typename DT, int RPL>
+__global__ __launch_bounds__(QUARTER_FINISH_THREADS) void k_draft_finish_quarters(DraftArgs a)
+{
+    const int b = blockIdx.x, lane = threadIdx.x & 63, nrec = a.geo.ns;
+    const long long o = (long long)b * a.io_stride;
+    asm volatile("" : : "s"(a.logits), "s"(a.row_stride), "s"(a.pos), "s"(a.stop_in), "s"(a.geo.V), "s"(a.part), "s"(a.sc.c),
+                 "s"(a.sc.c_hi), "s"(a.sc.c_lo), "s"(a.u), "s"(a.token), "s"(a.q_tok));       // requested at once
+    // independent loads first: the row's flag, its uniform and its records travel together
+    const unsigned flag = request_stop_flag(a, b);
+    float m[RPL];
+    double t[RPL], S4[RPL][4];
+#pragma unroll
+    for (int i = 0; i < RPL; ++i) {
+        m[i] = neg_inf();
+        t[i] = 0.0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) S4[i][q] = 0.0;
+        if (lane * RPL + i < nrec) {
+            const QuarterRec *p = static_cast<const QuarterRec *>(a.part) + (size_t)b * nrec + lane * RPL + i;
+            m[i] = p->m;
+            t[i] = p->t;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) S4[i][q] = p->S[q];
+        }
+    }
+    const float u = a.u[o];
+    if (flag_after_loads(a, flag)) return stopped_row(a, b, o);
+    // everything relative to the row maximum
+    float mrow = m[0];
+    if (RPL == 2) mrow = vmax(mrow, m[RPL - 1]);
+    mrow = wave_max(mrow);
+    double f[RPL], xd[RPL], rS[RPL], M = 0.0;
+#pragma unroll
+    for (int i = 0; i < RPL; ++i) {
+        rS[i] = (S4[i][0] + S4[i][1]) + (S4[i][2] + S4[i][3]);
+        f[i] = record_factor(m[i], rS[i], mrow, a.sc, &xd[i]);
+        M += f[i] * rS[i];
+    }
+    if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) == 1) {
+        double tt = 0.0;
+#pragma unroll
+        for (int i = 0; i < RPL; ++i) tt += f[i] * (t[i] + xd[i] * rS[i]);
+        const double S = wave_sum(M);
+        tt = wave_sum(tt);
+        if (lane == 0) write_row_outputs(a, b, o, mrow, S, tt);
+        return;
+    }
+    // the token: lane, record, chunk (masses of all in units of the row maximum)
+    const double incl = wave_inclusive_sum(M);
+    const double S = read_lane(incl, 63);
+    double target;
+    const int at = pick_slice(M, (double)u * S, incl, &target);
+    double G[4], frec = read_lane(f[0], at);
+    float mrec = read_lane(m[0], at);
+    int rec = at * RPL;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) G[q] = read_lane(f[0] * S4[0][q], at);
+    if (RPL == 2) {
+        const double M0 = read_lane(f[0] * rS[0], at), M1 = read_lane(f[RPL - 1] * rS[RPL - 1], at);
+        if (M1 > 0.0 && !(M0 > target)) {             // the second of the lane's two records
+            target -= M0;
+            frec = read_lane(f[RPL - 1], at);
+            mrec = read_lane(m[RPL - 1], at);
+            rec += 1;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) G[q] = read_lane(f[RPL - 1] * S4[RPL - 1][q], at);
+        }
+    }
+    double in_chunk;
+    const int chunk = rec * 4 + pick_tile(G, target, &in_chunk);
+    // inside the chunk in units of the record's own maximum, as k_draft_stats formed the weights; the division runs
+    // while the chunk is on its way
+    in_chunk = frec > 0.0 ? in_chunk / frec : 0.0;
+    const DT *row = static_cast<const DT *>(a.logits) + draft_row_offset(a, b);
+    search_chunk<DT>(row, a.geo.V, chunk, mrec, a.sc, in_chunk, StoreDraftToken{a, o, frec, S});
+}
+
+// GREEDY, grid (rows), one wave, RPL consecutive records per lane.
+template <int RPL>
+__global__ __launch_bounds__(64) void k_draft_finish_greedy(DraftArgs a)
+{
+    const int b = blockIdx.x, lane = threadIdx.x, nrec = a.geo.ns;
+    const long long o = (long long)b * a.io_stride;
+    const unsigned flag = request_stop_flag(a, b);        // travels together with the records
+    Partial p[RPL];
+#pragma unroll
+    for (int i = 0; i < RPL; ++i) {
+        p[i].m = neg_inf();
+        p[i].idx = -1;
+        p[i].S = 0.0;
+        p[i].t = 0.0;
+        if (lane * RPL + i < nrec) p[i] = static_cast<const Partial *>(a.part)[(size_t)b * nrec + lane * RPL + i];
+    }
+    if (flag_after_loads(a, flag)) return stopped_row(a, b, o);
+    float mrow = p[0].m;
+    if (RPL == 2) mrow = vmax(mrow, p[RPL - 1].m);
+    mrow = wave_max(mrow);
+    double S = 0.0, tt = 0.0;
+    int mine = -1;                                        // records are in index order: the first at the row maximum
+#pragma unroll
+    for (int i = RPL - 1; i >= 0; --i) {
+        double xd;
+        const double f = record_factor(p[i].m, p[i].S, mrow, a.sc, &xd);
+        S += f * p[i].S;
+        tt += f * (p[i].t + xd * p[i].S);
+        if (p[i].m == mrow && p[i].idx >= 0) mine = p[i].idx;
+    }
+    S = wave_sum(S);
+    tt = wave_sum(tt);
+    const unsigned long long at_max = __ballot(mine >= 0);
+    const int tok = at_max ? read_lane(mine, __ffsll((long long)at_max) - 1) : -1;
+    if (lane == 0) {
+        a.token[o] = tok;
+        if (a.q_tok) a.q_tok[o] = (float)(1.0 / S);       // the maximum has weight exp2(0) = 1
+        write_row_outputs(a, b, o, mrow, S, tt);
+    }
+}
+
+// TOTAL, grid (rows), a record per lane.  Every wave loads and merges the records for itself: the waves then agree on
+// the record to search without passing anything through LDS or waiting for one another.
 // Waves 0 .. 3 search for the token; the extra wave writes entropy, logsumexp and stop flag and ends, so that
 // work (an fp64 logarithm and a square root, 0.3 us) neither sits in front of the search nor holds up its barriers.
-constexpr int FINISH_THREADS = WG + 64;
-template <typename DT, bool ARG>
-__global__ __launch_bounds__(FINISH_THREADS, 4) void k_draft_finish(DraftArgs a)
+constexpr int TOTAL_FINISH_THREADS = WG + 64;
+template <typename DT>
+__global__ __launch_bounds__(TOTAL_FINISH_THREADS, 4) void k_draft_finish_total(DraftArgs a)
 {
     constexpr int N = VecOf<DT>::N;
     __shared__ LocateLds loc;
     const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, nrec = a.geo.ns;
     const long long o = (long long)b * a.io_stride;
-    // independent loads first: the row's flag, its uniform and its records travel together.  Every wave loads and
-    // merges the records for itself (a record per lane): the waves then agree on the record to search without
-    // passing anything through LDS or waiting for one another.
+    // independent loads first: the row's flag, its uniform and its records travel together
     const unsigned flag = request_stop_flag(a, b);
     Partial p;
     p.m = neg_inf();
-    p.idx = -1;
     p.S = 0.0;
     p.t = 0.0;
-    float u = 0.f;
-    if (lane < nrec) p = a.part[(size_t)b * nrec + lane];
-    if (!ARG) u = a.u[o];
-    if (flag_after_loads(a, flag)) {
-        if (tid == 0) {
-            a.token[o] = -1;
-            a.stop[b] = 1;
-        }
-        return;
-    }
+    if (lane < nrec) p = static_cast<const Partial *>(a.part)[(size_t)b * nrec + lane];
+    const float u = a.u[o];
+    if (flag_after_loads(a, flag)) return stopped_row(a, b, o);
     const DT *row = static_cast<const DT *>(a.logits) + draft_row_offset(a, b);
     // everything relative to the row maximum: this lane's record by the factor f
     const float mrow = wave_max(p.m);
-    double f = 0.0, xd = 0.0;
-    if (p.m != neg_inf() && p.S > 0.0) {
-        xd = ((double)p.m - (double)mrow) * a.sc.c;
-        f = exp2(xd);
-    }
+    double xd;
+    const double f = record_factor(p.m, p.S, mrow, a.sc, &xd);
     const double M = f * p.S;
     const double incl = wave_inclusive_sum(M);
     const double S = read_lane(incl, 63);
     const double tt = wave_sum(f * (p.t + xd * p.S));
-    if (ARG) {
-        // records are in index order: the first that reaches the row maximum holds its first index
-        const unsigned long long at_max = __ballot(p.m == mrow && p.idx >= 0);
-        const int tok = at_max ? read_lane(p.idx, __ffsll((long long)at_max) - 1) : -1;
-        if (tid == 0) {
-            a.token[o] = tok;
-            if (a.q_tok) a.q_tok[o] = (float)(1.0 / S);           // the maximum has weight exp2(0) = 1
-            write_row_outputs(a, b, o, mrow, S, tt);
-        }
-        return;
-    }
     // the extra wave: the outputs that do not depend on the token.  The test is on a scalar register, so the wave
     // branches to the end of the program and is gone before the other waves' first barrier.
     if (__builtin_amdgcn_readfirstlane(tid >> 6) == NWAVE) {
@@ -361,7 +595,7 @@ __global__ __launch_bounds__(FINISH_THREADS, 4) void k_draft_finish(DraftArgs a)
     const int rec = pick_slice(M, (double)u * S, incl, &target);
     SoftmaxWeights<DT> wf{row, a.geo.V, make_exp_ref(a.sc, (double)mrow * a.sc.c)};
     // the thread that finds the token stores it; nothing else in this kernel has used the search's LDS
-    const StoreDraftToken store{a, o, S};
+    const StoreDraftToken store{a, o, 1.0, S};
     float wtok;
     const int tb = rec * a.geo.tps, te = min(tb + a.geo.tps, a.geo.ntiles);
     // a record of one tile is searched as one batch of one tile, longer records two tiles at a time

@@ -62,6 +62,17 @@ __device__ __forceinline__ unsigned *ticket(unsigned *tickets_end, int b, int t)
 
 // ---- kernel arguments ------------------------------------------------------------------
 
+// A draft record with the mass of each of its chunks: relative to the record's maximum m, S[q] = sum of
+// exp2((z - m) c) over chunk q, t = sum over the record of exp2((z - m) c) (z - m) c.  64 bytes, so that a record fills
+// its half line alone: at 48, with the lines' halves written by different waves, a step of 64 rows took 0.16 us longer.
+struct QuarterRec {
+    double S[4];
+    double t;
+    float m;
+    float pad[5];
+};
+static_assert(sizeof(QuarterRec) == 64, "one store of six lanes, one half line");
+
 struct DraftArgs {
     const void *logits;
     long long row_stride;   // between the rows of consecutive sequences
@@ -82,7 +93,7 @@ struct DraftArgs {
     unsigned char *stop;
     int *draft_len;
     long long io_stride;
-    Partial *part;          // [B][ns] records of the row's waves
+    void *part;             // [B][ns] records of the row's waves: QuarterRec or Partial
     int common_range;       // 1: the temperature is in the range of wave_tile (draft_kernels.h)
     int rows_by_xcd;        // k_draft_stats: workgroup -> (row, records) mapping, see there
     unsigned div, div_magic;  // its one division, by div: n / div = div == 1 ? n : umulhi(n, div_magic), exact for n * div < 2^32

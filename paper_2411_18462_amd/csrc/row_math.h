@@ -55,6 +55,15 @@ struct Scale {
 __device__ __forceinline__ float neg_inf() { return -__builtin_inff(); }
 __device__ __forceinline__ float exp2_raw(float x) { return __builtin_amdgcn_exp2f(x); }
 
+// A uniform value in a vector register.  With several waves per SIMD an fp32 add, multiply or fused multiply-add whose
+// operands are all vector registers (or literals) issues every 2.3 cycles; one with a scalar-register operand, like
+// most other vector instructions, every 4.1 (v_exp_f32: 8.1).  Constants of the inner loops are therefore kept here.
+__device__ __forceinline__ float in_vgpr(float x)
+{
+    asm("" : "+v"(x));
+    return x;
+}
+
 // v_max_f32 / v_max3_f32 issued directly.  The instructions return the other operand when
 // one is NaN; going through fmaxf() instead makes the compiler quiet every input first
 // (one more instruction per logit).
@@ -137,6 +146,34 @@ __device__ __forceinline__ typename RawOf<DT>::type load_raw_checked(const DT *r
     return load_raw_edge(row, vi, V);
 }
 
+// Vectors v0, v0 + STEP, .. of which some may lie past the end of the row, all requested at once: every lane loads, those
+// past the end the row's last whole vector, and gets -inf instead; only where V is no multiple of the vector does
+// one vector go element by element.  The branch per vector of load_raw_checked makes each load wait for the one
+// before: on a row's last tile that was 0.5 us of a 6.7 us greedy draft step (8 rows of 128256 bf16 logits), 0.8 of 7.4
+// at 151936.
+template <typename DT> struct NegInfVec;
+template <> struct NegInfVec<float> { static __device__ __forceinline__ f32x4 value() { return f32x4{neg_inf(), neg_inf(), neg_inf(), neg_inf()}; } };
+template <> struct NegInfVec<bf16> { static __device__ __forceinline__ u32x4 value() { return u32x4{0xFF80FF80u, 0xFF80FF80u, 0xFF80FF80u, 0xFF80FF80u}; } };
+template <> struct NegInfVec<f16> { static __device__ __forceinline__ u32x4 value() { return u32x4{0xFC00FC00u, 0xFC00FC00u, 0xFC00FC00u, 0xFC00FC00u}; } };
+template <typename DT, int NU, int STEP>
+__device__ __forceinline__ void load_raw_tail(const DT *row, int v0, int V, typename RawOf<DT>::type (&raw)[NU])
+{
+    constexpr int N = VecOf<DT>::N;
+    const int whole = V / N;
+    if (whole > 0) {
+#pragma unroll
+        for (int u = 0; u < NU; ++u) raw[u] = load_raw<DT>(row, min(v0 + u * STEP, whole - 1));
+    }
+#pragma unroll
+    for (int u = 0; u < NU; ++u)
+        if (v0 + u * STEP >= whole) raw[u] = NegInfVec<DT>::value();
+    if (V % N != 0) {
+#pragma unroll
+        for (int u = 0; u < NU; ++u)
+            if (v0 + u * STEP == whole) raw[u] = load_raw_edge(row, whole, V);
+    }
+}
+
 // Widening of one 16-byte vector to fp32 (exact for every storage type).
 template <typename DT>
 __device__ __forceinline__ void unpack(const typename RawOf<DT>::type &v, float (&z)[VecOf<DT>::N]);
@@ -172,7 +209,9 @@ __device__ __forceinline__ void unpack<f16>(const u32x4 &v, float (&z)[8])
 
 // The most negative finite value of a storage type, and the widening of a vector with everything below it (-inf)
 // raised to it.  As unsigned integers the 16-bit negatives sort by magnitude with -inf above all finite ones, so one
-// packed minimum does two logits.
+// packed minimum does two logits.  (Widening and subtracting at once by v_dot2_f32_bf16 against (1, 0) and (0, 1), with
+// the maxima taken on the packed vectors, is a sixth fewer vector instructions for the draft statistics and changed
+// nothing measurable.)
 template <typename DT> struct FiniteLow;
 template <> struct FiniteLow<float> { static __device__ __forceinline__ float value() { return -3.402823466e38f; } };
 template <> struct FiniteLow<bf16> {
@@ -183,6 +222,17 @@ template <> struct FiniteLow<f16> {
     static constexpr unsigned short bits = 0xFBFF;
     static __device__ __forceinline__ float value() { return -65504.f; }
 };
+template <typename DT>
+__device__ __forceinline__ bool all_neg_inf(const f32x4 &v)
+{
+    return v.x == neg_inf() && v.y == neg_inf() && v.z == neg_inf() && v.w == neg_inf();
+}
+template <typename DT>
+__device__ __forceinline__ bool all_neg_inf(const u32x4 &v)
+{
+    constexpr unsigned inf2 = (FiniteLow<DT>::bits + 1u) * 0x10001u;       // -inf is the next pattern after the last finite one
+    return v.x == inf2 && v.y == inf2 && v.z == inf2 && v.w == inf2;
+}
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 template <typename DT>
 __device__ __forceinline__ void unpack_finite(const typename RawOf<DT>::type &v, float (&z)[VecOf<DT>::N])
@@ -273,8 +323,8 @@ struct ExpRef {
 __device__ __forceinline__ ExpRef make_exp_ref(const Scale &sc, double L)
 {
     ExpRef r;
-    r.c_hi = sc.c_hi;
-    r.c_lo = sc.c_lo;
+    r.c_hi = in_vgpr(sc.c_hi);
+    r.c_lo = in_vgpr(sc.c_lo);
     r.L_hi = (float)L;
     r.L_lo = (float)(L - (double)r.L_hi);
     return r;
@@ -282,17 +332,18 @@ __device__ __forceinline__ ExpRef make_exp_ref(const Scale &sc, double L)
 
 // Softmax statistics of a slice relative to its own maximum m:
 //   S = sum exp2((z - m) c),   t = sum exp2((z - m) c) * (z - m) c    (t only if WITH_T).
-struct Partial {
+// 32 bytes: at 24, where records of different waves share a sector of a cache line, the greedy draft step of 64 rows took
+// 0.17 us longer.
+struct alignas(32) Partial {
     float m;
     int idx;       // smallest index holding m (only filled by the argmax-tracking variants)
     double S;
     double t;
 };
 
-// Smallest token index among the batch's elements equal to v (-1 if none); z[u] is vector
-// (t0 + u) * TW + (thread index modulo TW) of the row: TW = WG for a workgroup reading tile by tile,
-// TW = 64 for a wave reading chunk by chunk.
-template <int N, int NU, int TW = WG>
+// Smallest token index among the batch's elements equal to v (-1 if none); z[u] is vector (t0 + u) * WG + thread of
+// the row.
+template <int N, int NU>
 __device__ __forceinline__ int first_equal(const float (&z)[NU][N], float v, int t0)
 {
     int found = -1;
@@ -300,62 +351,9 @@ __device__ __forceinline__ int first_equal(const float (&z)[NU][N], float v, int
     for (int u = NU - 1; u >= 0; --u) {
 #pragma unroll
         for (int e = N - 1; e >= 0; --e)
-            if (z[u][e] == v) found = ((t0 + u) * TW + (int)(threadIdx.x & (TW - 1))) * N + e;
+            if (z[u][e] == v) found = ((t0 + u) * WG + (int)threadIdx.x) * N + e;
     }
     return found;
-}
-
-// One batch of NU vectors per thread folded into the thread's running statistics: m, the maximum
-// of its logits so far; with x = (z - m) c and w = exp2(x):  ones = the number of weights that are
-// exactly 1 in fp32 (the maximum, its ties, anything within one rounding of it), S = the sum of all
-// other weights, t = sum w x.  Keeping the ones out of the fp32 sum is what keeps small entropies
-// accurate: next to a 1 the tail of a confident row (1e-4 and less) would lose its low bits.  The
-// loop sums fract(w) (fract(1) = 0, fract(w) = w below 1) beside w itself; the difference of the two
-// batch sums is the batch's count of ones up to rounding far below 1/2.  With ARG, idx follows the
-// smallest index that holds m: it moves only when the maximum strictly increases, so earlier equal
-// values keep it; the batch is one wave's chunks c0 .. c0 + NU - 1 (64 vectors each).
-template <int N, int NU, bool ARG>
-__device__ __forceinline__ void accumulate(const float (&z)[NU][N], float &m, float &ones, float &S, float &t,
-                                           const Scale &sc, int &idx, int c0)
-{
-    float mb = tree_max<N>(z[0]);
-#pragma unroll
-    for (int u = 1; u < NU; ++u) mb = vmax(mb, tree_max<N>(z[u]));
-    if (mb > m) {
-        if (ARG) idx = first_equal<N, NU, 64>(z, mb, c0);
-        if (m != neg_inf()) {
-            const float xd = scaled_diff(m, mb, sc);
-            const float f = exp2_raw(xd);
-            if (f < 1.0f) {                     // the old maximum becomes an ordinary term
-                const float all = S + ones;
-                t = f * fmaf(xd, all, t);
-                S = f * all;
-                ones = 0.f;
-            }                                   // else: still weight 1 at fp32 resolution, nothing moves
-        }
-        m = mb;
-    }
-    const float mref = (m == neg_inf()) ? 0.f : m;
-    float Wb = 0.f, Sb = 0.f, tb = 0.f;
-#pragma unroll
-    for (int u = 0; u < NU; ++u) {
-        float w[N], fr[N], wx[N];
-#pragma unroll
-        for (int i = 0; i < N; ++i) {
-            const float x = scaled_diff(z[u][i], mref, sc);
-            w[i] = exp2_raw(x);
-            wx[i] = w[i] * x;
-            fr[i] = __builtin_amdgcn_fractf(w[i]);
-        }
-        // group sums are formed first, then added to the batch sum: the running sums only
-        // ever take one addition per batch
-        Wb += tree_sum<N>(w);
-        Sb += tree_sum<N>(fr);
-        tb += tree_sum<N>(wx);
-    }
-    ones += rintf(Wb - Sb);
-    S += Sb;
-    t += tb;
 }
 
 // LDS of one workgroup combination (each field is written once, so two barriers suffice).
@@ -386,12 +384,13 @@ __device__ __forceinline__ void accumulate_lse(const float (&z)[NU][N], float &m
         ref = nref;
     }
     const float nr = (m == neg_inf()) ? 0.f : -ref;
+    const float c_up = in_vgpr(sc.c_up), c_dn = in_vgpr(sc.c_dn);
     float Sb = 0.f;
 #pragma unroll
     for (int u = 0; u < NU; ++u) {
         float e[N];
 #pragma unroll
-        for (int i = 0; i < N; ++i) e[i] = exp2_raw(fmaf(z[u][i], sc.c_up, fmaf(z[u][i], sc.c_dn, nr)));
+        for (int i = 0; i < N; ++i) e[i] = exp2_raw(fmaf(z[u][i], c_up, fmaf(z[u][i], c_dn, nr)));
         Sb += tree_sum<N>(e);
     }
     S += Sb;

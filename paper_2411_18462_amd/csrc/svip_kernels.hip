@@ -2,7 +2,7 @@
 // live in draft_kernels.h, verify_kernels.h, greedy_kernels.h, pair_kernels.h and warp_kernels.h.
 //
 // svip_draft_step  =  k_draft_stats    grid (rows * records / 4) one wave per record: (m, S, t) of a tile of a row
-//                     k_draft_finish   grid (rows)               merge of the records: entropy, stop test, inverse
+//                     k_draft_finish_* grid (rows)               merge of the records: entropy, stop test, inverse
 //                                      CDF inside the one record that holds the draw (greedy: the first maximum)
 // svip_verify      =  k_verify_stats   grid (stat rows * slices) per-slice (reference, sum) of every needed row
 //                     k_accept         grid (sequences), 1 wave  p/q tests, ballot scan for the first rejection
@@ -30,6 +30,8 @@
 #include <math.h>
 #include <stdint.h>
 #include <stdlib.h>
+
+#include <type_traits>
 
 #include "../../include/svip.h"
 #include "../../include/svip_bench.h"
@@ -191,6 +193,10 @@ static bool launch(void (*kernel)(A), unsigned grid, unsigned block, hipStream_t
            hipSuccess;
 }
 
+// Whether the sampling draft step keeps the masses of its records' chunks (see draft_kernels.h).
+constexpr long long DRAFT_QUARTER_WAVES = 8100;
+static bool quarter_records(int B, const Geo &g) { return g.tps == 1 && (long long)B * g.ns <= DRAFT_QUARTER_WAVES; }
+
 // ---- workspace each call needs (its own geometry; svip_workspace_bytes bounds them all) -------
 
 // flag word + records + ticket counters + slice masses of the residual pass (mass_slices per sequence)
@@ -199,7 +205,11 @@ static size_t ws_fixed_bytes(int B, int mass_slices)
     return HEADER_BYTES + ws_rec_bytes(B) + ws_mass_bytes(B, mass_slices) + ws_ticket_bytes(B);
 }
 
-static size_t need_draft(int B, const Geo &g) { return ws_fixed_bytes(B, 0) + align256((size_t)B * g.ns * sizeof(Partial)); }
+static size_t need_draft(int B, const Geo &g, bool greedy)
+{
+    const size_t rec = !greedy && quarter_records(B, g) ? sizeof(QuarterRec) : sizeof(Partial);
+    return ws_fixed_bytes(B, 0) + align256((size_t)B * g.ns * rec);
+}
 static size_t need_verify_greedy(int B, int k, const Geo &g)
 {
     return ws_fixed_bytes(B, 0) + align256((size_t)B * (k + 1) * g.ns * sizeof(unsigned long long));
@@ -222,12 +232,12 @@ static size_t need_pair(int B, int k, bool recompute_lse, const Geo &g, const Ge
 
 // The slicing each pass uses (forced = an experiment's override, 0 = the library's choice).
 // The draft step: one record (= one wave of the statistics launch) per tile of 32 logits per thread, so the
-// search reads a single tile again; rows of more than MAX_SLICES tiles put more tiles into a record, and so do
-// batches that would otherwise launch more than 8100 waves (eight per SIMD): about a quarter of a one-tile
-// wave's instructions are per-record overhead, which then outweighs the finer grain and the shorter search
-// (rows of 128K logits, us per step with 63 and with 32 records, rows placed by XCD in both: 48 rows 9.5 / 10.0,
-// 64 rows 10.2 / 10.5, 80 rows 11.0 / 11.9, 96 rows 11.7 / 12.1, 112 rows 12.3 / 13.2, 128 rows 13.2 / 13.6,
-// 144 rows 14.95 / 14.6).
+// search reads little again; up to 128 records per row (two per lane of the finish: 64 rows of 151936 bf16 logits, 75
+// tiles, 11.2 us per step instead of 11.7 with 38 records of two tiles, 16 rows of 128256 fp32 logits 7.75 / 8.67).
+// Rows of more tiles put more of them into a record, and so do batches that would otherwise launch more than 8100
+// waves (eight per SIMD): about a quarter of a one-tile wave's instructions are per-record overhead, which then
+// outweighs the finer grain and the shorter search (rows of 128256 logits, us per step with 63 and with 32 records: 128
+// rows 12.5 / 12.6, 192 rows 16.1 / 15.3, 256 rows 19.1 / 18.3).
 static Geo geo_draft(int B, int V, int vec, int forced)
 {
     Geo g;
@@ -235,7 +245,8 @@ static Geo geo_draft(int B, int V, int vec, int forced)
     const int nvec = (V + vec - 1) / vec;
     g.ntiles = (nvec + WG - 1) / WG;
     int ns = g.ntiles < MAX_SLICES ? g.ntiles : MAX_SLICES;
-    if ((long long)B * ns > 8100 && ns == g.ntiles && ns > 1) ns = (ns + 1) / 2;
+    if (g.ntiles > MAX_SLICES && g.ntiles <= 2 * MAX_SLICES && (long long)B * g.ntiles <= DRAFT_QUARTER_WAVES) ns = g.ntiles;
+    if ((long long)B * ns > DRAFT_QUARTER_WAVES && ns == g.ntiles && ns > 1) ns = (ns + 1) / 2;
     if (forced > 0) ns = forced < MAX_SLICES ? forced : MAX_SLICES;
     if (ns > g.ntiles) ns = g.ntiles;
     if (ns < 1) ns = 1;
@@ -268,7 +279,7 @@ svip_status draft_step_call(const DraftCall &c)
 
     DraftArgs a;
     a.geo = geo_draft(c.B, c.V, vec, g_tune.draft_slices);
-    if (!workspace_ok(c.workspace, c.workspace_bytes, need_draft(c.B, a.geo))) return SVIP_ERR_WORKSPACE;
+    if (!workspace_ok(c.workspace, c.workspace_bytes, need_draft(c.B, a.geo, c.greedy))) return SVIP_ERR_WORKSPACE;
     const Workspace w = carve(c.workspace, c.workspace_bytes, c.B, 0);
     a.logits = c.logits;
     a.row_stride = c.row_stride;
@@ -302,21 +313,29 @@ svip_status draft_step_call(const DraftCall &c)
     a.rows_by_xcd = waves <= 8100u && a.geo.ns >= NWAVE;
     const unsigned grid = a.rows_by_xcd ? ((rows + 7u) / 8u) * 8u * (((unsigned)a.geo.ns + NWAVE - 1) / NWAVE)
                                         : (waves + NWAVE - 1) / NWAVE;
-    // the kernel's division: floor(n / d) = umulhi(n, floor(2^32 / d) + 1) while n * d < 2^32 (n < 2^26 waves, d <= 64)
+    // the kernel's division: floor(n / d) = umulhi(n, floor(2^32 / d) + 1) while n * d < 2^32 (n < 2^26 waves with d <= 64,
+    // or n <= 8100 with d <= 128)
     a.div = a.rows_by_xcd ? ((unsigned)a.geo.ns + NWAVE - 1) / NWAVE : (unsigned)a.geo.ns;
     a.div_magic = a.div > 1u ? (unsigned)(0x100000000ull / a.div) + 1u : 0u;
     bool ok = false;
     by_dtype(c.dtype, [&](auto tag) {
         using DT = decltype(tag);
-        const bool two = a.geo.tps == 2;
+        const int tps = a.geo.tps;
+        const auto stats = [&](auto kind) {
+            constexpr RecordKind K = decltype(kind)::value;
+            return launch(tps == 1 ? k_draft_stats<DT, K, 1> : (tps == 2 ? k_draft_stats<DT, K, 2> : k_draft_stats<DT, K, 0>), grid,
+                          WG, st, a, SVIP_BENCH_K_DRAFT_STATS);
+        };
         if (c.greedy)
-            ok = launch(two ? k_draft_stats<DT, true, true> : k_draft_stats<DT, true, false>, grid, WG, st, a,
-                        SVIP_BENCH_K_DRAFT_STATS) &&
-                 launch(k_draft_finish<DT, true>, rows, 64, st, a, SVIP_BENCH_K_DRAFT_FINISH);
+            ok = stats(std::integral_constant<RecordKind, GREEDY>{}) &&
+                 launch(a.geo.ns <= 64 ? k_draft_finish_greedy<1> : k_draft_finish_greedy<2>, rows, 64, st, a, SVIP_BENCH_K_DRAFT_FINISH);
+        else if (quarter_records(c.B, a.geo))
+            ok = launch(k_draft_stats<DT, QUARTERS, 1>, grid, WG, st, a, SVIP_BENCH_K_DRAFT_STATS) &&
+                 launch(a.geo.ns <= 64 ? k_draft_finish_quarters<DT, 1> : k_draft_finish_quarters<DT, 2>, rows, QUARTER_FINISH_THREADS,
+                        st, a, SVIP_BENCH_K_DRAFT_FINISH);
         else
-            ok = launch(two ? k_draft_stats<DT, false, true> : k_draft_stats<DT, false, false>, grid, WG, st, a,
-                        SVIP_BENCH_K_DRAFT_STATS) &&
-                 launch(k_draft_finish<DT, false>, rows, FINISH_THREADS, st, a, SVIP_BENCH_K_DRAFT_FINISH);
+            ok = stats(std::integral_constant<RecordKind, TOTAL>{}) &&
+                 launch(k_draft_finish_total<DT>, rows, TOTAL_FINISH_THREADS, st, a, SVIP_BENCH_K_DRAFT_FINISH);
     });
     return ok ? SVIP_OK : SVIP_ERR_HIP;
 }
@@ -469,6 +488,9 @@ size_t svip_workspace_bytes(int B, int k_max, int V)
     const size_t tiles = ((size_t)V + 4 * WG - 1) / (4 * WG);
     const size_t ns_max = tiles < MAX_SLICES ? tiles : MAX_SLICES;
     size_t part_bytes = (size_t)B * ns_max * sizeof(Partial);
+    const size_t q_recs = (size_t)B * (tiles < 2 * MAX_SLICES ? tiles : 2 * MAX_SLICES);      // draft records with chunk masses
+    const size_t q_bytes = (q_recs < DRAFT_QUARTER_WAVES ? q_recs : DRAFT_QUARTER_WAVES) * sizeof(QuarterRec);
+    if (q_bytes > part_bytes) part_bytes = q_bytes;
     if ((vrows + 8192) * sizeof(Partial) > part_bytes) part_bytes = (vrows + 8192) * sizeof(Partial);
     // diagnostics: two logsumexps per position and three sums per slice of its second pass
     const size_t pos = (size_t)B * (size_t)k_max;
@@ -482,7 +504,7 @@ size_t svip_workspace_needed(int call, int dtype, int B, int k_max, int V)
     const int vec = vec_of(dtype);
     const long long rows_t = (long long)B * (k_max + 1), rows_all = (long long)B * (2 * k_max + 1);
     switch (call) {
-        case SVIP_CALL_DRAFT_STEP: return need_draft(B, geo_draft(B, V, vec, 0));
+        case SVIP_CALL_DRAFT_STEP: return need_draft(B, geo_draft(B, V, vec, 0), false);      // greedy records are no larger
         case SVIP_CALL_VERIFY: return need_verify(B, k_max, false, geo_stats(rows_t, V, vec, 0), geo_resid(B, V, vec, 0));
         case SVIP_CALL_VERIFY_RECOMPUTE:
             return need_verify(B, k_max, true, geo_stats(rows_all, V, vec, 0), geo_resid(B, V, vec, 0));
@@ -546,7 +568,7 @@ svip_status svip_draft_step_static(const void *draft_logits, int dtype, int B, i
     // sizes first: a batch whose slice records do not fit the fixed scratch is refused before anything else
     if (!dtype_ok(dtype)) return SVIP_ERR_DTYPE;
     if (B <= 0 || B > MAX_BATCH || V <= 0) return SVIP_ERR_SHAPE;
-    if (need_draft(B, geo_draft(B, V, vec_of(dtype), g_tune.draft_slices)) > (size_t)SVIP_STATIC_SCRATCH_BYTES)
+    if (need_draft(B, geo_draft(B, V, vec_of(dtype), g_tune.draft_slices), false) > (size_t)SVIP_STATIC_SCRATCH_BYTES)
         return SVIP_ERR_WORKSPACE;
     void *ws = static_scratch();
     if (!ws) return SVIP_ERR_HIP;

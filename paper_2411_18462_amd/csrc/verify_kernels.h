@@ -197,6 +197,13 @@ struct ResidSlot {
     double W[TILE_MASSES], P[TILE_MASSES];
 };
 
+struct FinishLds {
+    LocateLds loc;
+    double target;
+    int slice, tile;
+    int use_resid;
+};
+
 struct ResidLds {
     double sums[NWAVE][2 * TILE_MASSES];
     FinishLds fin;

@@ -14,10 +14,12 @@ constexpr int DPP_QUAD_XOR2 = 0x4E;   // quad_perm:[2,3,0,1]
 constexpr int DPP_ROW_ROR4 = 0x124;   // row_ror:4
 constexpr int DPP_ROW_ROR8 = 0x128;   // row_ror:8
 
+// (every lane has a source under these controls, so the value for lanes without one is never used; naming a constant
+// for it instead of v itself spares a copy of v per move)
 template <int CTRL>
 __device__ __forceinline__ int dpp_mov(int v)
 {
-    return __builtin_amdgcn_update_dpp(v, v, CTRL, 0xF, 0xF, false);
+    return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xF, 0xF, true);
 }
 template <int CTRL>
 __device__ __forceinline__ float dpp_mov(float v)
@@ -105,11 +107,44 @@ __device__ __forceinline__ float wave_max(float v)
 }
 #undef SVIP_MAX_STEP
 
-// Wave-uniform fp64 sum of all 64 lanes' values by the DPP butterfly (about 30 vector-ALU slots).  The same
-// sum as two v_mfma_f64_16x16x4 against a matrix of ones is exact too and needs 6 slots, but its long
-// dependent latency made every kernel that used it slower (a draft step of 64 rows 12.7 us against 12.2 us,
+// Values of v's lanes exchanged between the wave's rows of 16 lanes (permlane16_swap) or halves (permlane32_swap)
+// and added: afterwards every row holds row 0 + row 1 or row 2 + row 3; every half holds the sum of the halves.
+__device__ __forceinline__ double join(unsigned lo, unsigned hi) { return __hiloint2double((int)hi, (int)lo); }
+__device__ __forceinline__ double add_row_pairs(double v)
+{
+    const unsigned lo = (unsigned)__double2loint(v), hi = (unsigned)__double2hiint(v);
+    const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false), h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    return join(l[0], h[0]) + join(l[1], h[1]);
+}
+__device__ __forceinline__ double add_halves(double v)
+{
+    const unsigned lo = (unsigned)__double2loint(v), hi = (unsigned)__double2hiint(v);
+    const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false), h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+    return join(l[0], h[0]) + join(l[1], h[1]);
+}
+
+// Wave-uniform fp64 sum of all 64 lanes' values by the DPP butterfly and two row exchanges (about 24 vector-ALU
+// slots).  The same sum as two v_mfma_f64_16x16x4 against a matrix of ones is exact too and needs 6 slots, but its
+// long dependent latency made every kernel that used it slower (a draft step of 64 rows 12.7 us against 12.2 us,
 // the residual pass 13.45 us against 13.1 us), so the matrix cores stay unused in this library.
-__device__ __forceinline__ double wave_sum(double v) { return wave_reduce(v, OpSum{}); }
+__device__ __forceinline__ double wave_sum(double v)
+{
+    v = row_reduce(v, OpSum{});
+    return add_halves(add_row_pairs(v));
+}
+
+// Four sums at once: lane i gets the wave's sum of v[i % 4].  The first two steps halve the number of values a lane
+// carries instead of reducing each on its own: 33 vector-ALU slots more than one sum would be 72.
+__device__ __forceinline__ double wave_sum4(const double (&v)[4])
+{
+    const bool odd = threadIdx.x & 1, upper = threadIdx.x & 2;
+    const double a = (odd ? v[1] : v[0]) + dpp_mov<DPP_QUAD_XOR1>(odd ? v[0] : v[1]);
+    const double b = (odd ? v[3] : v[2]) + dpp_mov<DPP_QUAD_XOR1>(odd ? v[2] : v[3]);
+    double r = (upper ? b : a) + dpp_mov<DPP_QUAD_XOR2>(upper ? a : b);
+    r += dpp_mov<DPP_ROW_ROR4>(r);
+    r += dpp_mov<DPP_ROW_ROR8>(r);
+    return add_halves(add_row_pairs(r));
+}
 
 // DPP move that yields 0 where a lane has no source (row shifts) or its row is masked out.
 template <int CTRL, int ROW_MASK>

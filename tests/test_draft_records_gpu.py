@@ -1,0 +1,103 @@
+"""The draft step at the sizes where its records change form: one and two records per lane of the finish, more tiles
+than that, launches past the size up to which records keep their chunks' masses, rows that end inside a vector, a
+chunk or a tile, masked tiles and extreme logits -- against the same quantities in fp64."""
+import pytest
+import torch
+
+from helpers import MARGIN, REL
+
+pytestmark = pytest.mark.gpu
+
+BF, F16, F32 = torch.bfloat16, torch.float16, torch.float32
+CASES = [
+    (BF, 1, 1), (BF, 3, 8), (F16, 2, 513), (F32, 2, 1024), (BF, 2, 2047), (BF, 2, 2049),
+    (BF, 2, 64 * 2048), (BF, 2, 64 * 2048 + 1), (F32, 2, 65 * 1024 - 3), (F16, 1, 75 * 2048 - 1664),     # two records per lane
+    (BF, 1, 128 * 2048), (F32, 2, 128 * 1024 + 1), (BF, 1, 200 * 2048 + 9),                              # and more tiles than that
+    (BF, 4100, 2048 + 520), (F32, 2701, 2 * 1024 + 7), (BF, 8101, 100), (F16, 8100, 100),               # around 8100 waves
+]
+
+
+def _rows(dtype, B, V, seed):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    per16 = 4 if dtype == F32 else 8
+    x = torch.empty(B, (V + per16 - 1) // per16 * per16, dtype=dtype, device="cuda")[:, :V]
+    x.copy_(torch.randn(B, V, device="cuda", generator=g) * (1 + 4 * torch.rand(B, 1, device="cuda", generator=g)))
+    return x, torch.rand(B, device="cuda", generator=g)
+
+
+def _step(svip, x, u, T, greedy):
+    B, V = x.shape
+    o = dict(tok=torch.full((B,), -7, dtype=torch.int32, device="cuda"), ent=torch.empty(B, device="cuda"),
+             q=torch.empty(B, device="cuda"), lse=torch.empty(B, dtype=torch.float64, device="cuda"),
+             stop=torch.empty(B, dtype=torch.uint8, device="cuda"))
+    svip.draft_step(x, temperature=T, h=1.5, step_j=0, k_max=4, u_sample=None if greedy else u, greedy=greedy,
+                    token_out=o["tok"], entropy_out=o["ent"], q_tok_out=o["q"], lse_out=o["lse"], stop_out=o["stop"],
+                    workspace=svip.new_workspace(B, 4, V))
+    torch.cuda.synchronize()
+    return o
+
+
+def _check(o, x, u, T, greedy):
+    V = x.shape[1]
+    for b0 in range(0, x.shape[0], 512):
+        s = slice(b0, b0 + 512)
+        z = x[s].double() / T
+        top = z.amax(-1, keepdim=True)
+        lse0 = torch.logsumexp(z - top, -1)
+        lse = lse0 + top[:, 0]
+        p = torch.exp(z - top - lse0[:, None])
+        H = -(p * torch.log(p.clamp_min(1e-300))).sum(-1)
+        tok = o["tok"][s].long()
+        assert (tok >= 0).all() and (tok < V).all()
+        # a logsumexp sums fp32 weights of relative error 2^-22 in fp64; entropies and probabilities to the stated bar
+        assert ((o["lse"][s] - lse).abs() <= 2.0 ** -22 * lse.abs().clamp_min(1.0)).all()
+        assert ((o["ent"][s] - H).abs() <= REL * H + 1e-9).all()
+        q = p.gather(1, tok[:, None])[:, 0]
+        assert ((o["q"][s] - q).abs() <= REL * q).all()
+        if greedy:
+            assert torch.equal(tok, x[s].float().cpu().argmax(-1).to(tok.device))      # CPU argmax: the first maximum
+        else:
+            C = torch.cumsum(p, -1)
+            hi = C.gather(1, tok[:, None])[:, 0]
+            d = u[s].double() * C[:, -1]
+            assert ((d < hi + 2 * MARGIN) & (d >= hi - q - 2 * MARGIN)).all() and (q > 0).all()
+        sq = torch.sqrt(H)
+        clear = (sq - 1.5).abs() >= MARGIN
+        assert torch.equal(o["stop"][s][clear] != 0, (sq > 1.5)[clear])
+
+
+@pytest.mark.parametrize("dtype,B,V", CASES)
+def test_records_of_every_form(svip, dtype, B, V):
+    x, u = _rows(dtype, B, V, seed=V + B)
+    for greedy in (False, True):
+        for T in (1.0, 0.7):
+            _check(_step(svip, x, u, T, greedy), x, u, T, greedy)
+
+
+@pytest.mark.parametrize("dtype", [BF, F16, F32])
+@pytest.mark.parametrize("B,tiles", [(9, 5), (1400, 6)])
+def test_masked_tiles_and_extreme_logits(svip, dtype, B, tiles):
+    """Tiles that are masked but for one logit or altogether, rows of extremely negative logits, +0 beside -0 as
+    the maximum, logits of extreme size; in one-tile and in two-tile records."""
+    tile = 1024 if dtype == F32 else 2048
+    V = tiles * tile - 11
+    x, u = _rows(dtype, B, V, seed=5)
+    low, big = (torch.finfo(dtype).min, 6e4) if dtype == F16 else (-1e38, 1e35)      # |z| log2(e) stays finite in fp32
+    x[0, tile:3 * tile] = float("-inf")
+    x[0, 2 * tile + 77] = 1.0
+    x[2] = -3.0
+    x[2, [tile + 4, 2 * tile + 9]] = 0.0
+    x[2, tile + 2] = -0.0
+    x[3] = float("-inf")
+    x[3, V - 1] = 2.0
+    if B < 100:                          # the workgroup search of two-tile records forms z c in fp32 before it subtracts
+        x[1] = low
+        x[1, tile:] = float("-inf")
+        x[4, tile + 5] = big
+        x[5] = -big
+        x[5, 3] = -big * 0.5
+    x[6:] = x[6:].where(x[6:] > 2.0, torch.full_like(x[6:], float("-inf")))
+    x[6:, 17] = 3.0
+    for greedy in (False, True):
+        _check(_step(svip, x, u, 1.0, greedy), x, u, 1.0, greedy)
