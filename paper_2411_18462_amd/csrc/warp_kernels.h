@@ -14,7 +14,7 @@
 // in flight exceed L2), so the sweeps are few: count + maximum, mass + candidates, candidates of
 // the nucleus bin if it is another one, masked copy.  A small top_k skips the histograms: a pivot
 // from a sample, one sweep for the candidates above it (which also writes the output when that
-// is a different buffer), everything else on the list.
+// is a different buffer), everything else on the list.  top_p alone does likewise with two sweeps.
 #pragma once
 #include "row_math.h"
 
@@ -25,6 +25,10 @@ constexpr int WARP_WAVES = WARP_WG / 64;
 constexpr int WARP_BINS = 2048;            // histogram bins: digits of up to 11 bits
 constexpr int WARP_CAP = 8192;             // keys of one first-digit bin that fit the candidate list
 constexpr int DIGIT1_SHIFT = 21;           // first digit = top 11 bits of the key
+// Rows from which top_p alone takes its shortcut: below, the select over the list costs more than the sweeps it saves
+// (us, histogram path / shortcut: 136 rows of 50257 f16 28 / 33, 1 row of 32000 f32 18.7 / 22; 256 rows of 151936 bf16
+// 77 / 62, 1 row of 128256 bf16 50 / 40).
+constexpr int NUCLEUS_MIN_V = 98304;
 
 struct WarpArgs {
     const void *in;
@@ -402,6 +406,133 @@ __device__ __forceinline__ int small_k_shortcut(const DT *row, DT *dst, int V, c
     return 2;
 }
 
+// Shortcut for top_p alone.  A row's nucleus is usually some hundreds of tokens; the histogram path finds it with a
+// 64-bit LDS atomic for every logit, a further sweep for the keys of one bin and one that copies.  Here
+//   sweep 1: every thread's maximum.  The smallest maximum of four threads is the pivot: whatever the row's
+//            distribution, about 256 ln 256 = 1400 logits are at or above it;
+//   sweep 2: the keys >= pivot into L.list, the total mass in registers with the same integer arithmetic, hence the same
+//            threshold; with `fused` (output is not the input) it also writes the logits >= pivot, -inf below, and
+//            afterwards only the candidates below the threshold are overwritten.
+// Between the two an estimate tells whether the list will reach top_p of the total: the mass above the pivot is at least
+// that of the threads' maxima, and the mass below comes from a sample, which cannot miss much as no logit below the pivot
+// outweighs it.  A row that is too flat leaves here with the sweep behind it that the histogram path needs first anyway.
+// Returns 0: nothing decided (*m_out is the row maximum); 1, 2: as small_k_shortcut.
+template <typename DT, bool fused>
+__device__ __forceinline__ int nucleus_shortcut(const DT *row, DT *dst, int V, const WarpArgs &a, unsigned *tau_out,
+                                             int *kept_out, float *m_out, WarpLds &L)
+{
+    constexpr int N = VecOf<DT>::N;
+    constexpr float LOWEST = -3.402823466e38f;
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int nvec = (V + N - 1) / N;
+    const int nsamp = nvec < WARP_WG ? nvec : WARP_WG;            // sampled vectors
+    constexpr unsigned cap = fused ? WARP_CAP / 2 : WARP_CAP;
+    float mine_max = neg_inf();
+    for_each_vector<DT>(row, V, [&](int, const float(&z)[N]) { mine_max = vmax(mine_max, tree_max<N>(z)); });
+    float group = vmax(mine_max, __shfl_xor(mine_max, 1));
+    group = vmax(group, __shfl_xor(group, 2));
+    if (tid >= nvec) group = -neg_inf();
+    typename RawOf<DT>::type sample;
+    if (tid < nsamp)                                              // the same runs of whole cache lines as in small_k_shortcut
+        sample = warp_load<DT>(row, nvec <= WARP_WG ? tid : (int)((long long)(tid >> 6) * (nvec - 64) / 15) + (tid & 63), V);
+    {
+        const float hi = wave_max(mine_max), lo = -wave_max(-group);
+        if (lane == 0) {
+            L.wave_max[wave] = hi;
+            L.wave_tot[wave] = __float_as_uint(lo);
+        }
+    }
+    if (tid == 0) L.n_list = 0u;
+    __syncthreads();
+    float m = neg_inf(), pz = neg_inf();
+#pragma unroll
+    for (int w = 0; w < WARP_WAVES; ++w) {
+        m = vmax(m, L.wave_max[w]);
+        pz = vmax(pz, -__uint_as_float((unsigned)L.wave_tot[w]));
+    }
+    pz = vmax(-pz, LOWEST);                                       // masked logits are no candidates
+    *m_out = m;
+    float head = exp2_raw(scaled_diff(mine_max, m, a.sc)), tail = 0.f;
+    if (tid < nsamp) {
+        float z[N];
+        unpack<DT>(sample, z);
+#pragma unroll
+        for (int e = 0; e < N; ++e) tail += z[e] < pz ? exp2_raw(scaled_diff(z[e], m, a.sc)) : 0.f;
+    }
+    head = wave_reduce(head, OpSum{});
+    tail = wave_reduce(tail, OpSum{});
+    if (lane == 0) L.sub[wave] = ((unsigned long long)__float_as_uint(head) << 32) | __float_as_uint(tail);
+    __syncthreads();
+    head = tail = 0.f;
+#pragma unroll
+    for (int w = 0; w < WARP_WAVES; ++w) {
+        head += __uint_as_float((unsigned)(L.sub[w] >> 32));
+        tail += __uint_as_float((unsigned)L.sub[w]);
+    }
+    // a wrong yes costs a sweep, a wrong no the saving: a fifth of the tail allowed is kept as a margin
+    tail *= (float)V / (float)(nsamp * N);
+    if (!(0.8f * (1.f - (float)a.top_p) * head >= (float)a.top_p * tail)) return 0;
+    const MassMeasure mass{m, a.sc, a.fix_scale * (1.0f / 4294967296.0f)};
+    unsigned long long mine = 0ull;
+    for_each_vector<DT>(row, V, [&](int vi, const float(&z)[N]) {
+        float o[N];
+        unsigned c = 0u;
+#pragma unroll
+        for (int e = 0; e < N; ++e) {
+            const bool cand = !(z[e] < pz);                      // a NaN goes into the list, where its key decides
+            mine += mass(z[e]);
+            c += cand ? 1u : 0u;
+            o[e] = cand ? z[e] : neg_inf();
+        }
+        if (c) {
+            unsigned i = atomicAdd(&L.n_list, c);
+#pragma unroll
+            for (int e = 0; e < N; ++e) {
+                if (!(z[e] < pz)) {
+                    if (i < cap) {
+                        L.list[i] = value_key(z[e]);
+                        if (fused) L.list[cap + i] = (unsigned)(vi * N + e);
+                    }
+                    ++i;
+                }
+            }
+        }
+        if (fused) {
+            if ((vi + 1) * N <= V) {
+                store_vec<DT>(dst + (long long)vi * N, o);
+            } else {
+#pragma unroll
+                for (int e = 0; e < N; ++e)
+                    if (vi * N + e < V) store_one<DT>(dst + (long long)vi * N + e, o[e]);
+            }
+        }
+    });
+    const unsigned long long Z = wg_sum_u64(mine, L);             // its barriers also cover the list
+    const unsigned n = L.n_list;
+    if (n > cap) return 0;
+    const ListSource ls{L.list, n};
+    mine = 0ull;
+    ls.for_each([&](unsigned, float z) { mine += mass(z); });
+    const unsigned long long Zl = wg_sum_u64(mine, L);
+    unsigned long long target = (unsigned long long)llrint(a.top_p * (double)Z);
+    target = target ? target : 1ull;
+    if (Zl < target) return 0;
+    const unsigned tau = select_digits(ls, 0u, mass, 0u, 0, target, L);
+    *tau_out = tau;
+    if (!fused) return 1;
+    // the sweep's stores are complete (every barrier since waited for them): drop the candidates below tau
+    unsigned long long kept = 0ull;
+    for (unsigned i = tid; i < n; i += WARP_WG) {
+        const unsigned idx = L.list[cap + i];
+        if (idx < (unsigned)V) {
+            if (L.list[i] >= tau) kept += 1ull;
+            else store_one<DT>(dst + idx, neg_inf());
+        }
+    }
+    *kept_out = (int)wg_sum_u64(kept, L);
+    return 2;
+}
+
 // The keys of first-digit bin d1 into L.list (the caller has checked that they fit).
 template <typename DT>
 __device__ __forceinline__ void collect(const RowSource<DT> &rs, unsigned d1, WarpLds &L)
@@ -417,8 +548,9 @@ __device__ __forceinline__ void collect(const RowSource<DT> &rs, unsigned d1, Wa
     __syncthreads();
 }
 
-// grid (rows), WARP_WG threads.
-template <typename DT>
+// grid (rows), WARP_WG threads.  NUCLEUS: top_p alone (an instance of its own: either shortcut's code costs the other
+// one registers).
+template <typename DT, bool NUCLEUS>
 __global__ __launch_bounds__(WARP_WG, 8) void k_warp(WarpArgs a)
 {
     constexpr int N = VecOf<DT>::N;
@@ -430,7 +562,7 @@ __global__ __launch_bounds__(WARP_WG, 8) void k_warp(WarpArgs a)
     DT *dst = static_cast<DT *>(a.out) + off;
     const int V = a.V;
 
-    const bool K = a.top_k > 0 && a.top_k < V, P = a.top_p < 1.0;
+    const bool K = !NUCLEUS && a.top_k > 0 && a.top_k < V, P = NUCLEUS || a.top_p < 1.0;
     const RowSource<DT> rs{row, V};
     unsigned tau = 0u;                      // keep keys >= tau
     int kept = 0;
@@ -439,9 +571,13 @@ __global__ __launch_bounds__(WARP_WG, 8) void k_warp(WarpArgs a)
         decided = a.in != a.out && a.top_k <= WARP_CAP / 8
                       ? small_k_shortcut<DT, true>(row, dst, V, a, P, &tau, &kept, L)
                       : small_k_shortcut<DT, false>(row, dst, V, a, P, &tau, &kept, L);
+    float m = neg_inf();
+    const bool m_known = NUCLEUS && !a.no_shortcut && V >= NUCLEUS_MIN_V;
+    if (m_known)
+        decided = a.in != a.out ? nucleus_shortcut<DT, true>(row, dst, V, a, &tau, &kept, &m, L)
+                                : nucleus_shortcut<DT, false>(row, dst, V, a, &tau, &kept, &m, L);
     if (decided == 0 && (K || P)) {
         // sweep 1: keys per first digit (top-k), row maximum (reference of the top-p weights)
-        float m = neg_inf();
         unsigned d_k = 0u;
         unsigned long long k_rem = 0ull;
         if (K) {
@@ -449,19 +585,19 @@ __global__ __launch_bounds__(WARP_WG, 8) void k_warp(WarpArgs a)
             L.cnt[tid + WARP_WG] = 0u;
             __syncthreads();
         }
-        for_each_vector<DT>(row, V, [&](int, const float(&z)[N]) {
+        if (!m_known) for_each_vector<DT>(row, V, [&](int, const float(&z)[N]) {
             if (P) m = vmax(m, tree_max<N>(z));
             if (K) {
 #pragma unroll
                 for (int e = 0; e < N; ++e) atomicAdd(&L.cnt[value_key(z[e]) >> DIGIT1_SHIFT], 1u);
             }
         });
-        if (P) {
+        if (P && !m_known) {
             m = wave_max(m);
             if (lane == 0) L.wave_max[wave] = m;
         }
         __syncthreads();
-        if (P) {
+        if (P && !m_known) {
             m = L.wave_max[0];
 #pragma unroll
             for (int w = 1; w < WARP_WAVES; ++w) m = vmax(m, L.wave_max[w]);

@@ -174,6 +174,42 @@ def test_small_k_shortcut_equals_the_histogram_path(svip, dtype):
     _check(svip, x, 0.9, 0, 0.9, inplace=True)
 
 
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16, torch.float16])
+@pytest.mark.parametrize("V", [98303, 98304, 98309, 131072])
+def test_nucleus_shortcut_equals_the_histogram_path(svip, dtype, V):
+    """top_p alone on long rows: pivot from the threads' maxima, candidates in a list.  Bit for bit the histogram path,
+    for rows that are peaked, flat, masked, tied, clustered (the list overflows), all equal, or mostly dropped already."""
+    _say(f"warp nucleus shortcut {dtype} V={V}")
+    rng = np.random.default_rng(V)
+    z = rng.normal(-1.0, 5.0, (2, 5, V)).astype(np.float32)
+    z[0, 1] *= 0.3
+    z[0, 2] = np.round(z[0, 2])
+    z[0, 3, : V // 4] += 12.0
+    z[0, 4, ::3] = -np.inf
+    z[1, 0] = 1.25
+    z[1, 1, rng.random(V) < 0.999] = -np.inf
+    z[1, 2, -3:] += 30.0
+    z[1, 3, 5:] = -np.inf
+    z[1, 4] *= 0.8
+    x = torch.from_numpy(z).to(dtype)
+    bits = torch.int32 if dtype == torch.float32 else torch.int16
+    src = _padded_buf(x)[1]
+    for top_p in (0.05, 0.5, 0.9, 0.95, 0.999):
+        got = []
+        for no_shortcut, inplace in ((1, False), (0, False), (0, True)):
+            svip.bench_set_tuning(warp_no_shortcut=no_shortcut)
+            kept = torch.zeros(10, dtype=torch.int32, device="cuda")
+            a = _padded_buf(x)[1] if inplace else src
+            out = a if inplace else _padded_buf(torch.zeros_like(x))[1]
+            svip.warp_logits(a, temperature=0.9, top_p=top_p, out=out, kept_out=kept)
+            torch.cuda.synchronize()
+            got.append((out.contiguous().view(bits), kept))
+        svip.bench_set_tuning()
+        for o, kept in got[1:]:
+            assert torch.equal(got[0][0], o), top_p
+            assert torch.equal(got[0][1], kept), top_p
+
+
 @pytest.mark.parametrize("seed", range(24))
 def test_seeded_shapes_and_settings(svip, seed):
     """Random vocabulary sizes (ragged tails), storage types, temperatures, filters, row kinds, in place or not."""
