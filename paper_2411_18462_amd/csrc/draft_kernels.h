@@ -144,7 +144,7 @@ __device__ __forceinline__ bool wave_tile(const typename RawOf<DT>::type (&raw)[
     if (!(mt > FiniteLow<DT>::value() && mt < 1e30f)) return false;
     const bool higher = mt > mw;
     if (higher) {
-        if (mw != neg_inf()) sums.rescale(exp2_raw(scaled_diff(mw, mt, sc)), mw - mt, td);
+        if (mw != neg_inf()) sums.rescale(exp2_raw(scaled_below_floored(mw - mt, sc)), mw - mt, td);
         mw = mt;
         idx = -1;
     }
@@ -154,7 +154,7 @@ __device__ __forceinline__ bool wave_tile(const typename RawOf<DT>::type (&raw)[
 #pragma unroll
         for (int e = 0; e < N; ++e) {
             d[e] = z[u][e] - mw;
-            w[e] = exp2_raw(fmaf(d[e], sc.c_hi, d[e] * sc.c_lo));
+            w[e] = exp2_raw(scaled_below(d[e], sc));
         }
         // two chains of N / 2 terms: no more roundings in a row than the tree of products had
         float ta = w[0] * d[0], tb = w[N / 2] * d[N / 2];
@@ -227,7 +227,7 @@ __device__ __forceinline__ void uncommon_record(const DraftArgs &a, const DT *ro
         float w[N], fr[N], wx[N];
 #pragma unroll
         for (int e = 0; e < N; ++e) {
-            const float x = scaled_diff(z[e], mw, a.sc);
+            const float x = scaled_below_floored(z[e] - mw, a.sc);
             w[e] = exp2_raw(x);
             fr[e] = __builtin_amdgcn_fractf(w[e]);
             wx[e] = w[e] * x;
@@ -284,8 +284,8 @@ __global__ __launch_bounds__(WG, TPS == 1 ? 8 : 6) void k_draft_stats(DraftArgs 
     const int nrec = a.geo.ns;
     // All arguments are requested at once: left to itself the compiler loads those behind the first branch only there,
     // a second trip to the scalar cache before the first load of a logit.
-    asm volatile("" : : "s"(a.logits), "s"(a.row_stride), "s"(a.pos), "s"(a.stop_in), "s"(a.geo.V), "s"(a.part), "s"(a.sc.c_hi),
-                 "s"(a.sc.c_lo), "s"(a.sc.c), "s"(a.common_range), "s"(a.step_j));
+    asm volatile("" : : "s"(a.logits), "s"(a.row_stride), "s"(a.pos), "s"(a.stop_in), "s"(a.geo.V), "s"(a.part), "s"(a.sc.c_dn),
+                 "s"(a.sc.c_up), "s"(a.sc.c), "s"(a.common_range), "s"(a.step_j));
     // Which record this wave takes is the same in all its lanes: worked out in scalar registers, with the one
     // division done by a multiplication the host prepared, so that none of it takes vector-ALU slots.
     const unsigned wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -366,7 +366,7 @@ __device__ __forceinline__ void search_chunk(const DT *row, int V, int chunk, fl
     wave_load<DT, 1, true>(row, V, chunk, raw);
     unpack<DT>(raw[0], z);
 #pragma unroll
-    for (int e = 0; e < N; ++e) w[e] = exp2_raw(scaled_diff(z[e], m, sc));
+    for (int e = 0; e < N; ++e) w[e] = exp2_raw(scaled_below_floored(z[e] - m, sc));
     const double g = (double)tree_sum<N>(w);
     const double incl = wave_inclusive_sum(g);
     const unsigned long long hit = __ballot(g > 0.0 && incl > target), mass = __ballot(g > 0.0);
@@ -443,7 +443,7 @@ __global__ __launch_bounds__(QUARTER_FINISH_THREADS) void k_draft_finish_quarter
     const int b = blockIdx.x, lane = threadIdx.x & 63, nrec = a.geo.ns;
     const long long o = (long long)b * a.io_stride;
     asm volatile("" : : "s"(a.logits), "s"(a.row_stride), "s"(a.pos), "s"(a.stop_in), "s"(a.geo.V), "s"(a.part), "s"(a.sc.c),
-                 "s"(a.sc.c_hi), "s"(a.sc.c_lo), "s"(a.u), "s"(a.token), "s"(a.q_tok));       // requested at once
+                 "s"(a.sc.c_dn), "s"(a.sc.c_up), "s"(a.u), "s"(a.token), "s"(a.q_tok));       // requested at once
     // independent loads first: the row's flag, its uniform and its records travel together
     const unsigned flag = request_stop_flag(a, b);
     float m[RPL];

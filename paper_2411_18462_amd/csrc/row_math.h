@@ -309,6 +309,13 @@ __device__ __forceinline__ float scaled_diff(float z, float m, const Scale &sc)
     return vmax(fmaf(d, sc.c_hi, d * sc.c_lo), X_FLOOR);
 }
 
+// d * c for d <= 0, in exp2 units.  With the constant's parts c_dn and c_up both positive the two products have one sign,
+// so however large c is (a temperature near 0) the result lies in [-inf, 0].  Against c_hi and c_lo, the second product
+// of a very negative d overflows to +inf where c_lo < -1 (temperatures below 4e-8), and a masked logit would weigh inf.
+__device__ __forceinline__ float scaled_below(float d, const Scale &sc) { return fmaf(d, sc.c_dn, d * sc.c_up); }
+// The same with the floor of scaled_diff, which also takes the NaN of masked logits.
+__device__ __forceinline__ float scaled_below_floored(float d, const Scale &sc) { return vmax(scaled_below(d, sc), X_FLOOR); }
+
 // Probability-like weight exp2(z * c - L), L given as fp32 hi + lo.
 struct ExpRef {
     float c_hi, c_lo, L_hi, L_lo;
