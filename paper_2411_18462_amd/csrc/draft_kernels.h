@@ -124,8 +124,9 @@ template <> struct LaneSums<QUARTERS> {
 // that is worth grows with how far issue rather than latency bounds the launch; us per draft step in a graph, before
 // / after: 8 rows of 128256 bf16 logits 7.74 / 7.63, 64 rows 10.19 / 10.06 (greedy 9.75 / 9.26), 128 rows 13.6 / 12.8,
 // 256 rows 20.1 / 18.5.
-// Returns false for the tiles this form is not for: no logit above the most negative finite number (masked tiles), or
-// one beyond 1e30.
+// Returns false for the tiles this form is not for: those whose maximum is so close to the most negative finite number
+// that a lowered logit would not weigh exactly 0 (masked tiles; fp16 logits around -65504, or at temperatures in the
+// hundreds), or beyond 1e30.
 template <typename DT, int NU, RecordKind KIND>
 __device__ __forceinline__ bool wave_tile(const typename RawOf<DT>::type (&raw)[NU], int c0, float &mw, LaneSums<KIND> &sums,
                                           float &td, int &idx, const Scale &sc)
@@ -141,7 +142,7 @@ __device__ __forceinline__ bool wave_tile(const typename RawOf<DT>::type (&raw)[
 #pragma unroll
     for (int u = 1; u < NU; ++u) mt = vmax(mt, gm[u]);
     mt = wave_max(mt);
-    if (!(mt > FiniteLow<DT>::value() && mt < 1e30f)) return false;
+    if (!((mt - FiniteLow<DT>::value()) * sc.c_dn > -X_FLOOR && mt < 1e30f)) return false;
     const bool higher = mt > mw;
     if (higher) {
         if (mw != neg_inf()) sums.rescale(exp2_raw(scaled_below_floored(mw - mt, sc)), mw - mt, td);

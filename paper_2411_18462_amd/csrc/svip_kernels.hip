@@ -288,8 +288,7 @@ svip_status draft_step_call(const DraftCall &c)
     a.cap = c.cap;
     a.B = c.B;
     a.sc = make_scale(c.temperature);
-    // the most negative finite logit must weigh nothing, and the exponents of the others must not overflow
-    a.common_range = a.sc.c * (c.dtype == SVIP_F16 ? 65504.0 : 3.3e38) > 1e4 && a.sc.c < 1e30;
+    a.common_range = a.sc.c < 1e30;           // both parts of the constant are finite
     a.h = c.h;
     a.step_j = c.step_j;
     a.k_max = c.k_max;

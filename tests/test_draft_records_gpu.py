@@ -118,3 +118,21 @@ def test_temperatures_near_zero(svip, dtype, B, V):
         q_rel = REL + (2.0 ** -47 * x.float().abs()[x > -1e4].max().item() / T if B > 4 else 0.0)
         for greedy in (False, True):
             _check(_step(svip, x, u, T, greedy), x, u, T, greedy, q_rel)
+
+
+@pytest.mark.parametrize("B,V", [(6, 3 * 2048 + 77), (4100, 2048 + 520)])
+@pytest.mark.parametrize("T", [1.0, 9.0, 12.0, 300.0, 3000.0])
+def test_fp16_rows_near_the_lowest_number(svip, B, V, T):
+    """fp16 has no room below -65504 in which a masked logit could stand for -inf next to logits around it."""
+    x, u = _rows(F16, B, V, seed=V)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1)
+    low = (-65504.0 + 32.0 * torch.randint(0, 2, (2, V), device="cuda", generator=g)).half()
+    x[0:2] = low.where(torch.rand(2, V, device="cuda", generator=g) < 0.01, torch.full_like(low, float("-inf")))
+    x[1, :V // 2] = float("-inf")
+    x[2, torch.rand(V, device="cuda", generator=g) < 0.5] = float("-inf")
+    x[3, torch.rand(V, device="cuda", generator=g) < 0.5] = -65504.0
+    # (see test_temperatures_near_zero for the second term)
+    q_rel = REL + (2.0 ** -47 * 65504.0 / T if B > 6 else 0.0)
+    for greedy in (False, True):
+        _check(_step(svip, x, u, T, greedy), x, u, T, greedy, q_rel)
