@@ -194,7 +194,7 @@ __device__ __forceinline__ bool wave_tile(const typename RawOf<DT>::type (&raw)[
     return true;
 }
 
-// A record outside wave_tile's range (a masked tile, logits or a temperature of extreme size), from memory again:
+// A record outside wave_tile's range (a masked tile, NaN, logits or a temperature of extreme size), from memory again:
 // maximum first, then sums chunk by chunk with a floor under every exponent -- few registers, this is rare.
 // S[q]: this lane's sum over the record's chunks q, q + 4, ..; td in units of log2 here.
 template <typename DT, RecordKind KIND>
@@ -339,6 +339,9 @@ __global__ __launch_bounds__(WG, TPS == 1 ? 8 : 6) void k_draft_stats(DraftArgs 
             }
         }
     }
+    // A NaN among the logits (only the 16-bit types get one past unpack_finite) shows in td, whose terms are all finite and
+    // at most 0 otherwise; like a masked logit it weighs nothing, by the floor of uncommon_record's exponents.
+    ok = ok && __ballot(!(td > neg_inf())) == 0ull;
     const size_t at = (size_t)b * nrec + r;
     if (ok) {
         const double t = wave_sum((double)td) * a.sc.c;

@@ -136,3 +136,23 @@ def test_fp16_rows_near_the_lowest_number(svip, B, V, T):
     q_rel = REL + (2.0 ** -47 * 65504.0 / T if B > 6 else 0.0)
     for greedy in (False, True):
         _check(_step(svip, x, u, T, greedy), x, u, T, greedy, q_rel)
+
+
+@pytest.mark.parametrize("dtype", [BF, F16, F32])
+@pytest.mark.parametrize("B,tiles", [(4, 5), (1400, 6)])
+def test_nan_logits_weigh_nothing(svip, dtype, B, tiles):
+    """A NaN logit, of either sign, counts as a masked one: every output is that of the row with -inf in its place."""
+    V = tiles * (1024 if dtype == F32 else 2048) - 11
+    x, u = _rows(dtype, B, V, seed=8)
+    at = torch.rand(3, V, device="cuda") < 0.001
+    at[2, :V // 2] = True
+    x[:3] = x[:3].masked_fill(at, float("-inf"))
+    word, quiet = {BF: (torch.int16, 0x7FC0), F16: (torch.int16, 0x7E00), F32: (torch.int32, 0x7FC00000)}[dtype]
+    for nan in (quiet, quiet + torch.iinfo(word).min):
+        y, _ = _rows(dtype, B, V, seed=8)
+        y.copy_(x)
+        bits = y.view(word)
+        bits[:3] = bits[:3].masked_fill(at, nan)
+        assert torch.isnan(y[:3][at]).all()
+        for greedy in (False, True):
+            _check(_step(svip, y, u, 1.0, greedy), x, u, 1.0, greedy)
