@@ -514,6 +514,8 @@ __global__ __launch_bounds__(QUARTER_FINISH_THREADS) void k_draft_finish_quarter
     // inside the chunk in units of the record's own maximum, as k_draft_stats formed the weights; the division runs
     // while the chunk is on its way
     in_chunk = frec > 0.0 ? in_chunk / frec : 0.0;
+    // a record without mass is only picked where the row has none (a logit of +inf): nothing there has a weight then
+    mrec = frec > 0.0 ? mrec : -neg_inf();
     const DT *row = static_cast<const DT *>(a.logits) + draft_row_offset(a, b);
     search_chunk<DT>(row, a.geo.V, chunk, mrec, a.sc, in_chunk, StoreDraftToken{a, o, frec, S});
 }

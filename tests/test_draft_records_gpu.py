@@ -156,3 +156,18 @@ def test_nan_logits_weigh_nothing(svip, dtype, B, tiles):
         assert torch.isnan(y[:3][at]).all()
         for greedy in (False, True):
             _check(_step(svip, y, u, 1.0, greedy), x, u, 1.0, greedy)
+
+
+@pytest.mark.parametrize("dtype", [BF, F16, F32])
+@pytest.mark.parametrize("B,V", [(4, 5 * 2048 - 11), (4, 70 * 2048), (1400, 6 * 2048)])
+def test_rows_without_a_distribution_have_no_token(svip, dtype, B, V):
+    """Rows with a logit of +inf, in the first or in a later record, and rows without a finite one: token -1."""
+    x, u = _rows(dtype, B, V, seed=9)
+    u[:] = torch.linspace(0, 0.999, B, device="cuda")
+    x[0, 3] = float("inf")
+    x[1, V - 5] = float("inf")
+    x[2, [5, V // 2]] = float("inf")
+    x[3] = float("-inf")
+    o = _step(svip, x, u, 1.0, False)
+    assert (o["tok"][:4] == -1).all() and torch.isnan(o["q"][:4]).all() and (o["stop"][:4] == 0).all()
+    _check({n: t[4:] for n, t in o.items()}, x[4:], u[4:], 1.0, False)
