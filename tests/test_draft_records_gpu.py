@@ -171,3 +171,32 @@ def test_rows_without_a_distribution_have_no_token(svip, dtype, B, V):
     o = _step(svip, x, u, 1.0, False)
     assert (o["tok"][:4] == -1).all() and torch.isnan(o["q"][:4]).all() and (o["stop"][:4] == 0).all()
     _check({n: t[4:] for n, t in o.items()}, x[4:], u[4:], 1.0, False)
+
+
+@pytest.mark.parametrize("B,V,greedy", [(64, 6 * 2048 - 40, False), (64, 70 * 2048, False), (64, 6 * 2048, True), (1400, 6 * 2048, False)])
+def test_stop_flags_in_place_and_apart(svip, B, V, greedy):
+    """A step that reads and writes one array of flags gives, bit for bit, what it gives with two arrays, where rows are
+    already stopped, stop by their entropy, and all stop at the cap."""
+    x, u = _rows(BF, B, V, seed=10)
+    ws = svip.new_workspace(B, 4, V)
+    before = (torch.arange(B, device="cuda") % 5 == 3).to(torch.uint8)
+
+    def step(flags_in, flags_out, j):
+        o = dict(tok=torch.full((B,), -7, dtype=torch.int32, device="cuda"), ent=torch.zeros(B, device="cuda"),
+                 q=torch.zeros(B, device="cuda"), lse=torch.zeros(B, dtype=torch.float64, device="cuda"),
+                 len=torch.zeros(B, dtype=torch.int32, device="cuda"), stop=flags_out)
+        svip.draft_step(x, temperature=1.0, h=1.4, step_j=j, k_max=4, u_sample=None if greedy else u, greedy=greedy,
+                        stop_in=flags_in, token_out=o["tok"], entropy_out=o["ent"], q_tok_out=o["q"], lse_out=o["lse"],
+                        stop_out=o["stop"], draft_len_out=o["len"], workspace=ws)
+        torch.cuda.synchronize()
+        return o
+
+    for j in (1, 3):
+        apart = step(before, torch.full_like(before, 9), j)
+        live = before == 0
+        assert (apart["tok"][live] >= 0).all() and (apart["tok"][~live] == -1).all() and (apart["stop"][~live] == 1).all()
+        assert (apart["stop"][live] == 1).all() if j == 3 else 0 < apart["stop"][live].sum() < live.sum()
+        for _ in range(20):
+            flags = before.clone()
+            same = step(flags, flags, j)
+            assert all(torch.equal(same[n], apart[n]) for n in apart)
