@@ -9,7 +9,7 @@ namespace svip {
 
 __device__ __forceinline__ long long draft_row_offset(const DraftArgs &a, int b)
 {
-    return (long long)b * a.row_stride + (a.pos ? (long long)(a.pos[b] + a.step_j) * a.pos_stride : 0ll);
+    return (long long)b * a.row_stride + (a.pos ? (long long)(__builtin_amdgcn_readfirstlane(a.pos[b]) + a.step_j) * a.pos_stride : 0ll);
 }
 __device__ __forceinline__ bool at_cap(const DraftArgs &a, int b)
 {
@@ -97,7 +97,7 @@ template <RecordKind KIND> struct LaneSums {
     {
         if (f < 1.0f) {                     // the old maximum becomes an ordinary term
             const float all = S + ones;
-            td = f * fmaf(d, all, td);
+            td = f > 0.f ? f * fmaf(d, all, td) : 0.f;       // (d may be beyond what fp32 holds then)
             S = f * all;
             ones = 0.f;
         }
@@ -124,12 +124,17 @@ template <> struct LaneSums<QUARTERS> {
 // that is worth grows with how far issue rather than latency bounds the launch; us per draft step in a graph, before
 // / after: 8 rows of 128256 bf16 logits 7.74 / 7.63, 64 rows 10.19 / 10.06 (greedy 9.75 / 9.26), 128 rows 13.6 / 12.8,
 // 256 rows 20.1 / 18.5.
-// Returns false for the tiles this form is not for: those whose maximum is so close to the most negative finite number
-// that a lowered logit would not weigh exactly 0 (masked tiles; fp16 logits around -65504, or at temperatures in the
-// hundreds), or beyond 1e30.
+// A tile without any logit above the most negative finite number only counts, in `lowest` (see count_lowest), those that
+// are that number: they have weights if the wave never sees anything higher, and none otherwise.  Rows that were filtered
+// or masked consist mostly of such tiles, and all is decided from the registers that hold them (us per step, read again
+// as uncommon_record does / so: 256 rows of 151936 bf16 logits after top-k 50 38.9 / 21.2, 64 rows of 128256 fp32
+// 13.7 / 11.3).
+// Returns false where this form does not do: where the wave's maximum stays so close to that number that a lowered logit
+// would not weigh exactly 0 (fp16 logits around -65504, or at temperatures in the hundreds), where a vector holds that
+// number beside -inf and nothing higher, or for a maximum beyond 1e30.
 template <typename DT, int NU, RecordKind KIND>
 __device__ __forceinline__ bool wave_tile(const typename RawOf<DT>::type (&raw)[NU], int c0, float &mw, LaneSums<KIND> &sums,
-                                          float &td, int &idx, const Scale &sc)
+                                          float &td, int &idx, unsigned &lowest, const Scale &sc)
 {
     constexpr int N = VecOf<DT>::N;
     float z[NU][N], gm[NU];
@@ -142,7 +147,20 @@ __device__ __forceinline__ bool wave_tile(const typename RawOf<DT>::type (&raw)[
 #pragma unroll
     for (int u = 1; u < NU; ++u) mt = vmax(mt, gm[u]);
     mt = wave_max(mt);
-    if (!((mt - FiniteLow<DT>::value()) * sc.c_dn > -X_FLOOR && mt < 1e30f)) return false;
+    const float mn = mt > mw ? mt : mw;
+    if (!((mn - FiniteLow<DT>::value()) * sc.c_dn > -X_FLOOR && mn < 1e30f)) {
+        unsigned n;
+        if (!(mt == FiniteLow<DT>::value() && count_lowest<DT, NU>(raw, &n))) return false;
+        if (KIND == GREEDY && idx < 0) {
+#pragma unroll
+            for (int u = NU - 1; u >= 0; --u) {
+                const unsigned long long hit = __ballot((n >> (8 * u)) & 0xFFu);
+                if (hit) idx = ((c0 + u) * 64 + __ffsll((long long)hit) - 1) * N;
+            }
+        }
+        lowest += n;
+        return true;
+    }
     const bool higher = mt > mw;
     if (higher) {
         if (mw != neg_inf()) sums.rescale(exp2_raw(scaled_below_floored(mw - mt, sc)), mw - mt, td);
@@ -194,58 +212,73 @@ __device__ __forceinline__ bool wave_tile(const typename RawOf<DT>::type (&raw)[
     return true;
 }
 
-// A record outside wave_tile's range (a masked tile, NaN, logits or a temperature of extreme size), from memory again:
-// maximum first, then sums chunk by chunk with a floor under every exponent -- few registers, this is rare.
-// S[q]: this lane's sum over the record's chunks q, q + 4, ..; td in units of log2 here.
+// A record outside wave_tile's range, from memory again: tile by tile with a floor under every exponent, one chunk at a
+// time in registers.  S[q]: this lane's sum over the record's chunks q, q + 4, ..; td in units of log2 here.
 template <typename DT, RecordKind KIND>
 __device__ __forceinline__ void uncommon_record(const DraftArgs &a, const DT *row, int tb, int te, float &mw, double (&S)[4],
                                                 double &td, int &idx)
 {
     constexpr int N = VecOf<DT>::N, CPT = WG / 64;
-    float m = neg_inf(), z[N];
+    mw = neg_inf();
+    idx = -1;
+    td = 0.0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) S[q] = 0.0;
 #pragma unroll 1
     for (int t0 = tb; t0 < te; ++t0) {
         typename RawOf<DT>::type tile[CPT];
         if (t0 < a.geo.V / (WG * N)) wave_load<DT, CPT, false>(row, a.geo.V, t0 * CPT, tile);
         else wave_load<DT, CPT, true>(row, a.geo.V, t0 * CPT, tile);
+        float z[N], m = neg_inf();
 #pragma unroll
         for (int u = 0; u < CPT; ++u) {
             unpack<DT>(tile[u], z);
             m = vmax(m, tree_max<N>(z));
+            asm volatile("" : "+v"(tile[u]));       // unpacked again below, not kept
         }
-    }
-    mw = wave_max(m);
-    idx = -1;
-    td = 0.0;
+        m = wave_max(m);
+        if (m == neg_inf()) continue;
+        const bool higher = m > mw;
+        if (higher) {
+            const float x = scaled_below_floored(mw - m, a.sc);       // (the floor, and so 0, for the first tile)
+            const double f = (double)exp2_raw(x);
+            td = f * (td + (double)x * ((S[0] + S[1]) + (S[2] + S[3])));
 #pragma unroll
-    for (int q = 0; q < 4; ++q) S[q] = 0.0;
-    if (mw == neg_inf()) return;
-#pragma unroll 1
-    for (int c = tb * CPT; c < te * CPT; ++c) {
-        typename RawOf<DT>::type raw[1];
-        wave_load<DT, 1, true>(row, a.geo.V, c, raw);
-        unpack<DT>(raw[0], z);
-        float w[N], fr[N], wx[N];
-#pragma unroll
-        for (int e = 0; e < N; ++e) {
-            const float x = scaled_below_floored(z[e] - mw, a.sc);
-            w[e] = exp2_raw(x);
-            fr[e] = __builtin_amdgcn_fractf(w[e]);
-            wx[e] = w[e] * x;
+            for (int q = 0; q < 4; ++q) S[q] *= f;
+            mw = m;
+            idx = -1;
         }
-        const float below = tree_sum<N>(fr);
-        const double Su = (double)below + (double)rintf(tree_sum<N>(w) - below);
-        td += (double)tree_sum<N>(wx);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) S[q] += q == (c & (CPT - 1)) ? Su : 0.0;
-        if (KIND == GREEDY && idx < 0) {
-            const unsigned long long hit = __ballot(tree_max<N>(z) == mw);
-            if (hit) {
-                int at = 0;
+        for (int u = 0; u < CPT; ++u) {
+            unpack<DT>(tile[u], z);
+            float all = 0.f, below = 0.f, tx = 0.f;
 #pragma unroll
-                for (int e = N - 1; e >= 0; --e) at = z[e] == mw ? e : at;
-                const int first = __ffsll((long long)hit) - 1;
-                idx = (c * 64 + first) * N + read_lane(at, first);
+            for (int h = 0; h < N; h += 4) {
+                float w[4], fr[4], wx[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float x = scaled_below_floored(z[h + e] - mw, a.sc);
+                    w[e] = exp2_raw(x);
+                    fr[e] = __builtin_amdgcn_fractf(w[e]);
+                    wx[e] = w[e] * x;
+                }
+                all += tree_sum<4>(w);
+                below += tree_sum<4>(fr);
+                tx += tree_sum<4>(wx);
+                asm volatile("" : "+v"(all), "+v"(below), "+v"(tx));
+            }
+            S[u] += (double)below + (double)rintf(all - below);
+            td += (double)tx;
+            asm volatile("" : "+v"(td), "+v"(S[u]));
+            if (KIND == GREEDY && higher && idx < 0) {
+                const unsigned long long hit = __ballot(tree_max<N>(z) == mw);
+                if (hit) {
+                    int at = 0;
+#pragma unroll
+                    for (int e = N - 1; e >= 0; --e) at = z[e] == mw ? e : at;
+                    const int first = __ffsll((long long)hit) - 1;
+                    idx = ((t0 * CPT + u) * 64 + first) * N + read_lane(at, first);
+                }
             }
         }
     }
@@ -318,24 +351,26 @@ __global__ __launch_bounds__(WG, TPS == 1 ? 8 : 6) void k_draft_stats(DraftArgs 
     float mw = neg_inf(), td = 0.f;
     LaneSums<KIND> sums;
     int first = -1;
+    unsigned lowest = 0u;
     bool ok = a.common_range;
     if (TPS == 2 && te - tb == 2 && te <= fe) {
         typename RawOf<DT>::type raw2[CPT];
         wave_load<DT, CPT, false>(row, a.geo.V, tb * CPT, raw);
         wave_load<DT, CPT, false>(row, a.geo.V, (tb + 1) * CPT, raw2);
         if (flag_after_loads(a, flag)) return;
-        ok = ok && wave_tile<DT, CPT, KIND>(raw, tb * CPT, mw, sums, td, first, a.sc) &&
-             wave_tile<DT, CPT, KIND>(raw2, (tb + 1) * CPT, mw, sums, td, first, a.sc);
+        ok = ok && wave_tile<DT, CPT, KIND>(raw, tb * CPT, mw, sums, td, first, lowest, a.sc) &&
+             wave_tile<DT, CPT, KIND>(raw2, (tb + 1) * CPT, mw, sums, td, first, lowest, a.sc);
     } else {
         if (tb < fe) wave_load<DT, CPT, false>(row, a.geo.V, tb * CPT, raw);
         else wave_load<DT, CPT, true>(row, a.geo.V, tb * CPT, raw);
         if (flag_after_loads(a, flag)) return;
-        ok = ok && wave_tile<DT, CPT, KIND>(raw, tb * CPT, mw, sums, td, first, a.sc);
+        ok = ok && wave_tile<DT, CPT, KIND>(raw, tb * CPT, mw, sums, td, first, lowest, a.sc);
         if (TPS != 1) {
             for (int t0 = tb + 1; t0 < te && ok; ++t0) {
                 if (t0 < fe) wave_load<DT, CPT, false>(row, a.geo.V, t0 * CPT, raw);
                 else wave_load<DT, CPT, true>(row, a.geo.V, t0 * CPT, raw);
-                ok = wave_tile<DT, CPT, KIND>(raw, t0 * CPT, mw, sums, td, first, a.sc);
+                ok = wave_tile<DT, CPT, KIND>(raw, t0 * CPT, mw, sums, td, first, lowest, a.sc) &&
+                     __ballot(lowest & 0x80808080u) == 0ull;      // (the counts of 16 tiles or more leave their bytes)
             }
         }
     }
@@ -343,6 +378,11 @@ __global__ __launch_bounds__(WG, TPS == 1 ? 8 : 6) void k_draft_stats(DraftArgs 
     // at most 0 otherwise; like a masked logit it weighs nothing, by the floor of uncommon_record's exponents.
     ok = ok && __ballot(!(td > neg_inf())) == 0ull;
     const size_t at = (size_t)b * nrec + r;
+    if (ok && mw == neg_inf() && __ballot(lowest != 0u)) {                 // nothing but the lowest number: all ties
+        mw = FiniteLow<DT>::value();
+#pragma unroll
+        for (int u = 0; u < CPT; ++u) sums.add(u, 0.f, (float)((lowest >> (8 * u)) & 0xFFu));
+    }
     if (ok) {
         const double t = wave_sum((double)td) * a.sc.c;
         if constexpr (KIND == QUARTERS) store_record(a, at, mw, sums.S, t);

@@ -213,7 +213,10 @@ __device__ __forceinline__ void unpack<f16>(const u32x4 &v, float (&z)[8])
 // the maxima taken on the packed vectors, is a sixth fewer vector instructions for the draft statistics and changed
 // nothing measurable.)
 template <typename DT> struct FiniteLow;
-template <> struct FiniteLow<float> { static __device__ __forceinline__ float value() { return -3.402823466e38f; } };
+template <> struct FiniteLow<float> {
+    static constexpr unsigned bits = 0xFF7FFFFF;
+    static __device__ __forceinline__ float value() { return -3.402823466e38f; }
+};
 template <> struct FiniteLow<bf16> {
     static constexpr unsigned short bits = 0xFF7F;
     static __device__ __forceinline__ float value() { return __uint_as_float(0xFF7F0000u); }
@@ -222,16 +225,25 @@ template <> struct FiniteLow<f16> {
     static constexpr unsigned short bits = 0xFBFF;
     static __device__ __forceinline__ float value() { return -65504.f; }
 };
-template <typename DT>
-__device__ __forceinline__ bool all_neg_inf(const f32x4 &v)
+// The vectors of a wave none of whose logits is above that number, per lane as one byte per vector: how many of its logits
+// are that number.  False where a lane has a vector in which it stands beside -inf or NaN (nothing is counted there).  In
+// bits: a vector of -inf (or NaN of negative sign) has the sign and the whole exponent set in all of its logits, and
+// one that holds a -inf, a NaN or a smaller number has a bit the lowest number has not.
+template <typename DT, int NU>
+__device__ __forceinline__ bool count_lowest(const typename RawOf<DT>::type (&raw)[NU], unsigned *count)
 {
-    return v.x == neg_inf() && v.y == neg_inf() && v.z == neg_inf() && v.w == neg_inf();
-}
-template <typename DT>
-__device__ __forceinline__ bool all_neg_inf(const u32x4 &v)
-{
-    constexpr unsigned inf2 = (FiniteLow<DT>::bits + 1u) * 0x10001u;       // -inf is the next pattern after the last finite one
-    return v.x == inf2 && v.y == inf2 && v.z == inf2 && v.w == inf2;
+    constexpr unsigned low = VecOf<DT>::N == 4 ? FiniteLow<DT>::bits : FiniteLow<DT>::bits * 0x10001u;
+    constexpr unsigned top = VecOf<DT>::N == 4 ? 0xFF800000u : (FiniteLow<DT>::bits + 1u) * 0x10001u;
+    unsigned n = 0u, other = 0u;
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+        const u32x4 v = __builtin_bit_cast(u32x4, raw[u]);
+        const bool is_low = (v[0] | v[1] | v[2] | v[3]) == low;
+        n |= is_low ? (unsigned)VecOf<DT>::N << (8 * u) : 0u;
+        other |= is_low ? 0u : ~(v[0] & v[1] & v[2] & v[3]) & top;
+    }
+    *count = n;
+    return __ballot(other != 0u) == 0ull;
 }
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 template <typename DT>

@@ -104,6 +104,35 @@ def test_masked_tiles_and_extreme_logits(svip, dtype, B, tiles):
 
 
 @pytest.mark.parametrize("dtype", [BF, F16, F32])
+@pytest.mark.parametrize("B,tiles", [(9, 5), (1400, 6), (2, 64 * 34)])
+def test_tiles_of_the_lowest_number(svip, dtype, B, tiles):
+    """Masks of the type's most negative number, of -inf and of both (side by side in a vector, vector by vector, tile by
+    tile), rows with few logits above them, in records of one, two and more tiles."""
+    tile, low = 1024 if dtype == F32 else 2048, torch.finfo(dtype).min
+    V = tiles * tile - 11
+    x, u = _rows(dtype, B, V, seed=6)
+    keep = torch.rand(B, V, device="cuda") < 0.3 / tile
+    keep[:, V // 2] = True
+    x.copy_(x.where(keep, torch.full_like(x, low)))
+    x[1, :V // 3] = float("-inf")
+    if B > 2:
+        x[2, 3::16] = float("-inf")
+        x[3].view(-1)[: V // 16 * 16].view(-1, 16)[:, 8:] = float("-inf")
+        x[4, :2 * tile] = low
+        x[4, 2 * tile:] = 1.0
+        x[5, :2 * tile] = 1.0
+        x[5, 2 * tile:] = low
+    if B < 100 and tiles < 100:          # the workgroup search of longer records forms z c in fp32 before it subtracts
+        x[6] = low
+        x[7] = float("-inf")
+        x[7, tile + 8:3 * tile] = low
+        x[8] = float("-inf")
+        x[8, [tile + 9, 2 * tile + 3, V - 1]] = low
+    for greedy in (False, True):
+        _check(_step(svip, x, u, 1.0, greedy), x, u, 1.0, greedy)
+
+
+@pytest.mark.parametrize("dtype", [BF, F16, F32])
 @pytest.mark.parametrize("B,V", [(4, 50257), (4, 32768), (4100, 2048 + 520)])
 def test_temperatures_near_zero(svip, dtype, B, V):
     """Accepted are all temperatures above 0.  Masked logits (-inf or the type's most negative number) and the places past
