@@ -55,6 +55,13 @@ typedef struct svip_bench_tuning {
 svip_status svip_bench_set_tuning(const svip_bench_tuning *tuning /* host, or NULL */);
 
 /*
+ * From now on svip_warp_logits writes to routes[b * n_rows + j] what decided that row's thresholds: 0 the
+ * histograms (also where a shortcut gave up on the row), 1 a shortcut, 2 a shortcut that wrote the output as well.
+ * The array must hold the rows of every call made until it is removed (NULL).
+ */
+svip_status svip_bench_warp_routes(int *routes /* device, or NULL */);
+
+/*
  * Reference launches for stating floors and peaks next to the calls' own figures.
  *
  * svip_bench_empty_kernel: one launch of a kernel that does nothing (what a launch costs).

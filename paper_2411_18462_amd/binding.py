@@ -20,8 +20,8 @@ EXPORTS = ("svip_status_string", "svip_workspace_bytes", "svip_workspace_needed"
            "svip_workspace_flags", "svip_draft_step", "svip_draft_step_static", "svip_verify", "svip_draft_step_greedy",
            "svip_verify_greedy", "svip_pair_stats", "svip_warp_logits", "svip_loop_workspace_bytes", "svip_loop_init", "svip_loop_run")
 # every symbol include/svip_bench.h declares (benchmark and experiment hooks, not the product ABI)
-BENCH_EXPORTS = ("svip_bench_time_kernels", "svip_bench_events_used", "svip_bench_set_tuning", "svip_bench_empty_kernel",
-                 "svip_bench_stream_sink_words", "svip_bench_stream_read")
+BENCH_EXPORTS = ("svip_bench_time_kernels", "svip_bench_events_used", "svip_bench_set_tuning",
+                 "svip_bench_warp_routes", "svip_bench_empty_kernel", "svip_bench_stream_sink_words", "svip_bench_stream_read")
 BENCH_K_DRAFT_STATS, BENCH_K_VERIFY_STATS, BENCH_K_RESID, BENCH_K_ACCEPT, BENCH_K_DRAFT_FINISH = 0, 1, 2, 3, 4
 
 
@@ -107,6 +107,8 @@ def load():
     lib.svip_bench_stream_read.argtypes = [vp, sz, i, vp, vp]
     lib.svip_bench_set_tuning.restype = i
     lib.svip_bench_set_tuning.argtypes = [ctypes.POINTER(BenchTuning)]
+    lib.svip_bench_warp_routes.restype = i
+    lib.svip_bench_warp_routes.argtypes = [vp]
     _lib = lib
     return lib
 
@@ -417,6 +419,12 @@ def bench_set_tuning(**fields):
     """svip_bench_set_tuning: launch-shape overrides for experiments; no arguments = the library's own choices."""
     t = BenchTuning(**{k: int(v) for k, v in fields.items()})
     _check(load().svip_bench_set_tuning(ctypes.byref(t) if fields else None))
+
+
+def bench_warp_routes(routes: torch.Tensor = None):
+    """svip_bench_warp_routes: later warp_logits calls write each row's route to this int32 tensor (None: no longer);
+    the caller keeps it alive and at least as long as the rows of those calls."""
+    _check(load().svip_bench_warp_routes(_ptr(routes, torch.int32, "routes") if routes is not None else None))
 
 
 def bench_empty_kernel(stream=None):

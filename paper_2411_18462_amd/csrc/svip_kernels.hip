@@ -101,6 +101,7 @@ static __device__ __align__(256) unsigned char scratch[SVIP_STATIC_SCRATCH_BYTES
 // Workspace sizes are always computed for the library's own choice; a forced shape that needs more than
 // the workspace holds is rejected by the call.
 static svip_bench_tuning g_tune = {0, 0, 0, 0, 0, 0, 0};
+static int *g_warp_routes = nullptr;             // svip_bench_warp_routes
 
 // Slices per row of the passes that give a slice to a workgroup: enough workgroups to fill 256 CUs several
 // times over, at most MAX_SLICES; want_one_batch (the residual pass): slices of min_tiles tiles, which the
@@ -647,6 +648,7 @@ svip_status svip_warp_logits(const void *logits_in, void *logits_out, int dtype,
     a.fix_scale = ldexpf(1.f, shift);
     a.kept = kept_out;
     a.no_shortcut = g_tune.warp_no_shortcut;
+    a.routes = g_warp_routes;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     bool ok = false;
     by_dtype(dtype, [&](auto tag) {
@@ -781,6 +783,12 @@ svip_status svip_bench_set_tuning(const svip_bench_tuning *tuning)
         t.stats_workgroups < 0)
         return SVIP_ERR_PARAM;
     g_tune = t;
+    return SVIP_OK;
+}
+
+svip_status svip_bench_warp_routes(int *routes)
+{
+    g_warp_routes = routes;
     return SVIP_OK;
 }
 

@@ -25,10 +25,22 @@ constexpr int WARP_WAVES = WARP_WG / 64;
 constexpr int WARP_BINS = 2048;            // histogram bins: digits of up to 11 bits
 constexpr int WARP_CAP = 8192;             // keys of one first-digit bin that fit the candidate list
 constexpr int DIGIT1_SHIFT = 21;           // first digit = top 11 bits of the key
-// Rows from which top_p alone takes its shortcut: below, the select over the list costs more than the sweeps it saves
-// (us, histogram path / shortcut: 136 rows of 50257 f16 28 / 33, 1 row of 32000 f32 18.7 / 22; 256 rows of 151936 bf16
-// 77 / 62, 1 row of 128256 bf16 50 / 40).
+// Rows from which top_p alone takes its shortcut.  On peaked rows (N(0, s^2), s from 4 to 6.5; top_p 0.9) it saves two
+// sweeps for a fixed cost, the select over the list; on flat ones the estimate that turns them away is 1 to 3 us.  us,
+// histogram path / shortcut, peaked rows | flat rows:
+//   rows of bf16 logits      1 row                  64 rows                544 rows
+//     32000           19.0 / 21.8 | 20.6 / 22.0    20.7 / 24.6 | 21.6 / 23.0    49.6 / 55.7 | 52.3 / 55.5
+//     50257           25.5 / 25.8 | 28.0 / 29.8    28.3 / 29.7 | 29.9 / 31.5    71.3 / 66.9 | 76.9 / 79.9
+//     65536           30.0 / 27.8 | 33.4 / 35.2    33.0 / 32.6 | 35.2 / 36.6    83.2 / 75.3 | 91.1 / 94.2
+//     81920           36.0 / 32.3 | 40.9 / 42.5    40.6 / 37.9 | 43.1 / 44.5   100.3 / 87.0 | 110.9 / 114.9
+//     98304           41.4 / 34.8 | 46.9 / 48.6    46.6 / 47.7 | 48.9 / 50.0   115.8 / 95.0 | 128.0 / 131.2
+//     128256          56.0 / 43.8 | 58.8 / 60.3    57.8 / 59.2 | 60.7 / 62.2   142.7 / 117.6 | 162.4 / 165.1
+// The estimate's sample is one vector per thread: the shorter the row, the less the saving pays for a row it misjudges
+// (64 peaked rows of 65536 fp32 logits 34.9 / 58.5) and for flat ones.  From 98304 on, flat rows are no slower than with a
+// kernel that has only the histograms and so more registers for them (us, that kernel / this one: 544 flat rows of 98304
+// 133 / 131, of 128256 170 / 165), and peaked ones gain most.
 constexpr int NUCLEUS_MIN_V = 98304;
+static_assert(NUCLEUS_MIN_V >= 8 * WARP_WG, "every thread has a whole vector of its own");
 
 struct WarpArgs {
     const void *in;
@@ -42,6 +54,7 @@ struct WarpArgs {
     float fix_scale;           // weights in [0, 1] are summed as integers in units of 1 / fix_scale
     int *kept;                 // [rows] survivors per row, or nullptr
     int no_shortcut;           // always take the histogram path (for tests and measurements)
+    int *routes;               // [rows] what decided the row: 0 the histograms, 1 or 2 a shortcut; or nullptr (for tests)
 };
 
 struct WarpLds {
@@ -416,6 +429,7 @@ __device__ __forceinline__ int small_k_shortcut(const DT *row, DT *dst, int V, c
 // Between the two an estimate tells whether the list will reach top_p of the total: the mass above the pivot is at least
 // that of the threads' maxima, and the mass below comes from a sample, which cannot miss much as no logit below the pivot
 // outweighs it.  A row that is too flat leaves here with the sweep behind it that the histogram path needs first anyway.
+// For rows of at least NUCLEUS_MIN_V logits: every thread has at least one vector in sweep 1 and one in the sample.
 // Returns 0: nothing decided (*m_out is the row maximum); 1, 2: as small_k_shortcut.
 template <typename DT, bool fused>
 __device__ __forceinline__ int nucleus_shortcut(const DT *row, DT *dst, int V, const WarpArgs &a, unsigned *tau_out,
@@ -425,16 +439,13 @@ __device__ __forceinline__ int nucleus_shortcut(const DT *row, DT *dst, int V, c
     constexpr float LOWEST = -3.402823466e38f;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int nvec = (V + N - 1) / N;
-    const int nsamp = nvec < WARP_WG ? nvec : WARP_WG;            // sampled vectors
     constexpr unsigned cap = fused ? WARP_CAP / 2 : WARP_CAP;
     float mine_max = neg_inf();
     for_each_vector<DT>(row, V, [&](int, const float(&z)[N]) { mine_max = vmax(mine_max, tree_max<N>(z)); });
     float group = vmax(mine_max, __shfl_xor(mine_max, 1));
     group = vmax(group, __shfl_xor(group, 2));
-    if (tid >= nvec) group = -neg_inf();
-    typename RawOf<DT>::type sample;
-    if (tid < nsamp)                                              // the same runs of whole cache lines as in small_k_shortcut
-        sample = warp_load<DT>(row, nvec <= WARP_WG ? tid : (int)((long long)(tid >> 6) * (nvec - 64) / 15) + (tid & 63), V);
+    // the same runs of whole cache lines as in small_k_shortcut
+    const typename RawOf<DT>::type sample = warp_load<DT>(row, (int)((long long)(tid >> 6) * (nvec - 64) / 15) + (tid & 63), V);
     {
         const float hi = wave_max(mine_max), lo = -wave_max(-group);
         if (lane == 0) {
@@ -453,12 +464,10 @@ __device__ __forceinline__ int nucleus_shortcut(const DT *row, DT *dst, int V, c
     pz = vmax(-pz, LOWEST);                                       // masked logits are no candidates
     *m_out = m;
     float head = exp2_raw(scaled_diff(mine_max, m, a.sc)), tail = 0.f;
-    if (tid < nsamp) {
-        float z[N];
-        unpack<DT>(sample, z);
+    float zs[N];
+    unpack<DT>(sample, zs);
 #pragma unroll
-        for (int e = 0; e < N; ++e) tail += z[e] < pz ? exp2_raw(scaled_diff(z[e], m, a.sc)) : 0.f;
-    }
+    for (int e = 0; e < N; ++e) tail += zs[e] < pz ? exp2_raw(scaled_diff(zs[e], m, a.sc)) : 0.f;
     head = wave_reduce(head, OpSum{});
     tail = wave_reduce(tail, OpSum{});
     if (lane == 0) L.sub[wave] = ((unsigned long long)__float_as_uint(head) << 32) | __float_as_uint(tail);
@@ -470,7 +479,7 @@ __device__ __forceinline__ int nucleus_shortcut(const DT *row, DT *dst, int V, c
         tail += __uint_as_float((unsigned)L.sub[w]);
     }
     // a wrong yes costs a sweep, a wrong no the saving: a fifth of the tail allowed is kept as a margin
-    tail *= (float)V / (float)(nsamp * N);
+    tail *= (float)V / (float)(WARP_WG * N);
     if (!(0.8f * (1.f - (float)a.top_p) * head >= (float)a.top_p * tail)) return 0;
     const MassMeasure mass{m, a.sc, a.fix_scale * (1.0f / 4294967296.0f)};
     unsigned long long mine = 0ull;
@@ -576,6 +585,7 @@ __global__ __launch_bounds__(WARP_WG, 8) void k_warp(WarpArgs a)
     if (m_known)
         decided = a.in != a.out ? nucleus_shortcut<DT, true>(row, dst, V, a, &tau, &kept, &m, L)
                                 : nucleus_shortcut<DT, false>(row, dst, V, a, &tau, &kept, &m, L);
+    if (a.routes && tid == 0) a.routes[y] = decided;
     if (decided == 0 && (K || P)) {
         // sweep 1: keys per first digit (top-k), row maximum (reference of the top-p weights)
         unsigned d_k = 0u;

@@ -178,7 +178,9 @@ def test_small_k_shortcut_equals_the_histogram_path(svip, dtype):
 @pytest.mark.parametrize("V", [98303, 98304, 98309, 131072])
 def test_nucleus_shortcut_equals_the_histogram_path(svip, dtype, V):
     """top_p alone on long rows: pivot from the threads' maxima, candidates in a list.  Bit for bit the histogram path,
-    for rows that are peaked, flat, masked, tied, clustered (the list overflows), all equal, or mostly dropped already."""
+    for rows that are peaked, flat, masked, tied, clustered (the list overflows), all equal, or mostly dropped already.
+    The routes show that the shortcut decided the rows it is for, gave up on those it is not for, and was not taken below
+    its length."""
     _say(f"warp nucleus shortcut {dtype} V={V}")
     rng = np.random.default_rng(V)
     z = rng.normal(-1.0, 5.0, (2, 5, V)).astype(np.float32)
@@ -194,6 +196,7 @@ def test_nucleus_shortcut_equals_the_histogram_path(svip, dtype, V):
     x = torch.from_numpy(z).to(dtype)
     bits = torch.int32 if dtype == torch.float32 else torch.int16
     src = _padded_buf(x)[1]
+    routes = torch.empty(10, dtype=torch.int32, device="cuda")
     for top_p in (0.05, 0.5, 0.9, 0.95, 0.999):
         got = []
         for no_shortcut, inplace in ((1, False), (0, False), (0, True)):
@@ -201,8 +204,20 @@ def test_nucleus_shortcut_equals_the_histogram_path(svip, dtype, V):
             kept = torch.zeros(10, dtype=torch.int32, device="cuda")
             a = _padded_buf(x)[1] if inplace else src
             out = a if inplace else _padded_buf(torch.zeros_like(x))[1]
+            routes.fill_(-1)
+            svip.bench_warp_routes(routes)
             svip.warp_logits(a, temperature=0.9, top_p=top_p, out=out, kept_out=kept)
+            svip.bench_warp_routes(None)
             torch.cuda.synchronize()
+            r = routes.tolist()
+            if no_shortcut or V < 98304:
+                assert r == [0] * 10, (top_p, r)
+            else:
+                assert set(r) <= {0, 1 if inplace else 2}, (top_p, r)
+                # a few or a hundred logits left, all the mass on three, and N(-1, 5^2)
+                assert all(r[i] for i in (6, 7, 8)) and (r[0] or top_p > 0.9), (top_p, r)
+                # all equal: no list holds them; N(-0.3, 1.5^2): the nucleus is thousands of tokens
+                assert r[5] == 0 and (r[1] == 0 or top_p < 0.9), (top_p, r)
             got.append((out.contiguous().view(bits), kept))
         svip.bench_set_tuning()
         for o, kept in got[1:]:
