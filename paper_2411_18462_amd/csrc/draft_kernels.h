@@ -289,12 +289,12 @@ __device__ __forceinline__ void store_record(const DraftArgs &a, size_t at, floa
 {
     const double S = wave_sum(lane_sum);
     if ((threadIdx.x & 63) == 0) {
-        Partial p;
+        WaveRec p;
         p.m = mw;
         p.idx = first;
         p.S = S;
         p.t = t;
-        static_cast<Partial *>(a.part)[at] = p;
+        static_cast<WaveRec *>(a.part)[at] = p;
     }
 }
 __device__ __forceinline__ void store_record(const DraftArgs &a, size_t at, float mw, const double (&S)[4], double t)
@@ -579,14 +579,14 @@ __global__ __launch_bounds__(64) void k_draft_finish_greedy(DraftArgs a)
     const int b = blockIdx.x, lane = threadIdx.x, nrec = a.geo.ns;
     const long long o = (long long)b * a.io_stride;
     const unsigned flag = request_stop_flag(a, b);        // travels together with the records
-    Partial p[RPL];
+    WaveRec p[RPL];
 #pragma unroll
     for (int i = 0; i < RPL; ++i) {
         p[i].m = neg_inf();
         p[i].idx = -1;
         p[i].S = 0.0;
         p[i].t = 0.0;
-        if (lane * RPL + i < nrec) p[i] = static_cast<const Partial *>(a.part)[(size_t)b * nrec + lane * RPL + i];
+        if (lane * RPL + i < nrec) p[i] = static_cast<const WaveRec *>(a.part)[(size_t)b * nrec + lane * RPL + i];
     }
     if (flag_after_loads(a, flag)) return stopped_row(a, b, o);
     float mrow = p[0].m;
@@ -627,11 +627,11 @@ __global__ __launch_bounds__(TOTAL_FINISH_THREADS, 4) void k_draft_finish_total(
     const long long o = (long long)b * a.io_stride;
     // independent loads first: the row's flag, its uniform and its records travel together
     const unsigned flag = request_stop_flag(a, b);
-    Partial p;
+    WaveRec p;
     p.m = neg_inf();
     p.S = 0.0;
     p.t = 0.0;
-    if (lane < nrec) p = static_cast<const Partial *>(a.part)[(size_t)b * nrec + lane];
+    if (lane < nrec) p = static_cast<const WaveRec *>(a.part)[(size_t)b * nrec + lane];
     const float u = a.u[o];
     if (flag_for_all_waves(a, flag)) return stopped_row(a, b, o);
     const DT *row = static_cast<const DT *>(a.logits) + draft_row_offset(a, b);

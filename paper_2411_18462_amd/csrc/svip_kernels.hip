@@ -208,7 +208,7 @@ static size_t ws_fixed_bytes(int B, int mass_slices)
 
 static size_t need_draft(int B, const Geo &g, bool greedy)
 {
-    const size_t rec = !greedy && quarter_records(B, g) ? sizeof(QuarterRec) : sizeof(Partial);
+    const size_t rec = !greedy && quarter_records(B, g) ? sizeof(QuarterRec) : sizeof(WaveRec);
     return ws_fixed_bytes(B, 0) + align256((size_t)B * g.ns * rec);
 }
 static size_t need_verify_greedy(int B, int k, const Geo &g)
@@ -487,7 +487,7 @@ size_t svip_workspace_bytes(int B, int k_max, int V)
     // a row has at most `tiles` slices (fp32 rows have the most vectors)
     const size_t tiles = ((size_t)V + 4 * WG - 1) / (4 * WG);
     const size_t ns_max = tiles < MAX_SLICES ? tiles : MAX_SLICES;
-    size_t part_bytes = (size_t)B * ns_max * sizeof(Partial);
+    size_t part_bytes = (size_t)B * ns_max * sizeof(WaveRec);
     const size_t q_recs = (size_t)B * (tiles < 2 * MAX_SLICES ? tiles : 2 * MAX_SLICES);      // draft records with chunk masses
     const size_t q_bytes = (q_recs < DRAFT_QUARTER_WAVES ? q_recs : DRAFT_QUARTER_WAVES) * sizeof(QuarterRec);
     if (q_bytes > part_bytes) part_bytes = q_bytes;

@@ -4,6 +4,9 @@ import ctypes
 import os
 import re
 
+import pytest
+import torch
+
 import paper_2411_18462_amd as svip
 from paper_2411_18462_amd.binding import BENCH_EXPORTS, EXPORTS
 
@@ -202,6 +205,13 @@ def test_workspace_bytes_covers_every_call_for_every_shape():
     assert lib.svip_loop_workspace_bytes(8, 40, 151936) > svip.workspace_bytes(8, 40, 151936)
 
 
+@pytest.mark.parametrize("B,k,V,needs", [(1, 8, 32000, (1536, 2048, 2048, 2560)), (64, 16, 128256, (254208, 274176, 377088, 397056)),
+                                         (8, 64, 151936, (123136, 184320, 232192, 293376))])
+def test_verification_and_diagnostics_need_24_bytes_a_slice(B, k, V, needs):
+    """The draft step's padded records are its own: the other calls take the workspaces they always took."""
+    assert tuple(svip.workspace_needed(call, torch.bfloat16, B, k, V) for call in (1, 2, 4, 5)) == needs
+
+
 def test_header_is_plain_c(tmp_path):
     """include/svip.h must compile as C99 on its own (the boundary is a C ABI)."""
     import subprocess
@@ -244,12 +254,13 @@ def test_binding_structs_match_the_headers(tmp_path):
 
 def test_division_by_multiplication_is_exact_over_the_kernels_range():
     """k_draft_stats divides a wave number by the records (or workgroups) per row as umulhi(n, floor(2^32 / d) + 1),
-    with n < 2^26 (MAX_BATCH rows of at most 64 records) and d <= 64: exact while n * d < 2^32."""
+    with n < 2^26 (MAX_BATCH rows of at most 64 records) and d <= 64, or n <= 8100 waves and d <= 128: exact while
+    n * d < 2^32."""
     import numpy as np
     rng = np.random.default_rng(0)
-    for d in range(2, 65):
+    for d in range(2, 129):
         magic = (1 << 32) // d + 1
         n = np.concatenate([np.arange(0, 4096), rng.integers(0, 1 << 26, 20000), (1 << 26) - 1 - np.arange(0, 4096),
                             np.arange(1, 3000) * d - 1, np.arange(1, 3000) * d]).astype(np.uint64)
-        n = n[n < (1 << 26)]
+        n = n[n < (1 << 26)] if d <= 64 else np.arange(8101, dtype=np.uint64)
         assert ((n * np.uint64(magic)) >> np.uint64(32) == n // np.uint64(d)).all(), d
