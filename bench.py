@@ -29,6 +29,7 @@ import ctypes
 import hashlib
 import json
 import os
+import re
 import sys
 import time
 
@@ -530,7 +531,7 @@ def merge_counters(cells, directory):
 
     def classify(name):
         for kn in ("k_draft_stats", "k_draft_finish", "k_verify_stats", "k_accept", "k_resid"):
-            if f"svip::{kn}<" in name:
+            if re.search(rf"svip::{kn}(_quarters|_total)?<", name):
                 return kn
         return None
 

@@ -44,8 +44,9 @@ __device__ __forceinline__ void write_row_outputs(const DraftArgs &a, int b, lon
 //             one vector per lane, one scan over the lanes -- no LDS, no barrier;
 //   TOTAL     (beyond) one sum: the chosen record's tiles are read and searched by a workgroup.  The statistics of a
 //             launch this large are bound by vector-ALU issue, and the quarters' sums cost them more than the
-//             shorter search gives back: us per step of 128256 bf16 logits, quarters / totals: 1 row 6.16 / 6.6, 8 rows
-//             6.9 / 7.5, 64 rows 9.85 / 10.0, 128 rows 12.6 / 12.6, but 192 rows 16.4 / 15.3, 256 rows 19.7 / 18.3;
+//             shorter search gives back: us per step of 128256 bf16 logits, quarters / totals: 1 row 5.9 / 6.2, 8 rows
+//             6.6 / 7.0, 64 rows 9.7 / 9.8, 128 rows 12.6 / 12.4, 192 rows 16.3 / 15.4, 256 rows 19.5 / 18.6 (the last two
+//             with records of two tiles for the totals);
 //   GREEDY    one sum and the first index of the maximum, which is the token: nothing is read again.
 //
 // A single launch in which the row's last workgroup does the second part (hand-over through
@@ -83,8 +84,8 @@ __device__ __forceinline__ void wave_load(const DT *row, int V, int c0, typename
     }
 }
 // Per lane, what a wave has summed so far.  QUARTERS: the sum of the weights of each chunk of its one tile.  Otherwise:
-// the sum of the weights below 1 and the number of weights that are exactly 1, which have to stay out of the fp32 sum
-// (next to a 1 the tail of a confident row, 1e-4 and less, would lose its low bits).
+// the sum of the weights, and beside it the number of weights that are exactly 1 in the vectors that hold the maximum.
+// Those have to stay out of the fp32 sum (next to a 1 the tail of a confident row, 1e-4 and less, would lose its low bits).
 template <RecordKind KIND> struct LaneSums {
     float S = 0.f, ones = 0.f;
     __device__ __forceinline__ void add(int, float below) { S += below; }
@@ -113,17 +114,20 @@ template <> struct LaneSums<QUARTERS> {
 
 // One tile of a wave relative to the WAVE's running maximum mw (the same in every lane): the sums of the weights and
 // td = sum w (z - mw), per lane.  One reference for the whole wave instead of one per lane saves per logit
-//  - the count of weights that are exactly 1 (the maximum, its ties): only vectors that hold the maximum have any;
-//    one comparison per vector (its own maximum is there anyway) and a branch the whole wave takes find them, about
-//    one vector in four.  There sum fract(w) (fract(1) = 0) is what goes into the fp32 sum;
+//  - the count of weights that are exactly 1 in most vectors: the maximum and its ties are found by one comparison per
+//    vector (its own maximum is there anyway) and a branch the whole wave takes, for about one vector in four.  There
+//    sum fract(w) (fract(1) = 0) is what goes into the fp32 sum.  A logit below the maximum by less than 2^-25 / c also
+//    rounds to a weight of 1; in another vector it goes into the lane's fp32 sum, whose roundings are then 2^-24 of a
+//    sum of at least 1 -- next to an entropy of at least ln 2, as the row has two tokens of equal weight;
 //  - the floor of the exponent: masked (-inf) logits are lowered to the most negative finite number while still
 //    packed (half an instruction per logit), so z - mw stays finite and 0 * (z - mw) is 0;
 //  - a product per term of the entropy sum: w (z - mw) is accumulated by fused multiply-adds, and the scale is
 //    applied once per record in fp64,
-// and per wave the rescaling of its lanes to one another: about 9 issue slots per bf16 logit instead of 12.5.  What
-// that is worth grows with how far issue rather than latency bounds the launch; us per draft step in a graph, before
-// / after: 8 rows of 128256 bf16 logits 7.74 / 7.63, 64 rows 10.19 / 10.06 (greedy 9.75 / 9.26), 128 rows 13.6 / 12.8,
-// 256 rows 20.1 / 18.5.
+// and per wave the rescaling of its lanes to one another.  What that is worth grows with how far issue rather than
+// latency bounds the launch; us per draft step in a graph, before / after: 8 rows of 128256 bf16 logits 7.74 / 7.63, 64 rows
+// 10.19 / 10.06 (greedy 9.75 / 9.26), 128 rows 13.6 / 12.8, 256 rows 20.1 / 18.5.  Together with the records' chunk masses,
+// the shorter searches and the tails' loads (below), the same step: 1 row 6.5 / 5.9, 8 rows 7.5 / 6.6, 64 rows 10.2 / 9.65
+// (greedy 9.8 / 8.75), 128 rows 13.6 / 12.9, 256 rows 20.2 / 18.9 (greedy 21.0 / 18.1), 16 rows of 32000 fp32 6.64 / 6.1.
 // A tile without any logit above the most negative finite number only counts, in `lowest` (see count_lowest), those that
 // are that number: they have weights if the wave never sees anything higher, and none otherwise.  Rows that were filtered
 // or masked consist mostly of such tiles, and all is decided from the registers that hold them (us per step, read again

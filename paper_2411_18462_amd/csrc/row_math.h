@@ -56,8 +56,9 @@ __device__ __forceinline__ float neg_inf() { return -__builtin_inff(); }
 __device__ __forceinline__ float exp2_raw(float x) { return __builtin_amdgcn_exp2f(x); }
 
 // A uniform value in a vector register.  With several waves per SIMD an fp32 add, multiply or fused multiply-add whose
-// operands are all vector registers (or literals) issues every 2.3 cycles; one with a scalar-register operand, like
-// most other vector instructions, every 4.1 (v_exp_f32: 8.1).  Constants of the inner loops are therefore kept here.
+// operands are all vector registers (or literals) issues every 2.4 cycles; one with a scalar-register operand, like
+// most other vector instructions, every 4.2 (v_exp_f32: 8.2; profiles/valu_issue_rates.txt).  Constants of the inner
+// loops are therefore kept here.
 __device__ __forceinline__ float in_vgpr(float x)
 {
     asm("" : "+v"(x));

@@ -234,11 +234,11 @@ static size_t need_pair(int B, int k, bool recompute_lse, const Geo &g, const Ge
 // The slicing each pass uses (forced = an experiment's override, 0 = the library's choice).
 // The draft step: one record (= one wave of the statistics launch) per tile of 32 logits per thread, so the
 // search reads little again; up to 128 records per row (two per lane of the finish: 64 rows of 151936 bf16 logits, 75
-// tiles, 11.2 us per step instead of 11.7 with 38 records of two tiles, 16 rows of 128256 fp32 logits 7.75 / 8.67).
+// tiles, 10.7 us per step instead of 11.4 with 38 records of two tiles, 16 rows of 128256 fp32 logits 7.6 / 8.65).
 // Rows of more tiles put more of them into a record, and so do batches that would otherwise launch more than 8100
 // waves (eight per SIMD): about a quarter of a one-tile wave's instructions are per-record overhead, which then
-// outweighs the finer grain and the shorter search (rows of 128256 logits, us per step with 63 and with 32 records: 128
-// rows 12.5 / 12.6, 192 rows 16.1 / 15.3, 256 rows 19.1 / 18.3).
+// outweighs the finer grain and the shorter search (rows of 128256 logits, us per step with 63 and with 32 records: 64
+// rows 9.6 / 10.1, 128 rows 12.6 / 12.75, 144 rows 13.8 / 13.9, 192 rows 16.3 / 15.4, 256 rows 19.5 / 18.6).
 static Geo geo_draft(int B, int V, int vec, int forced)
 {
     Geo g;
