@@ -281,13 +281,17 @@ svip_status svip_pair_stats(
  * The models are stood in for by traces: row n of sequence b's trace holds the logits for the token
  * at absolute position n (independent of the tokens chosen before).  A sequence starts a new round
  * while it has produced fewer than max_new tokens and its trace holds limit + 1 more rows; a round
- * produces the accepted draft tokens followed by the correction or bonus token.  Everything per
- * round stays on the device; the host learns one counter per round (and, if check_every > 0, one
- * more every check_every draft steps to end the drafting phase early).  The counters come as
+ * produces the accepted draft tokens followed by the correction or bonus token.  The rows of several
+ * draft positions are read at once where one position of the batch would not fill the GPU, so rows
+ * behind the position that ends a draft may be read too (never past the sequence's limit).
+ * Everything per round stays on the device; the host learns one counter per round (and, if
+ * check_every > 0, one more about every check_every draft positions, to end the drafting phase early
+ * where several launches of it are left).  The counters come as
  * messages the counting kernels store into pinned host memory -- no copy is enqueued and the stream
  * is not synchronised between rounds -- and the host launches one round ahead of the counter it
  * waits for: a round launched after the last sequence finished changes nothing (its sequences are
- * all marked done) except that, with a log, it may fill its round_log entries with -1.  The first
+ * all marked done) except that, with a log, it may fill its round_log entries with -1.  With greedy
+ * decoding the sequences of such a batch do not wait for one another at the end of a round.  The first
  * svip_loop_run of a host thread allocates 512 bytes of pinned host memory for those messages and
  * keeps them until the process ends.
  *

@@ -7,9 +7,9 @@ namespace svip {
 
 // ---- draft step -------------------------------------------------------------------------------
 
-__device__ __forceinline__ long long draft_row_offset(const DraftArgs &a, int b)
+__device__ __forceinline__ long long draft_row_offset(const DraftArgs &a, int b, int j)
 {
-    return (long long)b * a.row_stride + (a.pos ? (long long)(__builtin_amdgcn_readfirstlane(a.pos[b]) + a.step_j) * a.pos_stride : 0ll);
+    return (long long)b * a.row_stride + (a.pos ? (long long)(__builtin_amdgcn_readfirstlane(a.pos[b]) + j) * a.pos_stride : 0ll);
 }
 __device__ __forceinline__ bool at_cap(const DraftArgs &a, int b)
 {
@@ -17,16 +17,26 @@ __device__ __forceinline__ bool at_cap(const DraftArgs &a, int b)
     return a.step_j + 1 >= cap;
 }
 
-// Entropy of weights e_i = exp2(x_i) with sum S and tt = sum e_i x_i:  H = ln S - ln2 tt / S, then the
-// stop test and the row's outputs that do not depend on the token (Section 2.2, Eq. stop_condition).
-__device__ __forceinline__ void write_row_outputs(const DraftArgs &a, int b, long long o, float m, double S, double tt)
+// Entropy of weights e_i = exp2(x_i) with sum S and tt = sum e_i x_i:  H = ln S - ln2 tt / S, and whether it is above the
+// threshold of the stop test (Section 2.2, Eq. stop_condition).
+__device__ __forceinline__ double entropy_of(double lnS, double S, double tt)
 {
-    const double lnS = log(S);
-    double H = lnS - 0.6931471805599453 * tt / S;
-    H = H > 0.0 ? H : 0.0;
+    const double H = lnS - 0.6931471805599453 * tt / S;
+    return H > 0.0 ? H : 0.0;
+}
+__device__ __forceinline__ bool above_threshold(const DraftArgs &a, double H) { return sqrt(H) > (double)a.h; }
+// The row's outputs that follow from it; returns whether it is above the threshold.
+__device__ __forceinline__ bool write_entropy(const DraftArgs &a, long long o, float m, double S, double tt)
+{
+    const double lnS = log(S), H = entropy_of(lnS, S, tt);
     if (a.entropy) a.entropy[o] = (float)H;
     a.lse[o] = (double)m * a.sc.inv_T + lnS;
-    const bool stop = (sqrt(H) > (double)a.h) || at_cap(a, b);
+    return above_threshold(a, H);
+}
+// The same with the stop test and draft length of a single step.
+__device__ __forceinline__ void write_row_outputs(const DraftArgs &a, int b, long long o, float m, double S, double tt)
+{
+    const bool stop = write_entropy(a, o, m, S, tt) || at_cap(a, b);
     a.stop[b] = stop ? 1 : 0;
     if (a.draft_len) a.draft_len[b] = a.step_j + 1;
 }
@@ -311,40 +321,15 @@ __device__ __forceinline__ void store_record(const DraftArgs &a, size_t at, floa
     if (lane < 6) reinterpret_cast<double *>(static_cast<QuarterRec *>(a.part) + at)[lane] = x;
 }
 
-// grid (ceil(rows * records / 4)), one wave per record.  TPS: tiles per record, 1, 2 or 0 for more.  A record of two
-// whole tiles requests both before it works on the first (the arithmetic of the first runs while the second is
-// still on its way), which takes more registers; launches with one tile per record keep the other form.
+// The record of one wave: tiles [r * tps, (r + 1) * tps) of sequence b's row, stored at index `at`.  TPS: tiles per record, 1,
+// 2 or 0 for more.  A record of two whole tiles requests both before it works on the first (the arithmetic of the
+// first runs while the second is still on its way), which takes more registers; launches with one tile per record keep the
+// other form.
 template <typename DT, RecordKind KIND, int TPS>
-__global__ __launch_bounds__(WG, TPS == 1 ? 8 : 6) void k_draft_stats(DraftArgs a)
+__device__ __forceinline__ void draft_record(const DraftArgs &a, const DT *row, int b, int r, size_t at)
 {
     constexpr int N = VecOf<DT>::N, CPT = WG / 64;       // chunks of 64 vectors per tile
     static_assert(KIND != QUARTERS || TPS == 1, "a quarter is a chunk");
-    const int nrec = a.geo.ns;
-    // All arguments are requested at once: left to itself the compiler loads those behind the first branch only there,
-    // a second trip to the scalar cache before the first load of a logit.
-    asm volatile("" : : "s"(a.logits), "s"(a.row_stride), "s"(a.pos), "s"(a.stop_in), "s"(a.geo.V), "s"(a.part), "s"(a.sc.c_dn),
-                 "s"(a.sc.c_up), "s"(a.sc.c), "s"(a.common_range), "s"(a.step_j));
-    // Which record this wave takes is the same in all its lanes: worked out in scalar registers, with the one
-    // division done by a multiplication the host prepared, so that none of it takes vector-ALU slots.
-    const unsigned wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    int b, r;
-    if (a.rows_by_xcd) {
-        // Workgroups go to the chip's 8 XCDs in turn, and so do the rows' workgroups of the finish: keeping row b on
-        // XCD b % 8 lets that kernel find the row's records (and what it reads again) in the L2 of its own XCD, and
-        // the lines of the records are written by one L2 each.  The grid is ceil(B / 8) * 8 * ceil(nrec / 4)
-        // workgroups; those of rows past B exit.
-        const unsigned xcd = blockIdx.x & 7u, slot = blockIdx.x >> 3;           // div = workgroups per row
-        const unsigned q = a.div == 1u ? slot : __umulhi(slot, a.div_magic);
-        b = (int)(q * 8u + xcd);
-        r = (int)((slot - q * a.div) * NWAVE + wv);
-        if (b >= a.B || r >= nrec) return;
-    } else {
-        const unsigned gw = blockIdx.x * NWAVE + wv;                            // div = records per row
-        if (gw >= (unsigned)a.B * (unsigned)nrec) return;
-        b = (int)(a.div == 1u ? gw : __umulhi(gw, a.div_magic));
-        r = (int)(gw - (unsigned)b * (unsigned)nrec);
-    }
-    const DT *row = static_cast<const DT *>(a.logits) + draft_row_offset(a, b);
     const int tps = TPS ? TPS : a.geo.tps;
     const int tb = r * tps, te = min(tb + tps, a.geo.ntiles);
     const int fe = min(te, a.geo.V / (WG * N));           // end of the tiles wholly inside the row
@@ -381,7 +366,6 @@ __global__ __launch_bounds__(WG, TPS == 1 ? 8 : 6) void k_draft_stats(DraftArgs 
     // A NaN among the logits (only the 16-bit types get one past unpack_finite) shows in td, whose terms are all finite and
     // at most 0 otherwise; like a masked logit it weighs nothing, by the floor of uncommon_record's exponents.
     ok = ok && __ballot(!(td > neg_inf())) == 0ull;
-    const size_t at = (size_t)b * nrec + r;
     if (ok && mw == neg_inf() && __ballot(lowest != 0u)) {                 // nothing but the lowest number: all ties
         mw = FiniteLow<DT>::value();
 #pragma unroll
@@ -398,6 +382,44 @@ __global__ __launch_bounds__(WG, TPS == 1 ? 8 : 6) void k_draft_stats(DraftArgs 
         if constexpr (KIND == QUARTERS) store_record(a, at, mw, S, t);
         else store_record(a, at, mw, first, (S[0] + S[1]) + (S[2] + S[3]), t);
     }
+}
+
+// Which record wave `wv` of this workgroup takes: row *b of `rows`, record *r of that row; false: none.
+__device__ __forceinline__ bool wave_to_record(const DraftArgs &a, unsigned rows, int *b, int *r)
+{
+    const int nrec = a.geo.ns;
+    // Which record this wave takes is the same in all its lanes: worked out in scalar registers, with the one
+    // division done by a multiplication the host prepared, so that none of it takes vector-ALU slots.
+    const unsigned wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (a.rows_by_xcd) {
+        // Workgroups go to the chip's 8 XCDs in turn, and so do the rows' workgroups of the finish: keeping row b on
+        // XCD b % 8 lets that kernel find the row's records (and what it reads again) in the L2 of its own XCD, and
+        // the lines of the records are written by one L2 each.  The grid is ceil(rows / 8) * 8 * ceil(nrec / 4)
+        // workgroups; those of rows past the last exit.
+        const unsigned xcd = blockIdx.x & 7u, slot = blockIdx.x >> 3;           // div = workgroups per row
+        const unsigned q = a.div == 1u ? slot : __umulhi(slot, a.div_magic);
+        *b = (int)(q * 8u + xcd);
+        *r = (int)((slot - q * a.div) * NWAVE + wv);
+        return *b < (int)rows && *r < nrec;
+    }
+    const unsigned gw = blockIdx.x * NWAVE + wv;                            // div = records per row
+    if (gw >= rows * (unsigned)nrec) return false;
+    *b = (int)(a.div == 1u ? gw : __umulhi(gw, a.div_magic));
+    *r = (int)(gw - (unsigned)*b * (unsigned)nrec);
+    return true;
+}
+
+// grid (ceil(rows * records / 4)), one wave per record.
+template <typename DT, RecordKind KIND, int TPS>
+__global__ __launch_bounds__(WG, TPS == 1 ? 8 : 6) void k_draft_stats(DraftArgs a)
+{
+    // All arguments are requested at once: left to itself the compiler loads those behind the first branch only there,
+    // a second trip to the scalar cache before the first load of a logit.
+    asm volatile("" : : "s"(a.logits), "s"(a.row_stride), "s"(a.pos), "s"(a.stop_in), "s"(a.geo.V), "s"(a.part), "s"(a.sc.c_dn),
+                 "s"(a.sc.c_up), "s"(a.sc.c), "s"(a.common_range), "s"(a.step_j));
+    int b, r;
+    if (!wave_to_record(a, (unsigned)a.B, &b, &r)) return;
+    draft_record<DT, KIND, TPS>(a, static_cast<const DT *>(a.logits) + draft_row_offset(a, b, a.step_j), b, r, (size_t)b * a.geo.ns + r);
 }
 
 // The inverse CDF inside one chunk of a row by one wave: the smallest index whose inclusive prefix of weights
@@ -493,6 +515,90 @@ __device__ __forceinline__ double record_factor(float m, double S, float mrow, c
     return f;
 }
 
+// A row's QUARTERS records, RPL consecutive ones per lane; `at` is the index of its first record.
+template <int RPL>
+struct QuarterRow {
+    float m[RPL];
+    double t[RPL], S4[RPL][4];
+    float mrow;                          // after merge(): row maximum, factors and masses relative to it
+    double f[RPL], xd[RPL], rS[RPL], M;
+    __device__ __forceinline__ void load(const DraftArgs &a, size_t at)
+    {
+        const int lane = threadIdx.x & 63, nrec = a.geo.ns;
+#pragma unroll
+        for (int i = 0; i < RPL; ++i) {
+            m[i] = neg_inf();
+            t[i] = 0.0;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) S4[i][q] = 0.0;
+            if (lane * RPL + i < nrec) {
+                const QuarterRec *p = static_cast<const QuarterRec *>(a.part) + at + lane * RPL + i;
+                m[i] = p->m;
+                t[i] = p->t;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) S4[i][q] = p->S[q];
+            }
+        }
+    }
+    __device__ __forceinline__ void merge(const DraftArgs &a)
+    {
+        mrow = m[0];
+#pragma unroll
+        for (int i = 1; i < RPL; ++i) mrow = vmax(mrow, m[i]);
+        mrow = wave_max(mrow);
+        M = 0.0;
+#pragma unroll
+        for (int i = 0; i < RPL; ++i) {
+            rS[i] = (S4[i][0] + S4[i][1]) + (S4[i][2] + S4[i][3]);
+            f[i] = record_factor(m[i], rS[i], mrow, a.sc, &xd[i]);
+            M += f[i] * rS[i];
+        }
+    }
+    __device__ __forceinline__ double entropy_sum() const
+    {
+        double tt = 0.0;
+#pragma unroll
+        for (int i = 0; i < RPL; ++i) tt += f[i] * (t[i] + xd[i] * rS[i]);
+        return wave_sum(tt);
+    }
+    // The token for the uniform u: lane, record and chunk from the masses (all in units of the row maximum), then the
+    // search inside the chunk.
+    template <typename DT>
+    __device__ __forceinline__ void find_token(const DraftArgs &a, const DT *row, float u, long long o) const
+    {
+        const double incl = wave_inclusive_sum(M);
+        const double S = read_lane(incl, 63);
+        double target;
+        const int at = pick_slice(M, (double)u * S, incl, &target);
+        double G[4], frec = read_lane(f[0], at), Mrec = read_lane(f[0] * rS[0], at);
+        float mrec = read_lane(m[0], at);
+        int rec = at * RPL;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) G[q] = read_lane(f[0] * S4[0][q], at);
+#pragma unroll
+        for (int i = 1; i < RPL; ++i) {               // a later one of the lane's records
+            const double Mi = read_lane(f[i] * rS[i], at);
+            if (Mi > 0.0 && !(Mrec > target)) {
+                target -= Mrec;
+                Mrec = Mi;
+                frec = read_lane(f[i], at);
+                mrec = read_lane(m[i], at);
+                rec = at * RPL + i;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) G[q] = read_lane(f[i] * S4[i][q], at);
+            }
+        }
+        double in_chunk;
+        const int chunk = rec * 4 + pick_tile(G, target, &in_chunk);
+        // inside the chunk in units of the record's own maximum, as k_draft_stats formed the weights; the division runs
+        // while the chunk is on its way
+        in_chunk = frec > 0.0 ? in_chunk / frec : 0.0;
+        // a record without mass is only picked where the row has none (a logit of +inf): nothing there has a weight then
+        mrec = frec > 0.0 ? mrec : -neg_inf();
+        search_chunk<DT>(row, a.geo.V, chunk, mrec, a.sc, in_chunk, StoreDraftToken{a, o, frec, S});
+    }
+};
+
 // QUARTERS, grid (rows): two waves that share nothing but the flag's barrier; each loads and merges the records for
 // itself, RPL consecutive records per lane.  Wave 1 writes entropy, logsumexp and stop flag (an fp64 logarithm and a square
 // root), wave 0 finds the token.
@@ -500,120 +606,82 @@ constexpr int QUARTER_FINISH_THREADS = 128;
 template <typename DT, int RPL>
 __global__ __launch_bounds__(QUARTER_FINISH_THREADS) void k_draft_finish_quarters(DraftArgs a)
 {
-    const int b = blockIdx.x, lane = threadIdx.x & 63, nrec = a.geo.ns;
+    const int b = blockIdx.x, lane = threadIdx.x & 63;
     const long long o = (long long)b * a.io_stride;
     asm volatile("" : : "s"(a.logits), "s"(a.row_stride), "s"(a.pos), "s"(a.stop_in), "s"(a.geo.V), "s"(a.part), "s"(a.sc.c),
                  "s"(a.sc.c_dn), "s"(a.sc.c_up), "s"(a.u), "s"(a.token), "s"(a.q_tok));       // requested at once
     // independent loads first: the row's flag, its uniform and its records travel together
     const unsigned flag = request_stop_flag(a, b);
-    float m[RPL];
-    double t[RPL], S4[RPL][4];
-#pragma unroll
-    for (int i = 0; i < RPL; ++i) {
-        m[i] = neg_inf();
-        t[i] = 0.0;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) S4[i][q] = 0.0;
-        if (lane * RPL + i < nrec) {
-            const QuarterRec *p = static_cast<const QuarterRec *>(a.part) + (size_t)b * nrec + lane * RPL + i;
-            m[i] = p->m;
-            t[i] = p->t;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) S4[i][q] = p->S[q];
-        }
-    }
+    QuarterRow<RPL> r;
+    r.load(a, (size_t)b * a.geo.ns);
     const float u = a.u[o];
     if (flag_for_all_waves(a, flag)) return stopped_row(a, b, o);
-    // everything relative to the row maximum
-    float mrow = m[0];
-    if (RPL == 2) mrow = vmax(mrow, m[RPL - 1]);
-    mrow = wave_max(mrow);
-    double f[RPL], xd[RPL], rS[RPL], M = 0.0;
-#pragma unroll
-    for (int i = 0; i < RPL; ++i) {
-        rS[i] = (S4[i][0] + S4[i][1]) + (S4[i][2] + S4[i][3]);
-        f[i] = record_factor(m[i], rS[i], mrow, a.sc, &xd[i]);
-        M += f[i] * rS[i];
-    }
+    r.merge(a);
     if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) == 1) {
-        double tt = 0.0;
-#pragma unroll
-        for (int i = 0; i < RPL; ++i) tt += f[i] * (t[i] + xd[i] * rS[i]);
-        const double S = wave_sum(M);
-        tt = wave_sum(tt);
-        if (lane == 0) write_row_outputs(a, b, o, mrow, S, tt);
+        const double tt = r.entropy_sum(), S = wave_sum(r.M);
+        if (lane == 0) write_row_outputs(a, b, o, r.mrow, S, tt);
         return;
     }
-    // the token: lane, record, chunk (masses of all in units of the row maximum)
-    const double incl = wave_inclusive_sum(M);
-    const double S = read_lane(incl, 63);
-    double target;
-    const int at = pick_slice(M, (double)u * S, incl, &target);
-    double G[4], frec = read_lane(f[0], at);
-    float mrec = read_lane(m[0], at);
-    int rec = at * RPL;
+    r.template find_token<DT>(a, static_cast<const DT *>(a.logits) + draft_row_offset(a, b, a.step_j), u, o);
+}
+
+// A row's GREEDY records, RPL consecutive ones per lane; `at` is the index of its first record.
+template <int RPL>
+struct GreedyRow {
+    WaveRec p[RPL];
+    float mrow;                          // after merge(): row maximum, sums, token (uniform)
+    double S, tt;
+    int tok;
+    __device__ __forceinline__ void load(const DraftArgs &a, size_t at)
+    {
+        const int lane = threadIdx.x & 63;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) G[q] = read_lane(f[0] * S4[0][q], at);
-    if (RPL == 2) {
-        const double M0 = read_lane(f[0] * rS[0], at), M1 = read_lane(f[RPL - 1] * rS[RPL - 1], at);
-        if (M1 > 0.0 && !(M0 > target)) {             // the second of the lane's two records
-            target -= M0;
-            frec = read_lane(f[RPL - 1], at);
-            mrec = read_lane(m[RPL - 1], at);
-            rec += 1;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) G[q] = read_lane(f[RPL - 1] * S4[RPL - 1][q], at);
+        for (int i = 0; i < RPL; ++i) {
+            p[i].m = neg_inf();
+            p[i].idx = -1;
+            p[i].S = 0.0;
+            p[i].t = 0.0;
+            if (lane * RPL + i < a.geo.ns) p[i] = static_cast<const WaveRec *>(a.part)[at + lane * RPL + i];
         }
     }
-    double in_chunk;
-    const int chunk = rec * 4 + pick_tile(G, target, &in_chunk);
-    // inside the chunk in units of the record's own maximum, as k_draft_stats formed the weights; the division runs
-    // while the chunk is on its way
-    in_chunk = frec > 0.0 ? in_chunk / frec : 0.0;
-    // a record without mass is only picked where the row has none (a logit of +inf): nothing there has a weight then
-    mrec = frec > 0.0 ? mrec : -neg_inf();
-    const DT *row = static_cast<const DT *>(a.logits) + draft_row_offset(a, b);
-    search_chunk<DT>(row, a.geo.V, chunk, mrec, a.sc, in_chunk, StoreDraftToken{a, o, frec, S});
-}
+    __device__ __forceinline__ void merge(const DraftArgs &a)
+    {
+        mrow = p[0].m;
+#pragma unroll
+        for (int i = 1; i < RPL; ++i) mrow = vmax(mrow, p[i].m);
+        mrow = wave_max(mrow);
+        S = tt = 0.0;
+        int mine = -1;                                        // records are in index order: the first at the row maximum
+#pragma unroll
+        for (int i = RPL - 1; i >= 0; --i) {
+            double xd;
+            const double f = record_factor(p[i].m, p[i].S, mrow, a.sc, &xd);
+            S += f * p[i].S;
+            tt += f * (p[i].t + xd * p[i].S);
+            if (p[i].m == mrow && p[i].idx >= 0) mine = p[i].idx;
+        }
+        S = wave_sum(S);
+        tt = wave_sum(tt);
+        const unsigned long long at_max = __ballot(mine >= 0);
+        tok = at_max ? read_lane(mine, __ffsll((long long)at_max) - 1) : -1;
+    }
+};
 
 // GREEDY, grid (rows), one wave, RPL consecutive records per lane.
 template <int RPL>
 __global__ __launch_bounds__(64) void k_draft_finish_greedy(DraftArgs a)
 {
-    const int b = blockIdx.x, lane = threadIdx.x, nrec = a.geo.ns;
+    const int b = blockIdx.x;
     const long long o = (long long)b * a.io_stride;
     const unsigned flag = request_stop_flag(a, b);        // travels together with the records
-    WaveRec p[RPL];
-#pragma unroll
-    for (int i = 0; i < RPL; ++i) {
-        p[i].m = neg_inf();
-        p[i].idx = -1;
-        p[i].S = 0.0;
-        p[i].t = 0.0;
-        if (lane * RPL + i < nrec) p[i] = static_cast<const WaveRec *>(a.part)[(size_t)b * nrec + lane * RPL + i];
-    }
+    GreedyRow<RPL> r;
+    r.load(a, (size_t)b * a.geo.ns);
     if (flag_after_loads(a, flag)) return stopped_row(a, b, o);
-    float mrow = p[0].m;
-    if (RPL == 2) mrow = vmax(mrow, p[RPL - 1].m);
-    mrow = wave_max(mrow);
-    double S = 0.0, tt = 0.0;
-    int mine = -1;                                        // records are in index order: the first at the row maximum
-#pragma unroll
-    for (int i = RPL - 1; i >= 0; --i) {
-        double xd;
-        const double f = record_factor(p[i].m, p[i].S, mrow, a.sc, &xd);
-        S += f * p[i].S;
-        tt += f * (p[i].t + xd * p[i].S);
-        if (p[i].m == mrow && p[i].idx >= 0) mine = p[i].idx;
-    }
-    S = wave_sum(S);
-    tt = wave_sum(tt);
-    const unsigned long long at_max = __ballot(mine >= 0);
-    const int tok = at_max ? read_lane(mine, __ffsll((long long)at_max) - 1) : -1;
-    if (lane == 0) {
-        a.token[o] = tok;
-        if (a.q_tok) a.q_tok[o] = (float)(1.0 / S);       // the maximum has weight exp2(0) = 1
-        write_row_outputs(a, b, o, mrow, S, tt);
+    r.merge(a);
+    if (threadIdx.x == 0) {
+        a.token[o] = r.tok;
+        if (a.q_tok) a.q_tok[o] = (float)(1.0 / r.S);     // the maximum has weight exp2(0) = 1
+        write_row_outputs(a, b, o, r.mrow, r.S, r.tt);
     }
 }
 
@@ -638,7 +706,7 @@ __global__ __launch_bounds__(TOTAL_FINISH_THREADS, 4) void k_draft_finish_total(
     if (lane < nrec) p = static_cast<const WaveRec *>(a.part)[(size_t)b * nrec + lane];
     const float u = a.u[o];
     if (flag_for_all_waves(a, flag)) return stopped_row(a, b, o);
-    const DT *row = static_cast<const DT *>(a.logits) + draft_row_offset(a, b);
+    const DT *row = static_cast<const DT *>(a.logits) + draft_row_offset(a, b, a.step_j);
     // everything relative to the row maximum: this lane's record by the factor f
     const float mrow = wave_max(p.m);
     double xd;

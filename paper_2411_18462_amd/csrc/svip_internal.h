@@ -33,6 +33,41 @@ struct DraftCall {
     void *stream;
 };
 
+// A message to the host: the word of its mailbox and the ticket that shows it has arrived.
+struct Mail {
+    unsigned long long *word;
+    unsigned ticket;
+};
+
+// Buffers of a round of the decoding loop, carved from the loop workspace after the kernels' own.
+struct RoundBuffers {
+    int *tokens;               // [B, gamma_max]
+    double *lse;               // [B, gamma_max]
+    unsigned char *stop;       // [B]
+    unsigned char *done;       // [B] 1: the sequence has finished, verification skips it
+    int *draft_len;            // [B]
+    int *n_accepted;           // [B]
+    int *next_token;           // [B]
+    int *pos;                  // [B] trace position of the round (0 for finished sequences)
+    int *cap;                  // [B] length limit of the round
+    int *counter;              // [3]: sequences not finished; still drafting (greedy stream: taking part in this call);
+                               //      rounds begun before this call + the most that any sequence has ended in it
+    int *drafted, *round;      // greedy stream [B]: positions drafted in the round so far, the sequence's round
+    int *argmax;               // greedy stream [B, gamma_max + 1]: argmax of the round's target rows so far
+    char *group;               // grouped positions: draft records, then (greedy) keys
+    size_t group_bytes;
+};
+
+struct LoopArgs {
+    int *state;                // [B, SVIP_LOOP_NSTATE]
+    int B, L, gamma_max, inc, dec, max_new, round;
+    RoundBuffers rb;
+    int *out_tokens;
+    long long out_stride;
+    int *round_log;            // [rounds, B, 4] or nullptr
+    Mail mail;                 // k_round_end: where the count of running sequences goes
+};
+
 struct VerifyCall {
     bool greedy;                 // Algorithms 3 and 5: only the target, tokens and lengths are used
     const void *target, *draft;  // device
@@ -56,6 +91,17 @@ struct VerifyCall {
 };
 
 svip_status draft_step_call(const DraftCall &c);
+// Several positions per pair of launches (loop_kernels.h), for the decoding loop: calls with pos, cap, stop_in and
+// draft_len_out; their records go to `buffer` and the call's workspace is only used for its flag word.
+// group_waves: waves per position, 0 where rows are too long; group_bytes: the buffer that `group` positions need.
+int group_waves(int B, int V, int dtype);
+size_t group_bytes(int B, int V, int dtype, int group, bool greedy);
+bool draft_shape_forced();           // an experiment's override asks for records of another size
+svip_status draft_group_call(const DraftCall &c, int group, void *buffer, size_t bytes);
+// Greedy: every active sequence `group` positions further in its own round; step_j is not used.
+svip_status greedy_stream_call(const DraftCall &c, const void *target, int group, const LoopArgs &l, int last_round, Mail active,
+                               Mail running, Mail rounds);
+constexpr int STREAM_MAX_GROUP = 64;
 svip_status verify_call(const VerifyCall &c);
 
 }  // namespace svip

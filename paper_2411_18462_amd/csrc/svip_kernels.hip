@@ -1,5 +1,5 @@
 // SVIP hot path for MI355X (gfx950): launch code and the C ABI declared in include/svip.h; the kernels
-// live in draft_kernels.h, verify_kernels.h, greedy_kernels.h, pair_kernels.h and warp_kernels.h.
+// live in draft_kernels.h, loop_kernels.h, verify_kernels.h, greedy_kernels.h, pair_kernels.h and warp_kernels.h.
 //
 // svip_draft_step  =  k_draft_stats    grid (rows * records / 4) one wave per record: (m, S, t) of a tile of a row
 //                     k_draft_finish_* grid (rows)               merge of the records: entropy, stop test, inverse
@@ -14,6 +14,9 @@
 // svip_pair_stats  =  k_verify_stats   (rows j < draft_len of both models), k_pair_L (logsumexps),
 //                     k_pair_sums      grid (slices, positions)  sum min(p,q), sum q log(q/p), sum q log q
 //                     k_pair_finish    one thread per position   beta, KL, cross entropy, the bounds
+//
+// svip_loop_run   =  k_group_stats, k_group_finish   several draft positions per pair of launches (sampling)
+//                     k_stream_rows, k_stream_advance   the same with the greedy verification of the round
 //
 // svip_warp_logits =  k_warp           grid (rows), 1024 threads  top-k / top-p thresholds by radix select, masked copy
 //
@@ -42,6 +45,7 @@
 #include "sample_weights.h"
 #include "draft_kernels.h"
 #include "greedy_kernels.h"
+#include "loop_kernels.h"
 #include "verify_kernels.h"
 #include "pair_kernels.h"
 #include "warp_kernels.h"
@@ -267,7 +271,7 @@ static bool workspace_ok(const void *ws, size_t have, size_t need)
     return ws && (reinterpret_cast<uintptr_t>(ws) & 255u) == 0 && (have & ~(size_t)255) >= need;
 }
 
-svip_status draft_step_call(const DraftCall &c)
+static svip_status check_draft(const DraftCall &c)
 {
     if (!c.logits || (!c.greedy && !c.u_sample) || !c.token_out || !c.lse_out || !c.stop_out) return SVIP_ERR_NULL;
     if (!dtype_ok(c.dtype)) return SVIP_ERR_DTYPE;
@@ -277,11 +281,17 @@ svip_status draft_step_call(const DraftCall &c)
     const int vec = vec_of(c.dtype);
     if (!aligned16(c.logits) || c.row_stride % vec != 0 || (c.pos && c.pos_stride % vec != 0)) return SVIP_ERR_ALIGN;
     if (!(c.temperature > 0.f) || !isfinite(c.temperature) || !(c.h >= 0.f)) return SVIP_ERR_PARAM;
+    return SVIP_OK;
+}
 
+// floor(n / d) = umulhi(n, magic_of(d)) for d > 1 while n * d < 2^32
+static unsigned magic_of(unsigned d) { return d > 1u ? (unsigned)(0x100000000ull / d) + 1u : 0u; }
+
+// The arguments of the draft kernels but for the launch's shape.
+static DraftArgs draft_args(const DraftCall &c, const Geo &geo, void *records)
+{
     DraftArgs a;
-    a.geo = geo_draft(c.B, c.V, vec, g_tune.draft_slices);
-    if (!workspace_ok(c.workspace, c.workspace_bytes, need_draft(c.B, a.geo, c.greedy))) return SVIP_ERR_WORKSPACE;
-    const Workspace w = carve(c.workspace, c.workspace_bytes, c.B, 0);
+    a.geo = geo;
     a.logits = c.logits;
     a.row_stride = c.row_stride;
     a.pos = c.pos;
@@ -302,9 +312,14 @@ svip_status draft_step_call(const DraftCall &c)
     a.stop = c.stop_out;
     a.draft_len = c.draft_len_out;
     a.io_stride = c.io_stride;
-    a.part = w.part;
-    hipStream_t st = static_cast<hipStream_t>(c.stream);
-    const unsigned waves = (unsigned)a.geo.ns * (unsigned)c.B, rows = (unsigned)c.B;
+    a.part = records;
+    return a;
+}
+
+// The shape of the statistics launch over `rows` rows; returns its workgroups.
+static unsigned shape_draft_stats(DraftArgs &a, unsigned rows)
+{
+    const unsigned waves = (unsigned)a.geo.ns * rows;
     // Rows pinned to XCDs (see k_draft_stats) while the launch has at most 8100 waves: measured, rows of 128K bf16
     // logits, us per step without / with: 16 rows 8.15 / 8.07, 32 rows 9.2 / 8.9, 64 rows 11.2 / 10.8, 72 rows
     // (4536 one-tile waves) 11.5 / 10.85, 88 rows 12.3 / 11.5, 192 rows (6144 two-tile waves) 16.8 / 16.4; 64 and
@@ -313,10 +328,22 @@ svip_status draft_step_call(const DraftCall &c)
     a.rows_by_xcd = waves <= 8100u && a.geo.ns >= NWAVE;
     const unsigned grid = a.rows_by_xcd ? ((rows + 7u) / 8u) * 8u * (((unsigned)a.geo.ns + NWAVE - 1) / NWAVE)
                                         : (waves + NWAVE - 1) / NWAVE;
-    // the kernel's division: floor(n / d) = umulhi(n, floor(2^32 / d) + 1) while n * d < 2^32 (n < 2^26 waves with d <= 64,
-    // or n <= 8100 with d <= 128)
+    // the kernel's division: n < 2^26 waves with d <= 64, or n <= 8100 with d <= 128 (grouped positions: n <= 2^15, d <= 192)
     a.div = a.rows_by_xcd ? ((unsigned)a.geo.ns + NWAVE - 1) / NWAVE : (unsigned)a.geo.ns;
-    a.div_magic = a.div > 1u ? (unsigned)(0x100000000ull / a.div) + 1u : 0u;
+    a.div_magic = magic_of(a.div);
+    return grid;
+}
+
+svip_status draft_step_call(const DraftCall &c)
+{
+    const svip_status s = check_draft(c);
+    if (s != SVIP_OK) return s;
+    const Geo geo = geo_draft(c.B, c.V, vec_of(c.dtype), g_tune.draft_slices);
+    if (!workspace_ok(c.workspace, c.workspace_bytes, need_draft(c.B, geo, c.greedy))) return SVIP_ERR_WORKSPACE;
+    const unsigned rows = (unsigned)c.B;
+    DraftArgs a = draft_args(c, geo, carve(c.workspace, c.workspace_bytes, c.B, 0).part);
+    const unsigned grid = shape_draft_stats(a, rows);
+    hipStream_t st = static_cast<hipStream_t>(c.stream);
     bool ok = false;
     by_dtype(c.dtype, [&](auto tag) {
         using DT = decltype(tag);
@@ -337,6 +364,101 @@ svip_status draft_step_call(const DraftCall &c)
             ok = stats(std::integral_constant<RecordKind, TOTAL>{}) &&
                  launch(k_draft_finish_total<DT>, rows, TOTAL_FINISH_THREADS, st, a, SVIP_BENCH_K_DRAFT_FINISH);
     });
+    return ok ? SVIP_OK : SVIP_ERR_HIP;
+}
+
+// Grouped positions: records of one tile, at most three per lane of the finish, for every position of a launch.  Rows per
+// position are rounded up to whole rounds of the XCDs where there are that many, so that a row's records are on XCD b % 8,
+// where the workgroup of its sequence reads them.
+static Geo geo_group(int V, int vec)
+{
+    Geo g;
+    g.V = V;
+    g.ntiles = ((V + vec - 1) / vec + WG - 1) / WG;
+    g.ns = g.ntiles;
+    g.tps = 1;
+    return g;
+}
+constexpr int GROUP_MAX_RECORDS = 3 * 64;
+static int group_lane_rows(int B) { return B < 8 ? B : (B + 7) / 8 * 8; }
+
+int group_waves(int B, int V, int dtype)
+{
+    const Geo g = geo_group(V, vec_of(dtype));
+    return g.ns <= GROUP_MAX_RECORDS && B <= (1 << 16) ? B * g.ns : 0;
+}
+bool draft_shape_forced() { return g_tune.draft_slices != 0; }
+static size_t group_record_bytes(int B, const Geo &g, int group, bool greedy)
+{
+    return align256((size_t)group_lane_rows(B) * group * g.ns * (greedy ? sizeof(WaveRec) : sizeof(QuarterRec)));
+}
+size_t group_bytes(int B, int V, int dtype, int group, bool greedy)
+{
+    const Geo g = geo_group(V, vec_of(dtype));
+    return group_record_bytes(B, g, group, greedy) +
+           (greedy ? align256((size_t)group_lane_rows(B) * (group + 1) * g.ns * sizeof(unsigned long long)) : 0);
+}
+
+static svip_status group_args(const DraftCall &c, int group, void *buffer, size_t bytes, GroupArgs *a)
+{
+    const svip_status s = check_draft(c);
+    if (s != SVIP_OK) return s;
+    if (!c.pos || !c.cap || !c.stop_in || !c.draft_len_out) return SVIP_ERR_NULL;
+    if (group_waves(c.B, c.V, c.dtype) == 0 || group < 1 || group > c.k_max) return SVIP_ERR_SHAPE;
+    if (bytes < group_bytes(c.B, c.V, c.dtype, group, c.greedy)) return SVIP_ERR_WORKSPACE;
+    a->d = draft_args(c, geo_group(c.V, vec_of(c.dtype)), buffer);
+    a->group = group;
+    a->lane_rows = group_lane_rows(c.B);
+    a->lane_magic = magic_of((unsigned)a->lane_rows);
+    return SVIP_OK;
+}
+// A kernel's instance for one, two or three records per lane.
+template <typename K>
+static K by_records(int ns, K k1, K k2, K k3) { return ns <= 64 ? k1 : (ns <= 128 ? k2 : k3); }
+
+svip_status draft_group_call(const DraftCall &c, int group, void *buffer, size_t bytes)
+{
+    GroupArgs a;
+    const svip_status s = group_args(c, group, buffer, bytes, &a);
+    if (s != SVIP_OK) return s;
+    if (c.greedy || c.step_j + group > c.k_max) return SVIP_ERR_SHAPE;
+    const unsigned grid = shape_draft_stats(a.d, (unsigned)(a.lane_rows * group));
+    const unsigned threads = 64u * (unsigned)(group < GROUP_FINISH_WAVES ? group : GROUP_FINISH_WAVES);
+    hipStream_t st = static_cast<hipStream_t>(c.stream);
+    bool ok = false;
+    by_dtype(c.dtype, [&](auto tag) {
+        using DT = decltype(tag);
+        ok = launch(k_group_stats<DT>, grid, WG, st, a, SVIP_BENCH_K_DRAFT_STATS) &&
+             launch(by_records(a.d.geo.ns, k_group_finish<DT, 1>, k_group_finish<DT, 2>, k_group_finish<DT, 3>), (unsigned)c.B, threads,
+                    st, a, SVIP_BENCH_K_DRAFT_FINISH);
+    });
+    return ok ? SVIP_OK : SVIP_ERR_HIP;
+}
+
+svip_status greedy_stream_call(const DraftCall &c, const void *target, int group, const LoopArgs &l, int last_round, Mail active,
+                               Mail running, Mail rounds)
+{
+    GroupArgs a;
+    const svip_status s = group_args(c, group, l.rb.group, l.rb.group_bytes, &a);
+    if (s != SVIP_OK) return s;
+    if (!c.greedy || group > STREAM_MAX_GROUP || !target) return SVIP_ERR_SHAPE;
+    if (!aligned16(target)) return SVIP_ERR_ALIGN;
+    a.target = target;
+    a.keys = reinterpret_cast<unsigned long long *>(l.rb.group + group_record_bytes(c.B, a.d.geo, group, true));
+    a.flags = static_cast<unsigned *>(c.workspace);
+    a.last_round = last_round;
+    a.active = active;
+    a.running = running;
+    a.rounds = rounds;
+    a.l = l;
+    const int per_seq = 2 * group + 1;
+    const unsigned grid = shape_draft_stats(a.d, (unsigned)(a.lane_rows * per_seq));
+    const unsigned threads = 64u * (unsigned)(per_seq < GROUP_FINISH_WAVES ? per_seq : GROUP_FINISH_WAVES);
+    hipStream_t st = static_cast<hipStream_t>(c.stream);
+    bool ok = false;
+    by_dtype(c.dtype, [&](auto tag) { ok = launch(k_stream_rows<decltype(tag)>, grid, WG, st, a, SVIP_BENCH_K_DRAFT_STATS); });
+    ok = ok && launch(by_records(a.d.geo.ns, k_stream_advance<1>, k_stream_advance<2>, k_stream_advance<3>), (unsigned)c.B, threads, st, a,
+                      SVIP_BENCH_K_DRAFT_FINISH);
     return ok ? SVIP_OK : SVIP_ERR_HIP;
 }
 

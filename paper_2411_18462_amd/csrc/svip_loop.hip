@@ -1,14 +1,18 @@
 // Decoding loop over logit traces (Algorithm 1 and Algorithm 6) with the draft-length rules of
 // the paper's baselines (Section 3: Constant, Heuristic), built on the draft and verify calls.
 //
-// Per round:  k_round_begin  -> per-sequence trace position, length limit and stop flag of the round
-//             draft steps    -> svip_draft_step kernels reading trace row pos[b] + j, flags chained on the
-//                               device; every `check_every` steps the host reads one counter and ends
-//                               the drafting phase once every sequence has stopped
+// Sampling, per round:
+//             drafting       -> the rows of a trace are all there, so one pair of launches covers a group of draft
+//                               positions of every sequence (draft_group_call); a sequence's draft ends at the
+//                               first position of the group that stops it.  Where a position alone fills the
+//                               chip, svip_draft_step's kernels run once per position.  Flags are chained on the device.
 //             verify         -> svip_verify kernels on trace rows pos[b] .. pos[b] + draft_len[b]
 //             k_round_end    -> appends the produced tokens, advances positions, applies the length
-//                               rule, updates the counters and counts the sequences still running
-// The two counts reach the host as messages: the counting kernel stores (ticket, count) as one 8-byte word
+//                               rule, updates the counters, counts the sequences still running and sets up the next round
+// Greedy:     every sequence goes through its own rounds, a few positions per pair of launches (greedy_stream_call);
+//             the rounds as above only where a position alone fills the chip.
+// k_round_begin sets up what the first launches of a call read.
+// The counts reach the host as messages: the counting kernel stores (ticket, count) as one 8-byte word
 // into pinned host memory and the host reads that word until the ticket shows.  No copy is enqueued and the
 // stream is never synchronised inside the loop; the host launches one round ahead of the count it waits for,
 // so the GPU always has the next round queued (a round launched after the last sequence finished finds
@@ -21,43 +25,20 @@
 #include <chrono>
 
 #include "../../include/svip.h"
+#include "loop_round.h"
 #include "svip_internal.h"
 
 namespace svip {
 
 constexpr int LOOP_WG = 256;
 
-struct RoundBuffers {          // carved from the loop workspace after the kernels' own workspace
-    int *tokens;               // [B, gamma_max]
-    double *lse;               // [B, gamma_max]
-    unsigned char *stop;       // [B]
-    unsigned char *done;       // [B] 1: the sequence has finished, verification skips it
-    int *draft_len;            // [B]
-    int *n_accepted;           // [B]
-    int *next_token;           // [B]
-    int *pos;                  // [B] trace position of the round (0 for finished sequences)
-    int *cap;                  // [B] length limit of the round
-    int *counter;              // [2]: sequences still running after the round, sequences still drafting
-};
-
-struct LoopArgs {
-    int *state;                // [B, SVIP_LOOP_NSTATE]
-    int B, L, gamma_max, inc, dec, max_new, round;
-    RoundBuffers rb;
-    int *out_tokens;
-    long long out_stride;
-    int *round_log;            // [rounds, B, 4] or nullptr
-    unsigned long long *mail;  // k_round_end: where the count of running sequences goes (pinned host memory)
-    unsigned ticket;           // and the ticket it goes with
-};
-
 // ---- messages from the device to the host ----------------------------------------------------
 //
 // A host thread's mailbox: MAIL_SLOTS words of pinned host memory, allocated by the thread's first
 // svip_loop_run and kept until the process ends.  A message is (ticket << 32 | value), stored by one
 // thread of a kernel with a single system-scope store; tickets count up per host thread and never repeat
-// within 2^32 messages, message t uses word t % MAIL_SLOTS, and the loop never has more than three
-// messages outstanding, so a word is not reused before it has been read.
+// within 2^32 messages, message t uses word t % MAIL_SLOTS, and the loop never has more than
+// nine messages outstanding, so a word is not reused before it has been read.
 constexpr unsigned MAIL_SLOTS = 64;
 struct Mailbox {
     unsigned long long *host, *dev;
@@ -91,6 +72,8 @@ static bool mailbox_ready()
     return true;
 }
 
+static Mail mail_of(const Ticket &t) { return Mail{t.dev, t.id}; }
+
 static Ticket new_ticket()
 {
     Ticket t;
@@ -99,12 +82,6 @@ static Ticket new_ticket()
     t.dev = g_mail.dev + t.id % MAIL_SLOTS;
     t.host = g_mail.host + t.id % MAIL_SLOTS;
     return t;
-}
-
-__device__ __forceinline__ void post(unsigned long long *word, unsigned ticket, int value)
-{
-    __hip_atomic_store(word, ((unsigned long long)ticket << 32) | (unsigned)value, __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // Waits until the message of ticket t is there.  The kernel that posts it is already in the stream, so the
@@ -139,13 +116,63 @@ static svip_status await(const Ticket &t, int *value, hipStream_t st)
 
 static inline size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-static size_t round_buffer_bytes(int B, int k)
+// ---- which positions of a draft share a pair of launches ---------------------------------------
+//
+// A launch's time goes up by about 1 us per 1000 waves (records of one tile, 4 KB each) once it has more than about 1500 of
+// them, and a pair of launches that finds nothing to do costs about 4.5 us.
+//   Sampling: the first group takes what GROUP_WAVES_FIRST waves cover -- a whole draft of a few sequences, 8 positions of 8
+//   sequences of 152K bf16 logits, at least 2 -- and the next one, which most rounds find empty, as much of the rest
+//   as the buffer for the records holds.
+//   Greedy: STREAM_WAVES draft records per launch, at least 2 positions; the target rows come on top.  8 sequences of 152K bf16
+//   logits, 48 tokens with drafts of 1.3 positions: 600 and 1200 waves (2 positions) 482 and 472 us, 2400 (4) 483, 4000 (6) 539;
+//   more positions help longer drafts.
+// Beyond GROUP_WAVES_FIRST waves per position (64 sequences of 152K logits are just below) a position fills the chip.
+// us for 32 tokens per sequence, position by position / in groups (greedy; sampling), drafts of 1.3 | 20 positions:
+//    1 x 32000 fp32      1255 / 341; 958 / 613   | 2227 / 221; 1087 / 297
+//    8 x 151936 bf16     1301 / 326; 1479 / 887  | 2581 / 950; 2834 / 965
+//   33 x 128256 bf16     1823 / 478; 1961 / 1409 | 3921 / 2544; 3669 / 1636
+//   64 x 151936 bf16     2211 / 654; 2570 / 1731 | 5386 / 3796; 5276 / 2941
+constexpr int GROUP_WAVES_FIRST = 4800, GROUP_WAVES_MAX = 32768, STREAM_WAVES = 2400;
+
+// Positions of the first group (0: positions go one by one, they fill the chip on their own) and of later ones.
+struct GroupPlan {
+    int first, next;
+};
+static GroupPlan plan_groups(int B, int k, int V, int dtype, bool greedy)
 {
-    const size_t n = (size_t)B, nk = n * (size_t)k;
-    return up256(nk * 4) + up256(nk * 8) + 2 * up256(n) + 6 * up256(n * 4) + 256;
+    GroupPlan p = {0, 0};
+    const int waves = group_waves(B, V, dtype);
+    if (waves == 0 || waves > GROUP_WAVES_FIRST) return p;
+    const int rows = group_waves(1, V, dtype) * ((B + 7) / 8 * 8);        // waves per position with rows kept on XCDs
+    const int n = (greedy ? STREAM_WAVES : GROUP_WAVES_FIRST) / waves;
+    p.first = n > 2 ? n : 2;
+    if (greedy && p.first > STREAM_MAX_GROUP) p.first = STREAM_MAX_GROUP;
+    p.next = greedy ? p.first : GROUP_WAVES_MAX / rows;
+    if (p.first > k) p.first = k;
+    if (p.next > k) p.next = k;
+    if (p.next < p.first) p.next = p.first;
+    return p;
+}
+// Bytes for the records of the largest group; the loop's workspace has to do for every type, sampling and greedy.
+static size_t plan_bytes(int B, int k, int V)
+{
+    size_t most = 0;
+    for (int dtype = SVIP_F32; dtype <= SVIP_F16; ++dtype)
+        for (int greedy = 0; greedy < 2; ++greedy) {
+            const GroupPlan p = plan_groups(B, k, V, dtype, greedy);
+            const size_t n = p.first ? group_bytes(B, V, dtype, p.next, greedy) : 0;
+            if (n > most) most = n;
+        }
+    return most;
 }
 
-static RoundBuffers carve_round(char *p, int B, int k)
+static size_t round_buffer_bytes(int B, int k, int V)
+{
+    const size_t n = (size_t)B, nk = n * (size_t)k;
+    return up256(nk * 4) + up256(nk * 8) + 2 * up256(n) + 8 * up256(n * 4) + 256 + up256((nk + n) * 4) + plan_bytes(B, k, V);
+}
+
+static RoundBuffers carve_round(char *p, int B, int k, int V)
 {
     const size_t n = (size_t)B, nk = n * (size_t)k;
     RoundBuffers r;
@@ -158,16 +185,13 @@ static RoundBuffers carve_round(char *p, int B, int k)
     r.next_token = reinterpret_cast<int *>(p); p += up256(n * 4);
     r.pos = reinterpret_cast<int *>(p); p += up256(n * 4);
     r.cap = reinterpret_cast<int *>(p); p += up256(n * 4);
-    r.counter = reinterpret_cast<int *>(p);
+    r.counter = reinterpret_cast<int *>(p); p += 256;
+    r.drafted = reinterpret_cast<int *>(p); p += up256(n * 4);
+    r.round = reinterpret_cast<int *>(p); p += up256(n * 4);
+    r.argmax = reinterpret_cast<int *>(p); p += up256((nk + n) * 4);
+    r.group = p;
+    r.group_bytes = plan_bytes(B, k, V);
     return r;
-}
-
-// A sequence starts another round while it has produced fewer than max_new tokens and the trace
-// still holds cap + 1 rows from its position on (Algorithm 1's loop condition, plus the end of
-// the synthetic trace).
-__device__ __forceinline__ bool finished(int pos, int n0, int cap, int L, int max_new)
-{
-    return pos - n0 >= max_new || pos + cap + 1 > L;
 }
 
 __device__ __forceinline__ int block_count(int mine, int *lds)
@@ -205,23 +229,35 @@ __global__ __launch_bounds__(LOOP_WG) void k_loop_init(int *state, int B, int n0
     }
 }
 
-// one workgroup: what the round's kernels read
+// one workgroup: what the kernels of a call's first round read
 __global__ __launch_bounds__(LOOP_WG) void k_round_begin(LoopArgs a)
 {
+    __shared__ int lds[LOOP_WG / 64];
+    int running = 0;
     for (int b = threadIdx.x; b < a.B; b += LOOP_WG) {
         const int *st = a.state + (size_t)b * SVIP_LOOP_NSTATE;
-        const int done = st[2];
-        a.rb.pos[b] = done ? 0 : st[0];
-        a.rb.cap[b] = done ? 1 : st[1];
-        a.rb.stop[b] = done ? 1 : 0;
-        a.rb.done[b] = done ? 1 : 0;
-        a.rb.draft_len[b] = 0;
+        begin_sequence(a.rb, b, st[0], st[1], st[2]);
+        a.rb.drafted[b] = 0;
+        a.rb.round[b] = a.round;
+        running += st[2] ? 0 : 1;
+    }
+    const int total = block_count(running, lds);
+    if (threadIdx.x == 0) {
+        a.rb.counter[0] = a.rb.counter[1] = total;
+        a.rb.counter[2] = a.round;
     }
 }
 
+// grid (ceil(B / LOOP_WG)): the log of finished sequences up to round `a.round`, where the last of them ended
+__global__ __launch_bounds__(LOOP_WG) void k_log_idle(LoopArgs a)
+{
+    const int b = blockIdx.x * LOOP_WG + threadIdx.x;
+    if (b >= a.B || !a.rb.done[b]) return;
+    for (int r = a.rb.round[b]; r < a.round; ++r) log_idle(a, b, r);
+}
+
 // one workgroup: number of sequences that are still drafting
-__global__ __launch_bounds__(LOOP_WG) void k_count_drafting(const unsigned char *stop, int B, int *counter,
-                                                            unsigned long long *mail, unsigned ticket)
+__global__ __launch_bounds__(LOOP_WG) void k_count_drafting(const unsigned char *stop, int B, int *counter, Mail mail)
 {
     __shared__ int lds[LOOP_WG / 64];
     int n = 0;
@@ -229,7 +265,7 @@ __global__ __launch_bounds__(LOOP_WG) void k_count_drafting(const unsigned char 
     const int total = block_count(n, lds);
     if (threadIdx.x == 0) {
         counter[1] = total;
-        post(mail, ticket, total);
+        post(mail, total);
     }
 }
 
@@ -239,46 +275,99 @@ __global__ __launch_bounds__(LOOP_WG) void k_round_end(LoopArgs a)
     __shared__ int lds[LOOP_WG / 64];
     int running = 0;
     for (int b = threadIdx.x; b < a.B; b += LOOP_WG) {
-        int *st = a.state + (size_t)b * SVIP_LOOP_NSTATE;
-        int *lg = a.round_log ? a.round_log + ((size_t)a.round * a.B + b) * 4 : nullptr;
-        if (st[2]) {
-            if (lg) lg[0] = lg[1] = lg[2] = lg[3] = -1;
-            continue;
-        }
-        const int pos = st[0], cap = st[1];
-        const int g = a.rb.draft_len[b], na = a.rb.n_accepted[b];
-        int *o = a.out_tokens + (size_t)b * a.out_stride + st[6];
-        for (int j = 0; j < na; ++j) o[j] = a.rb.tokens[(size_t)b * a.gamma_max + j];
-        o[na] = a.rb.next_token[b];
-        if (lg) {
-            lg[0] = pos;
-            lg[1] = cap;
-            lg[2] = g;
-            lg[3] = na;
-        }
-        int ncap = cap + (na == g ? a.inc : -a.dec);          // every drafted token accepted: longer next time
-        ncap = ncap < 1 ? 1 : (ncap > a.gamma_max ? a.gamma_max : ncap);
-        const int npos = pos + na + 1;
-        const int done = finished(npos, st[7], ncap, a.L, a.max_new) ? 1 : 0;
-        st[0] = npos;
-        st[1] = ncap;
-        st[2] = done;
-        st[3] += 1;
-        st[4] += g;
-        st[5] += na;
-        st[6] += na + 1;
-        running += !done;
+        const int *tokens = a.rb.tokens + (size_t)b * a.gamma_max;
+        if (a.rb.done[b]) log_idle(a, b, a.round);
+        else running += end_sequence(a, b, a.round, a.rb.draft_len[b], a.rb.n_accepted[b], a.rb.next_token[b], 0, 1,
+                                     [&](int j) { return tokens[j]; });
     }
     const int total = block_count(running, lds);
     if (threadIdx.x == 0) {
         a.rb.counter[0] = total;
-        post(a.mail, a.ticket, total);
+        post(a.mail, total);
     }
 }
 
 static svip_status read_counter(const int *dev, int *host, hipStream_t st)
 {
     if (hipMemcpyAsync(host, dev, sizeof(int), hipMemcpyDeviceToHost, st) != hipSuccess) return SVIP_ERR_HIP;
+    return hipStreamSynchronize(st) == hipSuccess ? SVIP_OK : SVIP_ERR_HIP;
+}
+
+static LoopArgs loop_args(const svip_loop_config *c, const RoundBuffers &rb, int round)
+{
+    LoopArgs a;
+    a.state = c->state;
+    a.B = c->B;
+    a.L = c->L;
+    a.gamma_max = c->gamma_max;
+    a.inc = c->gamma_inc;
+    a.dec = c->gamma_dec;
+    a.max_new = c->max_new;
+    a.round = round;
+    a.rb = rb;
+    a.out_tokens = c->out_tokens;
+    a.out_stride = c->out_stride;
+    a.round_log = c->round_log;
+    a.mail = Mail{nullptr, 0};
+    return a;
+}
+
+// The draft call of round `round` for position j (of a group: its first); base: bytes of the kernels' own workspace.
+static DraftCall draft_call(const svip_loop_config *c, const RoundBuffers &rb, size_t base, int round, int j)
+{
+    DraftCall d;
+    d.greedy = c->greedy != 0;
+    d.logits = c->draft_trace;
+    d.dtype = c->dtype;
+    d.B = c->B;
+    d.V = c->V;
+    d.row_stride = c->seq_stride;
+    d.pos = rb.pos;
+    d.pos_stride = c->row_stride;
+    d.cap = rb.cap;
+    d.temperature = c->temperature;
+    d.h = c->h;
+    d.step_j = j;
+    d.k_max = c->gamma_max;
+    d.u_sample = c->greedy ? nullptr : c->u_sample + (size_t)round * c->B * c->gamma_max + j;
+    d.stop_in = rb.stop;
+    d.token_out = rb.tokens + j;
+    d.entropy_out = nullptr;
+    d.q_tok_out = nullptr;
+    d.lse_out = rb.lse + j;
+    d.stop_out = rb.stop;
+    d.draft_len_out = rb.draft_len;
+    d.io_stride = c->gamma_max;
+    d.workspace = c->workspace;
+    d.workspace_bytes = base;
+    d.stream = c->hip_stream;
+    return d;
+}
+
+// The greedy loop: pairs of launches until no sequence is active any more.  Each pair's first kernel reports what the pairs
+// before it left, so the next pair is launched while the GPU works on this one.
+static svip_status run_greedy_stream(const svip_loop_config *c, const RoundBuffers &rb, size_t base, int group, int first_round,
+                                     int max_rounds, int *rounds_run, int *running)
+{
+    hipStream_t st = static_cast<hipStream_t>(c->hip_stream);
+    LoopArgs a = loop_args(c, rb, first_round);
+    hipLaunchKernelGGL(k_round_begin, dim3(1), dim3(LOOP_WG), 0, st, a);
+    if (hipPeekAtLastError() != hipSuccess) return SVIP_ERR_HIP;
+    const DraftCall d = draft_call(c, rb, base, first_round, 0);
+    for (int active = 1; active > 0;) {
+        const Ticket t0 = new_ticket(), t1 = new_ticket(), t2 = new_ticket();
+        svip_status r = greedy_stream_call(d, c->target_trace, group, a, first_round + max_rounds, mail_of(t0), mail_of(t1), mail_of(t2));
+        if (r == SVIP_OK) r = await(t0, &active, st);
+        if (r == SVIP_OK) r = await(t1, running, st);
+        if (r == SVIP_OK) r = await(t2, rounds_run, st);
+        if (r != SVIP_OK) return r;
+    }
+    *rounds_run -= first_round;
+    if (c->round_log) {
+        a.round = first_round + *rounds_run;
+        hipLaunchKernelGGL(k_log_idle, dim3((unsigned)((c->B + LOOP_WG - 1) / LOOP_WG)), dim3(LOOP_WG), 0, st, a);
+        if (hipPeekAtLastError() != hipSuccess) return SVIP_ERR_HIP;
+    }
     return hipStreamSynchronize(st) == hipSuccess ? SVIP_OK : SVIP_ERR_HIP;
 }
 
@@ -309,7 +398,7 @@ size_t svip_loop_workspace_bytes(int B, int gamma_max, int V)
 {
     const size_t base = svip_workspace_bytes(B, gamma_max, V);
     if (base == 0) return 0;
-    return up256(base) + round_buffer_bytes(B, gamma_max);
+    return up256(base) + round_buffer_bytes(B, gamma_max, V);
 }
 
 svip_status svip_loop_init(const svip_loop_config *c)
@@ -318,7 +407,7 @@ svip_status svip_loop_init(const svip_loop_config *c)
     if (s != SVIP_OK) return s;
     hipStream_t st = static_cast<hipStream_t>(c->hip_stream);
     const size_t base = up256(svip_workspace_bytes(c->B, c->gamma_max, c->V));
-    const RoundBuffers rb = carve_round(static_cast<char *>(c->workspace) + base, c->B, c->gamma_max);
+    const RoundBuffers rb = carve_round(static_cast<char *>(c->workspace) + base, c->B, c->gamma_max, c->V);
     const svip_status r = svip_workspace_reset(c->workspace, base, c->hip_stream);
     if (r != SVIP_OK) return r;
     hipLaunchKernelGGL(k_loop_init, dim3(1), dim3(LOOP_WG), 0, st, c->state, c->B, c->n0, c->gamma0, c->L,
@@ -334,11 +423,21 @@ svip_status svip_loop_run(const svip_loop_config *c, int first_round, int max_ro
     if (first_round < 0 || max_rounds < 0 || (long long)first_round + max_rounds > c->rounds) return SVIP_ERR_SHAPE;
     hipStream_t st = static_cast<hipStream_t>(c->hip_stream);
     const size_t base = up256(svip_workspace_bytes(c->B, c->gamma_max, c->V));
-    const RoundBuffers rb = carve_round(static_cast<char *>(c->workspace) + base, c->B, c->gamma_max);
+    const RoundBuffers rb = carve_round(static_cast<char *>(c->workspace) + base, c->B, c->gamma_max, c->V);
     const int B = c->B, k = c->gamma_max;
+    const GroupPlan plan = draft_shape_forced() ? GroupPlan{0, 0} : plan_groups(B, k, c->V, c->dtype, c->greedy != 0);
 
     int running = 0, done_rounds = 0;
-    svip_status r = read_counter(rb.counter, &running, st);
+    svip_status r;
+    if (c->greedy && plan.first != 0 && max_rounds > 0) {
+        if (!mailbox_ready()) return SVIP_ERR_HIP;
+        r = run_greedy_stream(c, rb, base, plan.first, first_round, max_rounds, &done_rounds, &running);
+        if (r != SVIP_OK) return r;
+        if (rounds_run_host) *rounds_run_host = done_rounds;
+        if (running_host) *running_host = running;
+        return SVIP_OK;
+    }
+    r = read_counter(rb.counter, &running, st);
     if (r != SVIP_OK) return r;
     if (running > 0 && max_rounds > 0 && !mailbox_ready()) return SVIP_ERR_HIP;
     // `running` is the count after the last round whose message has been read; `before` is the ticket of the
@@ -350,58 +449,21 @@ svip_status svip_loop_run(const svip_loop_config *c, int first_round, int max_ro
     for (int i = 0; i < max_rounds && running > 0; ++i) {
         const int round = first_round + i;
         const Ticket mine = new_ticket();
-        LoopArgs a;
-        a.state = c->state;
-        a.B = B;
-        a.L = c->L;
-        a.gamma_max = k;
-        a.inc = c->gamma_inc;
-        a.dec = c->gamma_dec;
-        a.max_new = c->max_new;
-        a.round = round;
-        a.rb = rb;
-        a.out_tokens = c->out_tokens;
-        a.out_stride = c->out_stride;
-        a.round_log = c->round_log;
-        a.mail = mine.dev;
-        a.ticket = mine.id;
-        hipLaunchKernelGGL(k_round_begin, dim3(1), dim3(LOOP_WG), 0, st, a);
+        LoopArgs a = loop_args(c, rb, round);
+        a.mail = mail_of(mine);
+        if (i == 0) hipLaunchKernelGGL(k_round_begin, dim3(1), dim3(LOOP_WG), 0, st, a);
 
-        const size_t uoff = (size_t)round * B * k;
         bool idle = false;        // the round before this one finished the last sequence
-        for (int j = 0; j < k; ++j) {
-            DraftCall d;
-            d.greedy = c->greedy != 0;
-            d.logits = c->draft_trace;
-            d.dtype = c->dtype;
-            d.B = B;
-            d.V = c->V;
-            d.row_stride = c->seq_stride;
-            d.pos = rb.pos;
-            d.pos_stride = c->row_stride;
-            d.cap = rb.cap;
-            d.temperature = c->temperature;
-            d.h = c->h;
-            d.step_j = j;
-            d.k_max = k;
-            d.u_sample = c->greedy ? nullptr : c->u_sample + uoff + j;
-            d.stop_in = rb.stop;
-            d.token_out = rb.tokens + j;
-            d.entropy_out = nullptr;
-            d.q_tok_out = nullptr;
-            d.lse_out = rb.lse + j;
-            d.stop_out = rb.stop;
-            d.draft_len_out = rb.draft_len;
-            d.io_stride = k;
-            d.workspace = c->workspace;
-            d.workspace_bytes = base;             // the kernels' own part of the loop workspace
-            d.stream = c->hip_stream;
-            r = draft_step_call(d);
-            if (r != SVIP_OK) return r;
-            if (c->check_every > 0 && (j + 1) % c->check_every == 0 && j + 1 < k) {
+        int polled = 0;           // draft positions launched when the device was last asked
+        for (int j = 0, n = 1; j < k; j += n) {
+            // asked before a launch that may find nothing to do, but not where it is the last pair of the round: that costs
+            // less than the answer (about 7 us)
+            n = plan.first == 0 ? 1 : (j == 0 ? plan.first : (k - j < plan.next ? k - j : plan.next));
+            const bool last_pair = plan.first != 0 && j + n == k;
+            if (j > 0 && c->check_every > 0 && j / c->check_every > polled / c->check_every && !last_pair) {
+                polled = j;
                 const Ticket poll = new_ticket();
-                hipLaunchKernelGGL(k_count_drafting, dim3(1), dim3(LOOP_WG), 0, st, rb.stop, B, rb.counter, poll.dev,
-                                   poll.id);
+                hipLaunchKernelGGL(k_count_drafting, dim3(1), dim3(LOOP_WG), 0, st, rb.stop, B, rb.counter, mail_of(poll));
                 if (hipPeekAtLastError() != hipSuccess) return SVIP_ERR_HIP;
                 int drafting = 0;
                 r = await(poll, &drafting, st);
@@ -417,6 +479,9 @@ svip_status svip_loop_run(const svip_loop_config *c, int first_round, int max_ro
                 }
                 if (drafting == 0) break;
             }
+            const DraftCall d = draft_call(c, rb, base, round, j);
+            r = plan.first == 0 ? draft_step_call(d) : draft_group_call(d, n, rb.group, rb.group_bytes);
+            if (r != SVIP_OK) return r;
         }
         if (idle) break;
 
@@ -436,7 +501,7 @@ svip_status svip_loop_run(const svip_loop_config *c, int first_round, int max_ro
         v.draft_tokens = rb.tokens;
         v.draft_len = rb.draft_len;
         v.draft_lse = rb.lse;
-        v.u_accept = c->greedy ? nullptr : c->u_accept + uoff;
+        v.u_accept = c->greedy ? nullptr : c->u_accept + (size_t)round * B * k;
         v.u_resample = c->greedy ? nullptr : c->u_resample + (size_t)round * B;
         v.n_accepted_out = rb.n_accepted;
         v.next_token_out = rb.next_token;
