@@ -81,18 +81,6 @@ __device__ __forceinline__ bool flag_after_loads(const DraftArgs &a, unsigned fl
     return a.stop_in && flag;
 }
 
-// One batch of a wave: chunks [c0, c0 + NU) of 64 vectors each; CHECKED for the row's last, partial tile.
-template <typename DT, int NU, bool CHECKED>
-__device__ __forceinline__ void wave_load(const DT *row, int V, int c0, typename RawOf<DT>::type (&raw)[NU])
-{
-    const int lane = threadIdx.x & 63;
-    if (CHECKED) {
-        load_raw_tail<DT, NU, 64>(row, c0 * 64 + lane, V, raw);
-    } else {
-#pragma unroll
-        for (int u = 0; u < NU; ++u) raw[u] = load_raw<DT>(row, (c0 + u) * 64 + lane);
-    }
-}
 // Per lane, what a wave has summed so far.  QUARTERS: the sum of the weights of each chunk of its one tile.  Otherwise:
 // the sum of the weights, and beside it the number of weights that are exactly 1 in the vectors that hold the maximum.
 // Those have to stay out of the fp32 sum (next to a 1 the tail of a confident row, 1e-4 and less, would lose its low bits).
@@ -422,50 +410,18 @@ __global__ __launch_bounds__(WG, TPS == 1 ? 8 : 6) void k_draft_stats(DraftArgs 
     draft_record<DT, KIND, TPS>(a, static_cast<const DT *>(a.logits) + draft_row_offset(a, b, a.step_j), b, r, (size_t)b * a.geo.ns + r);
 }
 
-// The inverse CDF inside one chunk of a row by one wave: the smallest index whose inclusive prefix of weights
-// exp2((z - m) c), counted from the start of the chunk, exceeds `target`.  A lane holds one vector; fp32 sums per
-// vector, fp64 over the lanes.  The lane that holds the token reports it (see locate_batch).  If rounding leaves no
-// crossing, it is the last index with positive weight (-1 if there is none).
+// The inverse CDF inside one chunk of a row by one wave (search_chunks) over weights exp2((z - m) c).
 template <typename DT, typename Report>
 __device__ __forceinline__ void search_chunk(const DT *row, int V, int chunk, float m, const Scale &sc, double target, Report report)
 {
     constexpr int N = VecOf<DT>::N;
-    const int lane = threadIdx.x & 63;
-    float z[N], w[N];
+    float z[N], w[1][N];
     typename RawOf<DT>::type raw[1];
     wave_load<DT, 1, true>(row, V, chunk, raw);
     unpack<DT>(raw[0], z);
 #pragma unroll
-    for (int e = 0; e < N; ++e) w[e] = exp2_raw(scaled_below_floored(z[e] - m, sc));
-    const double g = (double)tree_sum<N>(w);
-    const double incl = wave_inclusive_sum(g);
-    const unsigned long long hit = __ballot(g > 0.0 && incl > target), mass = __ballot(g > 0.0);
-    double C = incl - g;
-    int pick = -1, lastpos = -1;
-    float wp = 0.f, wl = 0.f;
-#pragma unroll
-    for (int e = 0; e < N; ++e) {
-        C += (double)w[e];
-        if (w[e] > 0.f) {
-            lastpos = e;
-            wl = w[e];
-            if (pick < 0 && C > target) {
-                pick = e;
-                wp = w[e];
-            }
-        }
-    }
-    const int base = (chunk * 64 + lane) * N;
-    if (hit) {
-        if (lane == __ffsll((long long)hit) - 1) {
-            if (pick < 0) report(base + lastpos, wl);
-            else report(base + pick, wp);
-        }
-    } else if (mass) {
-        if (lane == 63 - __clzll((long long)mass)) report(base + lastpos, wl);
-    } else if (lane == 0) {
-        report(-1, 0.f);
-    }
+    for (int e = 0; e < N; ++e) w[0][e] = exp2_raw(scaled_below_floored(z[e] - m, sc));
+    search_chunks<N, 1>(w, chunk, target, report);
 }
 
 // What the thread that finds the draft token does with it (see locate_batch's `report`); unit: the weight of 1 of the
@@ -589,7 +545,7 @@ struct QuarterRow {
             }
         }
         double in_chunk;
-        const int chunk = rec * 4 + pick_tile(G, target, &in_chunk);
+        const int chunk = rec * 4 + pick_piece(G, target, &in_chunk);
         // inside the chunk in units of the record's own maximum, as k_draft_stats formed the weights; the division runs
         // while the chunk is on its way
         in_chunk = frec > 0.0 ? in_chunk / frec : 0.0;

@@ -26,9 +26,9 @@ __global__ __launch_bounds__(64) void k_pair_L(PairArgs a)
     const int g = clamp_len(graw, a.v.k);
     if (graw != g && j == 0) atomicOr(a.v.ws.flags, (unsigned)SVIP_FLAG_BAD_DRAFT_LEN);
     if (j >= g) return;
-    a.L[2 * y] = row_L(a.v.ws.part, stat_row(a.v, b, a.v.kd + j), a.v.geo.ns);
+    a.L[2 * y] = row_L(a.v, b, a.v.kd + j);
     a.L[2 * y + 1] = a.v.draft_lse ? a.v.draft_lse[y] * 1.4426950408889634
-                                   : row_L(a.v.ws.part, stat_row(a.v, b, j), a.v.geo.ns);
+                                   : row_L(a.v, b, j);
 }
 
 // One batch of NU vector pairs per thread: with p = exp2(xp), q = exp2(xq) the normalised

@@ -175,6 +175,19 @@ __device__ __forceinline__ void load_raw_tail(const DT *row, int v0, int V, type
     }
 }
 
+// One batch of a wave: chunks [c0, c0 + NU) of 64 vectors each; CHECKED for the row's last, partial tile.
+template <typename DT, int NU, bool CHECKED>
+__device__ __forceinline__ void wave_load(const DT *row, int V, int c0, typename RawOf<DT>::type (&raw)[NU])
+{
+    const int lane = threadIdx.x & 63;
+    if (CHECKED) {
+        load_raw_tail<DT, NU, 64>(row, c0 * 64 + lane, V, raw);
+    } else {
+#pragma unroll
+        for (int u = 0; u < NU; ++u) raw[u] = load_raw<DT>(row, (c0 + u) * 64 + lane);
+    }
+}
+
 // Widening of one 16-byte vector to fp32 (exact for every storage type).
 template <typename DT>
 __device__ __forceinline__ void unpack(const typename RawOf<DT>::type &v, float (&z)[VecOf<DT>::N]);
@@ -427,12 +440,17 @@ __device__ __forceinline__ void lse_batch(const DT *row, int t0, float &m, float
     accumulate_lse<N, NU>(z, m, ref, S, sc);
 }
 
-// (ref, S) of tiles [tb, te) of one row with S = sum exp2(z c - ref): Partial::m holds ref (log2
-// units), Partial::S the sum; m = -inf marks a slice without finite logits.  Batches hold 32
+// (ref, S) of tiles [tb, te) of one row with S = sum exp2(z c - ref): m holds ref (log2
+// units); m = -inf marks a slice without finite logits.  Batches hold 32
 // logits per thread (4 bf16 vectors or 8 fp32 vectors): small enough for 8 waves per SIMD.
 // Result valid in thread 0.
+struct alignas(16) LsePart {
+    double S;
+    float m;
+    float pad;
+};
 template <typename DT>
-__device__ __forceinline__ Partial slice_lse(const DT *row, int V, int tb, int te, const Scale &sc,
+__device__ __forceinline__ LsePart slice_lse(const DT *row, int V, int tb, int te, const Scale &sc,
                                              CombineLds &lds)
 {
     constexpr int N = VecOf<DT>::N, NB = 32 / N;
@@ -461,11 +479,10 @@ __device__ __forceinline__ Partial slice_lse(const DT *row, int V, int tb, int t
     Sd = wave_sum(Sd);
     if (lane == 0) lds.S[wave] = Sd;
     __syncthreads();
-    Partial p;
+    LsePart p;
     p.m = rg;
-    p.idx = -1;
+    p.pad = 0.f;
     p.S = 0.0;
-    p.t = 0.0;
     if (tid == 0) {
 #pragma unroll
         for (int w = 0; w < NWAVE; ++w) p.S += lds.S[w];
@@ -540,6 +557,68 @@ __device__ __forceinline__ unsigned long long slice_argmax(const DT *row, int V,
 #pragma unroll
     for (int w = 1; w < NWAVE; ++w) best = lds[w] > best ? lds[w] : best;
     return best;
+}
+
+// ---- inverse CDF by one wave ----------------------------------------------------------
+//
+// The smallest index in chunks [chunk, chunk + NU) of a row whose inclusive prefix of weights, counted from the start of the
+// first of them, exceeds `target`.  w[u]: the weights of this lane's vector of chunk + u (fp32, >= 0); fp32 sums per
+// vector, fp64 over the lanes.  The lane that holds the token reports (token, its weight).  If rounding leaves no
+// crossing, it is the last index with positive weight (-1 if there is none).
+template <int N, int NU, typename Report>
+__device__ __forceinline__ void search_chunks(const float (&w)[NU][N], int chunk, double target, Report report)
+{
+    const int lane = threadIdx.x & 63;
+    double g[NU], incl[NU];
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+        g[u] = (double)tree_sum<N>(w[u]);
+        incl[u] = wave_inclusive_sum(g[u]);
+    }
+#pragma unroll
+    for (int u = 1; u < NU; ++u) incl[u] += read_lane(incl[u - 1], 63);
+    int at = -1, last = -1;                               // chunk that holds the crossing; the last one with mass
+    unsigned long long hit = 0ull, mass = 0ull;
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+        const unsigned long long h = __ballot(g[u] > 0.0 && incl[u] > target), m = __ballot(g[u] > 0.0);
+        if (h && at < 0) {
+            at = u;
+            hit = h;
+        }
+        if (m) {
+            last = u;
+            mass = m;
+        }
+    }
+    if (last < 0) {
+        if (lane == 0) report(-1, 0.f);
+        return;
+    }
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+        if (u != (at >= 0 ? at : last)) continue;
+        double C = incl[u] - g[u];
+        int pick = -1, lastpos = -1;
+        float wp = 0.f, wl = 0.f;
+#pragma unroll
+        for (int e = 0; e < N; ++e) {
+            C += (double)w[u][e];
+            if (w[u][e] > 0.f) {
+                lastpos = e;
+                wl = w[u][e];
+                if (pick < 0 && C > target) {
+                    pick = e;
+                    wp = w[u][e];
+                }
+            }
+        }
+        const int base = ((chunk + u) * 64 + lane) * N;
+        if (lane == (at >= 0 ? __ffsll((long long)hit) - 1 : 63 - __clzll((long long)mass))) {
+            if (at < 0 || pick < 0) report(base + lastpos, wl);
+            else report(base + pick, wp);
+        }
+    }
 }
 
 // ---- in-slice inverse CDF ---------------------------------------------------------

@@ -53,61 +53,58 @@ struct ResidualWeights {       // w_i = max(0, p_i - q_i), normalised p and q
     }
 };
 
-// One batch of NU vectors per thread of the rejected position's rows: the residual mass
-// max(0, p - q) (if RESID) and the target mass p of every tile of the batch, into Wt / Pt at tile
+// One batch of NU vectors per thread: the mass max(0, p - q) (RESID) or p of every tile of the batch, into M at tile
 // index u0 + u (tiles of a slice are numbered from 0; at most TILE_MASSES of them are kept apart,
 // later ones are added to the last entry).
 template <typename DT, int NU, bool RESID, bool CHECKED>
 __device__ __forceinline__ void mass_batch(const DT *prow, const DT *qrow, int V, int t0, int u0, const ExpRef &ep,
-                                           const ExpRef &eq, float (&Wt)[TILE_MASSES], float (&Pt)[TILE_MASSES])
+                                           const ExpRef &eq, float (&M)[TILE_MASSES])
 {
     constexpr int N = VecOf<DT>::N;
     const int tid = threadIdx.x;
     typename RawOf<DT>::type rp[NU], rq[NU];
+    if (CHECKED) {
+        load_raw_tail<DT, NU, WG>(prow, t0 * WG + tid, V, rp);
+        if (RESID) load_raw_tail<DT, NU, WG>(qrow, t0 * WG + tid, V, rq);
+    } else {
 #pragma unroll
-    for (int u = 0; u < NU; ++u) {
-        const int vi = (t0 + u) * WG + tid;
-        rp[u] = CHECKED ? load_raw_checked(prow, vi, V) : load_raw<DT>(prow, vi);
-        if (RESID) rq[u] = CHECKED ? load_raw_checked(qrow, vi, V) : load_raw<DT>(qrow, vi);
+        for (int u = 0; u < NU; ++u) {
+            rp[u] = load_raw<DT>(prow, (t0 + u) * WG + tid);
+            if (RESID) rq[u] = load_raw<DT>(qrow, (t0 + u) * WG + tid);
+        }
     }
 #pragma unroll
     for (int u = 0; u < NU; ++u) {
-        float zp[N], pw[N];
+        float zp[N], w[N];
         unpack<DT>(rp[u], zp);
 #pragma unroll
-        for (int e = 0; e < N; ++e) pw[e] = ep(zp[e]);
-        const float Pb = tree_sum<N>(pw);
-        float Wb = 0.f;
+        for (int e = 0; e < N; ++e) w[e] = ep(zp[e]);
         if (RESID) {
-            float zq[N], w[N];
+            float zq[N];
             unpack<DT>(rq[u], zq);
 #pragma unroll
-            for (int e = 0; e < N; ++e) w[e] = fmaxf(pw[e] - eq(zq[e]), 0.f);
-            Wb = tree_sum<N>(w);
+            for (int e = 0; e < N; ++e) w[e] = fmaxf(w[e] - eq(zq[e]), 0.f);
         }
+        const float mass = tree_sum<N>(w);
         const int slot = min(u0 + u, TILE_MASSES - 1);
 #pragma unroll
-        for (int v = 0; v < TILE_MASSES; ++v) {
-            Pt[v] += (v == slot) ? Pb : 0.f;
-            if (RESID) Wt[v] += (v == slot) ? Wb : 0.f;
-        }
+        for (int v = 0; v < TILE_MASSES; ++v) M[v] += (v == slot) ? mass : 0.f;
     }
 }
 
-// Per-thread residual and target masses of tiles [tb, te), tile by tile, in batches of up to
-// LOCATE_UNROLL vectors (the same grouping of additions as the in-slice search).
+// Per-thread masses of tiles [tb, te), tile by tile, in batches of up to LOCATE_UNROLL vectors (the same grouping of
+// additions as the in-slice search). 
 template <typename DT, bool RESID>
 __device__ __forceinline__ void slice_mass(const DT *prow, const DT *qrow, int V, int tb, int te,
-                                           const ExpRef &ep, const ExpRef &eq, float (&Wt)[TILE_MASSES],
-                                           float (&Pt)[TILE_MASSES])
+                                           const ExpRef &ep, const ExpRef &eq, float (&M)[TILE_MASSES])
 {
     constexpr int N = VecOf<DT>::N;
     const int fe = min(te, V / (WG * N));
     int t0 = tb;
-    for (; t0 + 4 <= fe; t0 += 4) mass_batch<DT, 4, RESID, false>(prow, qrow, V, t0, t0 - tb, ep, eq, Wt, Pt);
-    if (t0 + 2 <= fe) { mass_batch<DT, 2, RESID, false>(prow, qrow, V, t0, t0 - tb, ep, eq, Wt, Pt); t0 += 2; }
-    if (t0 + 1 <= fe) { mass_batch<DT, 1, RESID, false>(prow, qrow, V, t0, t0 - tb, ep, eq, Wt, Pt); t0 += 1; }
-    if (t0 < te) mass_batch<DT, 1, RESID, true>(prow, qrow, V, t0, t0 - tb, ep, eq, Wt, Pt);
+    for (; t0 + 4 <= fe; t0 += 4) mass_batch<DT, 4, RESID, false>(prow, qrow, V, t0, t0 - tb, ep, eq, M);
+    if (t0 + 2 <= fe) { mass_batch<DT, 2, RESID, false>(prow, qrow, V, t0, t0 - tb, ep, eq, M); t0 += 2; }
+    if (t0 + 1 <= fe) { mass_batch<DT, 1, RESID, false>(prow, qrow, V, t0, t0 - tb, ep, eq, M); t0 += 1; }
+    if (t0 < te) mass_batch<DT, 1, RESID, true>(prow, qrow, V, t0, t0 - tb, ep, eq, M);
 }
 
 // Choice of the slice that contains `target` among per-lane slice masses M (lane order =
@@ -125,18 +122,18 @@ __device__ __forceinline__ int pick_slice(double M, double target, double incl, 
     return s;
 }
 
-// Choice of the tile inside a slice from the slice's tile masses G (uniform values): the first tile
-// whose inclusive prefix exceeds `target` (relative to the slice start), else the last tile with mass.
-// Returns the tile and the target relative to the tile start.
-__device__ __forceinline__ int pick_tile(const double (&G)[TILE_MASSES], double target, double *local_target)
+// Choice of one of a few consecutive pieces from their masses G (uniform values): the first whose inclusive prefix exceeds
+// `target` (relative to the start of the first), else the last with mass.  Returns it and the target relative to its start.
+template <int K>
+__device__ __forceinline__ int pick_piece(const double (&G)[K], double target, double *local_target)
 {
-    int tile = -1, lastpos = 0;
+    int piece = -1, lastpos = 0;
     double before = 0.0, before_last = 0.0, run = 0.0;
 #pragma unroll
-    for (int v = 0; v < TILE_MASSES; ++v) {
+    for (int v = 0; v < K; ++v) {
         if (G[v] > 0.0) {
-            if (tile < 0 && run + G[v] > target) {
-                tile = v;
+            if (piece < 0 && run + G[v] > target) {
+                piece = v;
                 before = run;
             }
             lastpos = v;
@@ -144,12 +141,12 @@ __device__ __forceinline__ int pick_tile(const double (&G)[TILE_MASSES], double 
         }
         run += G[v];
     }
-    if (tile < 0) {
-        tile = lastpos;
+    if (piece < 0) {
+        piece = lastpos;
         before = before_last;
     }
     *local_target = target - before;
-    return tile;
+    return piece;
 }
 
 }  // namespace svip

@@ -5,9 +5,8 @@
 //                     k_draft_finish_* grid (rows)               merge of the records: entropy, stop test, inverse
 //                                      CDF inside the one record that holds the draw (greedy: the first maximum)
 // svip_verify      =  k_verify_stats   grid (stat rows * slices) per-slice (reference, sum) of every needed row
-//                     k_accept         grid (sequences), 1 wave  p/q tests, ballot scan for the first rejection
-//                     k_resid          grid (sequences * slices) slice masses of the residual / bonus row; the
-//                                      workgroup that finishes a sequence last draws the token
+//                     k_resid          grid (sequences * slices) p/q tests, ballot scan for the first rejection, slice masses
+//                                      of the residual / bonus row; the workgroup that finishes a sequence last draws the token
 // svip_verify_greedy = k_argmax        grid (target rows * slices) first maximum per slice, no exponentials
 //                     k_accept_greedy  grid (sequences), 1 wave  argmax p == x test, ballot, correction = argmax p
 //
@@ -204,10 +203,10 @@ static bool quarter_records(int B, const Geo &g) { return g.tps == 1 && (long lo
 
 // ---- workspace each call needs (its own geometry; svip_workspace_bytes bounds them all) -------
 
-// flag word + records + ticket counters + slice masses of the residual pass (mass_slices per sequence)
+// flag word + ticket counters + slice masses of the residual pass (mass_slices per sequence)
 static size_t ws_fixed_bytes(int B, int mass_slices)
 {
-    return HEADER_BYTES + ws_rec_bytes(B) + ws_mass_bytes(B, mass_slices) + ws_ticket_bytes(B);
+    return HEADER_BYTES + ws_unused_bytes(B) + ws_mass_bytes(B, mass_slices) + ws_ticket_bytes(B);
 }
 
 static size_t need_draft(int B, const Geo &g, bool greedy)
@@ -505,7 +504,7 @@ static svip_status verify_greedy_call(const VerifyCall &c)
     a.n_accepted = c.n_accepted_out;
     a.next_token = c.next_token_out;
     a.skip = c.skip;
-    a.keys = reinterpret_cast<unsigned long long *>(w.part);
+    a.keys = static_cast<unsigned long long *>(w.part);
     a.flags = w.flags;
     hipStream_t st = static_cast<hipStream_t>(c.stream);
     bool ok = false;
@@ -571,7 +570,6 @@ svip_status verify_call(const VerifyCall &c)
     by_dtype(c.dtype, [&](auto tag) {
         using DT = decltype(tag);
         ok = launch(k_verify_stats<DT>, g_stats, WG, st, a, SVIP_BENCH_K_VERIFY_STATS) &&
-             launch(k_accept<DT>, (unsigned)c.B, 64, st, a, SVIP_BENCH_K_ACCEPT) &&
              (a.geo_s.tps <= TILE_MASSES ? launch(k_resid<DT, true>, g_resid, WG, st, a, SVIP_BENCH_K_RESID)
                                          : launch(k_resid<DT, false>, g_resid, WG, st, a, SVIP_BENCH_K_RESID));
     });
@@ -829,7 +827,7 @@ svip_status svip_pair_stats(const void *target_logits, const void *draft_logits,
     a.v.next_token = nullptr;
     a.v.accept_prob = nullptr;
     a.v.ws = carve(workspace, workspace_bytes, B, 0);
-    char *after = reinterpret_cast<char *>(a.v.ws.part) + part_bytes;
+    char *after = static_cast<char *>(a.v.ws.part) + part_bytes;
     a.L = reinterpret_cast<double *>(after);
     a.sums = reinterpret_cast<double *>(after + L_bytes);
     a.c = c;

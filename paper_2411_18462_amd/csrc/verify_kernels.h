@@ -9,17 +9,18 @@ namespace svip {
 // ---- verify: statistics ------------------------------------------------------------------------
 
 // Statistics rows of sequence b are numbered jj = 0 .. kd + k: first the kd draft rows (only
-// when the draft logsumexps are recomputed), then the k + 1 target rows.
-__device__ __forceinline__ size_t stat_row(const VerifyArgs &a, int b, int jj)
+// when the draft logsumexps are recomputed), then the k + 1 target rows.  Slice s of row jj is at stat_at: a sequence's
+// rows lie side by side, as the lanes of the wave that merges them do.
+__device__ __forceinline__ size_t stat_at(const VerifyArgs &a, int b, int jj, int s)
 {
-    return (size_t)b * (a.kd + a.k + 1) + jj;
+    return ((size_t)b * a.geo.ns + s) * (a.kd + a.k + 1) + jj;
 }
 
 // grid (sequences * rows per sequence * slices).  Draft rows are needed for j < draft_len[b],
 // target rows for j <= draft_len[b]; workgroups of other rows exit at once.  (Handing the acceptance
 // test to the workgroup that finishes a sequence last was measured and dropped here: the wait for the
 // acknowledged stores and the ticket adds about 1 us to every workgroup of a kernel whose workgroups
-// live about 5 us, and the pass went from 47 us to 63 us; the separate one-wave kernel costs 5 us.)
+// live about 5 us, and the pass went from 47 us to 63 us.)
 template <typename DT>
 __global__ __launch_bounds__(WG, 8) void k_verify_stats(VerifyArgs a)
 {
@@ -44,60 +45,85 @@ __global__ __launch_bounds__(WG, 8) void k_verify_stats(VerifyArgs a)
         const int tb = s * a.geo.tps, te = min(tb + a.geo.tps, a.geo.ntiles);
         // the LDS block can be reused at once: every wave has read the maxima before the second barrier of
         // slice_lse, and thread 0 has read the sums before its wave reaches the next item's first barrier
-        const Partial p = slice_lse<DT>(row, a.geo.V, tb, te, a.sc, lds);
-        if (threadIdx.x == 0) a.ws.part[stat_row(a, b, jj) * a.geo.ns + s] = p;
+        const LsePart p = slice_lse<DT>(row, a.geo.V, tb, te, a.sc, lds);
+        if (threadIdx.x == 0) static_cast<LsePart *>(a.ws.part)[stat_at(a, b, jj, s)] = p;
     }
 }
 
 // ---- verify: acceptance test and first rejection -------------------------------------------
 
-// logsumexp * log2(e) of statistics row y from its slices' (ref, S) pairs (slice_lse): the sums are
-// brought to the largest reference with single-precision exp2 of the (small, exactly formed)
-// reference differences and added in fp64.  Slices are fetched four at a time so that the loads
-// of a chunk are in flight together.
-template <int CH = 4>       // slices fetched together
-__device__ __forceinline__ double row_L(const Partial *part, size_t y, int ns)
-{
+// The logsumexp of statistics row jj of sequence b from its slices: the sums are brought to the largest
+// reference with single-precision exp2 of the (small, exactly formed) reference differences and added in fp64.  CH slices
+// are requested together, the first of them (request) before the caller's other loads are waited for.
+template <int CH>
+struct RowStats {
     float r = neg_inf();
     double S = 0.0;
-    for (int s0 = 0; s0 < ns; s0 += CH) {
-        float pm[CH];
-        double pS[CH];
+    LsePart p[CH];
+    __device__ __forceinline__ void request(const VerifyArgs &a, int b, int jj, int s0 = 0)
+    {
 #pragma unroll
-        for (int u = 0; u < CH; ++u) {          // the loads first, all of them ...
-            const Partial *p = part + y * ns + (s0 + u < ns ? s0 + u : 0);
-            pm[u] = p->m;
-            pS[u] = p->S;
-        }
+        for (int u = 0; u < CH; ++u)
+            p[u] = static_cast<const LsePart *>(a.ws.part)[stat_at(a, b, jj, s0 + u < a.geo.ns ? s0 + u : s0)];
+    }
+    __device__ __forceinline__ void add(int n)
+    {
 #pragma unroll
-        for (int u = 0; u < CH; ++u) {          // ... then what depends on them (else each load is waited for in turn)
-            if (!(s0 + u < ns) || !(pS[u] > 0.0)) {
-                pm[u] = neg_inf();
-                pS[u] = 0.0;
+        for (int u = 0; u < CH; ++u)            // after all of the loads (else each is waited for in turn)
+            if (!(u < n) || !(p[u].S > 0.0)) {
+                p[u].m = neg_inf();
+                p[u].S = 0.0;
             }
-        }
-        float rc = pm[0];
+        float rc = p[0].m;
 #pragma unroll
-        for (int u = 1; u < CH; ++u) rc = vmax(rc, pm[u]);
-        if (rc == neg_inf()) continue;
+        for (int u = 1; u < CH; ++u) rc = vmax(rc, p[u].m);
+        if (rc == neg_inf()) return;
         if (rc > r) {
             if (r != neg_inf()) S *= (double)exp2_raw((float)((double)r - (double)rc));
             r = rc;
         }
 #pragma unroll
         for (int u = 0; u < CH; ++u)
-            if (pm[u] != neg_inf()) S += pS[u] * (double)exp2_raw((float)((double)pm[u] - (double)r));
+            if (p[u].m != neg_inf()) S += p[u].S * (double)exp2_raw((float)((double)p[u].m - (double)r));
     }
-    return (double)r + log2(S);
+    // what request() fetched, then the rest of the row
+    __device__ __forceinline__ void merge(const VerifyArgs &a, int b, int jj)
+    {
+        add(a.geo.ns);
+        for (int s0 = CH; s0 < a.geo.ns; s0 += CH) {
+            request(a, b, jj, s0);
+            add(a.geo.ns - s0);
+        }
+    }
+    __device__ __forceinline__ double L() const { return (double)r + log2(S); }      // logsumexp * log2(e)
+};
+template <int CH = 4>
+__device__ __forceinline__ double row_L(const VerifyArgs &a, int b, int jj)
+{
+    RowStats<CH> row;
+    row.request(a, b, jj);
+    row.merge(a, b, jj);
+    return row.L();
 }
 
-// The acceptance test of sequence b by one wave: lane = position, 64 positions per pass.  Lanes
-// j <= draft_len merge the statistics of target row j; lanes j < draft_len run the acceptance
-// test; a ballot finds the first rejection.  Returns (uniform over the wave) what the residual
-// kernels need; with `publish` lane 0 also writes n_accepted and the record, every tested lane its
-// accept probability, and bad device data sets the flags.
+// What the acceptance test of a sequence gives: what the draw needs (uniform over the wave), and what the call reports.
+struct Accepted {
+    double Lp, Lq;      // logsumexp * log2(e) of target row r, and of draft row r if that was rejected
+    int r;              // target row to draw from: the first rejection, or the draft length for a bonus
+    bool resid;         // residual of row r, or the bonus row
+    float prob;         // accept probability of position `lane` (of the first 64, those below the draft length)
+    unsigned flags;     // bad device data met on the way (per lane)
+};
+
+// Slices of a row requested together.  us per call, 4 / 8 / 10 of them: 64 sequences of 16 positions and 128256 bf16 logits (7
+// slices) 58.8 / 59.6 / 60.0, 32 of 8 and 50257 fp16 (3 slices) 24.2 / 24.9 / 25.6.
+constexpr int ACCEPT_SLICES = 4;
+
+// The acceptance test of sequence b by one wave: lane = position, 64 positions per pass.  Lanes j <= draft_len merge the
+// statistics of target row j; lanes j < draft_len run the acceptance test; a ballot finds the first rejection.
+// `all`: also the positions behind the first 64, with their accept probabilities written.
 template <typename DT>
-__device__ __forceinline__ SeqRec accept_sequence(const VerifyArgs &a, int b, int lane, bool publish)
+__device__ __forceinline__ Accepted accept_sequence(const VerifyArgs &a, int b, int lane, bool all)
 {
     // One wave, a chain of trips to memory: the draft length, then tokens / uniforms / logsumexps / slice
     // statistics, then the two gathered logits.  The first pass's loads that need no draft length (everything
@@ -114,14 +140,15 @@ __device__ __forceinline__ SeqRec accept_sequence(const VerifyArgs &a, int b, in
     }
     asm volatile("" : "+v"(graw) : : "memory");     // the draft length is first looked at here
     const int g = clamp_len(graw, a.k);
-    if (publish && graw != g && lane == 0) atomicOr(a.ws.flags, (unsigned)SVIP_FLAG_BAD_DRAFT_LEN);
     const DT *tgt = static_cast<const DT *>(a.target) + row_offset(a, a.seq_t, b, 0);
     const DT *drf = static_cast<const DT *>(a.draft) + row_offset(a, a.seq_d, b, 0);
     constexpr double LOG2E = 1.4426950408889634;
-    float *accept_prob = publish ? a.accept_prob : nullptr;
-    int r = -1;                 // first rejection, once known
-    double Lp_r = 0.0, Lq_r = 0.0;
-    for (int j0 = 0; j0 <= g && (r < 0 || accept_prob); j0 += 64) {
+    Accepted res;
+    res.r = -1;                 // first rejection, once known
+    res.Lp = res.Lq = 0.0;
+    res.prob = 0.f;
+    res.flags = graw != g ? (unsigned)SVIP_FLAG_BAD_DRAFT_LEN : 0u;
+    for (int j0 = 0; j0 <= g && (res.r < 0 || all); j0 += 64) {
         const int j = j0 + lane;
         bool reject = false;
         double Lp = 0.0, Lq = 0.0;
@@ -136,79 +163,68 @@ __device__ __forceinline__ SeqRec accept_sequence(const VerifyArgs &a, int b, in
             DT zp_stored = DT(), zq_stored = DT();          // requested here, widened after the statistics are merged
             if (j < g) {
                 if (x < 0 || x >= a.geo.V) {
-                    if (publish) atomicOr(a.ws.flags, (unsigned)SVIP_FLAG_BAD_TOKEN);
+                    res.flags |= (unsigned)SVIP_FLAG_BAD_TOKEN;
                     x = x < 0 ? 0 : a.geo.V - 1;
                 }
                 zp_stored = (tgt + (long long)j * a.row_stride)[x];
                 zq_stored = (drf + (long long)j * a.row_stride)[x];
             }
-            Lp = row_L<8>(a.ws.part, stat_row(a, b, a.kd + j), a.geo.ns);
+            RowStats<ACCEPT_SLICES> target, draft;
+            target.request(a, b, a.kd + j);
+            if (a.kd && j < g) draft.request(a, b, j);
+            target.merge(a, b, a.kd + j);
+            Lp = target.L();
             if (j < g) {
-                Lq = a.draft_lse ? lse_q * LOG2E : row_L<8>(a.ws.part, stat_row(a, b, j), a.geo.ns);
+                if (a.kd) {
+                    draft.merge(a, b, j);
+                    Lq = draft.L();
+                } else {
+                    Lq = lse_q * LOG2E;
+                }
                 const double zp = (double)widen(not_before_here(zp_stored)), zq = (double)widen(not_before_here(zq_stored));
                 const double p = exp2(zp * a.sc.c - Lp);
                 const double q = exp2(zq * a.sc.c - Lq);
                 reject = !(u * q < p);
-                if (accept_prob) {
-                    const double ratio = q > 0.0 ? p / q : (p > 0.0 ? 1.0 : 0.0);
-                    accept_prob[(size_t)b * a.k + j] = (float)(ratio < 1.0 ? ratio : 1.0);
-                }
+                const double ratio = q > 0.0 ? p / q : (p > 0.0 ? 1.0 : 0.0);
+                const float prob = (float)(ratio < 1.0 ? ratio : 1.0);
+                if (j0 == 0) res.prob = prob;
+                else if (all && a.accept_prob) a.accept_prob[(size_t)b * a.k + j] = prob;
             }
         }
-        if (r < 0) {
+        if (res.r < 0) {
             const unsigned long long rej = __ballot(reject);
             if (rej) {
                 const int first = __ffsll((long long)rej) - 1;
-                r = j0 + first;
-                Lp_r = read_lane(Lp, first);
-                Lq_r = read_lane(Lq, first);
+                res.r = j0 + first;
+                res.Lp = read_lane(Lp, first);
+                res.Lq = read_lane(Lq, first);
             } else if (g - j0 < 64) {      // row g (the bonus row) was merged in this pass
-                r = g;
-                Lp_r = read_lane(Lp, g - j0);
+                res.r = g;
+                res.Lp = read_lane(Lp, g - j0);
             }
         }
     }
-    SeqRec rec;
-    rec.r = r;
-    rec.resid = r < g ? 1 : 0;
-    rec.Lp = Lp_r;
-    rec.Lq = Lq_r;
-    if (publish && lane == 0) {
-        a.n_accepted[b] = r;
-        a.ws.rec[b] = rec;
-    }
-    return rec;
+    res.resid = res.r < g;
+    if (lane >= g) res.prob = -1.f;          // nothing to report there
+    return res;
 }
 
-// grid (sequences), one wave.
+// What the call reports of a sequence, by one wave.
 template <typename DT>
-__global__ __launch_bounds__(64) void k_accept(VerifyArgs a)
+__device__ __forceinline__ void report_sequence(const VerifyArgs &a, int b, int lane, const Accepted &res)
 {
-    if (a.skip && a.skip[blockIdx.x]) return;
-    accept_sequence<DT>(a, blockIdx.x, threadIdx.x, true);
+    unsigned flags = res.flags;
+    if (a.accept_prob && res.prob >= 0.f && lane < a.k) a.accept_prob[(size_t)b * a.k + lane] = res.prob;
+    if (a.k > 64) flags |= accept_sequence<DT>(a, b, lane, true).flags;
+    if (flags) atomicOr(a.ws.flags, flags);
+    if (lane == 0) a.n_accepted[b] = res.r;
 }
 
 // ---- verify: residual / bonus sampling ------------------------------------------------------
 
-// What a slice's workgroup hands to the sequence's last workgroup: residual and target mass of each
-// of its tiles (slices longer than TILE_MASSES tiles fold the rest into the last entry and are
-// searched as a whole).
-struct ResidSlot {
-    double W[TILE_MASSES], P[TILE_MASSES];
-};
-
-struct FinishLds {
-    LocateLds loc;
-    double target;
-    int slice, tile;
-    int use_resid;
-};
-
-struct ResidLds {
-    double sums[NWAVE][2 * TILE_MASSES];
-    FinishLds fin;
-    int last;
-};
+// What a slice's workgroup hands to the sequence's last workgroup: the mass of each half of its tiles (two chunks; slices
+// longer than TILE_MASSES tiles fold the rest into the last entries and are searched as a whole).
+constexpr int SLICE_MASSES = 2 * TILE_MASSES;
 
 // What the thread that finds the correction or bonus token does with it (see locate_batch's `report`).
 struct StoreNextToken {
@@ -218,17 +234,78 @@ struct StoreNextToken {
     __device__ __forceinline__ void operator()(int tok, float) const { next_token[b] = tok; }
 };
 
-// grid (sequences * slices), the whole residual / bonus draw in one launch.  Every workgroup sums
-// the weights of its slice tile by tile -- residual max(0, p - q) at the rejected position, and target p
-// of the row to sample -- and publishes them; the workgroup that draws the sequence's final ticket
-// chooses between residual and target weights (no residual mass: draw from p), picks the slice and
-// the tile that hold u * total and finds the token there by the inverse CDF.  TILES: slices have at
-// most TILE_MASSES tiles, so the search reads one tile; otherwise it walks the chosen slice.
+// Weights of chunks [chunk, chunk + NU) of a row, one vector of each per lane: residual max(0, p - q), or p alone.
+template <typename DT, int NU, bool RESID>
+__device__ __forceinline__ void chunk_weights(const DT *prow, const DT *qrow, int V, int chunk, const ExpRef &ep, const ExpRef &eq,
+                                              float (&w)[NU][VecOf<DT>::N])
+{
+    constexpr int N = VecOf<DT>::N;
+    typename RawOf<DT>::type rp[NU], rq[NU];
+    wave_load<DT, NU, true>(prow, V, chunk, rp);
+    if (RESID) wave_load<DT, NU, true>(qrow, V, chunk, rq);
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+        float z[N];
+        unpack<DT>(rp[u], z);
+#pragma unroll
+        for (int e = 0; e < N; ++e) w[u][e] = ep(z[e]);
+        if (RESID) {
+            unpack<DT>(rq[u], z);
+#pragma unroll
+            for (int e = 0; e < N; ++e) w[u][e] = fmaxf(w[u][e] - eq(z[e]), 0.f);
+        }
+    }
+}
+
+// No residual mass (p <= q everywhere, up to rounding): the token is drawn from p instead, by one wave that walks the row.
+// It takes a rejection where p and q agree to the last bits, so what this costs hardly matters.
+template <typename DT, typename Report>
+__device__ __forceinline__ void draw_from_target(const DT *prow, const Geo &geo, const ExpRef &ep, float u, Report report)
+{
+    constexpr int N = VecOf<DT>::N;
+    const int nchunks = geo.ntiles * (WG / 64);
+    float w[1][N];
+    double total = 0.0, before = 0.0;
+    int at = 0;
+#pragma unroll 1
+    for (int pass = 0; pass < 2; ++pass) {
+        // first the total, then the chunk that holds the crossing (else the last one with mass)
+        const double target = (double)u * total;
+        double run = 0.0;
+        bool crossed = false;
+#pragma unroll 1
+        for (int c = 0; c < nchunks && !crossed; ++c) {
+            chunk_weights<DT, 1, false>(prow, prow, geo.V, c, ep, ep, w);
+            const double mass = wave_sum((double)tree_sum<N>(w[0]));
+            if (pass == 1 && mass > 0.0) {
+                at = c;
+                before = run;
+                crossed = run + mass > target;
+            }
+            run += mass;
+        }
+        if (pass == 0) total = run;
+    }
+    chunk_weights<DT, 1, false>(prow, prow, geo.V, at, ep, ep, w);
+    search_chunks<N, 1>(w, at, (double)u * total - before, report);
+}
+
+// grid (sequences * slices): the acceptance test and the residual / bonus draw in one launch.  One wave of every workgroup works out
+// the first rejection from the statistics of the sequence's rows (a few kilobytes), then the workgroup sums the
+// weights of its slice by half tiles -- residual max(0, p - q) of the rejected position, or target p of the bonus row --
+// and publishes them; the workgroup that draws the sequence's final ticket reports the acceptance test (every other one has
+// read the sequence's inputs by then, so outputs may lie on inputs), picks the half tile that holds u * total, and
+// one wave finds the token there by the inverse CDF.  What bounds it is the chain of trips to memory (statistics, two rows,
+// publish, ticket, masses, half tile).  us per call with the test in a launch of its own (one wave per sequence) and the
+// search in a workgroup / so: 64 sequences of 16 positions and 128256 bf16 logits 61.0 / 58.9 (this kernel alone 13.3 + 4.7
+// / 14.6), 8 of 64 and 151936 28.7 / 27.3, 32 of 8 and 50257 fp16 26.5 / 24.6.  With every wave testing for itself instead of
+// one for its workgroup: 60.5, 27.3, 25.8 -- the loads of the statistics are many and small.  TILES: slices have at most TILE_MASSES tiles; otherwise the search
+// walks the chosen slice.
 template <typename DT, bool TILES>
 __global__ __launch_bounds__(WG, 4) void k_resid(VerifyArgs a)
 {
     constexpr int N = VecOf<DT>::N;
-    __shared__ ResidLds sh;
+    __shared__ double sums[NWAVE][TILE_MASSES];
     const int ns = a.geo_s.ns;
     // Workgroups go to the chip's 8 XCDs in turn: all slices of sequence b are kept on XCD b % 8, so the
     // workgroup that finishes the sequence reads the chosen tile again from the L2 that already streamed it
@@ -237,111 +314,96 @@ __global__ __launch_bounds__(WG, 4) void k_resid(VerifyArgs a)
     const int b = (int)((slot / (unsigned)ns) * 8u + xcd), s = (int)(slot % (unsigned)ns), tid = threadIdx.x;
     if (b >= a.B) return;
     if (a.skip && a.skip[b]) return;
-    const SeqRec rec = a.ws.rec[b];
-    const DT *prow = static_cast<const DT *>(a.target) + row_offset(a, a.seq_t, b, rec.r);
-    const DT *qrow = static_cast<const DT *>(a.draft) + row_offset(a, a.seq_d, b, rec.r);
-    const ExpRef ep = make_exp_ref(a.sc, rec.Lp), eq = make_exp_ref(a.sc, rec.Lq);
-    ResidSlot *slots = reinterpret_cast<ResidSlot *>(a.ws.mass) + (size_t)b * ns;
-    {
-        const int tb = s * a.geo_s.tps, te = min(tb + a.geo_s.tps, a.geo_s.ntiles);
-        float Wt[TILE_MASSES], Pt[TILE_MASSES];
-#pragma unroll
-        for (int v = 0; v < TILE_MASSES; ++v) Wt[v] = Pt[v] = 0.f;
-        if (rec.resid) slice_mass<DT, true>(prow, qrow, a.geo_s.V, tb, te, ep, eq, Wt, Pt);
-        else slice_mass<DT, false>(prow, qrow, a.geo_s.V, tb, te, ep, eq, Wt, Pt);
-        const int wave = tid >> 6, lane = tid & 63;
-#pragma unroll
-        for (int v = 0; v < TILE_MASSES; ++v) {
-            const double Wd = wave_sum((double)Wt[v]), Pd = wave_sum((double)Pt[v]);
-            if (lane == 0) {
-                sh.sums[wave][v] = Wd;
-                sh.sums[wave][TILE_MASSES + v] = Pd;
-            }
-        }
-        __syncthreads();
-        if (tid == 0) {
-#pragma unroll
-            for (int v = 0; v < TILE_MASSES; ++v) {
-                double W = 0.0, P = 0.0;
-#pragma unroll
-                for (int w = 0; w < NWAVE; ++w) {
-                    W += sh.sums[w][v];
-                    P += sh.sums[w][TILE_MASSES + v];
-                }
-                publish_f64(&slots[s].W[v], W);
-                publish_f64(&slots[s].P[v], P);
-            }
-            stores_done();
-            sh.last = take_ticket(ticket(a.ws.tickets, b, TICKET_RESID)) == (unsigned)ns - 1u;
-        }
-        __syncthreads();
-    }
-    if (!sh.last) return;
-
-    // ---- the sequence's last workgroup ----
-    if (tid < 64) {
-        const float u = a.u_resample[b];
-        double W[TILE_MASSES], P[TILE_MASSES];
-#pragma unroll
-        for (int v = 0; v < TILE_MASSES; ++v) W[v] = P[v] = 0.0;
-        if (tid < ns) {
-            unsigned long long x[2 * TILE_MASSES];
-#pragma unroll
-            for (int v = 0; v < TILE_MASSES; ++v) {          // all in flight together
-                x[v] = fetch_u64(&slots[tid].W[v]);
-                x[TILE_MASSES + v] = fetch_u64(&slots[tid].P[v]);
-            }
-#pragma unroll
-            for (int v = 0; v < TILE_MASSES; ++v) {
-                W[v] = __longlong_as_double((long long)x[v]);
-                P[v] = __longlong_as_double((long long)x[TILE_MASSES + v]);
-            }
-        }
-        if (tid == 0) reset_tickets(ticket(a.ws.tickets, b, TICKET_RESID));
-        double Ws = 0.0, Ps = 0.0;
-#pragma unroll
-        for (int v = 0; v < TILE_MASSES; ++v) {
-            Ws += W[v];
-            Ps += P[v];
-        }
-        const double inclW = wave_inclusive_sum(Ws), inclP = wave_inclusive_sum(Ps);
-        const double totW = read_lane(inclW, 63), totP = read_lane(inclP, 63);
-        const bool resid = rec.resid && totW > 0.0;   // no residual mass: draw from the target row
-        const double M = resid ? Ws : Ps, incl = resid ? inclW : inclP, tot = resid ? totW : totP;
-        double local;
-        const int sl = pick_slice(M, (double)u * tot, incl, &local);
-        int tile = 0;
-        if (TILES) {
-            double Gs[TILE_MASSES];
-#pragma unroll
-            for (int v = 0; v < TILE_MASSES; ++v) Gs[v] = read_lane(resid ? W[v] : P[v], sl);
-            double in_tile;
-            tile = pick_tile(Gs, local, &in_tile);
-            local = in_tile;
-        }
-        if (tid == 0) {
-            sh.fin.target = local;
-            sh.fin.slice = sl;
-            sh.fin.tile = tile;
-            sh.fin.use_resid = resid ? 1 : 0;
-        }
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    __shared__ Accepted shared_acc;
+    Accepted acc;
+    if (wave == 0) {
+        acc = accept_sequence<DT>(a, b, lane, false);
+        if (lane == 0) shared_acc = acc;
     }
     __syncthreads();
-    int tb = sh.fin.slice * a.geo_s.tps, te = min(tb + a.geo_s.tps, a.geo_s.ntiles);
-    if (TILES) {
-        tb += sh.fin.tile;
-        te = tb + 1;
+    if (wave != 0) acc = shared_acc;
+    acc.r = __builtin_amdgcn_readfirstlane(acc.r);
+    acc.resid = __builtin_amdgcn_readfirstlane(acc.resid);
+    const DT *prow = static_cast<const DT *>(a.target) + row_offset(a, a.seq_t, b, acc.r);
+    const DT *qrow = static_cast<const DT *>(a.draft) + row_offset(a, a.seq_d, b, acc.r);
+    const ExpRef ep = make_exp_ref(a.sc, acc.Lp), eq = make_exp_ref(a.sc, acc.Lq);
+    double *slots = a.ws.mass + (size_t)b * ns * SLICE_MASSES;
+    const int tb = s * a.geo_s.tps, te = min(tb + a.geo_s.tps, a.geo_s.ntiles);
+    float M[TILE_MASSES] = {};
+    if (acc.resid) slice_mass<DT, true>(prow, qrow, a.geo_s.V, tb, te, ep, eq, M);
+    else slice_mass<DT, false>(prow, qrow, a.geo_s.V, tb, te, ep, eq, M);
+    const double Md[TILE_MASSES] = {(double)M[0], (double)M[1], (double)M[2], (double)M[3]};
+    const double mine = wave_sum4(Md);                     // lane v: that of tile v
+    if (lane < TILE_MASSES) sums[wave][lane] = mine;
+    __syncthreads();
+    if (TILES && wave != 0) return;
+    bool last = false;
+    if (wave == 0) {
+        const int tile = lane >> 1, half = lane & 1;       // entry `lane` of the slice
+        if (lane < SLICE_MASSES) publish_f64(slots + s * SLICE_MASSES + lane, sums[2 * half][tile] + sums[2 * half + 1][tile]);
+        stores_done();
+        unsigned t = 0u;
+        if (lane == 0) t = take_ticket(ticket(a.ws.tickets, b, TICKET_RESID));
+        last = (unsigned)__builtin_amdgcn_readfirstlane((int)t) == (unsigned)ns - 1u;
+        if (TILES && !last) return;
     }
-    constexpr int LU = TILES ? 1 : 2;
-    // the thread that finds the token stores it; nothing else in this kernel has used sh.fin.loc
+
+    // ---- the sequence's last workgroup; lane = slice ----
     const StoreNextToken store{a.next_token, b};
-    float wtok;
-    if (sh.fin.use_resid) {
-        ResidualWeights<DT> wf{prow, qrow, a.geo_s.V, ep, eq};
-        locate_in_slice<N, LU>(wf, tb, te, sh.fin.target, sh.fin.loc, &wtok, NoHook(), true, store);
-    } else {
-        SoftmaxWeights<DT> wf{prow, a.geo_s.V, ep};
-        locate_in_slice<N, LU>(wf, tb, te, sh.fin.target, sh.fin.loc, &wtok, NoHook(), true, store);
+    int slice = -1;
+    double target = 0.0;
+    if (last) {
+        const float u = a.u_resample[b];
+        unsigned long long x[SLICE_MASSES] = {};
+        if (lane < ns) {
+#pragma unroll
+            for (int v = 0; v < SLICE_MASSES; ++v) x[v] = fetch_u64(slots + lane * SLICE_MASSES + v);     // all in flight together
+        }
+        if (lane == 0) reset_tickets(ticket(a.ws.tickets, b, TICKET_RESID));
+        double G[SLICE_MASSES], mass = 0.0;
+#pragma unroll
+        for (int v = 0; v < SLICE_MASSES; ++v) {
+            G[v] = __longlong_as_double((long long)x[v]);
+            mass += G[v];
+        }
+        const double incl = wave_inclusive_sum(mass), total = read_lane(incl, 63);
+        if (acc.resid && !(total > 0.0)) {
+            draw_from_target<DT>(prow, a.geo_s, ep, u, store);
+        } else {
+            slice = pick_slice(mass, (double)u * total, incl, &target);
+            if (TILES) {
+                double Gs[SLICE_MASSES], in_half;
+#pragma unroll
+                for (int v = 0; v < SLICE_MASSES; ++v) Gs[v] = read_lane(G[v], slice);
+                const int chunk = (slice * a.geo_s.tps * 2 + pick_piece(Gs, target, &in_half)) * (WG / 128);
+                float w[2][N];
+                if (acc.resid) chunk_weights<DT, 2, true>(prow, qrow, a.geo_s.V, chunk, ep, eq, w);
+                else chunk_weights<DT, 2, false>(prow, qrow, a.geo_s.V, chunk, ep, eq, w);
+                search_chunks<N, 2>(w, chunk, in_half, store);
+            }
+        }
+        report_sequence<DT>(a, b, lane, acc);
+    }
+    if constexpr (!TILES) {
+        __shared__ LocateLds loc;
+        __shared__ double at_target;
+        __shared__ int at_slice;
+        if (tid == 0) {
+            at_slice = slice;
+            at_target = target;
+        }
+        __syncthreads();
+        if (at_slice < 0) return;                          // not the last workgroup, or all done
+        const int fb = at_slice * a.geo_s.tps, fe = min(fb + a.geo_s.tps, a.geo_s.ntiles);
+        float wtok;
+        if (acc.resid) {
+            ResidualWeights<DT> wf{prow, qrow, a.geo_s.V, ep, eq};
+            locate_in_slice<N, 2>(wf, fb, fe, at_target, loc, &wtok, NoHook(), true, store);
+        } else {
+            SoftmaxWeights<DT> wf{prow, a.geo_s.V, ep};
+            locate_in_slice<N, 2>(wf, fb, fe, at_target, loc, &wtok, NoHook(), true, store);
+        }
     }
 }
 
