@@ -1,4 +1,5 @@
-"""ctypes binding of libsvip.so: argument marshalling only (see include/svip.h)."""
+"""Binding of libsvip.so: argument marshalling only (see include/svip.h), with ctypes; the calls a serving loop makes eagerly
+go through the same marshalling in native code (csrc/marshal.cpp) and come back here where an argument is not plainly right."""
 from __future__ import annotations
 
 import ctypes
@@ -8,7 +9,9 @@ import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libsvip.so")
+MARSHAL_PATH = os.path.join(_HERE, "_marshal.so")
 _lib = None
+_native = None
 
 MAX_K = 1024
 FLAG_BAD_TOKEN = 1
@@ -56,12 +59,12 @@ class BenchTuning(ctypes.Structure):
 
 def load():
     """Load libsvip.so (built by ``paper_2411_18462_amd.build``); raises if it is missing."""
-    global _lib
+    global _lib, _native
     if _lib is not None:
         return _lib
-    if not os.path.exists(LIB_PATH):
+    if not os.path.exists(LIB_PATH) or not os.path.exists(MARSHAL_PATH):
         raise RuntimeError(
-            f"{LIB_PATH} is not built; run `python -m paper_2411_18462_amd.build` "
+            f"{LIB_PATH} and {MARSHAL_PATH} are not both built; run `python -m paper_2411_18462_amd.build` "
             "(hipcc, gfx950).  There is no fallback path.")
     lib = ctypes.CDLL(LIB_PATH)
     vp, i, ll, f, sz = ctypes.c_void_p, ctypes.c_int, ctypes.c_longlong, ctypes.c_float, ctypes.c_size_t
@@ -109,8 +112,20 @@ def load():
     lib.svip_bench_set_tuning.argtypes = [ctypes.POINTER(BenchTuning)]
     lib.svip_bench_warp_routes.restype = i
     lib.svip_bench_warp_routes.argtypes = [vp]
-    _lib = lib
+    from . import _marshal
+
+    _marshal.bind(*(ctypes.cast(f, ctypes.c_void_p).value
+                    for f in (lib.svip_draft_step, lib.svip_draft_step_greedy, lib.svip_verify, lib.svip_verify_greedy)))
+    _lib, _native = lib, _marshal
     return lib
+
+
+_DECLINED = -1                    # of the native marshalling: nothing done, an argument is for the code here to judge
+
+
+def _load_native():
+    load()
+    return _native
 
 
 def _check(status: int):
@@ -179,6 +194,12 @@ def draft_step(draft_logits, *, temperature, h, step_j, k_max, token_out, lse_ou
     draft_logits: [B, V] view (unit stride along V); u_sample, token_out, entropy_out, q_tok_out,
     lse_out: [B] tensors or column views sharing one stride; stop_in / stop_out / draft_len_out:
     contiguous [B]."""
+    if workspace is not None and (greedy or u_sample is not None):
+        status = (_native or _load_native()).draft_step(
+            draft_logits, temperature, h, step_j, k_max, None if greedy else u_sample, token_out, entropy_out, q_tok_out, lse_out,
+            stop_in, stop_out, draft_len_out, workspace, None if stream is None else _stream(stream))
+        if status != _DECLINED:
+            return _check(status) if status else None
     if draft_logits.dim() != 2 or draft_logits.stride(1) != 1:
         raise ValueError("draft_logits must be [B, V] with unit stride along V")
     B, V = draft_logits.shape
@@ -216,6 +237,10 @@ def draft_step(draft_logits, *, temperature, h, step_j, k_max, token_out, lse_ou
 def verify_greedy(target_logits, *, draft_tokens, draft_len, n_accepted_out, next_token_out, workspace,
                   stream=None):
     """svip_verify_greedy.  target_logits [B, k+1, V] (unit stride along V); draft_tokens [B, k]."""
+    status = (_native or _load_native()).verify_greedy(
+        target_logits, draft_tokens, draft_len, n_accepted_out, next_token_out, workspace, None if stream is None else _stream(stream))
+    if status != _DECLINED:
+        return _check(status) if status else None
     if target_logits.dim() != 3 or target_logits.stride(2) != 1:
         raise ValueError("target_logits must be [B, k+1, V] with unit stride along V")
     B, kp1, V = target_logits.shape
@@ -296,6 +321,11 @@ def verify(target_logits, draft_logits, *, temperature, draft_tokens, draft_len,
            accept_prob_out=None, stream=None):
     """svip_verify.  target_logits [B, k+1, V], draft_logits [B, k, V] (unit stride along V,
     equal stride along the position axis); [B, k] arrays contiguous."""
+    status = (_native or _load_native()).verify(
+        target_logits, draft_logits, temperature, draft_tokens, draft_len, draft_lse, u_accept, u_resample, n_accepted_out,
+        next_token_out, accept_prob_out, workspace, None if stream is None else _stream(stream))
+    if status != _DECLINED:
+        return _check(status) if status else None
     if target_logits.dim() != 3 or draft_logits.dim() != 3:
         raise ValueError("logits must be [B, k+1, V] and [B, k, V]")
     B, kp1, V = target_logits.shape

@@ -1,9 +1,10 @@
-"""Builds libsvip.so (HIP kernels + C ABI) for gfx950 with hipcc, in-tree."""
+"""Builds libsvip.so (HIP kernels + C ABI) for gfx950 with hipcc, and the binding's host module with g++, in-tree."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -11,6 +12,8 @@ SOURCES = [os.path.join(HERE, "csrc", "svip_kernels.hip"), os.path.join(HERE, "c
 HEADERS = sorted(os.path.join(HERE, "csrc", f) for f in os.listdir(os.path.join(HERE, "csrc")) if f.endswith(".h")) + \
     [os.path.join(ROOT, "include", "svip.h")]
 LIB = os.path.join(HERE, "libsvip.so")
+MARSHAL_SRC = os.path.join(HERE, "csrc", "marshal.cpp")
+MARSHAL = os.path.join(HERE, "_marshal.so")
 EXAMPLE_SRC = os.path.join(HERE, "examples", "round_from_file.cpp")
 EXAMPLE_BIN = os.path.join(HERE, "examples", "round_from_file")
 
@@ -37,8 +40,29 @@ def build(verbose: bool = False) -> str:
     if verbose and out.strip():
         print(out)
     os.replace(tmp, LIB)
+    build_marshal(verbose)
     build_example(verbose)
     return LIB
+
+
+def build_marshal(verbose: bool = False) -> str:
+    """The binding's native argument marshalling: host code only, against the headers of the torch that is imported."""
+    import torch
+
+    inc = os.path.join(os.path.dirname(torch.__file__), "include")
+    lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    tmp = MARSHAL + f".tmp{os.getpid()}"
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-shared", "-fPIC", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__=1",
+           "-DUSE_ROCM=1", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I" + sysconfig.get_paths()["include"],
+           "-isystem", inc, "-isystem", os.path.join(inc, "torch", "csrc", "api", "include"), "-isystem", "/opt/rocm/include", MARSHAL_SRC,
+           "-L" + lib, "-ltorch_python", "-ltorch_cpu", "-lc10_hip", "-lc10", "-o", tmp]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    proc = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if proc.returncode != 0:
+        raise RuntimeError("g++ failed on the marshalling module:\n" + proc.stdout)
+    os.replace(tmp, MARSHAL)
+    return MARSHAL
 
 
 def build_example(verbose: bool = False) -> str:
@@ -61,9 +85,9 @@ def is_stale() -> bool:
     if not os.path.exists(LIB):
         return True
     t = os.path.getmtime(LIB)
-    if not os.path.exists(EXAMPLE_BIN):
+    if not os.path.exists(EXAMPLE_BIN) or not os.path.exists(MARSHAL):
         return True
-    return any(os.path.getmtime(p) > t for p in SOURCES + HEADERS + [EXAMPLE_SRC])
+    return any(os.path.getmtime(p) > t for p in SOURCES + HEADERS + [EXAMPLE_SRC, MARSHAL_SRC])
 
 
 if __name__ == "__main__":
