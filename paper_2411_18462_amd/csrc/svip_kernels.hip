@@ -766,6 +766,7 @@ svip_status svip_warp_logits(const void *logits_in, void *logits_out, int dtype,
     while ((1ll << lg) < (long long)V) ++lg;
     const int shift = 62 - lg < 44 ? 62 - lg : 44;
     a.fix_scale = ldexpf(1.f, shift);
+    a.stream = 2.0 * B * k_max * V * (dtype == SVIP_F32 ? 4 : 2) > 288e6;        // (the cache: 256 MiB)
     a.kept = kept_out;
     a.no_shortcut = g_tune.warp_no_shortcut;
     a.routes = g_warp_routes;

@@ -24,21 +24,22 @@ constexpr int WARP_WG = 1024;              // threads of the workgroup that owns
 constexpr int WARP_WAVES = WARP_WG / 64;
 constexpr int WARP_BINS = 2048;            // histogram bins: digits of up to 11 bits
 constexpr int WARP_CAP = 8192;             // keys of one first-digit bin that fit the candidate list
+constexpr int WARP_PAIRS = 7168;           // candidates of a shortcut that keeps their indices too
 constexpr int DIGIT1_SHIFT = 21;           // first digit = top 11 bits of the key
 // Rows from which top_p alone takes its shortcut.  On peaked rows (N(0, s^2), s from 4 to 6.5; top_p 0.9) it saves two
 // sweeps for a fixed cost, the select over the list; on flat ones the estimate that turns them away is 1 to 3 us.  us,
 // histogram path / shortcut, peaked rows | flat rows:
 //   rows of bf16 logits      1 row                  64 rows                544 rows
-//     32000           19.0 / 21.8 | 20.6 / 22.0    20.7 / 24.6 | 21.6 / 23.0    49.6 / 55.7 | 52.3 / 55.5
-//     50257           25.5 / 25.8 | 28.0 / 29.8    28.3 / 29.7 | 29.9 / 31.5    71.3 / 66.9 | 76.9 / 79.9
-//     65536           30.0 / 27.8 | 33.4 / 35.2    33.0 / 32.6 | 35.2 / 36.6    83.2 / 75.3 | 91.1 / 94.2
-//     81920           36.0 / 32.3 | 40.9 / 42.5    40.6 / 37.9 | 43.1 / 44.5   100.3 / 87.0 | 110.9 / 114.9
-//     98304           41.4 / 34.8 | 46.9 / 48.6    46.6 / 47.7 | 48.9 / 50.0   115.8 / 95.0 | 128.0 / 131.2
-//     128256          56.0 / 43.8 | 58.8 / 60.3    57.8 / 59.2 | 60.7 / 62.2   142.7 / 117.6 | 162.4 / 165.1
-// The estimate's sample is one vector per thread: the shorter the row, the less the saving pays for a row it misjudges
-// (64 peaked rows of 65536 fp32 logits 34.9 / 58.5) and for flat ones.  From 98304 on, flat rows are no slower than with a
-// kernel that has only the histograms and so more registers for them (us, that kernel / this one: 544 flat rows of 98304
-// 133 / 131, of 128256 170 / 165), and peaked ones gain most.
+//     32000           16.9 / 16.9 | 19.3 / 21.7    19.2 / 19.1 | 20.3 / 22.5    45.6 / 43.8 | 49.0 / 54.4
+//     50257           22.5 / 20.5 | 26.1 / 28.5    25.0 / 22.3 | 27.7 / 30.1    65.1 / 56.9 | 71.1 / 78.0
+//     65536           25.9 / 22.0 | 31.0 / 33.0    31.2 / 24.7 | 32.5 / 34.9    78.1 / 62.3 | 85.7 / 89.7
+//     81920           33.1 / 25.3 | 37.5 / 39.5    35.5 / 27.7 | 39.2 / 41.6    92.9 / 71.0 | 103.9 / 108.0
+//   rows of fp32 logits
+//     50257           25.7 / 22.6 | 28.6 / 30.6    28.2 / 25.8 | 30.7 / 32.6    95.9 / 74.7 | 96.4 / 102.4
+//     65536           29.7 / 26.6 | 34.0 / 35.8    35.0 / 28.0 | 36.2 / 38.3   122.6 / 101.0 | 123.5 / 127.0
+//     81920           36.8 / 29.2 | 40.6 / 42.7    41.3 / 33.2 | 44.1 / 45.9   148.8 / 117.4 | 151.3 / 155.1
+// The estimate's sample is one vector per thread: the shorter the row, the less the saving pays for a row it misjudges, and
+// flat rows of 16-bit logits below 65536, of fp32 ones below 98304, would be 1 to 6 % slower than with the histograms.
 constexpr int NUCLEUS_MIN_V = 98304;
 static_assert(NUCLEUS_MIN_V >= 8 * WARP_WG, "every thread has a whole vector of its own");
 
@@ -51,6 +52,7 @@ struct WarpArgs {
     Scale sc;
     int top_k;                 // 0: filter off
     double top_p;              // >= 1: filter off
+    int stream;                // input and output are more than the last-level cache holds (see candidate_sweep)
     float fix_scale;           // weights in [0, 1] are summed as integers in units of 1 / fix_scale
     int *kept;                 // [rows] survivors per row, or nullptr
     int no_shortcut;           // always take the histogram path (for tests and measurements)
@@ -58,10 +60,15 @@ struct WarpArgs {
 };
 
 struct WarpLds {
-    unsigned long long hist[WARP_BINS];    // mass per first digit
-    unsigned long long sub[WARP_BINS];     // measure per later digit while a bin is refined
-    unsigned cnt[WARP_BINS];               // keys per first digit
-    unsigned list[WARP_CAP];               // the keys of one first-digit bin
+    union {
+        struct {
+            unsigned list[WARP_CAP];               // the keys of one first-digit bin, or a shortcut's candidates
+            unsigned long long hist[WARP_BINS];    // mass per first digit
+            unsigned cnt[WARP_BINS];               // keys per first digit
+        };
+        unsigned pairs[2 * WARP_PAIRS];            // a shortcut's candidates with their indices (no histogram is in use then)
+    };
+    unsigned long long sub[WARP_BINS];             // measure per later digit while a bin is refined
     unsigned long long wave_tot[WARP_WAVES];
     float wave_max[WARP_WAVES];
     int wave_kept[WARP_WAVES];
@@ -70,6 +77,8 @@ struct WarpLds {
     unsigned long long rem;
     unsigned long long acc;
 };
+static_assert(sizeof(unsigned[2 * WARP_PAIRS]) == sizeof(unsigned[WARP_CAP]) + sizeof(unsigned long long[WARP_BINS]) + sizeof(unsigned[WARP_BINS]),
+              "the pairs take the place of list, hist and cnt");
 
 // Order-preserving key of an fp32 value (-0 and +0 share a key) and the value of a key.
 __device__ __forceinline__ unsigned value_key(float v)
@@ -102,7 +111,34 @@ __device__ __forceinline__ unsigned long long wave_inclusive_sum_u64(unsigned lo
     return v;
 }
 
-// Vector vi of a row through the cached path (the row is read several times): a vector wholly
+// Vectors v0, v0 + WARP_WG, .. of a row through the cached path (the row is read several times), all requested at once and
+// without a branch between them: every thread loads, those past the end the row's last whole vector.  The vector at the
+// end of a row goes element by element; past the end the caller must not look.  last_use: nothing reads the row again.
+template <typename DT, int U>
+__device__ __forceinline__ void warp_load_batch(const DT *row, int v0, int V, typename RawOf<DT>::type (&r)[U], bool last_use)
+{
+    constexpr int N = VecOf<DT>::N;
+    typedef typename RawOf<DT>::type R;
+    const int whole = V / N;
+    if (whole > 0) {
+        if (last_use) {
+            asm volatile("");            // (else the compiler makes one of the two branches, and drops what differs)
+#pragma unroll
+            for (int u = 0; u < U; ++u) r[u] = load_raw<DT>(row, min(v0 + u * WARP_WG, whole - 1));
+            asm volatile("");
+        } else {
+#pragma unroll
+            for (int u = 0; u < U; ++u) r[u] = *(reinterpret_cast<const R *>(row) + min(v0 + u * WARP_WG, whole - 1));
+        }
+    }
+    if (V % N != 0) {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (v0 + u * WARP_WG == whole) r[u] = load_raw_edge(row, whole, V);
+    }
+}
+
+// Vector vi of a row through the cached path: a vector wholly
 // inside the row as one 16-byte load, the one at the end element by element, -inf past the end.
 template <typename DT>
 __device__ __forceinline__ typename RawOf<DT>::type warp_load(const DT *row, int vi, int V)
@@ -170,14 +206,125 @@ struct MassMeasure {
     float fix_hi;              // fix_scale / 2^32
     // w * fix_scale truncated to an integer; fix_scale = 2^s with s >= 32.  The float is split at
     // 2^32 (both parts convert exactly), which is cheaper than a 64-bit conversion.
+    __device__ __forceinline__ float weight(float z) const { return exp2_raw(scaled_diff(z, m, sc)); }
     __device__ __forceinline__ unsigned long long operator()(float z) const
     {
-        const float t = exp2_raw(scaled_diff(z, m, sc)) * fix_hi;          // = w * 2^(s - 32), < 2^13
+        const float t = weight(z) * fix_hi;          // = w * 2^(s - 32), < 2^13
         const unsigned hi = (unsigned)t;
         const unsigned lo = (unsigned)(__builtin_amdgcn_fractf(t) * 4294967296.0f);
         return ((unsigned long long)hi << 32) | lo;
     }
 };
+
+// The same masses of many logits, summed in a double of the binade whose last place is the unit: with rounding towards
+// zero an addition there truncates the weight to whole units, one conversion and one addition per logit (8.4 cycles of
+// issue) instead of two conversions, a fract, two multiplications and a 64-bit integer addition (26).  The rounding mode
+// of doubles is the wave's, so nothing else in double precision may stand between begin() and end(); a double holds the
+// sum of 2^5 weights with room to spare, and total() then takes it over.
+struct MassSum {
+    double zero;                   // 2^52 units
+    unsigned long long units = 0ull;
+    __device__ __forceinline__ explicit MassSum(float fix_scale) : zero(4503599627370496.0 / (double)fix_scale) {}
+    __device__ __forceinline__ static void begin() { asm volatile("s_setreg_imm32_b32 hwreg(HW_REG_MODE, 2, 2), 3" ::: "memory"); }
+    __device__ __forceinline__ static void end() { asm volatile("s_setreg_imm32_b32 hwreg(HW_REG_MODE, 2, 2), 0" ::: "memory"); }
+    __device__ __forceinline__ static void add(double &acc, float w) { asm volatile("v_add_f64 %0, %0, %1" : "+v"(acc) : "v"((double)w)); }
+    __device__ __forceinline__ void take(double acc)
+    {
+        units += (unsigned long long)__double_as_longlong(acc) - (unsigned long long)__double_as_longlong(zero);
+    }
+};
+
+// The logits of a stored vector against a threshold key, without widening them: sign-magnitude numbers as two's complement
+// ones of the same order, a saturating difference, its sign spread over the element.  A logit is below the threshold
+// exactly if its 32-bit key is (so -0 counts as +0; NaN of positive sign is above, of negative sign below everything).
+typedef short i16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ i16x2 ordered(i16x2 v) { return v ^ ((v >> 15) & (short)0x7FFF); }
+__device__ __forceinline__ int ordered(int v) { return v ^ ((v >> 31) & 0x7FFFFFFF); }
+// the 16-bit number from which on the logits of the type are at or above a key of 32 bits, in the order of ordered(); the
+// key, as a signed number of the same order, need not be that of a number of the type
+__device__ __forceinline__ short lowest_kept(bf16, int o)
+{
+    // (widened, numbers below zero end in ones and the others in zeros)
+    return (short)(o == 0 ? -1 : (o < 0 ? o >> 16 : min((int)(((unsigned)o + 0xFFFFu) >> 16), 32767)));
+}
+__device__ __forceinline__ short lowest_kept(f16, int o)
+{
+    const float t = __int_as_float(ordered(o));
+    if (o == 0) return -1;
+    if (t != t) return (short)(o < 0 ? -32768 : 32767);
+    const _Float16 h = (_Float16)t;
+    const short k = ordered(i16x2{__builtin_bit_cast(short, h), 0})[0];
+    return (float)h < t ? (short)(k + 1) : k;
+}
+template <typename DT> struct Threshold {
+    i16x2 p;
+    __device__ __forceinline__ explicit Threshold(unsigned key)
+    {
+        const short k = lowest_kept(DT{}, (int)(key ^ 0x80000000u));
+        p = i16x2{k, k};
+    }
+    // all bits of the logits below the threshold, for one word of the vector
+    __device__ __forceinline__ unsigned below(unsigned word) const
+    {
+        unsigned m = __builtin_bit_cast(unsigned, __builtin_elementwise_sub_sat(ordered(__builtin_bit_cast(i16x2, word)), p) >> 15);
+        asm("" : "+v"(m));                         // (or it becomes a comparison and a select per logit)
+        return m;
+    }
+};
+template <> struct Threshold<float> {
+    int p;
+    __device__ __forceinline__ explicit Threshold(unsigned key) : p((int)(key ^ 0x80000000u)) { p = p == 0 ? -1 : p; }
+    __device__ __forceinline__ unsigned below(unsigned word) const
+    {
+        unsigned m = (unsigned)(__builtin_elementwise_sub_sat(ordered((int)word), p) >> 31);
+        asm("" : "+v"(m));
+        return m;
+    }
+};
+template <typename DT> __device__ __forceinline__ u32x4 neg_inf_words() { return __builtin_bit_cast(u32x4, NegInfVec<DT>::value()); }
+
+template <typename DT> struct StoreBits;
+template <> struct StoreBits<float> {
+    static __device__ __forceinline__ void one(float *p, float z) { *p = z; }
+};
+// 16-bit storage: the fp32 values came from the storage type, so converting back is exact.
+template <> struct StoreBits<bf16> {
+    static __device__ __forceinline__ uint32_t bits(float z) { return __float_as_uint(z) >> 16; }
+};
+template <> struct StoreBits<f16> {
+    static __device__ __forceinline__ uint32_t bits(float z)
+    {
+        return (uint32_t)__builtin_bit_cast(unsigned short, (_Float16)z);
+    }
+};
+template <typename DT>
+__device__ __forceinline__ void store_one(DT *p, float z)
+{
+    if constexpr (VecOf<DT>::N == 4) StoreBits<DT>::one(p, z);
+    else p->bits = (uint16_t)StoreBits<DT>::bits(z);
+}
+// Vector vi of the output; the one at the end of a row element by element.
+template <typename DT>
+__device__ __forceinline__ void store_words(DT *dst, int vi, int V, const u32x4 &o, bool past_caches)
+{
+    constexpr int N = VecOf<DT>::N;
+    if ((vi + 1) * N <= V) {
+        u32x4 *to = reinterpret_cast<u32x4 *>(dst + (long long)vi * N);
+        if (past_caches) {
+            asm volatile("");                      // (else the compiler makes one of the two branches, and drops what differs)
+            __builtin_nontemporal_store(o, to);
+            asm volatile("");
+        } else {
+            *to = o;
+        }
+    } else {
+        float z[N];
+        unpack<DT>(__builtin_bit_cast(typename RawOf<DT>::type, o), z);
+#pragma unroll
+        for (int e = 0; e < N; ++e)
+            if (vi * N + e < V) store_one<DT>(dst + (long long)vi * N + e, z[e]);
+    }
+}
 
 // Going down from the highest digit over a histogram h[WARP_BINS] in LDS (filled and barriered
 // by the caller): the digit d with  sum(h above d) < target <= sum(h at and above d),  and
@@ -278,45 +425,86 @@ __device__ __forceinline__ unsigned long long wg_sum_u64(unsigned long long mine
     return r;
 }
 
-template <typename DT> struct StoreBits;
-template <> struct StoreBits<float> {
-    static __device__ __forceinline__ void one(float *p, float z) { *p = z; }
-    static __device__ __forceinline__ void vec(float *p, const float (&z)[4])
-    {
-        f32x4 r;
-        r.x = z[0]; r.y = z[1]; r.z = z[2]; r.w = z[3];
-        *reinterpret_cast<f32x4 *>(p) = r;
-    }
-};
-// 16-bit storage: the fp32 values came from the storage type, so converting back is exact.
-template <> struct StoreBits<bf16> {
-    static __device__ __forceinline__ uint32_t bits(float z) { return __float_as_uint(z) >> 16; }
-};
-template <> struct StoreBits<f16> {
-    static __device__ __forceinline__ uint32_t bits(float z)
-    {
-        return (uint32_t)__builtin_bit_cast(unsigned short, (_Float16)z);
-    }
-};
-template <typename DT>
-__device__ __forceinline__ void store_one(DT *p, float z)
+// An LDS counter's old value, per lane.  Through atomicAdd() the compiler first adds the lanes' values up one by one, which
+// takes longer than the few lanes that have something to add.
+__device__ __forceinline__ unsigned lds_add(unsigned *p, unsigned n)
 {
-    if constexpr (VecOf<DT>::N == 4) StoreBits<DT>::one(p, z);
-    else p->bits = (uint16_t)StoreBits<DT>::bits(z);
+    unsigned old;
+    const unsigned at = (unsigned)(unsigned long long)(__attribute__((address_space(3))) unsigned *)p;
+    asm volatile("ds_add_rtn_u32 %0, %1, %2\n\ts_waitcnt lgkmcnt(0)" : "=&v"(old) : "v"(at), "v"(n) : "memory");
+    return old;
 }
-template <typename DT>
-__device__ __forceinline__ void store_vec(DT *p, const float (&z)[VecOf<DT>::N])
+
+// One sweep over the row: the keys of the logits at or above the pivot into L.list (n_list counts them, also those that do
+// not fit), with `FUSED` their indices behind them (`cap` of each) and the output -- the logit itself at and above the pivot,
+// -inf below; with `MASS` the total mass of the row (per thread).
+// A row's chunk of 64 vectors holds some candidates more often than not, so what every logit pays for is kept apart from
+// what a candidate does: the comparison works on the stored words (11 cycles of issue per 16-bit logit), and the lanes
+// that have candidates go through them one at a time.
+// `stream` (MASS, which sweeps the row for the second and last time): for calls that move more than the last-level cache,
+// loads and stores go past the caches, so that they keep the rows whose second sweep is still to come.  us, through the
+// caches / past them, top_p 0.9 on inputs not used just before | the same input again and again: 1088 rows of 128256 bf16
+// logits 211 / 195 | 211 / 178, 685 rows of 151936 158 / 140 | 156 / 126, 256 rows of 151936 fp32 (311 MB in all) 114 / 87 |
+// 94 / 84, but 300 rows of 151936 bf16 (182 MB) 96 / 86 | 73 / 85.  A single sweep gains nothing (top_k 50, 1088 rows
+// 165 / 167); a plain copy does (1088 rows 114 / 110).
+template <typename DT, bool FUSED, bool MASS, int U>
+__device__ __forceinline__ unsigned long long candidate_sweep(const DT *row, DT *dst, int V, unsigned pivot, unsigned cap, const MassMeasure &mass,
+                                                              float fix_scale, bool stream, WarpLds &L)
 {
-    if constexpr (VecOf<DT>::N == 4) {
-        StoreBits<DT>::vec(p, z);
-    } else {
-        u32x4 r;
-        r.x = StoreBits<DT>::bits(z[0]) | (StoreBits<DT>::bits(z[1]) << 16);
-        r.y = StoreBits<DT>::bits(z[2]) | (StoreBits<DT>::bits(z[3]) << 16);
-        r.z = StoreBits<DT>::bits(z[4]) | (StoreBits<DT>::bits(z[5]) << 16);
-        r.w = StoreBits<DT>::bits(z[6]) | (StoreBits<DT>::bits(z[7]) << 16);
-        *reinterpret_cast<u32x4 *>(p) = r;
+    constexpr int N = VecOf<DT>::N, PER = N / 4;                 // logits per word
+    const Threshold<DT> pv(pivot);
+    const u32x4 low = neg_inf_words<DT>();
+    const int nvec = (V + N - 1) / N;
+    MassSum sum(fix_scale);
+    if (MASS) MassSum::begin();
+    for (int v0 = threadIdx.x; v0 < nvec; v0 += U * WARP_WG) {
+        typename RawOf<DT>::type r[U];
+        double acc = sum.zero;
+        warp_load_batch<DT, U>(row, v0, V, r, FUSED && MASS && stream);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int vi = v0 + u * WARP_WG;
+            if (vi >= nvec) continue;
+            if (MASS) {
+                float z[N];
+                unpack<DT>(r[u], z);
+#pragma unroll
+                for (int e = 0; e < N; ++e) MassSum::add(acc, mass.weight(z[e]));
+            }
+            const u32x4 w = __builtin_bit_cast(u32x4, r[u]);
+            u32x4 o;
+            unsigned m[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                m[i] = pv.below(w[i]);
+                o[i] = (w[i] & ~m[i]) | (low[i] & m[i]);
+            }
+            if ((m[0] & m[1] & m[2] & m[3]) != 0xFFFFFFFFu) {
+                unsigned at = 0u;                                // one bit per candidate
+#pragma unroll
+                for (int i = 0; i < 4; ++i) at |= (~m[i] & (PER == 2 ? 0x00010001u : 1u)) << (PER * i);
+                if (PER == 2) at = (at | (at >> 15)) & 0xFFu;
+                unsigned slot = lds_add(&L.n_list, (unsigned)__popc(at));
+                while (at) {
+                    const int e = __ffs((int)at) - 1, i = e / PER;
+                    at &= at - 1u;
+                    const unsigned word = i & 2 ? (i & 1 ? w[3] : w[2]) : (i & 1 ? w[1] : w[0]);
+                    float z;
+                    if constexpr (PER == 1) z = __uint_as_float(word);
+                    else z = widen(DT{(uint16_t)(e & 1 ? word >> 16 : word)});
+                    if (slot < cap) {
+                        L.pairs[slot] = value_key(z);
+                        if (FUSED) L.pairs[cap + slot] = (unsigned)(vi * N + e);
+                    }
+                    ++slot;
+                }
+            }
+            if (FUSED) store_words<DT>(dst, vi, V, o, MASS && stream);
+        }
+        if (MASS) sum.take(acc);
     }
+    if (MASS) MassSum::end();
+    return sum.units;
 }
 
 // Shortcut for a small top_k: a pivot from a sample of the row (one vector per thread), aimed at
@@ -326,7 +514,7 @@ __device__ __forceinline__ void store_vec(DT *p, const float (&z)[VecOf<DT>::N])
 // arithmetic as the histogram path, hence the same result.
 // With `fused` (output is not the input, top_k <= 1024) the same sweep already writes the output:
 // -inf below the pivot, the logit itself at and above it, and the list also keeps the candidates'
-// indices (4096 of each); afterwards only the candidates below the final threshold are overwritten,
+// indices (WARP_PAIRS of each); afterwards only the candidates below the final threshold are overwritten,
 // so the row is read once.
 // Returns 0: nothing decided (the sample misjudged the row; the caller takes the histogram path,
 // which rewrites the whole output), 1: *tau_out is the threshold, 2: output and *kept_out are done.
@@ -338,7 +526,7 @@ __device__ __forceinline__ int small_k_shortcut(const DT *row, DT *dst, int V, c
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int nvec = (V + N - 1) / N;
     const int nsamp = nvec < WARP_WG ? nvec : WARP_WG;            // sampled vectors
-    constexpr unsigned cap = fused ? WARP_CAP / 2 : WARP_CAP;
+    constexpr unsigned cap = fused ? WARP_PAIRS : WARP_CAP;
     const long long want = 3ll * a.top_k * ((long long)nsamp * N) / V + 8;
     if (a.top_k > (int)cap / 4 || want > (long long)nsamp * N / 4) return 0;
     if (tid < nsamp) {
@@ -354,30 +542,7 @@ __device__ __forceinline__ int small_k_shortcut(const DT *row, DT *dst, int V, c
     const unsigned pivot = select_digits(sample, 0u, CountMeasure{}, 0u, 0, (unsigned long long)want, L);
     if (tid == 0) L.n_list = 0u;
     __syncthreads();
-    for_each_vector<DT, 2>(row, V, [&](int vi, const float(&z)[N]) {
-        float o[N];
-#pragma unroll
-        for (int e = 0; e < N; ++e) {
-            const unsigned key = value_key(z[e]);
-            o[e] = key >= pivot ? z[e] : neg_inf();
-            if (key >= pivot) {
-                const unsigned i = atomicAdd(&L.n_list, 1u);
-                if (i < cap) {
-                    L.list[i] = key;
-                    if (fused) L.list[cap + i] = (unsigned)(vi * N + e);
-                }
-            }
-        }
-        if (fused) {
-            if ((vi + 1) * N <= V) {
-                store_vec<DT>(dst + (long long)vi * N, o);
-            } else {
-                #pragma unroll
-                for (int e = 0; e < N; ++e)
-                    if (vi * N + e < V) store_one<DT>(dst + (long long)vi * N + e, o[e]);
-            }
-        }
-    });
+    candidate_sweep<DT, fused, false, 4>(row, dst, V, pivot, cap, MassMeasure{}, a.fix_scale, a.stream, L);
     __syncthreads();
     const unsigned n = L.n_list;
     __syncthreads();
@@ -409,7 +574,7 @@ __device__ __forceinline__ int small_k_shortcut(const DT *row, DT *dst, int V, c
     // the sweep's stores are complete (every barrier since waited for them): drop the candidates below tau
     unsigned long long kept = 0ull;
     for (unsigned i = tid; i < n; i += WARP_WG) {
-        const unsigned idx = L.list[cap + i];
+        const unsigned idx = L.pairs[cap + i];
         if (idx < (unsigned)V) {
             if (L.list[i] >= tau) kept += 1ull;
             else store_one<DT>(dst + idx, neg_inf());
@@ -422,7 +587,8 @@ __device__ __forceinline__ int small_k_shortcut(const DT *row, DT *dst, int V, c
 // Shortcut for top_p alone.  A row's nucleus is usually some hundreds of tokens; the histogram path finds it with a
 // 64-bit LDS atomic for every logit, a further sweep for the keys of one bin and one that copies.  Here
 //   sweep 1: every thread's maximum.  The smallest maximum of four threads is the pivot: whatever the row's
-//            distribution, about 256 ln 256 = 1400 logits are at or above it;
+//            distribution, about 256 ln 256 = 1600 logits are at or above it; where that will not do the smallest of two
+//            threads (about 512 ln 512 = 3500);
 //   sweep 2: the keys >= pivot into L.list, the total mass in registers with the same integer arithmetic, hence the same
 //            threshold; with `fused` (output is not the input) it also writes the logits >= pivot, -inf below, and
 //            afterwards only the candidates below the threshold are overwritten.
@@ -439,83 +605,64 @@ __device__ __forceinline__ int nucleus_shortcut(const DT *row, DT *dst, int V, c
     constexpr float LOWEST = -3.402823466e38f;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int nvec = (V + N - 1) / N;
-    constexpr unsigned cap = fused ? WARP_CAP / 2 : WARP_CAP;
+    constexpr unsigned cap = fused ? WARP_PAIRS : WARP_CAP;
     float mine_max = neg_inf();
     for_each_vector<DT>(row, V, [&](int, const float(&z)[N]) { mine_max = vmax(mine_max, tree_max<N>(z)); });
-    float group = vmax(mine_max, __shfl_xor(mine_max, 1));
-    group = vmax(group, __shfl_xor(group, 2));
+    const float pair = vmax(mine_max, __shfl_xor(mine_max, 1));
+    const float group = vmax(pair, __shfl_xor(pair, 2));
     // the same runs of whole cache lines as in small_k_shortcut
     const typename RawOf<DT>::type sample = warp_load<DT>(row, (int)((long long)(tid >> 6) * (nvec - 64) / 15) + (tid & 63), V);
     {
-        const float hi = wave_max(mine_max), lo = -wave_max(-group);
+        const float hi = wave_max(mine_max), lo4 = -wave_max(-group), lo2 = -wave_max(-pair);
         if (lane == 0) {
             L.wave_max[wave] = hi;
-            L.wave_tot[wave] = __float_as_uint(lo);
+            L.wave_tot[wave] = ((unsigned long long)__float_as_uint(lo2) << 32) | __float_as_uint(lo4);
         }
     }
     if (tid == 0) L.n_list = 0u;
     __syncthreads();
-    float m = neg_inf(), pz = neg_inf();
+    float m = neg_inf(), pz = neg_inf(), pz2 = neg_inf();
 #pragma unroll
     for (int w = 0; w < WARP_WAVES; ++w) {
         m = vmax(m, L.wave_max[w]);
         pz = vmax(pz, -__uint_as_float((unsigned)L.wave_tot[w]));
+        pz2 = vmax(pz2, -__uint_as_float((unsigned)(L.wave_tot[w] >> 32)));
     }
     pz = vmax(-pz, LOWEST);                                       // masked logits are no candidates
+    pz2 = vmax(-pz2, LOWEST);
     *m_out = m;
-    float head = exp2_raw(scaled_diff(mine_max, m, a.sc)), tail = 0.f;
+    float head = exp2_raw(scaled_diff(mine_max, m, a.sc)), tail = 0.f, tail2 = 0.f;
     float zs[N];
     unpack<DT>(sample, zs);
 #pragma unroll
-    for (int e = 0; e < N; ++e) tail += zs[e] < pz ? exp2_raw(scaled_diff(zs[e], m, a.sc)) : 0.f;
+    for (int e = 0; e < N; ++e) {
+        const float w = exp2_raw(scaled_diff(zs[e], m, a.sc));
+        tail += zs[e] < pz ? w : 0.f;
+        tail2 += zs[e] < pz2 ? w : 0.f;
+    }
     head = wave_reduce(head, OpSum{});
     tail = wave_reduce(tail, OpSum{});
-    if (lane == 0) L.sub[wave] = ((unsigned long long)__float_as_uint(head) << 32) | __float_as_uint(tail);
+    tail2 = wave_reduce(tail2, OpSum{});
+    if (lane == 0) {
+        L.sub[wave] = ((unsigned long long)__float_as_uint(head) << 32) | __float_as_uint(tail);
+        L.sub[WARP_WAVES + wave] = __float_as_uint(tail2);
+    }
     __syncthreads();
-    head = tail = 0.f;
+    head = tail = tail2 = 0.f;
 #pragma unroll
     for (int w = 0; w < WARP_WAVES; ++w) {
         head += __uint_as_float((unsigned)(L.sub[w] >> 32));
         tail += __uint_as_float((unsigned)L.sub[w]);
+        tail2 += __uint_as_float((unsigned)L.sub[WARP_WAVES + w]);
     }
     // a wrong yes costs a sweep, a wrong no the saving: a fifth of the tail allowed is kept as a margin
-    tail *= (float)V / (float)(WARP_WG * N);
-    if (!(0.8f * (1.f - (float)a.top_p) * head >= (float)a.top_p * tail)) return 0;
+    const float per = (float)V / (float)(WARP_WG * N) * (float)a.top_p, room = 0.8f * (1.f - (float)a.top_p) * head;
+    if (!(room >= per * tail)) {
+        if (!(room >= per * tail2)) return 0;
+        pz = pz2;
+    }
     const MassMeasure mass{m, a.sc, a.fix_scale * (1.0f / 4294967296.0f)};
-    unsigned long long mine = 0ull;
-    for_each_vector<DT>(row, V, [&](int vi, const float(&z)[N]) {
-        float o[N];
-        unsigned c = 0u;
-#pragma unroll
-        for (int e = 0; e < N; ++e) {
-            const bool cand = !(z[e] < pz);                      // a NaN goes into the list, where its key decides
-            mine += mass(z[e]);
-            c += cand ? 1u : 0u;
-            o[e] = cand ? z[e] : neg_inf();
-        }
-        if (c) {
-            unsigned i = atomicAdd(&L.n_list, c);
-#pragma unroll
-            for (int e = 0; e < N; ++e) {
-                if (!(z[e] < pz)) {
-                    if (i < cap) {
-                        L.list[i] = value_key(z[e]);
-                        if (fused) L.list[cap + i] = (unsigned)(vi * N + e);
-                    }
-                    ++i;
-                }
-            }
-        }
-        if (fused) {
-            if ((vi + 1) * N <= V) {
-                store_vec<DT>(dst + (long long)vi * N, o);
-            } else {
-#pragma unroll
-                for (int e = 0; e < N; ++e)
-                    if (vi * N + e < V) store_one<DT>(dst + (long long)vi * N + e, o[e]);
-            }
-        }
-    });
+    unsigned long long mine = candidate_sweep<DT, fused, true, 4>(row, dst, V, value_key(pz), cap, mass, a.fix_scale, a.stream, L);
     const unsigned long long Z = wg_sum_u64(mine, L);             // its barriers also cover the list
     const unsigned n = L.n_list;
     if (n > cap) return 0;
@@ -532,7 +679,7 @@ __device__ __forceinline__ int nucleus_shortcut(const DT *row, DT *dst, int V, c
     // the sweep's stores are complete (every barrier since waited for them): drop the candidates below tau
     unsigned long long kept = 0ull;
     for (unsigned i = tid; i < n; i += WARP_WG) {
-        const unsigned idx = L.list[cap + i];
+        const unsigned idx = L.pairs[cap + i];
         if (idx < (unsigned)V) {
             if (L.list[i] >= tau) kept += 1ull;
             else store_one<DT>(dst + idx, neg_inf());
@@ -540,6 +687,44 @@ __device__ __forceinline__ int nucleus_shortcut(const DT *row, DT *dst, int V, c
     }
     *kept_out = (int)wg_sum_u64(kept, L);
     return 2;
+}
+
+// The output: the logits whose keys are at or above tau, -inf for the others.  Returns how many this thread kept.
+template <typename DT, int U = 4>
+__device__ __forceinline__ int masked_copy(const DT *row, DT *dst, int V, unsigned tau, bool stream)
+{
+    constexpr int N = VecOf<DT>::N, BITS = 128 / N;
+    const Threshold<DT> th(tau);
+    const u32x4 low = neg_inf_words<DT>();
+    const int nvec = (V + N - 1) / N;
+    int bits = 0;                                                // of the logits kept
+    for (int v0 = threadIdx.x; v0 < nvec; v0 += U * WARP_WG) {
+        typename RawOf<DT>::type r[U];
+        warp_load_batch<DT, U>(row, v0, V, r, stream);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int vi = v0 + u * WARP_WG;
+            if (vi >= nvec) continue;
+            const u32x4 w = __builtin_bit_cast(u32x4, r[u]);
+            u32x4 o;
+            int here = 0;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const unsigned m = th.below(w[i]);
+                o[i] = (w[i] & ~m) | (low[i] & m);
+                here += __popc(~m);
+            }
+            if ((vi + 1) * N > V) {                              // -inf stands past the end of the row, kept or not
+                here = 0;
+#pragma unroll
+                for (int e = 0; e < N; ++e)
+                    if (vi * N + e < V) here += __popc(~(N == 4 ? th.below(w[e & 3]) : th.below(w[e / 2]) | (e & 1 ? 0x0000FFFFu : 0xFFFF0000u)));
+            }
+            bits += here;
+            store_words<DT>(dst, vi, V, o, stream);
+        }
+    }
+    return bits / BITS;
 }
 
 // The keys of first-digit bin d1 into L.list (the caller has checked that they fit).
@@ -682,22 +867,7 @@ __global__ __launch_bounds__(WARP_WG, 8) void k_warp(WarpArgs a)
         if (a.kept && tid == 0) a.kept[y] = kept;
         return;
     }
-    for_each_vector<DT>(row, V, [&](int vi, const float(&z)[N]) {
-        float o[N];
-#pragma unroll
-        for (int e = 0; e < N; ++e) {
-            const bool keep = value_key(z[e]) >= tau;
-            o[e] = keep ? z[e] : neg_inf();
-            kept += (keep && vi * N + e < V) ? 1 : 0;
-        }
-        if ((vi + 1) * N <= V) {
-            store_vec<DT>(dst + (long long)vi * N, o);
-        } else {
-            #pragma unroll
-                for (int e = 0; e < N; ++e)
-                    if (vi * N + e < V) store_one<DT>(dst + (long long)vi * N + e, o[e]);
-        }
-    });
+    kept = masked_copy<DT>(row, dst, V, tau, a.stream);
     if (a.kept) {
         kept = wave_reduce(kept, OpSum{});
         if (lane == 0) L.wave_kept[wave] = kept;
