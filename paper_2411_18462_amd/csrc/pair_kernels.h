@@ -26,9 +26,15 @@ __global__ __launch_bounds__(64) void k_pair_L(PairArgs a)
     const int g = clamp_len(graw, a.v.k);
     if (graw != g && j == 0) atomicOr(a.v.ws.flags, (unsigned)SVIP_FLAG_BAD_DRAFT_LEN);
     if (j >= g) return;
-    a.L[2 * y] = row_L(a.v, b, a.v.kd + j);
-    a.L[2 * y + 1] = a.v.draft_lse ? a.v.draft_lse[y] * 1.4426950408889634
-                                   : row_L(a.v, b, j);
+    RowStats<8> target, draft;                             // both rows' slices travel together
+    double lse = 0.0;
+    target.request(a.v, b, a.v.kd + j);
+    if (a.v.draft_lse) lse = a.v.draft_lse[y];
+    else draft.request(a.v, b, j);
+    target.merge(a.v, b, a.v.kd + j);
+    a.L[2 * y] = target.L();
+    if (!a.v.draft_lse) draft.merge(a.v, b, j);
+    a.L[2 * y + 1] = a.v.draft_lse ? lse * 1.4426950408889634 : draft.L();
 }
 
 // One batch of NU vector pairs per thread: with p = exp2(xp), q = exp2(xq) the normalised
@@ -127,11 +133,21 @@ __global__ __launch_bounds__(64) void k_pair_finish(PairArgs a)
         return;
     }
     double beta = 0.0, A = 0.0, Bq = 0.0;
-    for (int s = 0; s < a.geo2.ns; ++s) {
-        const double *src = a.sums + ((size_t)y * a.geo2.ns + s) * 3;
-        beta += src[0];
-        A += src[1];
-        Bq += src[2];
+    for (int s0 = 0; s0 < a.geo2.ns; s0 += 8) {            // eight slices in flight at a time
+        double x[8][3];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const double *src = a.sums + ((size_t)y * a.geo2.ns + min(s0 + u, a.geo2.ns - 1)) * 3;
+#pragma unroll
+            for (int i = 0; i < 3; ++i) x[u][i] = src[i];
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            if (s0 + u >= a.geo2.ns) continue;
+            beta += x[u][0];
+            A += x[u][1];
+            Bq += x[u][2];
+        }
     }
     constexpr double LN2 = 0.6931471805599453;
     double kl = LN2 * A, hq = -LN2 * Bq;

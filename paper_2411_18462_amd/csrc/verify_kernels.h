@@ -97,15 +97,6 @@ struct RowStats {
     }
     __device__ __forceinline__ double L() const { return (double)r + log2(S); }      // logsumexp * log2(e)
 };
-template <int CH = 4>
-__device__ __forceinline__ double row_L(const VerifyArgs &a, int b, int jj)
-{
-    RowStats<CH> row;
-    row.request(a, b, jj);
-    row.merge(a, b, jj);
-    return row.L();
-}
-
 // What the acceptance test of a sequence gives: what the draw needs (uniform over the wave), and what the call reports.
 struct Accepted {
     double Lp, Lq;      // logsumexp * log2(e) of target row r, and of draft row r if that was rejected
