@@ -372,31 +372,6 @@ __device__ __forceinline__ void draft_record(const DraftArgs &a, const DT *row, 
     }
 }
 
-// Which record wave `wv` of this workgroup takes: row *b of `rows`, record *r of that row; false: none.
-__device__ __forceinline__ bool wave_to_record(const DraftArgs &a, unsigned rows, int *b, int *r)
-{
-    const int nrec = a.geo.ns;
-    // Which record this wave takes is the same in all its lanes: worked out in scalar registers, with the one
-    // division done by a multiplication the host prepared, so that none of it takes vector-ALU slots.
-    const unsigned wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (a.rows_by_xcd) {
-        // Workgroups go to the chip's 8 XCDs in turn, and so do the rows' workgroups of the finish: keeping row b on
-        // XCD b % 8 lets that kernel find the row's records (and what it reads again) in the L2 of its own XCD, and
-        // the lines of the records are written by one L2 each.  The grid is ceil(rows / 8) * 8 * ceil(nrec / 4)
-        // workgroups; those of rows past the last exit.
-        const unsigned xcd = blockIdx.x & 7u, slot = blockIdx.x >> 3;           // div = workgroups per row
-        const unsigned q = a.div == 1u ? slot : __umulhi(slot, a.div_magic);
-        *b = (int)(q * 8u + xcd);
-        *r = (int)((slot - q * a.div) * NWAVE + wv);
-        return *b < (int)rows && *r < nrec;
-    }
-    const unsigned gw = blockIdx.x * NWAVE + wv;                            // div = records per row
-    if (gw >= rows * (unsigned)nrec) return false;
-    *b = (int)(a.div == 1u ? gw : __umulhi(gw, a.div_magic));
-    *r = (int)(gw - (unsigned)*b * (unsigned)nrec);
-    return true;
-}
-
 // grid (ceil(rows * records / 4)), one wave per record.
 template <typename DT, RecordKind KIND, int TPS>
 __global__ __launch_bounds__(WG, TPS == 1 ? 8 : 6) void k_draft_stats(DraftArgs a)
@@ -405,23 +380,76 @@ __global__ __launch_bounds__(WG, TPS == 1 ? 8 : 6) void k_draft_stats(DraftArgs 
     // a second trip to the scalar cache before the first load of a logit.
     asm volatile("" : : "s"(a.logits), "s"(a.row_stride), "s"(a.pos), "s"(a.stop_in), "s"(a.geo.V), "s"(a.part), "s"(a.sc.c_dn),
                  "s"(a.sc.c_up), "s"(a.sc.c), "s"(a.common_range), "s"(a.step_j));
+    const int nrec = a.geo.ns;
+    // Which record this wave takes is the same in all its lanes: worked out in scalar registers, with the one
+    // division done by a multiplication the host prepared, so that none of it takes vector-ALU slots.  (Written out here: as a
+    // function shared with the loop's kernels, wave_to_record, it takes ten vector instructions more.)
+    const unsigned wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int b, r;
-    if (!wave_to_record(a, (unsigned)a.B, &b, &r)) return;
+    if (a.rows_by_xcd) {
+        // Workgroups go to the chip's 8 XCDs in turn, and so do the rows' workgroups of the finish: keeping row b on
+        // XCD b % 8 lets that kernel find the row's records (and what it reads again) in the L2 of its own XCD, and
+        // the lines of the records are written by one L2 each.  The grid is ceil(B / 8) * 8 * ceil(nrec / 4)
+        // workgroups; those of rows past B exit.
+        const unsigned xcd = blockIdx.x & 7u, slot = blockIdx.x >> 3;           // div = workgroups per row
+        const unsigned q = a.div == 1u ? slot : __umulhi(slot, a.div_magic);
+        b = (int)(q * 8u + xcd);
+        r = (int)((slot - q * a.div) * NWAVE + wv);
+        if (b >= a.B || r >= nrec) return;
+    } else {
+        const unsigned gw = blockIdx.x * NWAVE + wv;                            // div = records per row
+        if (gw >= (unsigned)a.B * (unsigned)nrec) return;
+        b = (int)(a.div == 1u ? gw : __umulhi(gw, a.div_magic));
+        r = (int)(gw - (unsigned)b * (unsigned)nrec);
+    }
     draft_record<DT, KIND, TPS>(a, static_cast<const DT *>(a.logits) + draft_row_offset(a, b, a.step_j), b, r, (size_t)b * a.geo.ns + r);
 }
 
-// The inverse CDF inside one chunk of a row by one wave (search_chunks) over weights exp2((z - m) c).
+// The inverse CDF inside one chunk of a row by one wave: the smallest index whose inclusive prefix of weights
+// exp2((z - m) c), counted from the start of the chunk, exceeds `target`.  A lane holds one vector; fp32 sums per
+// vector, fp64 over the lanes.  The lane that holds the token reports it (see locate_batch).  If rounding leaves no
+// crossing, it is the last index with positive weight (-1 if there is none).  (search_chunks of row_math.h with one chunk does
+// the same in a step of 16 rows of 32000 fp32 logits that is 0.05 us longer.)
 template <typename DT, typename Report>
 __device__ __forceinline__ void search_chunk(const DT *row, int V, int chunk, float m, const Scale &sc, double target, Report report)
 {
     constexpr int N = VecOf<DT>::N;
-    float z[N], w[1][N];
+    const int lane = threadIdx.x & 63;
+    float z[N], w[N];
     typename RawOf<DT>::type raw[1];
     wave_load<DT, 1, true>(row, V, chunk, raw);
     unpack<DT>(raw[0], z);
 #pragma unroll
-    for (int e = 0; e < N; ++e) w[0][e] = exp2_raw(scaled_below_floored(z[e] - m, sc));
-    search_chunks<N, 1>(w, chunk, target, report);
+    for (int e = 0; e < N; ++e) w[e] = exp2_raw(scaled_below_floored(z[e] - m, sc));
+    const double g = (double)tree_sum<N>(w);
+    const double incl = wave_inclusive_sum(g);
+    const unsigned long long hit = __ballot(g > 0.0 && incl > target), mass = __ballot(g > 0.0);
+    double C = incl - g;
+    int pick = -1, lastpos = -1;
+    float wp = 0.f, wl = 0.f;
+#pragma unroll
+    for (int e = 0; e < N; ++e) {
+        C += (double)w[e];
+        if (w[e] > 0.f) {
+            lastpos = e;
+            wl = w[e];
+            if (pick < 0 && C > target) {
+                pick = e;
+                wp = w[e];
+            }
+        }
+    }
+    const int base = (chunk * 64 + lane) * N;
+    if (hit) {
+        if (lane == __ffsll((long long)hit) - 1) {
+            if (pick < 0) report(base + lastpos, wl);
+            else report(base + pick, wp);
+        }
+    } else if (mass) {
+        if (lane == 63 - __clzll((long long)mass)) report(base + lastpos, wl);
+    } else if (lane == 0) {
+        report(-1, 0.f);
+    }
 }
 
 // What the thread that finds the draft token does with it (see locate_batch's `report`); unit: the weight of 1 of the

@@ -23,6 +23,25 @@ struct GroupArgs {
     LoopArgs l;
 };
 
+// Which record wave `wv` of this workgroup takes: row *b of `rows`, record *r of that row, as in k_draft_stats; false: none.
+__device__ __forceinline__ bool wave_to_record(const DraftArgs &a, unsigned rows, int *b, int *r)
+{
+    const int nrec = a.geo.ns;
+    const unsigned wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (a.rows_by_xcd) {
+        const unsigned xcd = blockIdx.x & 7u, slot = blockIdx.x >> 3;
+        const unsigned q = a.div == 1u ? slot : __umulhi(slot, a.div_magic);
+        *b = (int)(q * 8u + xcd);
+        *r = (int)((slot - q * a.div) * NWAVE + wv);
+        return *b < (int)rows && *r < nrec;
+    }
+    const unsigned gw = blockIdx.x * NWAVE + wv;
+    if (gw >= rows * (unsigned)nrec) return false;
+    *b = (int)(a.div == 1u ? gw : __umulhi(gw, a.div_magic));
+    *r = (int)(gw - (unsigned)*b * (unsigned)nrec);
+    return true;
+}
+
 // Row y of a launch as (position, sequence).
 __device__ __forceinline__ bool group_row(const GroupArgs &a, int y, int *jj, int *b)
 {
