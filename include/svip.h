@@ -327,7 +327,9 @@ typedef struct svip_loop_config {
     void *hip_stream;
 } svip_loop_config;
 
-/* Bytes of device workspace the loop needs (kernel workspace plus the buffers of one round). */
+/* Bytes of device workspace for the loop (kernel workspace plus the buffers of one round).  A call that brings less, but
+ * enough for a round that takes its draft positions one by one, is run that way (same results, more launches);
+ * below that: SVIP_ERR_WORKSPACE. */
 size_t svip_loop_workspace_bytes(int B, int gamma_max, int V);
 
 /* Set every sequence to position n0 with limit gamma0 and clear the counters and flags (enqueued). */

@@ -166,13 +166,21 @@ static size_t plan_bytes(int B, int k, int V)
     return most;
 }
 
+// What a round taken position by position needs: the least a call may bring.
+static size_t serial_buffer_bytes(int B, int k)
+{
+    const size_t n = (size_t)B, nk = n * (size_t)k;
+    return up256(nk * 4) + up256(nk * 8) + 2 * up256(n) + 6 * up256(n * 4) + 256;
+}
+
 static size_t round_buffer_bytes(int B, int k, int V)
 {
     const size_t n = (size_t)B, nk = n * (size_t)k;
-    return up256(nk * 4) + up256(nk * 8) + 2 * up256(n) + 8 * up256(n * 4) + 256 + up256((nk + n) * 4) + plan_bytes(B, k, V);
+    return serial_buffer_bytes(B, k) + 2 * up256(n * 4) + up256((nk + n) * 4) + plan_bytes(B, k, V);
 }
 
-static RoundBuffers carve_round(char *p, int B, int k, int V)
+// bytes: of the round's buffers.  Where they do only for the serial loop there are none for groups (group is null).
+static RoundBuffers carve_round(char *p, int B, int k, int V, size_t bytes)
 {
     const size_t n = (size_t)B, nk = n * (size_t)k;
     RoundBuffers r;
@@ -186,11 +194,16 @@ static RoundBuffers carve_round(char *p, int B, int k, int V)
     r.pos = reinterpret_cast<int *>(p); p += up256(n * 4);
     r.cap = reinterpret_cast<int *>(p); p += up256(n * 4);
     r.counter = reinterpret_cast<int *>(p); p += 256;
-    r.drafted = reinterpret_cast<int *>(p); p += up256(n * 4);
-    r.round = reinterpret_cast<int *>(p); p += up256(n * 4);
-    r.argmax = reinterpret_cast<int *>(p); p += up256((nk + n) * 4);
-    r.group = p;
-    r.group_bytes = plan_bytes(B, k, V);
+    r.drafted = r.round = r.argmax = nullptr;
+    r.group = nullptr;
+    r.group_bytes = 0;
+    if (bytes >= round_buffer_bytes(B, k, V)) {
+        r.drafted = reinterpret_cast<int *>(p); p += up256(n * 4);
+        r.round = reinterpret_cast<int *>(p); p += up256(n * 4);
+        r.argmax = reinterpret_cast<int *>(p); p += up256((nk + n) * 4);
+        r.group = p;
+        r.group_bytes = plan_bytes(B, k, V);
+    }
     return r;
 }
 
@@ -237,8 +250,10 @@ __global__ __launch_bounds__(LOOP_WG) void k_round_begin(LoopArgs a)
     for (int b = threadIdx.x; b < a.B; b += LOOP_WG) {
         const int *st = a.state + (size_t)b * SVIP_LOOP_NSTATE;
         begin_sequence(a.rb, b, st[0], st[1], st[2]);
-        a.rb.drafted[b] = 0;
-        a.rb.round[b] = a.round;
+        if (a.rb.group) {
+            a.rb.drafted[b] = 0;
+            a.rb.round[b] = a.round;
+        }
         running += st[2] ? 0 : 1;
     }
     const int total = block_count(running, lds);
@@ -382,8 +397,9 @@ static svip_status check_config(const svip_loop_config *c)
         c->out_stride < (long long)c->max_new + c->gamma_max || c->rounds < 1)
         return SVIP_ERR_SHAPE;
     if (c->gamma_inc < 0 || c->gamma_dec < 0 || c->check_every < 0) return SVIP_ERR_PARAM;
-    const size_t need = svip_loop_workspace_bytes(c->B, c->gamma_max, c->V);
-    if (!c->workspace || (reinterpret_cast<uintptr_t>(c->workspace) & 255u) || need == 0 || c->workspace_bytes < need)
+    const size_t base = up256(svip_workspace_bytes(c->B, c->gamma_max, c->V));
+    if (!c->workspace || (reinterpret_cast<uintptr_t>(c->workspace) & 255u) || base == 0 ||
+        c->workspace_bytes < base + serial_buffer_bytes(c->B, c->gamma_max))
         return SVIP_ERR_WORKSPACE;
     return SVIP_OK;
 }
@@ -407,7 +423,8 @@ svip_status svip_loop_init(const svip_loop_config *c)
     if (s != SVIP_OK) return s;
     hipStream_t st = static_cast<hipStream_t>(c->hip_stream);
     const size_t base = up256(svip_workspace_bytes(c->B, c->gamma_max, c->V));
-    const RoundBuffers rb = carve_round(static_cast<char *>(c->workspace) + base, c->B, c->gamma_max, c->V);
+    const RoundBuffers rb = carve_round(static_cast<char *>(c->workspace) + base, c->B, c->gamma_max, c->V,
+                                        c->workspace_bytes - base);
     const svip_status r = svip_workspace_reset(c->workspace, base, c->hip_stream);
     if (r != SVIP_OK) return r;
     hipLaunchKernelGGL(k_loop_init, dim3(1), dim3(LOOP_WG), 0, st, c->state, c->B, c->n0, c->gamma0, c->L,
@@ -423,9 +440,10 @@ svip_status svip_loop_run(const svip_loop_config *c, int first_round, int max_ro
     if (first_round < 0 || max_rounds < 0 || (long long)first_round + max_rounds > c->rounds) return SVIP_ERR_SHAPE;
     hipStream_t st = static_cast<hipStream_t>(c->hip_stream);
     const size_t base = up256(svip_workspace_bytes(c->B, c->gamma_max, c->V));
-    const RoundBuffers rb = carve_round(static_cast<char *>(c->workspace) + base, c->B, c->gamma_max, c->V);
+    const RoundBuffers rb = carve_round(static_cast<char *>(c->workspace) + base, c->B, c->gamma_max, c->V,
+                                        c->workspace_bytes - base);
     const int B = c->B, k = c->gamma_max;
-    const GroupPlan plan = draft_shape_forced() ? GroupPlan{0, 0} : plan_groups(B, k, c->V, c->dtype, c->greedy != 0);
+    const GroupPlan plan = draft_shape_forced() || !rb.group ? GroupPlan{0, 0} : plan_groups(B, k, c->V, c->dtype, c->greedy != 0);
 
     int running = 0, done_rounds = 0;
     svip_status r;

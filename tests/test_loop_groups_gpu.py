@@ -93,3 +93,31 @@ def test_paused_loop_reports_as_before(svip):
     assert a.run(3) == (0, 0)                                   # nothing is left to do
     done = a.state[:, 3].max().item()
     assert sum(r for r, _ in seen) == done and (a.round_log[done:] == -2).all()
+
+
+@pytest.mark.parametrize("greedy", [True, False])
+def test_workspace_for_single_positions(svip, greedy):
+    """A workspace that holds a round's buffers but none for groups: position by position, with the same results, and nothing
+    written behind it; one byte less is refused."""
+    B, k, V, max_new = 5, 6, 9000, 12
+    draft, target = _trace(B, max_new + k + 1, V, torch.float16, 11, False)
+    up = lambda n: (n + 255) // 256 * 256
+    least = up(svip.workspace_bytes(B, k, V)) + up(4 * B * k) + up(8 * B * k) + 2 * up(B) + 6 * up(4 * B) + 256
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    u = {} if greedy else dict(u_sample=torch.rand(max_new, B, k, device="cuda", generator=g),
+                               u_accept=torch.rand(max_new, B, k, device="cuda", generator=g),
+                               u_resample=torch.rand(max_new, B, device="cuda", generator=g))
+    a, b = (svip.Loop(target, draft, temperature=1.0, h=1.3, gamma0=k, gamma_max=k, max_new=max_new, rounds=max_new,
+                      greedy=greedy, **u) for _ in range(2))
+    assert b.workspace.numel() > least
+    b.workspace[least:] = 0xA5
+    b.config.workspace_bytes = least - 1
+    with pytest.raises(svip.SvipError):
+        b.run()
+    b.config.workspace_bytes = least
+    ran, running = a.run()
+    assert b.run() == (ran, running)
+    assert torch.equal(a.state, b.state) and torch.equal(a.out_tokens, b.out_tokens)
+    assert torch.equal(a.round_log[:ran], b.round_log[:ran])       # a round launched ahead may have filled its entries behind
+    assert (b.workspace[least:] == 0xA5).all()
