@@ -26,7 +26,9 @@ __global__ __launch_bounds__(64) void k_pair_L(PairArgs a)
     const int g = clamp_len(graw, a.v.k);
     if (graw != g && j == 0) atomicOr(a.v.ws.flags, (unsigned)SVIP_FLAG_BAD_DRAFT_LEN);
     if (j >= g) return;
-    RowStats<8> target, draft;                             // both rows' slices travel together
+    // Both rows' slices travel together, four at a time: small rows have few (a call of 63 positions of 32000 fp32 logits
+    // 15.8 us, with eight at a time 16.2, one by one 16.1; 20 positions of 151936 22.7, 22.4, 25.8).
+    RowStats<4> target, draft;
     double lse = 0.0;
     target.request(a.v, b, a.v.kd + j);
     if (a.v.draft_lse) lse = a.v.draft_lse[y];
