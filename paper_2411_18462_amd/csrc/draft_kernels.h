@@ -309,15 +309,66 @@ __device__ __forceinline__ void store_record(const DraftArgs &a, size_t at, floa
     if (lane < 6) reinterpret_cast<double *>(static_cast<QuarterRec *>(a.part) + at)[lane] = x;
 }
 
-// The record of one wave: tiles [r * tps, (r + 1) * tps) of sequence b's row, stored at index `at`.  TPS: tiles per record, 1,
-// 2 or 0 for more.  A record of two whole tiles requests both before it works on the first (the arithmetic of the
-// first runs while the second is still on its way), which takes more registers; launches with one tile per record keep the
-// other form.
+// What a wave stores of the tiles [tb, te) it has summed (ok: within wave_tile's range throughout).
+template <typename DT, RecordKind KIND>
+__device__ __forceinline__ void finish_record(const DraftArgs &a, const DT *row, int tb, int te, size_t at, bool ok, float mw,
+                                              LaneSums<KIND> &sums, float td, int first, unsigned lowest)
+{
+    constexpr int CPT = WG / 64;
+    if (ok && mw == neg_inf() && __ballot(lowest != 0u)) {                 // nothing but the lowest number: all ties
+        mw = FiniteLow<DT>::value();
+#pragma unroll
+        for (int u = 0; u < CPT; ++u) sums.add(u, 0.f, (float)((lowest >> (8 * u)) & 0xFFu));
+    }
+    if (ok) {
+        const double t = wave_sum((double)td) * a.sc.c;
+        if constexpr (KIND == QUARTERS) store_record(a, at, mw, sums.S, t);
+        else store_record(a, at, mw, first, sums.total(), t);
+    } else {
+        double S[4], t2;
+        uncommon_record<DT, KIND>(a, row, tb, te, mw, S, t2, first);
+        const double t = wave_sum(t2);
+        if constexpr (KIND == QUARTERS) store_record(a, at, mw, S, t);
+        else store_record(a, at, mw, first, (S[0] + S[1]) + (S[2] + S[3]), t);
+    }
+}
+
+// grid (ceil(rows * records / 4)), one wave per record.  TPS: tiles per record, 1, 2 or 0 for more.  A record of two
+// whole tiles requests both before it works on the first (the arithmetic of the first runs while the second is
+// still on its way), which takes more registers; launches with one tile per record keep the other form.
 template <typename DT, RecordKind KIND, int TPS>
-__device__ __forceinline__ void draft_record(const DraftArgs &a, const DT *row, int b, int r, size_t at)
+__global__ __launch_bounds__(WG, TPS == 1 ? 8 : 6) void k_draft_stats(DraftArgs a)
 {
     constexpr int N = VecOf<DT>::N, CPT = WG / 64;       // chunks of 64 vectors per tile
     static_assert(KIND != QUARTERS || TPS == 1, "a quarter is a chunk");
+    const int nrec = a.geo.ns;
+    // All arguments are requested at once: left to itself the compiler loads those behind the first branch only there,
+    // a second trip to the scalar cache before the first load of a logit.
+    asm volatile("" : : "s"(a.logits), "s"(a.row_stride), "s"(a.pos), "s"(a.stop_in), "s"(a.geo.V), "s"(a.part), "s"(a.sc.c_dn),
+                 "s"(a.sc.c_up), "s"(a.sc.c), "s"(a.common_range), "s"(a.step_j));
+    // Which record this wave takes is the same in all its lanes: worked out in scalar registers, with the one
+    // division done by a multiplication the host prepared, so that none of it takes vector-ALU slots.  (This and the
+    // reading of the tiles are written out here: shared with the loop's kernels as functions they compile to 8 vector
+    // instructions more and, in fp32, 44 registers instead of 55; 16 steps of 16 rows of 32000 fp32 logits take 1 % longer.)
+    const unsigned wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int b, r;
+    if (a.rows_by_xcd) {
+        // Workgroups go to the chip's 8 XCDs in turn, and so do the rows' workgroups of the finish: keeping row b on
+        // XCD b % 8 lets that kernel find the row's records (and what it reads again) in the L2 of its own XCD, and
+        // the lines of the records are written by one L2 each.  The grid is ceil(B / 8) * 8 * ceil(nrec / 4)
+        // workgroups; those of rows past B exit.
+        const unsigned xcd = blockIdx.x & 7u, slot = blockIdx.x >> 3;           // div = workgroups per row
+        const unsigned q = a.div == 1u ? slot : __umulhi(slot, a.div_magic);
+        b = (int)(q * 8u + xcd);
+        r = (int)((slot - q * a.div) * NWAVE + wv);
+        if (b >= a.B || r >= nrec) return;
+    } else {
+        const unsigned gw = blockIdx.x * NWAVE + wv;                            // div = records per row
+        if (gw >= (unsigned)a.B * (unsigned)nrec) return;
+        b = (int)(a.div == 1u ? gw : __umulhi(gw, a.div_magic));
+        r = (int)(gw - (unsigned)b * (unsigned)nrec);
+    }
+    const DT *row = static_cast<const DT *>(a.logits) + draft_row_offset(a, b, a.step_j);
     const int tps = TPS ? TPS : a.geo.tps;
     const int tb = r * tps, te = min(tb + tps, a.geo.ntiles);
     const int fe = min(te, a.geo.V / (WG * N));           // end of the tiles wholly inside the row
@@ -354,55 +405,7 @@ __device__ __forceinline__ void draft_record(const DraftArgs &a, const DT *row, 
     // A NaN among the logits (only the 16-bit types get one past unpack_finite) shows in td, whose terms are all finite and
     // at most 0 otherwise; like a masked logit it weighs nothing, by the floor of uncommon_record's exponents.
     ok = ok && __ballot(!(td > neg_inf())) == 0ull;
-    if (ok && mw == neg_inf() && __ballot(lowest != 0u)) {                 // nothing but the lowest number: all ties
-        mw = FiniteLow<DT>::value();
-#pragma unroll
-        for (int u = 0; u < CPT; ++u) sums.add(u, 0.f, (float)((lowest >> (8 * u)) & 0xFFu));
-    }
-    if (ok) {
-        const double t = wave_sum((double)td) * a.sc.c;
-        if constexpr (KIND == QUARTERS) store_record(a, at, mw, sums.S, t);
-        else store_record(a, at, mw, first, sums.total(), t);
-    } else {
-        double S[4], t2;
-        uncommon_record<DT, KIND>(a, row, tb, te, mw, S, t2, first);
-        const double t = wave_sum(t2);
-        if constexpr (KIND == QUARTERS) store_record(a, at, mw, S, t);
-        else store_record(a, at, mw, first, (S[0] + S[1]) + (S[2] + S[3]), t);
-    }
-}
-
-// grid (ceil(rows * records / 4)), one wave per record.
-template <typename DT, RecordKind KIND, int TPS>
-__global__ __launch_bounds__(WG, TPS == 1 ? 8 : 6) void k_draft_stats(DraftArgs a)
-{
-    // All arguments are requested at once: left to itself the compiler loads those behind the first branch only there,
-    // a second trip to the scalar cache before the first load of a logit.
-    asm volatile("" : : "s"(a.logits), "s"(a.row_stride), "s"(a.pos), "s"(a.stop_in), "s"(a.geo.V), "s"(a.part), "s"(a.sc.c_dn),
-                 "s"(a.sc.c_up), "s"(a.sc.c), "s"(a.common_range), "s"(a.step_j));
-    const int nrec = a.geo.ns;
-    // Which record this wave takes is the same in all its lanes: worked out in scalar registers, with the one
-    // division done by a multiplication the host prepared, so that none of it takes vector-ALU slots.  (Written out here: as a
-    // function shared with the loop's kernels, wave_to_record, it takes ten vector instructions more.)
-    const unsigned wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    int b, r;
-    if (a.rows_by_xcd) {
-        // Workgroups go to the chip's 8 XCDs in turn, and so do the rows' workgroups of the finish: keeping row b on
-        // XCD b % 8 lets that kernel find the row's records (and what it reads again) in the L2 of its own XCD, and
-        // the lines of the records are written by one L2 each.  The grid is ceil(B / 8) * 8 * ceil(nrec / 4)
-        // workgroups; those of rows past B exit.
-        const unsigned xcd = blockIdx.x & 7u, slot = blockIdx.x >> 3;           // div = workgroups per row
-        const unsigned q = a.div == 1u ? slot : __umulhi(slot, a.div_magic);
-        b = (int)(q * 8u + xcd);
-        r = (int)((slot - q * a.div) * NWAVE + wv);
-        if (b >= a.B || r >= nrec) return;
-    } else {
-        const unsigned gw = blockIdx.x * NWAVE + wv;                            // div = records per row
-        if (gw >= (unsigned)a.B * (unsigned)nrec) return;
-        b = (int)(a.div == 1u ? gw : __umulhi(gw, a.div_magic));
-        r = (int)(gw - (unsigned)b * (unsigned)nrec);
-    }
-    draft_record<DT, KIND, TPS>(a, static_cast<const DT *>(a.logits) + draft_row_offset(a, b, a.step_j), b, r, (size_t)b * a.geo.ns + r);
+    finish_record<DT, KIND>(a, row, tb, te, (size_t)b * nrec + r, ok, mw, sums, td, first, lowest);
 }
 
 // The inverse CDF inside one chunk of a row by one wave: the smallest index whose inclusive prefix of weights
@@ -487,16 +490,15 @@ __device__ __forceinline__ void stopped_row(const DraftArgs &a, int b, long long
     }
 }
 
-// Factor that brings a record with maximum m and sum S to the row maximum, and its log2 (0, 0 for an empty record).
+// Factor that brings a record with maximum m and sum S to the row maximum, and its log2 (0, 0 for an empty record).  Formed for
+// empty records too and then dropped: with a branch around it the exponential waits for the sum and cannot run beside the
+// merge's other chains.
 __device__ __forceinline__ double record_factor(float m, double S, float mrow, const Scale &sc, double *xd)
 {
-    double f = 0.0;
-    *xd = 0.0;
-    if (m != neg_inf() && S > 0.0) {
-        *xd = ((double)m - (double)mrow) * sc.c;
-        f = exp2(*xd);
-    }
-    return f;
+    const double x = ((double)m - (double)mrow) * sc.c, f = exp2(x);
+    const bool any = m != neg_inf() && S > 0.0;
+    *xd = any ? x : 0.0;
+    return any ? f : 0.0;
 }
 
 // A row's QUARTERS records, RPL consecutive ones per lane; `at` is the index of its first record.

@@ -50,6 +50,23 @@ __device__ __forceinline__ bool group_row(const GroupArgs &a, int y, int *jj, in
     return *b < a.d.B;
 }
 
+// The record of tile r of a row, stored at index `at`: what k_draft_stats does for records of one tile, without its flag.
+template <typename DT, RecordKind KIND>
+__device__ __forceinline__ void tile_record(const DraftArgs &a, const DT *row, int r, size_t at)
+{
+    constexpr int N = VecOf<DT>::N, CPT = WG / 64;
+    typename RawOf<DT>::type raw[CPT];
+    float mw = neg_inf(), td = 0.f;
+    LaneSums<KIND> sums;
+    int first = -1;
+    unsigned lowest = 0u;
+    if (r < a.geo.V / (WG * N)) wave_load<DT, CPT, false>(row, a.geo.V, r * CPT, raw);
+    else wave_load<DT, CPT, true>(row, a.geo.V, r * CPT, raw);
+    bool ok = a.common_range && wave_tile<DT, CPT, KIND>(raw, r * CPT, mw, sums, td, first, lowest, a.sc);
+    ok = ok && __ballot(!(td > neg_inf())) == 0ull;       // (a NaN among the logits, see k_draft_stats)
+    finish_record<DT, KIND>(a, row, r, r + 1, at, ok, mw, sums, td, first, lowest);
+}
+
 // The draft records of positions step_j .. step_j + group - 1, one wave per record as in k_draft_stats.  Rows past a
 // sequence's limit may lie past the end of its trace: nothing of them is touched.
 template <typename DT>
@@ -59,7 +76,7 @@ __global__ __launch_bounds__(WG, 8) void k_group_stats(GroupArgs a)
     if (!wave_to_record(a.d, (unsigned)(a.group * a.lane_rows), &y, &r) || !group_row(a, y, &jj, &b)) return;
     const int cap = min(a.d.cap[b], a.d.k_max), stopped = a.d.stop_in[b], j = a.d.step_j + jj;
     if (stopped || j >= cap) return;
-    draft_record<DT, QUARTERS, 1>(a.d, static_cast<const DT *>(a.d.logits) + draft_row_offset(a.d, b, j), b, r, (size_t)y * a.d.geo.ns + r);
+    tile_record<DT, QUARTERS>(a.d, static_cast<const DT *>(a.d.logits) + draft_row_offset(a.d, b, j), r, (size_t)y * a.d.geo.ns + r);
 }
 
 // ... and what follows from them: grid (sequences), a wave per position (positions in turn where there are more of them
@@ -151,7 +168,7 @@ __global__ __launch_bounds__(WG, 8) void k_stream_rows(GroupArgs a)
         const unsigned long long key = tile_argmax<DT>(static_cast<const DT *>(a.target) + off, a.d.geo.V, r);
         if ((threadIdx.x & 63) == 0) a.keys[(size_t)(y - a.group * a.lane_rows) * a.d.geo.ns + r] = key;
     } else {
-        draft_record<DT, GREEDY, 1>(a.d, static_cast<const DT *>(a.d.logits) + off, b, r, (size_t)y * a.d.geo.ns + r);
+        tile_record<DT, GREEDY>(a.d, static_cast<const DT *>(a.d.logits) + off, r, (size_t)y * a.d.geo.ns + r);
     }
 }
 
