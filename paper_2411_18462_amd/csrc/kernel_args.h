@@ -7,9 +7,17 @@ namespace svip {
 
 // ---- workspace layout ----------------------------------------------------------------
 
+struct SeqRec {          // what an acceptance test in a launch of its own hands to the residual pass, one per sequence
+    double Lp;           // logsumexp(target row r) * log2(e)
+    double Lq;           // logsumexp(draft row r) * log2(e) (residual mode only)
+    int r;               // target row to sample from (first rejection, or draft_len for a bonus)
+    int resid;           // 1: residual of row r, 0: bonus from row r
+};
+
 struct Workspace {
     unsigned *flags;     // sticky device-data flags
     unsigned *tickets;   // END of the ticket counters (see ticket()): they grow downwards from here
+    SeqRec *rec;         // [B]
     double *mass;        // [B][slices of the residual pass] masses of half tiles, verification only
     void *part;          // slice statistics (LsePart, sized for sizeof(Partial) each), keys or records of the call
 };
@@ -22,11 +30,11 @@ constexpr size_t HEADER_BYTES = 256;
 constexpr int TICKETS_PER_ROW = SVIP_TICKET_STRIDE;   // words between the counters of consecutive rows
 __host__ __device__ inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-static size_t ws_unused_bytes(int B) { return align256((size_t)B * 24); }      // sizes stay what callers have sized for
+static size_t ws_rec_bytes(int B) { return align256((size_t)B * sizeof(SeqRec)); }
 static size_t ws_mass_bytes(int B, int slices) { return align256((size_t)B * slices * 2 * TILE_MASSES * sizeof(double)); }
 static size_t ws_ticket_bytes(int B) { return align256((size_t)B * TICKETS_PER_ROW * sizeof(unsigned)); }
 
-// Layout: flag word | (unused) | slice masses | slice statistics ...            ... ticket counters.
+// Layout: flag word | records | slice masses | slice statistics ...            ... ticket counters.
 // The counters sit at the END of the workspace (the given size rounded down to 256 bytes) and counter
 // t of row b lies TICKETS_PER_ROW * b + t + 1 words below that end, whatever the batch size of the call: regions at the
 // front never reach them (every call checks front + counters <= size), so they keep the zeros that
@@ -39,7 +47,8 @@ static Workspace carve(void *ws, size_t bytes, int B, int mass_slices)
     w.flags = reinterpret_cast<unsigned *>(p);
     w.tickets = reinterpret_cast<unsigned *>(p + (bytes & ~(size_t)255));
     p += HEADER_BYTES;
-    p += ws_unused_bytes(B);
+    w.rec = reinterpret_cast<SeqRec *>(p);
+    p += ws_rec_bytes(B);
     w.mass = reinterpret_cast<double *>(p);
     p += ws_mass_bytes(B, mass_slices);
     w.part = p;

@@ -5,8 +5,9 @@
 //                     k_draft_finish_* grid (rows)               merge of the records: entropy, stop test, inverse
 //                                      CDF inside the one record that holds the draw (greedy: the first maximum)
 // svip_verify      =  k_verify_stats   grid (stat rows * slices) per-slice (reference, sum) of every needed row
-//                     k_resid          grid (sequences * slices) p/q tests, ballot scan for the first rejection, slice masses
-//                                      of the residual / bonus row; the workgroup that finishes a sequence last draws the token
+//                     k_accept         grid (sequences), 1 wave  p/q tests, ballot scan for the first rejection (small calls: in k_resid)
+//                     k_resid          grid (sequences * slices) slice masses of the residual / bonus row; the workgroup
+//                                      that finishes a sequence last draws the token
 // svip_verify_greedy = k_argmax        grid (target rows * slices) first maximum per slice, no exponentials
 //                     k_accept_greedy  grid (sequences), 1 wave  argmax p == x test, ballot, correction = argmax p
 //
@@ -206,7 +207,7 @@ static bool quarter_records(int B, const Geo &g) { return g.tps == 1 && (long lo
 // flag word + ticket counters + slice masses of the residual pass (mass_slices per sequence)
 static size_t ws_fixed_bytes(int B, int mass_slices)
 {
-    return HEADER_BYTES + ws_unused_bytes(B) + ws_mass_bytes(B, mass_slices) + ws_ticket_bytes(B);
+    return HEADER_BYTES + ws_rec_bytes(B) + ws_mass_bytes(B, mass_slices) + ws_ticket_bytes(B);
 }
 
 static size_t need_draft(int B, const Geo &g, bool greedy)
@@ -515,6 +516,11 @@ static svip_status verify_greedy_call(const VerifyCall &c)
     return ok ? SVIP_OK : SVIP_ERR_HIP;
 }
 
+// Whether the acceptance test runs inside the residual pass, where every workgroup of a sequence repeats it, or in a launch of its
+// own.  Drafts longer than one pass of a wave have theirs: the passes are a serial chain, those behind the first rejection
+// are needed only once, and what they read may lie under next_token_out.
+static bool accept_in_resid(int k_max) { return k_max <= LANE_POSITIONS; }
+
 svip_status verify_call(const VerifyCall &c)
 {
     if (c.greedy) return verify_greedy_call(c);
@@ -566,12 +572,15 @@ svip_status verify_call(const VerifyCall &c)
     unsigned g_stats = (unsigned)a.stat_items;
     if (g_tune.stats_workgroups > 0 && (unsigned)g_tune.stats_workgroups < g_stats) g_stats = (unsigned)g_tune.stats_workgroups;
     const unsigned g_resid = (unsigned)a.geo_s.ns * (((unsigned)c.B + 7u) / 8u) * 8u;   // sequences by XCD, see k_resid
+    const bool test = accept_in_resid(c.k_max);
     bool ok = false;
     by_dtype(c.dtype, [&](auto tag) {
         using DT = decltype(tag);
         ok = launch(k_verify_stats<DT>, g_stats, WG, st, a, SVIP_BENCH_K_VERIFY_STATS) &&
-             (a.geo_s.tps <= TILE_MASSES ? launch(k_resid<DT, true>, g_resid, WG, st, a, SVIP_BENCH_K_RESID)
-                                         : launch(k_resid<DT, false>, g_resid, WG, st, a, SVIP_BENCH_K_RESID));
+             (test || launch(k_accept<DT>, (unsigned)c.B, 64, st, a, SVIP_BENCH_K_ACCEPT)) &&
+             launch(a.geo_s.tps <= TILE_MASSES ? (test ? k_resid<DT, true, true> : k_resid<DT, true, false>)
+                                               : (test ? k_resid<DT, false, true> : k_resid<DT, false, false>),
+                    g_resid, WG, st, a, SVIP_BENCH_K_RESID);
     });
     return ok ? SVIP_OK : SVIP_ERR_HIP;
 }

@@ -102,7 +102,7 @@ struct Accepted {
     double Lp, Lq;      // logsumexp * log2(e) of target row r, and of draft row r if that was rejected
     int r;              // target row to draw from: the first rejection, or the draft length for a bonus
     bool resid;         // residual of row r, or the bonus row
-    float prob;         // accept probability of position `lane` (of the first 64, those below the draft length)
+    float prob;         // not PASSES: accept probability of position `lane`, -1 from the draft length on
     unsigned flags;     // bad device data met on the way (per lane)
 };
 
@@ -110,11 +110,15 @@ struct Accepted {
 // slices) 58.8 / 59.6 / 60.0, 32 of 8 and 50257 fp16 (3 slices) 24.2 / 24.9 / 25.6.
 constexpr int ACCEPT_SLICES = 4;
 
+// Drafts of at most this many positions have a lane for each (and one more pass for the bonus row behind 64 accepted ones).
+constexpr int LANE_POSITIONS = 64;
+
 // The acceptance test of sequence b by one wave: lane = position, 64 positions per pass.  Lanes j <= draft_len merge the
 // statistics of target row j; lanes j < draft_len run the acceptance test; a ballot finds the first rejection.
-// `all`: also the positions behind the first 64, with their accept probabilities written.
-template <typename DT>
-__device__ __forceinline__ Accepted accept_sequence(const VerifyArgs &a, int b, int lane, bool all)
+// PASSES: drafts of any length; goes on behind the pass of the first rejection only if the accept probabilities are wanted, and
+// writes them.  Otherwise (k <= LANE_POSITIONS) nothing is written.
+template <typename DT, bool PASSES>
+__device__ __forceinline__ Accepted accept_sequence(const VerifyArgs &a, int b, int lane)
 {
     // One wave, a chain of trips to memory: the draft length, then tokens / uniforms / logsumexps / slice
     // statistics, then the two gathered logits.  The first pass's loads that need no draft length (everything
@@ -139,14 +143,14 @@ __device__ __forceinline__ Accepted accept_sequence(const VerifyArgs &a, int b, 
     res.Lp = res.Lq = 0.0;
     res.prob = 0.f;
     res.flags = graw != g ? (unsigned)SVIP_FLAG_BAD_DRAFT_LEN : 0u;
-    for (int j0 = 0; j0 <= g && (res.r < 0 || all); j0 += 64) {
+    for (int j0 = 0; j0 <= g && (res.r < 0 || (PASSES && a.accept_prob)); j0 += 64) {
         const int j = j0 + lane;
         bool reject = false;
         double Lp = 0.0, Lq = 0.0;
         if (j <= g) {
             int x = x0;
             double u = (double)u0, lse_q = lse0;
-            if (j0 > 0 && j < g) {
+            if (PASSES && j0 > 0 && j < g) {
                 x = a.tokens[(size_t)b * a.k + j];
                 u = (double)a.u_accept[(size_t)b * a.k + j];
                 if (a.draft_lse) lse_q = a.draft_lse[(size_t)b * a.k + j];
@@ -178,8 +182,8 @@ __device__ __forceinline__ Accepted accept_sequence(const VerifyArgs &a, int b, 
                 reject = !(u * q < p);
                 const double ratio = q > 0.0 ? p / q : (p > 0.0 ? 1.0 : 0.0);
                 const float prob = (float)(ratio < 1.0 ? ratio : 1.0);
-                if (j0 == 0) res.prob = prob;
-                else if (all && a.accept_prob) a.accept_prob[(size_t)b * a.k + j] = prob;
+                if (!PASSES) res.prob = prob;
+                else if (a.accept_prob) a.accept_prob[(size_t)b * a.k + j] = prob;
             }
         }
         if (res.r < 0) {
@@ -200,15 +204,23 @@ __device__ __forceinline__ Accepted accept_sequence(const VerifyArgs &a, int b, 
     return res;
 }
 
-// What the call reports of a sequence, by one wave.
+// grid (sequences), one wave: the acceptance test in a launch of its own (see accept_in_resid in svip_kernels.hip).
 template <typename DT>
-__device__ __forceinline__ void report_sequence(const VerifyArgs &a, int b, int lane, const Accepted &res)
+__global__ __launch_bounds__(64) void k_accept(VerifyArgs a)
 {
-    unsigned flags = res.flags;
-    if (a.accept_prob && res.prob >= 0.f && lane < a.k) a.accept_prob[(size_t)b * a.k + lane] = res.prob;
-    if (a.k > 64) flags |= accept_sequence<DT>(a, b, lane, true).flags;
-    if (flags) atomicOr(a.ws.flags, flags);
-    if (lane == 0) a.n_accepted[b] = res.r;
+    const int b = blockIdx.x, lane = threadIdx.x;
+    if (a.skip && a.skip[b]) return;
+    const Accepted acc = accept_sequence<DT, true>(a, b, lane);
+    if (acc.flags) atomicOr(a.ws.flags, acc.flags);
+    if (lane == 0) {
+        SeqRec rec;
+        rec.Lp = acc.Lp;
+        rec.Lq = acc.Lq;
+        rec.r = acc.r;
+        rec.resid = acc.resid ? 1 : 0;
+        a.ws.rec[b] = rec;
+        a.n_accepted[b] = acc.r;
+    }
 }
 
 // ---- verify: residual / bonus sampling ------------------------------------------------------
@@ -281,18 +293,18 @@ __device__ __forceinline__ void draw_from_target(const DT *prow, const Geo &geo,
     search_chunks<N, 1>(w, at, (double)u * total - before, report);
 }
 
-// grid (sequences * slices): the acceptance test and the residual / bonus draw in one launch.  One wave of every workgroup works out
-// the first rejection from the statistics of the sequence's rows (a few kilobytes), then the workgroup sums the
-// weights of its slice by half tiles -- residual max(0, p - q) of the rejected position, or target p of the bonus row --
-// and publishes them; the workgroup that draws the sequence's final ticket reports the acceptance test (every other one has
-// read the sequence's inputs by then, so outputs may lie on inputs), picks the half tile that holds u * total, and
-// one wave finds the token there by the inverse CDF.  What bounds it is the chain of trips to memory (statistics, two rows,
-// publish, ticket, masses, half tile).  us per call with the test in a launch of its own (one wave per sequence) and the
-// search in a workgroup / so: 64 sequences of 16 positions and 128256 bf16 logits 61.0 / 58.9 (this kernel alone 13.3 + 4.7
-// / 14.6), 8 of 64 and 151936 28.7 / 27.3, 32 of 8 and 50257 fp16 26.5 / 24.6.  With every wave testing for itself instead of
-// one for its workgroup: 60.5, 27.3, 25.8 -- the loads of the statistics are many and small.  TILES: slices have at most TILE_MASSES tiles; otherwise the search
-// walks the chosen slice.
-template <typename DT, bool TILES>
+// grid (sequences * slices): the residual / bonus draw, and (TEST; k <= LANE_POSITIONS) the acceptance test before it.  One wave of
+// every workgroup works out the first rejection from the statistics of the sequence's rows (a few kilobytes), or reads what
+// k_accept has left; then the workgroup sums the weights of its slice by half tiles -- residual max(0, p - q) of the rejected
+// position, or target p of the bonus row -- and publishes them; the workgroup that draws the sequence's final ticket picks the
+// half tile that holds u * total, and one wave finds the token there by the inverse CDF and reports the test.  All workgroups
+// of the sequence have read its inputs by then, so a sequence's outputs may lie on its own inputs (not on another sequence's).
+// What bounds it is the chain of trips to memory (statistics, two rows, publish, ticket, masses, half tile).  us per call with
+// the test in a launch of its own (one wave per sequence) and the search in a workgroup / so: 64 sequences of 16 positions and
+// 128256 bf16 logits 61.0 / 58.9 (this kernel alone 13.3 + 4.7 / 14.6), 8 of 64 and 151936 28.7 / 27.3, 32 of 8 and 50257 fp16
+// 26.5 / 24.6.  With every wave testing for itself instead of one for its workgroup: 60.5, 27.3, 25.8 -- the loads of the
+// statistics are many and small.  TILES: slices have at most TILE_MASSES tiles; otherwise the search walks the chosen slice.
+template <typename DT, bool TILES, bool TEST>
 __global__ __launch_bounds__(WG, 4) void k_resid(VerifyArgs a)
 {
     constexpr int N = VecOf<DT>::N;
@@ -306,16 +318,24 @@ __global__ __launch_bounds__(WG, 4) void k_resid(VerifyArgs a)
     if (b >= a.B) return;
     if (a.skip && a.skip[b]) return;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-    __shared__ Accepted shared_acc;
     Accepted acc;
-    if (wave == 0) {
-        acc = accept_sequence<DT>(a, b, lane, false);
-        if (lane == 0) shared_acc = acc;
+    if constexpr (TEST) {
+        __shared__ Accepted shared_acc;
+        if (wave == 0) {
+            acc = accept_sequence<DT, false>(a, b, lane);
+            if (lane == 0) shared_acc = acc;
+        }
+        __syncthreads();
+        if (wave != 0) acc = shared_acc;
+        acc.r = __builtin_amdgcn_readfirstlane(acc.r);
+        acc.resid = __builtin_amdgcn_readfirstlane(acc.resid);
+    } else {
+        const SeqRec rec = a.ws.rec[b];
+        acc.Lp = rec.Lp;
+        acc.Lq = rec.Lq;
+        acc.r = rec.r;
+        acc.resid = rec.resid != 0;
     }
-    __syncthreads();
-    if (wave != 0) acc = shared_acc;
-    acc.r = __builtin_amdgcn_readfirstlane(acc.r);
-    acc.resid = __builtin_amdgcn_readfirstlane(acc.resid);
     const DT *prow = static_cast<const DT *>(a.target) + row_offset(a, a.seq_t, b, acc.r);
     const DT *qrow = static_cast<const DT *>(a.draft) + row_offset(a, a.seq_d, b, acc.r);
     const ExpRef ep = make_exp_ref(a.sc, acc.Lp), eq = make_exp_ref(a.sc, acc.Lq);
@@ -374,7 +394,11 @@ __global__ __launch_bounds__(WG, 4) void k_resid(VerifyArgs a)
                 search_chunks<N, 2>(w, chunk, in_half, store);
             }
         }
-        report_sequence<DT>(a, b, lane, acc);
+        if constexpr (TEST) {
+            if (acc.flags) atomicOr(a.ws.flags, acc.flags);
+            if (a.accept_prob && acc.prob >= 0.f) a.accept_prob[(size_t)b * a.k + lane] = acc.prob;
+            if (lane == 0) a.n_accepted[b] = acc.r;
+        }
     }
     if constexpr (!TILES) {
         __shared__ LocateLds loc;

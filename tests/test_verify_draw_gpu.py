@@ -112,3 +112,48 @@ def test_rejection_without_residual_mass_draws_from_the_target(svip, V, dtype):
         c = np.concatenate([[0.0], np.cumsum(p)])
         t, u = int(nxt[b]), float(ur[b])
         assert p[t] > 0 and c[t] - 2e-6 <= u * c[-1] <= c[t + 1] + 2e-6, (b, t, u)
+
+
+@pytest.mark.parametrize("k", [64, 70, 130])
+@pytest.mark.parametrize("mass", [True, False])
+def test_next_token_on_the_draft_lengths(svip, k, mass):
+    """next_token_out may be draft_len, whether a draft has one pass of positions or several, and whether a rejection leaves
+    residual mass or not (see test_rejection_without_residual_mass_draws_from_the_target)."""
+    B, V = 9, 4104
+    print(f"verify draw next token on draft_len k={k} mass={mass}", flush=True)
+    draft, target, _, ua, ur = (x.cuda() for x in _case(B, k, V, torch.bfloat16, k, noise=0.05))
+    if not mass:
+        draft = target[:, :k].clone()
+        ua[:] = 0.2
+        ua[:, k // 2] = 0.9
+    lse = torch.logsumexp(draft.double(), -1) - (0.0 if mass else 1.0)
+    tokens = draft.argmax(-1).int()
+    dlen = torch.tensor([k, k - 1, k // 2 + 1, 0, min(k, 64), 1, min(k, 65), k, k], dtype=torch.int32, device="cuda")
+
+    def out():
+        return torch.full((B,), -5, dtype=torch.int32, device="cuda"), torch.full((B, k), -5.0, device="cuda")
+    (n0, p0), (n1, p1) = out(), out()
+    t0, d1 = n0.clone(), dlen.clone()
+    _verify(svip, draft, target, tokens, dlen, lse, ua, ur, n0, t0, p0)
+    _verify(svip, draft, target, tokens, d1, lse, ua, ur, n1, d1, p1)         # checks the flags too
+    assert torch.equal(n0, n1) and torch.equal(t0, d1) and torch.equal(p0, p1)
+
+
+@pytest.mark.parametrize("k,at", [(64, 50), (70, 66), (200, 130), (200, 40)])
+def test_flags_of_tokens_behind_the_first_rejection(svip, k, at):
+    """A bad token is recorded if its position was tested: in the 64 positions of the first rejection, and behind them only
+    where the accept probabilities are asked for."""
+    B, V = 3, 1000
+    draft, target, _, ua, ur = (x.cuda() for x in _case(B, k, V, torch.float32, k))
+    tokens = draft.argmax(-1).int()
+    ws = svip.new_workspace(B, k, V)
+    target[:, 3] = target[:, 3].scatter(1, tokens[:, 3:4].long(), -float("inf"))         # position 3 at the latest is rejected
+    tokens[1, at] = V + 7
+    dlen = torch.full((B,), k, dtype=torch.int32, device="cuda")
+    nacc, nxt = torch.empty(B, dtype=torch.int32, device="cuda"), torch.empty(B, dtype=torch.int32, device="cuda")
+    for prob in (None, torch.empty(B, k, device="cuda")):
+        svip.verify(target, draft, temperature=1.0, draft_tokens=tokens, draft_len=dlen, draft_lse=torch.logsumexp(draft.double(), -1),
+                    u_accept=ua, u_resample=ur, n_accepted_out=nacc, next_token_out=nxt, accept_prob_out=prob, workspace=ws)
+        assert (nacc <= 3).all()
+        seen = at < 64 or prob is not None
+        assert svip.workspace_flags(ws) == (svip.FLAG_BAD_TOKEN if seen else 0), prob is not None
