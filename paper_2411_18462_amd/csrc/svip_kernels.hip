@@ -517,9 +517,24 @@ static svip_status verify_greedy_call(const VerifyCall &c)
 }
 
 // Whether the acceptance test runs inside the residual pass, where every workgroup of a sequence repeats it, or in a launch of its
-// own.  Drafts longer than one pass of a wave have theirs: the passes are a serial chain, those behind the first rejection
-// are needed only once, and what they read may lie under next_token_out.
-static bool accept_in_resid(int k_max) { return k_max <= LANE_POSITIONS; }
+// own.
+//   - Drafts of more positions than a wave has lanes have their own launch: the passes are a serial chain, those behind the first
+//     rejection are needed only once, and what they read may lie under next_token_out.
+//   - About 1500 workgroups of the residual pass are resident at a time (1280 of the form for slices of more than TILE_MASSES
+//     tiles); those behind them wait for the test's chain of loads once more.  us per call, in the pass / own launch:
+//       workgroups   128256 bf16, 4 positions   32000 fp32, 4      50257 fp16, 4      8000 fp16, 1
+//         ~1000       44.7 / 46.7 (16 positions)    27.5 / 29.0        30.7 / 32.0        26.4 / 28.3
+//         ~1536       35.9 / 38.8                   34.9 / 36.3        40.1 / 39.7
+//         ~2048       45.0 / 45.5                   42.6 / 42.6        46.1 / 45.2        40.0 / 41.6
+//         ~3072       59.3 / 58.7                   57.2 / 56.5        54.9 / 54.0        52.2 / 52.6
+//         ~4096       72.9 / 71.5                   69.0 / 67.4        66.5 / 64.1
+//         ~8192      128.6 / 126.4
+//       longer slices: 1024: 28672 bf16 49.0 / 51.2, 14336 fp32 43.6 / 45.4; 1280: 59.2 / 58.1, 50.6 / 52.6; 1536: 32000 bf16
+//       54.7 / 54.0; 4608: 128256 bf16 144.6 / 135.2.
+static bool accept_in_resid(int k_max, int tiles_per_slice, unsigned workgroups)
+{
+    return k_max <= LANE_POSITIONS && workgroups <= (tiles_per_slice <= TILE_MASSES ? 2048u : 1024u);
+}
 
 svip_status verify_call(const VerifyCall &c)
 {
@@ -572,7 +587,7 @@ svip_status verify_call(const VerifyCall &c)
     unsigned g_stats = (unsigned)a.stat_items;
     if (g_tune.stats_workgroups > 0 && (unsigned)g_tune.stats_workgroups < g_stats) g_stats = (unsigned)g_tune.stats_workgroups;
     const unsigned g_resid = (unsigned)a.geo_s.ns * (((unsigned)c.B + 7u) / 8u) * 8u;   // sequences by XCD, see k_resid
-    const bool test = accept_in_resid(c.k_max);
+    const bool test = accept_in_resid(c.k_max, a.geo_s.tps, g_resid);
     bool ok = false;
     by_dtype(c.dtype, [&](auto tag) {
         using DT = decltype(tag);

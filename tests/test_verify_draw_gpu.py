@@ -157,3 +157,21 @@ def test_flags_of_tokens_behind_the_first_rejection(svip, k, at):
         assert (nacc <= 3).all()
         seen = at < 64 or prob is not None
         assert svip.workspace_flags(ws) == (svip.FLAG_BAD_TOKEN if seen else 0), prob is not None
+
+
+@pytest.mark.parametrize("B,more,V,dtype", [(2048, 2056, 8000, torch.float16), (512, 520, 28672, torch.bfloat16)])
+def test_acceptance_in_the_draws_launch_and_in_its_own(svip, B, more, V, dtype):
+    """`B` sequences are the most whose acceptance test runs inside the residual pass (2048 workgroups of whole tiles, 1024 of longer
+    slices): with a few more it has a launch of its own, and the same sequences get the same results."""
+    k = 1
+    print(f"verify draw in its own launch B={more} V={V} {dtype}", flush=True)
+    draft, target, _, ua, ur = (x.cuda() for x in _case(more, k, V, dtype, V))
+    lse, tokens = torch.logsumexp(draft.double(), -1), draft.argmax(-1).int()
+    dlen = (torch.arange(more, device="cuda") % 2).int()
+    full = [torch.full(s, -5, dtype=t, device="cuda") for s, t in (((more,), torch.int32), ((more,), torch.int32), ((more, k), torch.float32))]
+    part = [x[:B].clone() for x in full]
+    _verify(svip, draft, target, tokens, dlen, lse, ua, ur, *full)
+    _verify(svip, draft[:B], target[:B], tokens[:B], dlen[:B], lse[:B], ua[:B], ur[:B], *part)
+    for x, y in zip(full, part):
+        assert torch.equal(x[:B], y)
+    assert (full[0] >= 0).all() and (full[1] >= 0).all() and (full[0] == 0).any() and (full[0] == 1).any()
