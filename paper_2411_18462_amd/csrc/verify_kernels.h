@@ -1,5 +1,7 @@
 // Kernels of svip_verify (Algorithm 2 Verify, Algorithm 4 Correct, the bonus sample of Algorithm 1).
 #pragma once
+#include <type_traits>
+
 #include "exchange.h"
 #include "kernel_args.h"
 #include "sample_weights.h"
@@ -260,38 +262,76 @@ __device__ __forceinline__ void chunk_weights(const DT *prow, const DT *qrow, in
     }
 }
 
-// No residual mass (p <= q everywhere, up to rounding): the token is drawn from p instead, by one wave that walks the row.
-// It takes a rejection where p and q agree to the last bits, so what this costs hardly matters.
+// Sum of the target weights p of chunks [chunk, chunk + NU) of a row, per lane.
+template <typename DT, int NU>
+__device__ __forceinline__ double target_mass(const DT *prow, int V, int chunk, const ExpRef &ep)
+{
+    constexpr int N = VecOf<DT>::N;
+    double mass = 0.0;
+    const auto add = [&](const typename RawOf<DT>::type &raw) {
+        float w[N];
+        unpack<DT>(raw, w);
+#pragma unroll
+        for (int e = 0; e < N; ++e) w[e] = ep(w[e]);
+        mass += (double)tree_sum<N>(w);
+        if constexpr (N == 8) asm volatile("" : "+v"(mass));        // one vector after the other, behind all of the loads
+    };
+    if ((chunk + NU) * 64 <= V / N) {
+        typename RawOf<DT>::type raw[NU];
+        wave_load<DT, NU, false>(prow, V, chunk, raw);         // all in flight together
+#pragma unroll
+        for (int u = 0; u < NU; ++u) add(raw[u]);
+    } else {
+#pragma unroll 1
+        for (int u = 0; u < NU && (long long)(chunk + u) * 64 * N < V; ++u) {
+            typename RawOf<DT>::type one[1];
+            wave_load<DT, 1, true>(prow, V, chunk + u, one);
+            add(one[0]);
+        }
+    }
+    return mass;
+}
+
+// No residual mass (p <= q everywhere, up to rounding): the token is drawn from p instead, by one wave that walks the row in
+// groups of chunks -- once for the masses, of which lane l keeps that of its share of the row, then through the share that holds
+// the crossing.  It takes a rejection where p and q agree to the last bits, or draft logsumexps that are not the rows', so
+// it may not cost the usual call anything: target masses summed beside the residual's, as a second number per slice, take
+// 0.3 to 0.8 us of every call of 20 to 60.  us per call, 8 sequences of 151936 bf16 logits, one chunk / four / eight in flight:
+// 244 / 78 / 66 (with mass 20); 8 of 32000 fp32 98 / 34 / 30; 64 of 128256 fp16, one / eight 358 / 87 (with mass 36).
 template <typename DT, typename Report>
 __device__ __forceinline__ void draw_from_target(const DT *prow, const Geo &geo, const ExpRef &ep, float u, Report report)
 {
-    constexpr int N = VecOf<DT>::N;
-    const int nchunks = geo.ntiles * (WG / 64);
-    float w[1][N];
-    double total = 0.0, before = 0.0;
-    int at = 0;
+    constexpr int N = VecOf<DT>::N, GROUP = 8;
+    const int lane = threadIdx.x & 63;
+    const int groups = (geo.ntiles * (WG / 64) + GROUP - 1) / GROUP, share = (groups + 63) / 64;
+    double mine = 0.0;
 #pragma unroll 1
-    for (int pass = 0; pass < 2; ++pass) {
-        // first the total, then the chunk that holds the crossing (else the last one with mass)
-        const double target = (double)u * total;
-        double run = 0.0;
-        bool crossed = false;
-#pragma unroll 1
-        for (int c = 0; c < nchunks && !crossed; ++c) {
-            chunk_weights<DT, 1, false>(prow, prow, geo.V, c, ep, ep, w);
-            const double mass = wave_sum((double)tree_sum<N>(w[0]));
-            if (pass == 1 && mass > 0.0) {
-                at = c;
-                before = run;
-                crossed = run + mass > target;
-            }
-            run += mass;
-        }
-        if (pass == 0) total = run;
+    for (int g = 0; g < groups; ++g) {
+        const double mass = wave_sum(target_mass<DT, GROUP>(prow, geo.V, g * GROUP, ep));
+        if (g / share == lane) mine += mass;
     }
+    const double incl = wave_inclusive_sum(mine), total = read_lane(incl, 63);
+    double target, before = 0.0, run = 0.0;
+    const int first = pick_slice(mine, (double)u * total, incl, &target) * share * GROUP;
+    int at = first;                              // the chunk that holds the crossing, else the last one with mass
+#pragma unroll 1
+    for (int c = first; c < first + share * GROUP && !(run > target); ++c) {
+        const double mass = wave_sum(target_mass<DT, 1>(prow, geo.V, c, ep));
+        if (mass > 0.0) {
+            at = c;
+            before = run;
+        }
+        run += mass;
+    }
+    float w[1][N];
     chunk_weights<DT, 1, false>(prow, prow, geo.V, at, ep, ep, w);
-    search_chunks<N, 1>(w, at, (double)u * total - before, report);
+    search_chunks<N, 1>(w, at, target - before, report);
 }
+
+// Waves per SIMD the residual pass is compiled for: 6 where its registers allow (draw_from_target would otherwise take the
+// common path's sixth wave with it); the bf16 draw without the test, and the forms for longer slices, need more than 80.
+template <typename DT>
+constexpr int resid_waves(bool tiles, bool test) { return tiles && (test || !std::is_same<DT, bf16>::value) ? 6 : 4; }
 
 // grid (sequences * slices): the residual / bonus draw, and (TEST; k <= LANE_POSITIONS) the acceptance test before it.  One wave of
 // every workgroup works out the first rejection from the statistics of the sequence's rows (a few kilobytes), or reads what
@@ -305,7 +345,7 @@ __device__ __forceinline__ void draw_from_target(const DT *prow, const Geo &geo,
 // 26.5 / 24.6.  With every wave testing for itself instead of one for its workgroup: 60.5, 27.3, 25.8 -- the loads of the
 // statistics are many and small.  TILES: slices have at most TILE_MASSES tiles; otherwise the search walks the chosen slice.
 template <typename DT, bool TILES, bool TEST>
-__global__ __launch_bounds__(WG, 4) void k_resid(VerifyArgs a)
+__global__ __launch_bounds__(WG, resid_waves<DT>(TILES, TEST)) void k_resid(VerifyArgs a)
 {
     constexpr int N = VecOf<DT>::N;
     __shared__ double sums[NWAVE][TILE_MASSES];

@@ -86,7 +86,7 @@ def test_outputs_on_inputs_and_slices_of_any_length(svip, B, k, V, dtype):
         assert (t2 != t0).sum() <= 1 + B // 16, ns
 
 
-@pytest.mark.parametrize("V,dtype", [(40, torch.float32), (5001, torch.bfloat16), (32000, torch.float16)])
+@pytest.mark.parametrize("V,dtype", [(40, torch.float32), (5001, torch.bfloat16), (32000, torch.float16), (32005, torch.float32), (530001, torch.bfloat16)])
 def test_rejection_without_residual_mass_draws_from_the_target(svip, V, dtype):
     """Logsumexps 1 too small make q = e p everywhere: a token is rejected with u >= 1 / e, and nothing of p is above q."""
     print(f"verify draw without mass V={V} {dtype}", flush=True)
