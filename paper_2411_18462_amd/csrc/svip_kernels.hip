@@ -520,20 +520,23 @@ static svip_status verify_greedy_call(const VerifyCall &c)
 // own.
 //   - Drafts of more positions than a wave has lanes have their own launch: the passes are a serial chain, those behind the first
 //     rejection are needed only once, and what they read may lie under next_token_out.
-//   - About 1500 workgroups of the residual pass are resident at a time (1280 of the form for slices of more than TILE_MASSES
-//     tiles); those behind them wait for the test's chain of loads once more.  us per call, in the pass / own launch:
-//       workgroups   128256 bf16, 4 positions   32000 fp32, 4      50257 fp16, 4      8000 fp16, 1
-//         ~1000       44.7 / 46.7 (16 positions)    27.5 / 29.0        30.7 / 32.0        26.4 / 28.3
-//         ~1536       35.9 / 38.8                   34.9 / 36.3        40.1 / 39.7
-//         ~2048       45.0 / 45.5                   42.6 / 42.6        46.1 / 45.2        40.0 / 41.6
-//         ~3072       59.3 / 58.7                   57.2 / 56.5        54.9 / 54.0        52.2 / 52.6
-//         ~4096       72.9 / 71.5                   69.0 / 67.4        66.5 / 64.1
-//         ~8192      128.6 / 126.4
-//       longer slices: 1024: 28672 bf16 49.0 / 51.2, 14336 fp32 43.6 / 45.4; 1280: 59.2 / 58.1, 50.6 / 52.6; 1536: 32000 bf16
-//       54.7 / 54.0; 4608: 128256 bf16 144.6 / 135.2.
-static bool accept_in_resid(int k_max, int tiles_per_slice, unsigned workgroups)
+//   - 1536 workgroups of the residual pass are resident at a time (1280 and fewer of the form for slices of more than TILE_MASSES
+//     tiles); those behind them wait for the test's chain of loads once more, and the more slices a sequence has the more often
+//     the test is repeated.  us per call of 4 positions, in the pass / own launch:
+//       workgroups   128256 bf16, 16 slices   50257 fp16, 7   32000 fp32, 8   32000 bf16, 4   8000 bf16, 1
+//         1024           29.8 / 31.1                                           31.6 / 32.9     31.6 / 33.9
+//         1536           36.0 / 37.9           36.5 / 38.6     34.6 / 36.2     38.3 / 41.8     39.8 / 44.3
+//        ~1670           39.7 / 39.8           39.6 / 39.2     38.1 / 37.9     42.9 / 43.4
+//        ~2048           44.8 / 44.6           45.4 / 44.7     42.2 / 42.4     48.7 / 48.9     50.8 / 52.3
+//         2560           51.2 / 50.1                           49.4 / 49.5                     59.8 / 61.0
+//         4096           73.7 / 70.3                                                           86.9 / 87.5
+//       (with draft logsumexps recomputed the second number is 1 to 4 % better from 1670 on: 16 slices, 2048: 58.7 / 57.3).
+//       Longer slices, 1024 workgroups: 28672 bf16 48.8 / 50.6, 14336 fp32 43.2 / 45.2; 1280: 59.1 / 57.9, 49.9 / 51.8;
+//       1536: 67.1 / 65.5, 58.9 / 58.6; 4608: 128256 bf16 144.6 / 135.2.
+static bool accept_in_resid(int k_max, const Geo &slices, unsigned workgroups)
 {
-    return k_max <= LANE_POSITIONS && workgroups <= (tiles_per_slice <= TILE_MASSES ? 2048u : 1024u);
+    const unsigned most = slices.tps > TILE_MASSES ? 1024u : (slices.ns > 4 ? 1536u : 2560u);
+    return k_max <= LANE_POSITIONS && workgroups <= most;
 }
 
 svip_status verify_call(const VerifyCall &c)
@@ -587,7 +590,7 @@ svip_status verify_call(const VerifyCall &c)
     unsigned g_stats = (unsigned)a.stat_items;
     if (g_tune.stats_workgroups > 0 && (unsigned)g_tune.stats_workgroups < g_stats) g_stats = (unsigned)g_tune.stats_workgroups;
     const unsigned g_resid = (unsigned)a.geo_s.ns * (((unsigned)c.B + 7u) / 8u) * 8u;   // sequences by XCD, see k_resid
-    const bool test = accept_in_resid(c.k_max, a.geo_s.tps, g_resid);
+    const bool test = accept_in_resid(c.k_max, a.geo_s, g_resid);
     bool ok = false;
     by_dtype(c.dtype, [&](auto tag) {
         using DT = decltype(tag);

@@ -159,10 +159,11 @@ def test_flags_of_tokens_behind_the_first_rejection(svip, k, at):
         assert svip.workspace_flags(ws) == (svip.FLAG_BAD_TOKEN if seen else 0), prob is not None
 
 
-@pytest.mark.parametrize("B,more,V,dtype", [(2048, 2056, 8000, torch.float16), (512, 520, 28672, torch.bfloat16)])
+@pytest.mark.parametrize("B,more,V,dtype", [(2560, 2568, 8000, torch.float16), (304, 312, 40000, torch.bfloat16), (512, 520, 28672, torch.bfloat16)])
 def test_acceptance_in_the_draws_launch_and_in_its_own(svip, B, more, V, dtype):
-    """`B` sequences are the most whose acceptance test runs inside the residual pass (2048 workgroups of whole tiles, 1024 of longer
-    slices): with a few more it has a launch of its own, and the same sequences get the same results."""
+    """`B` sequences are the most whose acceptance test runs inside the residual pass (2560 workgroups of up to four slices a
+    sequence, 1536 of more, 1024 of slices longer than four tiles): with eight more it has a launch of its own, and the same
+    sequences get the same results."""
     k = 1
     print(f"verify draw in its own launch B={more} V={V} {dtype}", flush=True)
     draft, target, _, ua, ur = (x.cuda() for x in _case(more, k, V, dtype, V))
