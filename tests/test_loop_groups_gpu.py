@@ -3,9 +3,12 @@ where a position alone fills the chip, and where an override asks for records of
 same bit for bit.  64 records per row, the override used here, is what the rows of these shapes have anyway, so both sides
 sum the same partial results."""
 import math
+from types import SimpleNamespace
 
 import pytest
 import torch
+
+from test_loop_gpu import _check
 
 pytestmark = pytest.mark.gpu
 
@@ -121,3 +124,59 @@ def test_workspace_for_single_positions(svip, greedy):
     assert torch.equal(a.state, b.state) and torch.equal(a.out_tokens, b.out_tokens)
     assert torch.equal(a.round_log[:ran], b.round_log[:ran])       # a round launched ahead may have filled its entries behind
     assert (b.workspace[least:] == 0xA5).all()
+
+
+def _rows_with_ties(B, L, V, dtype, seed):
+    """Traces whose maxima lie in every part of a row: ties in the first, a middle and the last tile, in two of the last tiles, a
+    single one in the row's last logit; heavy-tailed rows in between."""
+    draft, target = _trace(B, L, V, dtype, seed, False)
+    tile = 256 * (16 // draft.element_size())
+    for t, at in ((draft, 0), (target, 1)):
+        top = t.amax(-1, keepdim=True)
+        for j0, cols in ((1, [5, V // 2, V - 1]), (2, [V - 1 - 2 * tile, V - 1 - tile, V - 1]), (3, [V - 1])):
+            rows = slice((j0 + at) % 5, None, 5)
+            t[:, rows, cols] = top[:, rows] + (0.5 if dtype != torch.float16 else 1.0)
+    return draft, target
+
+
+@pytest.mark.parametrize("greedy", [True, False])
+@pytest.mark.parametrize("B,V,dtype", [
+    (9, 151936, torch.bfloat16),         # 75 tiles: two records per lane of the finish
+    (2, 65537, torch.float32),           # 65 tiles, the last with one logit: the second record of lane 32 is the last
+    (3, 151936, torch.float32),          # 149 tiles: three records per lane
+    (1, 262145, torch.float16),          # 129 tiles, one logit in the last
+    (2, 196608, torch.float32),          # 192 tiles, the most that are taken in groups
+])
+def test_rows_of_several_records_per_lane(svip, B, V, dtype, greedy):
+    """Round by round against the oracle; up to 128 tiles also bit for bit against the loop that takes positions one by one (beyond,
+    svip_draft_step keeps one sum for several tiles, and the two agree to rounding)."""
+    print(f"loop records B={B} V={V} {dtype} greedy={greedy}", flush=True)
+    k, max_new = 6, 10
+    draft, target = _rows_with_ties(B, max_new + k + 1, V, dtype, V + B)
+    g = torch.Generator(device="cuda").manual_seed(B)
+    u = dict(u_sample=torch.rand(max_new, B, k, device="cuda", generator=g), u_accept=torch.rand(max_new, B, k, device="cuda", generator=g),
+             u_resample=torch.rand(max_new, B, device="cuda", generator=g))
+    h = 1.5
+    results = []
+    for small in (False, True):
+        loop = svip.Loop(target, draft, temperature=1.0, h=h, gamma0=k, gamma_max=k, max_new=max_new, rounds=max_new, greedy=greedy,
+                         **({} if greedy else u))
+        if small:
+            up = lambda n: (n + 255) // 256 * 256
+            loop.config.workspace_bytes = up(svip.workspace_bytes(B, k, V)) + up(4 * B * k) + up(8 * B * k) + 2 * up(B) + 6 * up(4 * B) + 256
+        ran, running = loop.run()
+        assert running == 0 and loop.flags() == 0 and ran == int(loop.state[:, 3].max())
+        results.append(dict(state=loop.state.cpu().numpy(), out=loop.out_tokens.cpu().numpy(), log=loop.round_log.cpu().numpy()[:ran], rounds=ran))
+    tiles = -(-V // (256 * (16 // draft.element_size())))
+    if tiles <= 128:
+        assert results[0]["rounds"] == results[1]["rounds"]
+        for key in ("state", "out", "log"):
+            assert (results[0][key] == results[1][key]).all(), key
+    rows = slice(0, 3)
+    trace = dict(draft=draft[rows].float().cpu(), target=target[rows].float().cpu(), u_sample=u["u_sample"][:, rows].cpu(),
+                 u_accept=u["u_accept"][:, rows].cpu(), u_resample=u["u_resample"][:, rows].cpu())
+    for res in results:
+        part = dict(state=res["state"][rows], out=res["out"][rows], log=res["log"][:, rows], rounds=res["rounds"])
+        st = _check(part, trace, SimpleNamespace(T=1.0), (h, k, k, 0, 0), max_new, greedy=greedy)
+        print("  ", st, flush=True)
+        assert st["rounds"] >= 2 * min(B, 3) and (not greedy or st["free_checked"] == min(B, 3))
