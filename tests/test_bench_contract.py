@@ -48,7 +48,11 @@ def test_bench_prints_one_json_line_with_the_required_objects():
     assert abs(r["frac"] - r["achieved"] / r["peak"]) < 1e-9 and 0.05 < r["frac"] < 1.0
     # the roofline object describes the kernel that holds the largest share of the step
     ks = d["kernels"]
-    assert set(ks) == {"k_draft_stats", "k_draft_finish", "k_verify_stats", "k_accept", "k_resid"}
+    # exactly the kernels the step launches, each with measured durations: the acceptance test of 64 sequences is part of k_resid
+    assert set(ks) == {"k_draft_stats", "k_draft_finish", "k_verify_stats", "k_resid"}
+    for name, x in ks.items():
+        assert x["launches_per_step"] == (16 if "draft" in name else 1), name
+        assert x["launches_timed"] == 4 * x["launches_per_step"] and 0 < x["p10_us"] <= x["p90_us"], name
     top = max(ks, key=lambda n: ks[n]["us_per_step"])
     assert r["kernel"].startswith(top) and r["bytes_per_launch"] == ks[top]["bytes_per_launch"]
     assert abs(sum(k["share_of_step_kernel_time"] for k in ks.values()) - 1.0) < 1e-9
