@@ -328,8 +328,10 @@ typedef struct svip_loop_config {
 } svip_loop_config;
 
 /* Bytes of device workspace for the loop (kernel workspace plus the buffers of one round).  A call that brings less, but
- * enough for a round that takes its draft positions one by one, is run that way (same results, more launches);
- * below that: SVIP_ERR_WORKSPACE. */
+ * enough for a round that takes its draft positions one by one, is run that way, with more launches; below that:
+ * SVIP_ERR_WORKSPACE.  The results are the same bit for bit for rows of up to 262144 16-bit or 131072 fp32 logits; the
+ * sums over longer rows are formed in another order, so a stop decision or a draw that lies within rounding of its threshold
+ * may fall on the other side. */
 size_t svip_loop_workspace_bytes(int B, int gamma_max, int V);
 
 /* Set every sequence to position n0 with limit gamma0 and clear the counters and flags (enqueued). */

@@ -4,13 +4,13 @@
 // Sampling, per round:
 //             drafting       -> the rows of a trace are all there, so one pair of launches covers a group of draft
 //                               positions of every sequence (draft_group_call); a sequence's draft ends at the
-//                               first position of the group that stops it.  Where a position alone fills the
-//                               chip, svip_draft_step's kernels run once per position.  Flags are chained on the device.
+//                               first position of the group that stops it.  In large batches (see below)
+//                               svip_draft_step's kernels run once per position.  Flags are chained on the device.
 //             verify         -> svip_verify kernels on trace rows pos[b] .. pos[b] + draft_len[b]
 //             k_round_end    -> appends the produced tokens, advances positions, applies the length
 //                               rule, updates the counters, counts the sequences still running and sets up the next round
 // Greedy:     every sequence goes through its own rounds, a few positions per pair of launches (greedy_stream_call);
-//             the rounds as above only where a position alone fills the chip.
+//             the rounds as above only in large batches.
 // k_round_begin sets up what the first launches of a call read.
 // The counts reach the host as messages: the counting kernel stores (ticket, count) as one 8-byte word
 // into pinned host memory and the host reads that word until the ticket shows.  No copy is enqueued and the
@@ -126,7 +126,8 @@ static inline size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
 //   Greedy: STREAM_WAVES draft records per launch, at least 2 positions; the target rows come on top.  8 sequences of 152K bf16
 //   logits, 48 tokens with drafts of 1.3 positions: 600 and 1200 waves (2 positions) 482 and 472 us, 2400 (4) 483, 4000 (6) 539;
 //   more positions help longer drafts.
-// Beyond GROUP_WAVES_FIRST waves per position (64 sequences of 152K logits are just below) a position fills the chip.
+// Beyond GROUP_WAVES_FIRST waves per position (64 sequences of 152K logits are just below) positions go one by one.  The line
+// stands behind the largest shape measured, where groups are still the faster form: it is not where the two meet.
 // us for 32 tokens per sequence, position by position / in groups (greedy; sampling), drafts of 1.3 | 20 positions:
 //    1 x 32000 fp32      1255 / 341; 958 / 613   | 2227 / 221; 1087 / 297
 //    8 x 151936 bf16     1301 / 326; 1479 / 887  | 2581 / 950; 2834 / 965
@@ -134,7 +135,7 @@ static inline size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
 //   64 x 151936 bf16     2211 / 654; 2570 / 1731 | 5386 / 3796; 5276 / 2941
 constexpr int GROUP_WAVES_FIRST = 4800, GROUP_WAVES_MAX = 32768, STREAM_WAVES = 2400;
 
-// Positions of the first group (0: positions go one by one, they fill the chip on their own) and of later ones.
+// Positions of the first group (0: positions go one by one) and of later ones.
 struct GroupPlan {
     int first, next;
 };

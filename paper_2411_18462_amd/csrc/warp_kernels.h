@@ -220,7 +220,7 @@ struct MassMeasure {
 // zero an addition there truncates the weight to whole units, one conversion and one addition per logit (8.4 cycles of
 // issue) instead of two conversions, a fract, two multiplications and a 64-bit integer addition (26).  The rounding mode
 // of doubles is the wave's, so nothing else in double precision may stand between begin() and end(); a double holds the
-// sum of 2^5 weights with room to spare, and total() then takes it over.
+// sum of 2^5 weights with room to spare, and take() then adds it to the total.
 struct MassSum {
     double zero;                   // 2^52 units
     unsigned long long units = 0ull;
@@ -445,8 +445,9 @@ __device__ __forceinline__ unsigned lds_add(unsigned *p, unsigned n)
 // loads and stores go past the caches, so that they keep the rows whose second sweep is still to come.  us, through the
 // caches / past them, top_p 0.9 on inputs not used just before | the same input again and again: 1088 rows of 128256 bf16
 // logits 211 / 195 | 211 / 178, 685 rows of 151936 158 / 140 | 156 / 126, 256 rows of 151936 fp32 (311 MB in all) 114 / 87 |
-// 94 / 84, but 300 rows of 151936 bf16 (182 MB) 96 / 86 | 73 / 85.  A single sweep gains nothing (top_k 50, 1088 rows
-// 165 / 167); a plain copy does (1088 rows 114 / 110).
+// 94 / 84, but 300 rows of 151936 bf16 (182 MB) 96 / 86 | 73 / 85: the line is drawn for inputs that are in the cache already.
+// A call that reads the output next finds none of it there: svip_verify behind 1088 rows takes 57 us instead of 47, and the two
+// together 280 / 254.  A single sweep gains nothing (top_k 50, 1088 rows 165 / 167); a plain copy does (1088 rows 114 / 110).
 template <typename DT, bool FUSED, bool MASS, int U>
 __device__ __forceinline__ unsigned long long candidate_sweep(const DT *row, DT *dst, int V, unsigned pivot, unsigned cap, const MassMeasure &mass,
                                                               float fix_scale, bool stream, WarpLds &L)

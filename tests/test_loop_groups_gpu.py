@@ -1,5 +1,5 @@
 """The decoding loop with several draft positions per launch against the loop that takes them one by one (which it still does
-where a position alone fills the chip, and where an override asks for records of another size): state, tokens and log are the
+in large batches, and where an override asks for records of another size): state, tokens and log are the
 same bit for bit.  64 records per row, the override used here, is what the rows of these shapes have anyway, so both sides
 sum the same partial results."""
 import math
