@@ -448,6 +448,9 @@ __device__ __forceinline__ unsigned lds_add(unsigned *p, unsigned n)
 // 94 / 84, but 300 rows of 151936 bf16 (182 MB) 96 / 86 | 73 / 85: the line is drawn for inputs that are in the cache already.
 // A call that reads the output next finds none of it there: svip_verify behind 1088 rows takes 57 us instead of 47, and the two
 // together 280 / 254.  A single sweep gains nothing (top_k 50, 1088 rows 165 / 167); a plain copy does (1088 rows 114 / 110).
+// Without masses there is little to do between the loads: two at a time, each with its own check, beat four without branches.
+// top_k 50, us, four / two: 1 row of 32000 fp32 logits 17.8 / 17.4, 1 of 50257 fp16 19.7 / 19.1, 512 of 32000 bf16 31.7 / 30.4, 1088 of 151936
+// bf16 179.7 / 176.2; but 16 of 151936 fp32 34.4 / 35.1.
 template <typename DT, bool FUSED, bool MASS, int U>
 __device__ __forceinline__ unsigned long long candidate_sweep(const DT *row, DT *dst, int V, unsigned pivot, unsigned cap, const MassMeasure &mass,
                                                               float fix_scale, bool stream, WarpLds &L)
@@ -461,7 +464,12 @@ __device__ __forceinline__ unsigned long long candidate_sweep(const DT *row, DT 
     for (int v0 = threadIdx.x; v0 < nvec; v0 += U * WARP_WG) {
         typename RawOf<DT>::type r[U];
         double acc = sum.zero;
-        warp_load_batch<DT, U>(row, v0, V, r, FUSED && MASS && stream);
+        if (MASS) {
+            warp_load_batch<DT, U>(row, v0, V, r, FUSED && stream);
+        } else {
+#pragma unroll
+            for (int u = 0; u < U; ++u) r[u] = warp_load<DT>(row, v0 + u * WARP_WG < nvec ? v0 + u * WARP_WG : v0, V);
+        }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int vi = v0 + u * WARP_WG;
@@ -543,7 +551,7 @@ __device__ __forceinline__ int small_k_shortcut(const DT *row, DT *dst, int V, c
     const unsigned pivot = select_digits(sample, 0u, CountMeasure{}, 0u, 0, (unsigned long long)want, L);
     if (tid == 0) L.n_list = 0u;
     __syncthreads();
-    candidate_sweep<DT, fused, false, 4>(row, dst, V, pivot, cap, MassMeasure{}, a.fix_scale, a.stream, L);
+    candidate_sweep<DT, fused, false, 2>(row, dst, V, pivot, cap, MassMeasure{}, a.fix_scale, a.stream, L);
     __syncthreads();
     const unsigned n = L.n_list;
     __syncthreads();
@@ -728,6 +736,24 @@ __device__ __forceinline__ int masked_copy(const DT *row, DT *dst, int V, unsign
     return bits / BITS;
 }
 
+// No filter: the row as it is.  us, as a masked copy that keeps everything / so: 1 row of 128256 bf16 logits 10.2 / 7.0, 512 of 32000 bf16
+// 17.9 / 15.2, 1088 of 128256 bf16 114 / 113, 512 of 151936 fp32 127 / 125, 512 of 32000 fp32 29.4 / 30.0.
+template <typename DT, int U = 4>
+__device__ __forceinline__ void plain_copy(const DT *row, DT *dst, int V, bool stream)
+{
+    constexpr int N = VecOf<DT>::N;
+    const int nvec = (V + N - 1) / N;
+    for (int v0 = threadIdx.x; v0 < nvec; v0 += U * WARP_WG) {
+        typename RawOf<DT>::type r[U];
+        warp_load_batch<DT, U>(row, v0, V, r, stream);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int vi = v0 + u * WARP_WG;
+            if (vi < nvec) store_words<DT>(dst, vi, V, __builtin_bit_cast(u32x4, r[u]), stream);
+        }
+    }
+}
+
 // The keys of first-digit bin d1 into L.list (the caller has checked that they fit).
 template <typename DT>
 __device__ __forceinline__ void collect(const RowSource<DT> &rs, unsigned d1, WarpLds &L)
@@ -758,6 +784,14 @@ __global__ __launch_bounds__(WARP_WG, 8) void k_warp(WarpArgs a)
     const int V = a.V;
 
     const bool K = !NUCLEUS && a.top_k > 0 && a.top_k < V, P = NUCLEUS || a.top_p < 1.0;
+    if (!K && !P) {
+        plain_copy<DT>(row, dst, V, a.stream);
+        if (tid == 0) {
+            if (a.routes) a.routes[y] = 0;
+            if (a.kept) a.kept[y] = V;
+        }
+        return;
+    }
     const RowSource<DT> rs{row, V};
     unsigned tau = 0u;                      // keep keys >= tau
     int kept = 0;
@@ -772,7 +806,7 @@ __global__ __launch_bounds__(WARP_WG, 8) void k_warp(WarpArgs a)
         decided = a.in != a.out ? nucleus_shortcut<DT, true>(row, dst, V, a, &tau, &kept, &m, L)
                                 : nucleus_shortcut<DT, false>(row, dst, V, a, &tau, &kept, &m, L);
     if (a.routes && tid == 0) a.routes[y] = decided;
-    if (decided == 0 && (K || P)) {
+    if (decided == 0) {
         // sweep 1: keys per first digit (top-k), row maximum (reference of the top-p weights)
         unsigned d_k = 0u;
         unsigned long long k_rem = 0ull;
