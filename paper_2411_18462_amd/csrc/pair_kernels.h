@@ -16,7 +16,24 @@ struct PairArgs {
     float *out;          // [B k][SVIP_PAIR_NSTAT]
 };
 
-// One thread per position (b, j < draft_len): logsumexps of its two rows from the slice statistics.
+// Logsumexps of position y's two rows from their slice statistics.  Both rows' slices travel together, CH at a time.
+template <int CH>
+__device__ __forceinline__ void pair_logsumexps(const PairArgs &a, long long y, int b, int j)
+{
+    RowStats<CH> target, draft;
+    double lse = 0.0;
+    target.request(a.v, b, a.v.kd + j);
+    if (a.v.draft_lse) lse = a.v.draft_lse[y];
+    else draft.request(a.v, b, j);
+    target.merge(a.v, b, a.v.kd + j);
+    a.L[2 * y] = target.L();
+    if (!a.v.draft_lse) draft.merge(a.v, b, j);
+    a.L[2 * y + 1] = a.v.draft_lse ? lse * 1.4426950408889634 : draft.L();
+}
+
+// One thread per position (b, j < draft_len): logsumexps of its two rows.  Four slices at a time (a call of 63 positions of 32000
+// fp32 logits 15.8 us, with eight at a time 16.2, one by one 16.1; 20 positions of 151936 22.7, 22.4, 25.8), but rows of one
+// slice have no more to request: 1 position of 18658 bf16 logits 14.7 / 14.1, with logsumexps recomputed 15.4 / 14.5.
 __global__ __launch_bounds__(64) void k_pair_L(PairArgs a)
 {
     const long long y = (long long)blockIdx.x * 64 + threadIdx.x;
@@ -26,17 +43,8 @@ __global__ __launch_bounds__(64) void k_pair_L(PairArgs a)
     const int g = clamp_len(graw, a.v.k);
     if (graw != g && j == 0) atomicOr(a.v.ws.flags, (unsigned)SVIP_FLAG_BAD_DRAFT_LEN);
     if (j >= g) return;
-    // Both rows' slices travel together, four at a time: small rows have few (a call of 63 positions of 32000 fp32 logits
-    // 15.8 us, with eight at a time 16.2, one by one 16.1; 20 positions of 151936 22.7, 22.4, 25.8).
-    RowStats<4> target, draft;
-    double lse = 0.0;
-    target.request(a.v, b, a.v.kd + j);
-    if (a.v.draft_lse) lse = a.v.draft_lse[y];
-    else draft.request(a.v, b, j);
-    target.merge(a.v, b, a.v.kd + j);
-    a.L[2 * y] = target.L();
-    if (!a.v.draft_lse) draft.merge(a.v, b, j);
-    a.L[2 * y + 1] = a.v.draft_lse ? lse * 1.4426950408889634 : draft.L();
+    if (a.v.geo.ns == 1) pair_logsumexps<1>(a, y, b, j);
+    else pair_logsumexps<4>(a, y, b, j);
 }
 
 // One batch of NU vector pairs per thread: with p = exp2(xp), q = exp2(xq) the normalised
@@ -122,6 +130,28 @@ __global__ __launch_bounds__(WG) void k_pair_sums(PairArgs a)
     }
 }
 
+// The three sums of position y over its slices, CH slices in flight at a time.
+template <int CH>
+__device__ __forceinline__ void add_slices(const PairArgs &a, long long y, double &beta, double &A, double &Bq)
+{
+    for (int s0 = 0; s0 < a.geo2.ns; s0 += CH) {
+        double x[CH][3];
+#pragma unroll
+        for (int u = 0; u < CH; ++u) {
+            const double *src = a.sums + ((size_t)y * a.geo2.ns + min(s0 + u, a.geo2.ns - 1)) * 3;
+#pragma unroll
+            for (int i = 0; i < 3; ++i) x[u][i] = src[i];
+        }
+#pragma unroll
+        for (int u = 0; u < CH; ++u) {
+            if (s0 + u >= a.geo2.ns) continue;
+            beta += x[u][0];
+            A += x[u][1];
+            Bq += x[u][2];
+        }
+    }
+}
+
 // One thread per position: slice sums added in slice order, then the bounds.
 __global__ __launch_bounds__(64) void k_pair_finish(PairArgs a)
 {
@@ -135,22 +165,8 @@ __global__ __launch_bounds__(64) void k_pair_finish(PairArgs a)
         return;
     }
     double beta = 0.0, A = 0.0, Bq = 0.0;
-    for (int s0 = 0; s0 < a.geo2.ns; s0 += 8) {            // eight slices in flight at a time
-        double x[8][3];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const double *src = a.sums + ((size_t)y * a.geo2.ns + min(s0 + u, a.geo2.ns - 1)) * 3;
-#pragma unroll
-            for (int i = 0; i < 3; ++i) x[u][i] = src[i];
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            if (s0 + u >= a.geo2.ns) continue;
-            beta += x[u][0];
-            A += x[u][1];
-            Bq += x[u][2];
-        }
-    }
+    if (a.geo2.ns == 1) add_slices<1>(a, y, beta, A, Bq);
+    else add_slices<8>(a, y, beta, A, Bq);
     constexpr double LN2 = 0.6931471805599453;
     double kl = LN2 * A, hq = -LN2 * Bq;
     kl = kl > 0.0 ? kl : 0.0;             // both are non-negative; rounding can leave a tiny negative sum
