@@ -25,27 +25,35 @@ __device__ __forceinline__ void begin_sequence(const RoundBuffers &rb, int b, in
     rb.draft_len[b] = 0;
 }
 
-// Bookkeeping of round `round` for sequence b, which accepted `na` of its g drafted tokens token(j) and got `next` behind
-// them, and the beginning of its next round; by `lanes` threads of one wave, of which this one is `lane`.  Returns (in
-// lane 0) whether the sequence goes on.
-template <typename F>
-__device__ __forceinline__ bool end_sequence(const LoopArgs &a, int b, int round, int g, int na, int next, int lane, int lanes, F token)
+// The limit of the round behind one that accepted all of its draft, or did not.
+__device__ __forceinline__ int next_cap(const LoopArgs &a, int cap, bool all_accepted)
+{
+    const int c = cap + (all_accepted ? a.inc : -a.dec);
+    return c < 1 ? 1 : (c > a.gamma_max ? a.gamma_max : c);
+}
+
+// A round's entry in the log.
+__device__ __forceinline__ void log_round(const LoopArgs &a, int b, int round, int pos, int cap, int g, int na)
+{
+    if (!a.round_log) return;
+    int *lg = a.round_log + ((size_t)round * a.B + b) * 4;
+    lg[0] = pos;
+    lg[1] = cap;
+    lg[2] = g;
+    lg[3] = na;
+}
+
+// Bookkeeping of round `round` for sequence b, which accepted `na` of its g drafted tokens and got `next` behind
+// them, and the beginning of its next round.  Returns whether the sequence goes on.
+__device__ __forceinline__ bool end_sequence(const LoopArgs &a, int b, int round, int g, int na, int next, const int *tokens)
 {
     int *st = a.state + (size_t)b * SVIP_LOOP_NSTATE;
     const int pos = st[0], cap = st[1], start = st[7];
     int *o = a.out_tokens + (size_t)b * a.out_stride + st[6];
-    for (int j = lane; j < na; j += lanes) o[j] = token(j);
-    if (lane != 0) return false;
+    for (int j = 0; j < na; ++j) o[j] = tokens[j];
     o[na] = next;
-    if (a.round_log) {
-        int *lg = a.round_log + ((size_t)round * a.B + b) * 4;
-        lg[0] = pos;
-        lg[1] = cap;
-        lg[2] = g;
-        lg[3] = na;
-    }
-    int ncap = cap + (na == g ? a.inc : -a.dec);          // every drafted token accepted: longer next time
-    ncap = ncap < 1 ? 1 : (ncap > a.gamma_max ? a.gamma_max : ncap);
+    log_round(a, b, round, pos, cap, g, na);
+    const int ncap = next_cap(a, cap, na == g);
     const int npos = pos + na + 1;
     const int done = finished(npos, start, ncap, a.L, a.max_new) ? 1 : 0;
     st[0] = npos;
@@ -60,12 +68,7 @@ __device__ __forceinline__ bool end_sequence(const LoopArgs &a, int b, int round
 }
 
 // Its entry in the log of a round after a sequence's last one.
-__device__ __forceinline__ void log_idle(const LoopArgs &a, int b, int round)
-{
-    if (!a.round_log) return;
-    int *lg = a.round_log + ((size_t)round * a.B + b) * 4;
-    lg[0] = lg[1] = lg[2] = lg[3] = -1;
-}
+__device__ __forceinline__ void log_idle(const LoopArgs &a, int b, int round) { log_round(a, b, round, -1, -1, -1, -1); }
 
 // The message (ticket, value) as one word.
 __device__ __forceinline__ void post(const Mail &m, int value)

@@ -52,8 +52,9 @@ struct RoundBuffers {
     int *cap;                  // [B] length limit of the round
     int *counter;              // [3]: sequences not finished; still drafting (greedy stream: taking part in this call);
                                //      rounds begun before this call + the most that any sequence has ended in it
-    int *drafted, *round;      // greedy stream [B]: positions drafted in the round so far, the sequence's round
-    int *argmax;               // greedy stream [B, gamma_max + 1]: argmax of the round's target rows so far
+    int *drafted, *round;      // greedy stream [B]: positions of the round whose draft rows have been read, none of which ends the
+                               //      draft, and the target rows up to one behind them (-1: nothing); the sequence's round
+    int *argmax;               // greedy stream [B, gamma_max + 1]: argmax of those target rows (the drafted tokens: `tokens`)
     char *group;               // grouped positions: draft records, then (greedy) keys
     size_t group_bytes;
 };
@@ -98,10 +99,10 @@ int group_waves(int B, int V, int dtype);
 size_t group_bytes(int B, int V, int dtype, int group, bool greedy);
 bool draft_shape_forced();           // an experiment's override asks for records of another size
 svip_status draft_group_call(const DraftCall &c, int group, void *buffer, size_t bytes);
-// Greedy: every active sequence `group` positions further in its own round; step_j is not used.
-svip_status greedy_stream_call(const DraftCall &c, const void *target, int group, const LoopArgs &l, int last_round, Mail active,
-                               Mail running, Mail rounds);
-constexpr int STREAM_MAX_GROUP = 64;
+// Greedy: every active sequence up to `group` rows further, `ahead` where its next round may be its last; step_j is not used.
+svip_status greedy_stream_call(const DraftCall &c, const void *target, int group, int ahead, const LoopArgs &l, int last_round,
+                               Mail active, Mail running, Mail rounds);
+constexpr int STREAM_MAX_GROUP = 128;
 svip_status verify_call(const VerifyCall &c);
 
 }  // namespace svip

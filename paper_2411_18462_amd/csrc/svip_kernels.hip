@@ -328,7 +328,7 @@ static unsigned shape_draft_stats(DraftArgs &a, unsigned rows)
     a.rows_by_xcd = waves <= 8100u && a.geo.ns >= NWAVE;
     const unsigned grid = a.rows_by_xcd ? ((rows + 7u) / 8u) * 8u * (((unsigned)a.geo.ns + NWAVE - 1) / NWAVE)
                                         : (waves + NWAVE - 1) / NWAVE;
-    // the kernel's division: n < 2^26 waves with d <= 64, or n <= 8100 with d <= 128 (grouped positions: n <= 2^15, d <= 192)
+    // the kernel's division: n < 2^26 waves with d <= 64, or n <= 8100 with d <= 128 (grouped positions: n < 2^18, d <= 192)
     a.div = a.rows_by_xcd ? ((unsigned)a.geo.ns + NWAVE - 1) / NWAVE : (unsigned)a.geo.ns;
     a.div_magic = magic_of(a.div);
     return grid;
@@ -404,7 +404,7 @@ static svip_status group_args(const DraftCall &c, int group, void *buffer, size_
     const svip_status s = check_draft(c);
     if (s != SVIP_OK) return s;
     if (!c.pos || !c.cap || !c.stop_in || !c.draft_len_out) return SVIP_ERR_NULL;
-    if (group_waves(c.B, c.V, c.dtype) == 0 || group < 1 || group > c.k_max) return SVIP_ERR_SHAPE;
+    if (group_waves(c.B, c.V, c.dtype) == 0 || group < 1 || group > (c.greedy ? STREAM_MAX_GROUP : c.k_max)) return SVIP_ERR_SHAPE;
     if (bytes < group_bytes(c.B, c.V, c.dtype, group, c.greedy)) return SVIP_ERR_WORKSPACE;
     a->d = draft_args(c, geo_group(c.V, vec_of(c.dtype)), buffer);
     a->group = group;
@@ -435,17 +435,18 @@ svip_status draft_group_call(const DraftCall &c, int group, void *buffer, size_t
     return ok ? SVIP_OK : SVIP_ERR_HIP;
 }
 
-svip_status greedy_stream_call(const DraftCall &c, const void *target, int group, const LoopArgs &l, int last_round, Mail active,
-                               Mail running, Mail rounds)
+svip_status greedy_stream_call(const DraftCall &c, const void *target, int group, int ahead, const LoopArgs &l, int last_round,
+                               Mail active, Mail running, Mail rounds)
 {
     GroupArgs a;
     const svip_status s = group_args(c, group, l.rb.group, l.rb.group_bytes, &a);
     if (s != SVIP_OK) return s;
-    if (!c.greedy || group > STREAM_MAX_GROUP || !target) return SVIP_ERR_SHAPE;
+    if (!c.greedy || ahead < 1 || !target) return SVIP_ERR_SHAPE;
     if (!aligned16(target)) return SVIP_ERR_ALIGN;
     a.target = target;
     a.keys = reinterpret_cast<unsigned long long *>(l.rb.group + group_record_bytes(c.B, a.d.geo, group, true));
     a.flags = static_cast<unsigned *>(c.workspace);
+    a.ahead = ahead;
     a.last_round = last_round;
     a.active = active;
     a.running = running;

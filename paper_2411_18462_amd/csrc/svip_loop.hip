@@ -9,8 +9,8 @@
 //             verify         -> svip_verify kernels on trace rows pos[b] .. pos[b] + draft_len[b]
 //             k_round_end    -> appends the produced tokens, advances positions, applies the length
 //                               rule, updates the counters, counts the sequences still running and sets up the next round
-// Greedy:     every sequence goes through its own rounds, a few positions per pair of launches (greedy_stream_call);
-//             the rounds as above only in large batches.
+// Greedy:     every sequence goes through its own rounds, on rows that are read once, many per pair of launches
+//             (greedy_stream_call); the rounds as above only in large batches.
 // k_round_begin sets up what the first launches of a call read.
 // The counts reach the host as messages: the counting kernel stores (ticket, count) as one 8-byte word
 // into pinned host memory and the host reads that word until the ticket shows.  No copy is enqueued and the
@@ -123,19 +123,21 @@ static inline size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
 //   Sampling: the first group takes what GROUP_WAVES_FIRST waves cover -- a whole draft of a few sequences, 8 positions of 8
 //   sequences of 152K bf16 logits, at least 2 -- and the next one, which most rounds find empty, as much of the rest
 //   as the buffer for the records holds.
-//   Greedy: STREAM_WAVES draft records per launch, at least 2 positions; the target rows come on top.  8 sequences of 152K bf16
-//   logits, 48 tokens with drafts of 1.3 positions: 600 and 1200 waves (2 positions) 482 and 472 us, 2400 (4) 483, 4000 (6) 539;
-//   more positions help longer drafts.
+//   Greedy: each row is read once, so a launch reads as many as it is sure to need, up to STREAM_WAVES_MAX draft records (the target
+//   rows come on top): with 16384 / 32768 / 65536 of them 8 sequences of 151936 bf16 logits, 32 tokens in drafts of 1.3, take 138 / 122 /
+//   122 us, 64 sequences 445 / 396 / 367.  Where a call may only run a few rounds, and behind the last token, it is STREAM_WAVES
+//   records, at least 2 positions, and up to eight times as many for a draft that goes on.
 // Beyond GROUP_WAVES_FIRST waves per position (64 sequences of 152K logits are just below) positions go one by one.  The line
 // stands behind the largest shape measured, where groups are still the faster form: it is not where the two meet.
-// us for 32 tokens per sequence, position by position / in groups (greedy; sampling), drafts of 1.3 | 20 positions:
-//    1 x 32000 fp32      1255 / 341; 958 / 613   | 2227 / 221; 1087 / 297
-//    8 x 151936 bf16     1301 / 326; 1479 / 887  | 2581 / 950; 2834 / 965
-//   33 x 128256 bf16     1823 / 478; 1961 / 1409 | 3921 / 2544; 3669 / 1636
-//   64 x 151936 bf16     2211 / 654; 2570 / 1731 | 5386 / 3796; 5276 / 2941
-constexpr int GROUP_WAVES_FIRST = 4800, GROUP_WAVES_MAX = 32768, STREAM_WAVES = 2400;
+// us for 32 tokens per sequence, position by position / in groups (greedy; sampling), drafts of 1.3 | 20 positions (greedy with the
+// rows of one round per pair of launches, each round reading its own: 352, 327, 458, 637 | 228, 962, 2525, 3813):
+//    1 x 32000 fp32      1255 / 97;  958 / 613   | 2227 / 88;  1087 / 297
+//    8 x 151936 bf16     1301 / 122; 1479 / 887  | 2581 / 258; 2834 / 965
+//   33 x 128256 bf16     1823 / 210; 1961 / 1409 | 3921 / 440; 3669 / 1636
+//   64 x 151936 bf16     2211 / 367; 2570 / 1731 | 5386 / 716; 5276 / 2941
+constexpr int GROUP_WAVES_FIRST = 4800, GROUP_WAVES_MAX = 32768, STREAM_WAVES = 2400, STREAM_WAVES_MAX = 65536;
 
-// Positions of the first group (0: positions go one by one) and of later ones.
+// Positions of the first group (0: positions go one by one) and of later ones; greedy: rows of a small launch and of the largest.
 struct GroupPlan {
     int first, next;
 };
@@ -147,21 +149,23 @@ static GroupPlan plan_groups(int B, int k, int V, int dtype, bool greedy)
     const int rows = group_waves(1, V, dtype) * ((B + 7) / 8 * 8);        // waves per position with rows kept on XCDs
     const int n = (greedy ? STREAM_WAVES : GROUP_WAVES_FIRST) / waves;
     p.first = n > 2 ? n : 2;
-    if (greedy && p.first > STREAM_MAX_GROUP) p.first = STREAM_MAX_GROUP;
-    p.next = greedy ? p.first : GROUP_WAVES_MAX / rows;
+    if (greedy && p.first > 64) p.first = 64;
     if (p.first > k) p.first = k;
-    if (p.next > k) p.next = k;
+    p.next = (greedy ? STREAM_WAVES_MAX : GROUP_WAVES_MAX) / rows;
+    const int most = greedy ? STREAM_MAX_GROUP : k;
+    if (p.next > most) p.next = most;
     if (p.next < p.first) p.next = p.first;
     return p;
 }
-// Bytes for the records of the largest group; the loop's workspace has to do for every type, sampling and greedy.
-static size_t plan_bytes(int B, int k, int V)
+// Bytes for the records of the largest group; the loop's workspace has to do for every type, sampling and greedy.  least: what
+// groups are taken with at all, the greedy ones only as large as a small launch.
+static size_t plan_bytes(int B, int k, int V, bool least)
 {
     size_t most = 0;
     for (int dtype = SVIP_F32; dtype <= SVIP_F16; ++dtype)
         for (int greedy = 0; greedy < 2; ++greedy) {
             const GroupPlan p = plan_groups(B, k, V, dtype, greedy);
-            const size_t n = p.first ? group_bytes(B, V, dtype, p.next, greedy) : 0;
+            const size_t n = p.first ? group_bytes(B, V, dtype, least && greedy ? p.first : p.next, greedy) : 0;
             if (n > most) most = n;
         }
     return most;
@@ -174,13 +178,14 @@ static size_t serial_buffer_bytes(int B, int k)
     return up256(nk * 4) + up256(nk * 8) + 2 * up256(n) + 6 * up256(n * 4) + 256;
 }
 
-static size_t round_buffer_bytes(int B, int k, int V)
+static size_t round_buffer_bytes(int B, int k, int V, bool least)
 {
     const size_t n = (size_t)B, nk = n * (size_t)k;
-    return serial_buffer_bytes(B, k) + 2 * up256(n * 4) + up256((nk + n) * 4) + plan_bytes(B, k, V);
+    return serial_buffer_bytes(B, k) + 2 * up256(n * 4) + up256((nk + n) * 4) + plan_bytes(B, k, V, least);
 }
 
-// bytes: of the round's buffers.  Where they do only for the serial loop there are none for groups (group is null).
+// bytes: of the round's buffers.  Where they do only for the serial loop there are none for groups (group is null); what there is
+// beyond the least that groups need makes the greedy ones larger.
 static RoundBuffers carve_round(char *p, int B, int k, int V, size_t bytes)
 {
     const size_t n = (size_t)B, nk = n * (size_t)k;
@@ -198,12 +203,13 @@ static RoundBuffers carve_round(char *p, int B, int k, int V, size_t bytes)
     r.drafted = r.round = r.argmax = nullptr;
     r.group = nullptr;
     r.group_bytes = 0;
-    if (bytes >= round_buffer_bytes(B, k, V)) {
+    const size_t least = round_buffer_bytes(B, k, V, true);
+    if (bytes >= least) {
         r.drafted = reinterpret_cast<int *>(p); p += up256(n * 4);
         r.round = reinterpret_cast<int *>(p); p += up256(n * 4);
         r.argmax = reinterpret_cast<int *>(p); p += up256((nk + n) * 4);
         r.group = p;
-        r.group_bytes = plan_bytes(B, k, V);
+        r.group_bytes = plan_bytes(B, k, V, true) + (bytes - least);
     }
     return r;
 }
@@ -252,7 +258,7 @@ __global__ __launch_bounds__(LOOP_WG) void k_round_begin(LoopArgs a)
         const int *st = a.state + (size_t)b * SVIP_LOOP_NSTATE;
         begin_sequence(a.rb, b, st[0], st[1], st[2]);
         if (a.rb.group) {
-            a.rb.drafted[b] = 0;
+            a.rb.drafted[b] = -1;
             a.rb.round[b] = a.round;
         }
         running += st[2] ? 0 : 1;
@@ -262,14 +268,6 @@ __global__ __launch_bounds__(LOOP_WG) void k_round_begin(LoopArgs a)
         a.rb.counter[0] = a.rb.counter[1] = total;
         a.rb.counter[2] = a.round;
     }
-}
-
-// grid (ceil(B / LOOP_WG)): the log of finished sequences up to round `a.round`, where the last of them ended
-__global__ __launch_bounds__(LOOP_WG) void k_log_idle(LoopArgs a)
-{
-    const int b = blockIdx.x * LOOP_WG + threadIdx.x;
-    if (b >= a.B || !a.rb.done[b]) return;
-    for (int r = a.rb.round[b]; r < a.round; ++r) log_idle(a, b, r);
 }
 
 // one workgroup: number of sequences that are still drafting
@@ -293,8 +291,7 @@ __global__ __launch_bounds__(LOOP_WG) void k_round_end(LoopArgs a)
     for (int b = threadIdx.x; b < a.B; b += LOOP_WG) {
         const int *tokens = a.rb.tokens + (size_t)b * a.gamma_max;
         if (a.rb.done[b]) log_idle(a, b, a.round);
-        else running += end_sequence(a, b, a.round, a.rb.draft_len[b], a.rb.n_accepted[b], a.rb.next_token[b], 0, 1,
-                                     [&](int j) { return tokens[j]; });
+        else running += end_sequence(a, b, a.round, a.rb.draft_len[b], a.rb.n_accepted[b], a.rb.next_token[b], tokens);
     }
     const int total = block_count(running, lds);
     if (threadIdx.x == 0) {
@@ -361,29 +358,40 @@ static DraftCall draft_call(const svip_loop_config *c, const RoundBuffers &rb, s
 }
 
 // The greedy loop: pairs of launches until no sequence is active any more.  Each pair's first kernel reports what the pairs
-// before it left, so the next pair is launched while the GPU works on this one.
-static svip_status run_greedy_stream(const svip_loop_config *c, const RoundBuffers &rb, size_t base, int group, int first_round,
-                                     int max_rounds, int *rounds_run, int *running)
+// before it left, so the next pair is launched while the GPU works on this one.  The first launches are large, until every
+// sequence has the rows of max_new tokens; what comes behind them serves rounds that reach further.
+static svip_status run_greedy_stream(const svip_loop_config *c, const RoundBuffers &rb, size_t base, const GroupPlan &plan,
+                                     int first_round, int max_rounds, int *rounds_run, int *running)
 {
+    // a round may use no more than its first rows: a call of few rounds reads accordingly
+    int most = plan.next;
+    if ((long long)plan.first * max_rounds < most) most = plan.first * max_rounds;
+    while (most > plan.first && group_bytes(c->B, c->V, c->dtype, most, true) > rb.group_bytes) --most;
+    const long long sure = (long long)c->max_new + plan.first;
+    const int large = sure < most ? (int)sure : most;
+    int small = plan.first;
     hipStream_t st = static_cast<hipStream_t>(c->hip_stream);
-    LoopArgs a = loop_args(c, rb, first_round);
+    const LoopArgs a = loop_args(c, rb, first_round);
     hipLaunchKernelGGL(k_round_begin, dim3(1), dim3(LOOP_WG), 0, st, a);
     if (hipPeekAtLastError() != hipSuccess) return SVIP_ERR_HIP;
     const DraftCall d = draft_call(c, rb, base, first_round, 0);
+    long long covered = 0;
     for (int active = 1; active > 0;) {
         const Ticket t0 = new_ticket(), t1 = new_ticket(), t2 = new_ticket();
-        svip_status r = greedy_stream_call(d, c->target_trace, group, a, first_round + max_rounds, mail_of(t0), mail_of(t1), mail_of(t2));
+        int group = large;
+        if (covered >= sure) {
+            group = small;
+            if (2 * small <= most && 2 * small <= 8 * plan.first) small *= 2;      // (the last launch finds nothing to do)
+        }
+        covered += group;
+        svip_status r = greedy_stream_call(d, c->target_trace, group, plan.first, a, first_round + max_rounds, mail_of(t0), mail_of(t1),
+                                           mail_of(t2));
         if (r == SVIP_OK) r = await(t0, &active, st);
         if (r == SVIP_OK) r = await(t1, running, st);
         if (r == SVIP_OK) r = await(t2, rounds_run, st);
         if (r != SVIP_OK) return r;
     }
     *rounds_run -= first_round;
-    if (c->round_log) {
-        a.round = first_round + *rounds_run;
-        hipLaunchKernelGGL(k_log_idle, dim3((unsigned)((c->B + LOOP_WG - 1) / LOOP_WG)), dim3(LOOP_WG), 0, st, a);
-        if (hipPeekAtLastError() != hipSuccess) return SVIP_ERR_HIP;
-    }
     return hipStreamSynchronize(st) == hipSuccess ? SVIP_OK : SVIP_ERR_HIP;
 }
 
@@ -415,7 +423,7 @@ size_t svip_loop_workspace_bytes(int B, int gamma_max, int V)
 {
     const size_t base = svip_workspace_bytes(B, gamma_max, V);
     if (base == 0) return 0;
-    return up256(base) + round_buffer_bytes(B, gamma_max, V);
+    return up256(base) + round_buffer_bytes(B, gamma_max, V, false);
 }
 
 svip_status svip_loop_init(const svip_loop_config *c)
@@ -450,7 +458,7 @@ svip_status svip_loop_run(const svip_loop_config *c, int first_round, int max_ro
     svip_status r;
     if (c->greedy && plan.first != 0 && max_rounds > 0) {
         if (!mailbox_ready()) return SVIP_ERR_HIP;
-        r = run_greedy_stream(c, rb, base, plan.first, first_round, max_rounds, &done_rounds, &running);
+        r = run_greedy_stream(c, rb, base, plan, first_round, max_rounds, &done_rounds, &running);
         if (r != SVIP_OK) return r;
         if (rounds_run_host) *rounds_run_host = done_rounds;
         if (running_host) *running_host = running;

@@ -180,3 +180,48 @@ def test_rows_of_several_records_per_lane(svip, B, V, dtype, greedy):
         st = _check(part, trace, SimpleNamespace(T=1.0), (h, k, k, 0, 0), max_new, greedy=greedy)
         print("  ", st, flush=True)
         assert st["rounds"] >= 2 * min(B, 3) and (not greedy or st["free_checked"] == min(B, 3))
+
+
+@pytest.mark.parametrize("B,k,V,L,max_new,h,policy,workspace", [
+    (2, 200, 600, 420, 210, math.inf, (200, 0, 0), "full"),      # drafts longer than a launch's rows; all but a few rows accepted
+    (3, 300, 72, 700, 390, 4.0, (300, 0, 0), "full"),            # stops here and there, drafts of up to 300
+    (2, 130, 500, 300, 250, math.inf, (3, 7, 2), "least"),       # growing limits, small launches only
+    (5, 64, 400, 150, 200, math.inf, (64, 0, 0), "full"),        # the trace ends before max_new
+    (9, 1, 2500, 40, 38, 1.0, (1, 0, 0), "least"),               # drafts of one token
+    (4, 20, 300, 60, 30, 9.0, (20, 0, 0), "unfinished"),         # rows without any maximum: tokens of -1 are flagged and accepted
+])
+def test_greedy_rows_read_ahead(svip, B, k, V, L, max_new, h, policy, workspace):
+    """The greedy loop reads rows far ahead of its rounds: the same as position by position wherever launches end, for a whole run
+    and for one in pieces."""
+    print(f"loop ahead B={B} k={k} V={V} L={L} {policy} {workspace}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(V)
+    draft = (torch.randn(B, L, V, device="cuda", generator=g) * (1.0 + 5.0 * torch.rand(B, L, 1, device="cuda", generator=g)))
+    target = draft.clone()
+    other = torch.rand(B, L, device="cuda", generator=g) < 0.03
+    target[other] = target[other].roll(1, -1)                              # another argmax in these rows
+    if workspace == "unfinished":
+        draft[:, 7::9] = target[:, 7::9] = -math.inf
+    results = []
+    for one_by_one, chunk in ((True, None), (False, None), (False, 1), (False, 5)):
+        try:
+            if one_by_one:
+                svip.bench_set_tuning(draft_slices=64)
+            loop = svip.Loop(target, draft, temperature=1.0, h=h, gamma0=policy[0], gamma_max=k, gamma_inc=policy[1], gamma_dec=policy[2],
+                             max_new=max_new, rounds=max_new, greedy=True)
+            if workspace == "least" and not one_by_one:                    # what groups are taken with at all
+                up = lambda n: (n + 255) // 256 * 256
+                serial = up(svip.workspace_bytes(B, k, V)) + up(4 * B * k) + up(8 * B * k) + 2 * up(B) + 6 * up(4 * B) + 256
+                loop.config.workspace_bytes = min(loop.workspace.numel(), serial + 2 * up(4 * B) + up(4 * B * (k + 1)) + 64 * 8 * k * 16)
+            ran, running = 0, 1
+            while running and loop.next_round < max_new:
+                n, running = loop.run(chunk)
+                ran += n
+        finally:
+            svip.bench_set_tuning()
+        assert running == 0 and ran == int(loop.state[:, 3].max())
+        results.append((loop.state.cpu(), loop.out_tokens.cpu(), loop.round_log.cpu()[:ran], loop.flags()))
+    assert (results[0][3] != 0) == (workspace == "unfinished")
+    for got in results[1:]:
+        for x, y in zip(results[0][:3], got[:3]):
+            assert torch.equal(x, y)
+        assert got[3] == results[0][3]
