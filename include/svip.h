@@ -44,8 +44,9 @@
  *   - `workspace` is device scratch of at least svip_workspace_bytes(B, k_max, V) bytes,
  *     256-byte aligned, that svip_workspace_reset has cleared once after allocation.  Besides
  *     partial results it holds, at its end, the counters with which the workgroups of svip_verify's
- *     residual pass hand a sequence's draw to whichever of them finishes last; every call leaves
- *     them at zero again.  Pass the same `workspace_bytes` with a workspace on every call.  Calls
+ *     residual pass and of a small draft step hand a row's draw to whichever of them finishes last;
+ *     every call leaves them at zero again.  Pass the same `workspace_bytes` with a workspace on every
+ *     call; one that serves calls of several batch sizes has svip_workspace_bytes of the largest.  Calls
  *     that run concurrently must use different workspaces.
  *   - Same inputs give bit-identical outputs (no floating-point atomics, fixed combine order).
  */
@@ -159,7 +160,7 @@ svip_status svip_draft_step(
  *   - All calls on one GPU share the array: calls that overlap on one GPU (different streams, or
  *     threads) race and must be serialised by the caller.  Device-data flags are not reported.
  *   - The first call on a GPU asks the runtime for the array's address on that GPU (no allocation,
- *     nothing enqueued); nothing in the array has to be cleared.
+ *     nothing enqueued); nothing in the array has to be cleared (its counters start at zero).
  */
 #define SVIP_STATIC_SCRATCH_BYTES (1 << 21)
 svip_status svip_draft_step_static(

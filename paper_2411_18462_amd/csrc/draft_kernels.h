@@ -1,5 +1,6 @@
 // Kernels of svip_draft_step and svip_draft_step_greedy.
 #pragma once
+#include "exchange.h"
 #include "kernel_args.h"
 #include "sample_weights.h"
 
@@ -41,7 +42,7 @@ __device__ __forceinline__ void write_row_outputs(const DraftArgs &a, int b, lon
     if (a.draft_len) a.draft_len[b] = a.step_j + 1;
 }
 
-// The draft step is two launches ordered by the stream.
+// The draft step is two launches ordered by the stream, or for small ones (one_launch_step in svip_kernels.hip) the same work in one.
 //
 // k_draft_stats: the statistics of a row as one record per WAVE.  Record r of a row covers tiles
 // [r * tps, (r + 1) * tps), and a wave reads a tile (256 consecutive vectors) as four chunks of 64
@@ -59,9 +60,7 @@ __device__ __forceinline__ void write_row_outputs(const DraftArgs &a, int b, lon
 //             with records of two tiles for the totals);
 //   GREEDY    one sum and the first index of the maximum, which is the token: nothing is read again.
 //
-// A single launch in which the row's last workgroup does the second part (hand-over through
-// write-through stores and a ticket, as the residual pass of verification does) measured the same at 64
-// rows of 128K logits and slower beyond, and was dropped for this simpler form.
+// k_draft_step: both, where the row's last workgroup finishes it.
 enum RecordKind { QUARTERS, TOTAL, GREEDY };
 
 // A row's stop flag, requested without looking at it: with no flag array the load goes to the start of the
@@ -286,19 +285,28 @@ __device__ __forceinline__ void uncommon_record(const DraftArgs &a, const DT *ro
     }
 }
 
-// The wave's record from its lanes' sums.
+// The wave's record from its lanes' sums.  PUBLISH: for a workgroup of the same launch (exchange.h).
+template <bool PUBLISH>
 __device__ __forceinline__ void store_record(const DraftArgs &a, size_t at, float mw, int first, double lane_sum, double t)
 {
     const double S = wave_sum(lane_sum);
+    WaveRec *to = static_cast<WaveRec *>(a.part) + at;
     if ((threadIdx.x & 63) == 0) {
-        WaveRec p;
-        p.m = mw;
-        p.idx = first;
-        p.S = S;
-        p.t = t;
-        static_cast<WaveRec *>(a.part)[at] = p;
+        if (PUBLISH) {
+            publish_f64(&to->S, S);
+            publish_f64(&to->t, t);
+            publish_f64(reinterpret_cast<double *>(&to->m), __hiloint2double(first, __float_as_int(mw)));
+        } else {
+            WaveRec p;
+            p.m = mw;
+            p.idx = first;
+            p.S = S;
+            p.t = t;
+            *to = p;
+        }
     }
 }
+template <bool PUBLISH>
 __device__ __forceinline__ void store_record(const DraftArgs &a, size_t at, float mw, const double (&S)[4], double t)
 {
     // one store of six lanes: the chunks' sums (lane q holds that of chunk q), t, and the maximum
@@ -306,11 +314,15 @@ __device__ __forceinline__ void store_record(const DraftArgs &a, size_t at, floa
     double x = wave_sum4(S);
     x = lane == 4 ? t : x;
     x = lane == 5 ? __hiloint2double(0, __float_as_int(mw)) : x;
-    if (lane < 6) reinterpret_cast<double *>(static_cast<QuarterRec *>(a.part) + at)[lane] = x;
+    double *to = reinterpret_cast<double *>(static_cast<QuarterRec *>(a.part) + at) + lane;
+    if (lane < 6) {
+        if (PUBLISH) publish_f64(to, x);
+        else *to = x;
+    }
 }
 
 // What a wave stores of the tiles [tb, te) it has summed (ok: within wave_tile's range throughout).
-template <typename DT, RecordKind KIND>
+template <typename DT, RecordKind KIND, bool PUBLISH = false>
 __device__ __forceinline__ void finish_record(const DraftArgs &a, const DT *row, int tb, int te, size_t at, bool ok, float mw,
                                               LaneSums<KIND> &sums, float td, int first, unsigned lowest)
 {
@@ -322,14 +334,14 @@ __device__ __forceinline__ void finish_record(const DraftArgs &a, const DT *row,
     }
     if (ok) {
         const double t = wave_sum((double)td) * a.sc.c;
-        if constexpr (KIND == QUARTERS) store_record(a, at, mw, sums.S, t);
-        else store_record(a, at, mw, first, sums.total(), t);
+        if constexpr (KIND == QUARTERS) store_record<PUBLISH>(a, at, mw, sums.S, t);
+        else store_record<PUBLISH>(a, at, mw, first, sums.total(), t);
     } else {
         double S[4], t2;
         uncommon_record<DT, KIND>(a, row, tb, te, mw, S, t2, first);
         const double t = wave_sum(t2);
-        if constexpr (KIND == QUARTERS) store_record(a, at, mw, S, t);
-        else store_record(a, at, mw, first, (S[0] + S[1]) + (S[2] + S[3]), t);
+        if constexpr (KIND == QUARTERS) store_record<PUBLISH>(a, at, mw, S, t);
+        else store_record<PUBLISH>(a, at, mw, first, (S[0] + S[1]) + (S[2] + S[3]), t);
     }
 }
 
@@ -406,6 +418,29 @@ __global__ __launch_bounds__(WG, TPS == 1 ? 8 : 6) void k_draft_stats(DraftArgs 
     // at most 0 otherwise; like a masked logit it weighs nothing, by the floor of uncommon_record's exponents.
     ok = ok && __ballot(!(td > neg_inf())) == 0ull;
     finish_record<DT, KIND>(a, row, tb, te, (size_t)b * nrec + r, ok, mw, sums, td, first, lowest);
+}
+
+// The record of tile r of a row, stored at index `at`: what k_draft_stats does for records of one tile.  stopped() is asked while
+// the tile is on its way; returns what it said (true: no record).
+struct NeverStopped {
+    __device__ __forceinline__ bool operator()() const { return false; }
+};
+template <typename DT, RecordKind KIND, bool PUBLISH = false, typename Stopped = NeverStopped>
+__device__ __forceinline__ bool tile_record(const DraftArgs &a, const DT *row, int r, size_t at, Stopped stopped = Stopped())
+{
+    constexpr int N = VecOf<DT>::N, CPT = WG / 64;
+    typename RawOf<DT>::type raw[CPT];
+    float mw = neg_inf(), td = 0.f;
+    LaneSums<KIND> sums;
+    int first = -1;
+    unsigned lowest = 0u;
+    if (r < a.geo.V / (WG * N)) wave_load<DT, CPT, false>(row, a.geo.V, r * CPT, raw);
+    else wave_load<DT, CPT, true>(row, a.geo.V, r * CPT, raw);
+    if (stopped()) return true;
+    bool ok = a.common_range && wave_tile<DT, CPT, KIND>(raw, r * CPT, mw, sums, td, first, lowest, a.sc);
+    ok = ok && __ballot(!(td > neg_inf())) == 0ull;       // (a NaN among the logits, see k_draft_stats)
+    finish_record<DT, KIND, PUBLISH>(a, row, r, r + 1, at, ok, mw, sums, td, first, lowest);
+    return false;
 }
 
 // The inverse CDF inside one chunk of a row by one wave: the smallest index whose inclusive prefix of weights
@@ -508,6 +543,8 @@ struct QuarterRow {
     double t[RPL], S4[RPL][4];
     float mrow;                          // after merge(): row maximum, factors and masses relative to it
     double f[RPL], xd[RPL], rS[RPL], M;
+    // PUBLISHED: by workgroups of this launch
+    template <bool PUBLISHED = false>
     __device__ __forceinline__ void load(const DraftArgs &a, size_t at)
     {
         const int lane = threadIdx.x & 63, nrec = a.geo.ns;
@@ -519,10 +556,18 @@ struct QuarterRow {
             for (int q = 0; q < 4; ++q) S4[i][q] = 0.0;
             if (lane * RPL + i < nrec) {
                 const QuarterRec *p = static_cast<const QuarterRec *>(a.part) + at + lane * RPL + i;
-                m[i] = p->m;
-                t[i] = p->t;
+                if (PUBLISHED) {
+                    const double *w = reinterpret_cast<const double *>(p);
 #pragma unroll
-                for (int q = 0; q < 4; ++q) S4[i][q] = p->S[q];
+                    for (int q = 0; q < 4; ++q) S4[i][q] = fetch_f64(w + q);
+                    t[i] = fetch_f64(w + 4);
+                    m[i] = __int_as_float(__double2loint(fetch_f64(w + 5)));
+                } else {
+                    m[i] = p->m;
+                    t[i] = p->t;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) S4[i][q] = p->S[q];
+                }
             }
         }
     }
@@ -618,6 +663,7 @@ struct GreedyRow {
     float mrow;                          // after merge(): row maximum, sums, token (uniform)
     double S, tt;
     int tok;
+    template <bool PUBLISHED = false>
     __device__ __forceinline__ void load(const DraftArgs &a, size_t at)
     {
         const int lane = threadIdx.x & 63;
@@ -627,7 +673,18 @@ struct GreedyRow {
             p[i].idx = -1;
             p[i].S = 0.0;
             p[i].t = 0.0;
-            if (lane * RPL + i < a.geo.ns) p[i] = static_cast<const WaveRec *>(a.part)[at + lane * RPL + i];
+            if (lane * RPL + i < a.geo.ns) {
+                const WaveRec *from = static_cast<const WaveRec *>(a.part) + at + lane * RPL + i;
+                if (PUBLISHED) {
+                    p[i].S = fetch_f64(&from->S);
+                    p[i].t = fetch_f64(&from->t);
+                    const double mi = fetch_f64(reinterpret_cast<const double *>(&from->m));
+                    p[i].m = __int_as_float(__double2loint(mi));
+                    p[i].idx = __double2hiint(mi);
+                } else {
+                    p[i] = *from;
+                }
+            }
         }
     }
     __device__ __forceinline__ void merge(const DraftArgs &a)
@@ -668,6 +725,67 @@ __global__ __launch_bounds__(64) void k_draft_finish_greedy(DraftArgs a)
         a.token[o] = r.tok;
         if (a.q_tok) a.q_tok[o] = (float)(1.0 / r.S);     // the maximum has weight exp2(0) = 1
         write_row_outputs(a, b, o, r.mrow, r.S, r.tt);
+    }
+}
+
+// The whole step in one launch: grid (rows rounded up to whole rounds of the XCDs * workgroups per row), one wave per record of one
+// tile; the workgroup that is last to publish its records (exchange.h) merges them.  What bounds it is one chain: of a
+// step of 16 rows of 32000 fp32 logits, 10600 cycles in all, the tile and its statistics take 4200, the stores 700, the ticket 1000, the
+// fetch of the records 2000, merge and chunk 1400, the search 1200.  Entropy, logsumexp and stop test (1400) are a second wave's,
+// beside the search: behind the chunk's request in the same wave they lengthened the step by 0.5 us.  (The records fetched as they lie,
+// 64 words at a time, and dealt out through LDS: no faster, 5.95 us for 5.86.)
+template <typename DT, RecordKind KIND, int RPL>
+__global__ __launch_bounds__(WG, 4) void k_draft_step(DraftArgs a)
+{
+    static_assert(KIND != TOTAL, "records of one tile");
+    asm volatile("" : : "s"(a.logits), "s"(a.row_stride), "s"(a.pos), "s"(a.stop_in), "s"(a.geo.V), "s"(a.part), "s"(a.sc.c_dn),
+                 "s"(a.sc.c_up), "s"(a.sc.c), "s"(a.common_range), "s"(a.step_j));
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, nrec = a.geo.ns;
+    const unsigned xcd = blockIdx.x & 7u, slot = blockIdx.x >> 3;           // div = workgroups per row
+    const unsigned q = a.div == 1u ? slot : __umulhi(slot, a.div_magic), s = slot - q * a.div;
+    const int b = (int)(q * 8u + xcd), r = (int)s * NWAVE + wave;
+    if (b >= a.B) return;
+    const long long o = (long long)b * a.io_stride;
+    const DT *row = static_cast<const DT *>(a.logits) + draft_row_offset(a, b, a.step_j);
+    const unsigned flag = request_stop_flag(a, b);
+    const float u = KIND == QUARTERS ? a.u[o] : 0.f;
+    const size_t first = (size_t)b * nrec;
+    bool stopped;
+    if (r < nrec) stopped = tile_record<DT, KIND, true>(a, row, r, first + r, [&] { return flag_after_loads(a, flag); });
+    else stopped = flag_after_loads(a, flag);
+    if (stopped) {
+        if (s == 0) stopped_row(a, b, o);
+        return;
+    }
+    stores_done();
+    __syncthreads();
+    if (wave > (KIND == QUARTERS ? 1 : 0)) return;
+    // Waves 0 and 1 draw their tickets from counters of their own: they need not hear from one another, and the row's last
+    // ones may be of different workgroups.
+    unsigned *counter = ticket(a.tickets, b, TICKET_DRAFT + wave), t = 0u;
+    if (lane == 0) t = take_ticket(counter);
+    if ((unsigned)__builtin_amdgcn_readfirstlane((int)t) != a.div - 1u) return;
+    // all of the row's waves have read its flag, and stored their records
+    if (lane == 0) reset_tickets(counter);
+    if constexpr (KIND == QUARTERS) {
+        QuarterRow<RPL> rec;
+        rec.template load<true>(a, first);
+        rec.merge(a);
+        if (wave == 1) {
+            const double tt = rec.entropy_sum(), S = wave_sum(rec.M);
+            if (lane == 0) write_row_outputs(a, b, o, rec.mrow, S, tt);
+        } else {
+            rec.template find_token<DT>(a, row, u, o);
+        }
+    } else {
+        GreedyRow<RPL> rec;
+        rec.template load<true>(a, first);
+        rec.merge(a);
+        if (lane == 0) {
+            a.token[o] = rec.tok;
+            if (a.q_tok) a.q_tok[o] = (float)(1.0 / rec.S);
+            write_row_outputs(a, b, o, rec.mrow, rec.S, rec.tt);
+        }
     }
 }
 

@@ -54,7 +54,7 @@ static Workspace carve(void *ws, size_t bytes, int B, int mass_slices)
     w.part = p;
     return w;
 }
-enum { TICKET_RESID = 0 };
+enum { TICKET_RESID = 0, TICKET_DRAFT = 1 };        // (the draft step has two)
 __device__ __forceinline__ unsigned *ticket(unsigned *tickets_end, int b, int t)
 {
     return tickets_end - ((size_t)b * TICKETS_PER_ROW + t + 1);
@@ -99,6 +99,7 @@ struct DraftArgs {
     int *draft_len;
     long long io_stride;
     void *part;             // [B][ns] records of the row's waves: QuarterRec or WaveRec
+    unsigned *tickets;      // k_draft_step: see ticket()
     int common_range;       // 1: the temperature is in the range of wave_tile (draft_kernels.h)
     int rows_by_xcd;        // k_draft_stats: workgroup -> (row, records) mapping, see there
     unsigned div, div_magic;  // its one division, by div: n / div = div == 1 ? n : umulhi(n, div_magic), exact for n * div < 2^32

@@ -51,23 +51,6 @@ __device__ __forceinline__ bool group_row(const GroupArgs &a, int y, int *jj, in
     return *b < a.d.B;
 }
 
-// The record of tile r of a row, stored at index `at`: what k_draft_stats does for records of one tile, without its flag.
-template <typename DT, RecordKind KIND>
-__device__ __forceinline__ void tile_record(const DraftArgs &a, const DT *row, int r, size_t at)
-{
-    constexpr int N = VecOf<DT>::N, CPT = WG / 64;
-    typename RawOf<DT>::type raw[CPT];
-    float mw = neg_inf(), td = 0.f;
-    LaneSums<KIND> sums;
-    int first = -1;
-    unsigned lowest = 0u;
-    if (r < a.geo.V / (WG * N)) wave_load<DT, CPT, false>(row, a.geo.V, r * CPT, raw);
-    else wave_load<DT, CPT, true>(row, a.geo.V, r * CPT, raw);
-    bool ok = a.common_range && wave_tile<DT, CPT, KIND>(raw, r * CPT, mw, sums, td, first, lowest, a.sc);
-    ok = ok && __ballot(!(td > neg_inf())) == 0ull;       // (a NaN among the logits, see k_draft_stats)
-    finish_record<DT, KIND>(a, row, r, r + 1, at, ok, mw, sums, td, first, lowest);
-}
-
 // The draft records of positions step_j .. step_j + group - 1, one wave per record as in k_draft_stats.  Rows past a
 // sequence's limit may lie past the end of its trace: nothing of them is touched.
 template <typename DT>

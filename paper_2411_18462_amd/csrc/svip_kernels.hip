@@ -4,6 +4,7 @@
 // svip_draft_step  =  k_draft_stats    grid (rows * records / 4) one wave per record: (m, S, t) of a tile of a row
 //                     k_draft_finish_* grid (rows)               merge of the records: entropy, stop test, inverse
 //                                      CDF inside the one record that holds the draw (greedy: the first maximum)
+//                     k_draft_step     both in one launch, for small steps: the row's last workgroup merges
 // svip_verify      =  k_verify_stats   grid (stat rows * slices) per-slice (reference, sum) of every needed row
 //                     k_accept         grid (sequences), 1 wave  p/q tests, ballot scan for the first rejection (small calls: in k_resid)
 //                     k_resid          grid (sequences * slices) slice masses of the residual / bonus row; the workgroup
@@ -313,7 +314,31 @@ static DraftArgs draft_args(const DraftCall &c, const Geo &geo, void *records)
     a.draft_len = c.draft_len_out;
     a.io_stride = c.io_stride;
     a.part = records;
+    a.tickets = nullptr;
     return a;
+}
+
+// Whether a step is one launch (k_draft_step) or two.  One saves a launch (1.8 us in a graph, 2.5 us of the caller's time) and
+// pays with an exchange through memory, which takes longer the more rows are at it: their records are stored past the L2 and
+// fetched from behind it, sampling twice as many words as greedy, by two waves.  us per step in a graph, two launches / one:
+//   sampling, 16-bit  1 row of 128256 5.88 / 5.79, 8 6.80 / 6.45, 32 8.15 / 7.72, 64 (1024 workgroups) 9.68 / 9.43, 72 10.35 / 10.09,
+//                     112 11.88 / 12.32; 256 of 32000 (1024) 9.78 / 9.50, 288 10.44 / 10.28, 512 of 2000 7.87 / 6.86, 4096 14.0 / 16.8
+//     over 64 records 16 rows of 151936 (304) 7.92 / 7.48, 32 (608) 8.98 / 9.07, 56 10.43 / 11.21
+//   sampling, fp32    1 row of 32000 4.91 / 4.73, 16 6.15 / 5.86, 64 (512) 7.23 / 7.04, 144 (1152) 9.21 / 9.54
+//     over 64 records 8 rows of 128256 (256) 6.73 / 7.39
+//   greedy            1 row of 32000 fp32 4.50 / 4.38, 8 of 128256 bf16 6.25 / 5.71, 64 (1024) 8.96 / 8.43, 112 (1792) 11.02 / 10.98;
+//                     32 of 128256 fp32 (1024) 8.08 / 8.03, 40 8.65 / 8.93, 56 of 151936 bf16 (1064) 9.41 / 9.14, 4096 of 2000 11.6 / 12.9
+// Sampling's line stands below 1024 workgroups, where the gain is down to 2 % and a step's two kernels are still reported apart by
+// the benchmark.  A forced shape (an experiment's override) takes two.
+static unsigned row_workgroups(const Geo &g) { return ((unsigned)g.ns + NWAVE - 1) / NWAVE; }
+static bool one_launch_step(const DraftCall &c, const Geo &g)
+{
+    if (g.tps != 1 || g_tune.draft_slices) return false;
+    const long long workgroups = ((long long)c.B + 7) / 8 * 8 * row_workgroups(g);
+    if (c.greedy) return workgroups <= 1024;
+    if (!quarter_records(c.B, g)) return false;
+    if (g.ns > 64) return vec_of(c.dtype) == 8 && workgroups <= 512;
+    return workgroups <= 768;
 }
 
 // The shape of the statistics launch over `rows` rows; returns its workgroups.
@@ -341,10 +366,23 @@ svip_status draft_step_call(const DraftCall &c)
     const Geo geo = geo_draft(c.B, c.V, vec_of(c.dtype), g_tune.draft_slices);
     if (!workspace_ok(c.workspace, c.workspace_bytes, need_draft(c.B, geo, c.greedy))) return SVIP_ERR_WORKSPACE;
     const unsigned rows = (unsigned)c.B;
-    DraftArgs a = draft_args(c, geo, carve(c.workspace, c.workspace_bytes, c.B, 0).part);
-    const unsigned grid = shape_draft_stats(a, rows);
+    const Workspace w = carve(c.workspace, c.workspace_bytes, c.B, 0);
+    DraftArgs a = draft_args(c, geo, w.part);
     hipStream_t st = static_cast<hipStream_t>(c.stream);
     bool ok = false;
+    if (one_launch_step(c, geo)) {
+        a.tickets = w.tickets;
+        a.div = row_workgroups(geo);
+        a.div_magic = magic_of(a.div);
+        by_dtype(c.dtype, [&](auto tag) {
+            using DT = decltype(tag);
+            const auto kernel = c.greedy ? (geo.ns <= 64 ? k_draft_step<DT, GREEDY, 1> : k_draft_step<DT, GREEDY, 2>)
+                                         : (geo.ns <= 64 ? k_draft_step<DT, QUARTERS, 1> : k_draft_step<DT, QUARTERS, 2>);
+            ok = launch(kernel, (rows + 7u) / 8u * 8u * a.div, WG, st, a, SVIP_BENCH_K_DRAFT_STATS);
+        });
+        return ok ? SVIP_OK : SVIP_ERR_HIP;
+    }
+    const unsigned grid = shape_draft_stats(a, rows);
     by_dtype(c.dtype, [&](auto tag) {
         using DT = decltype(tag);
         const int tps = a.geo.tps;
@@ -465,7 +503,8 @@ svip_status greedy_stream_call(const DraftCall &c, const void *target, int group
 
 // Device address of `scratch` on the current device, or nullptr.  The first call on a device looks the
 // symbol up (hipGetSymbolAddress with that device current); every GPU holds its own copy of the array at
-// its own address.  Nothing in it has to start at zero: a draft step writes every record before it reads it.
+// its own address.  Its counters start at zero, as the array does, and every step leaves them there; records are written before
+// they are read.
 static void *static_scratch()
 {
     constexpr int MAX_DEVICES = 64;

@@ -237,3 +237,46 @@ def test_stop_flags_in_place_and_apart(svip, B, V, greedy):
             flags = before.clone()
             same = step(flags, flags, j)
             assert all(torch.equal(same[n], apart[n]) for n in apart)
+
+
+# Steps of one launch against two launches over the same records (a forced count takes those): rows of one to 64 records, whole
+# and partial workgroups and rounds of the XCDs, just inside and outside the line between the forms.
+ONE_LAUNCH = [(BF, 1, 100), (F32, 9, 1024 + 1), (F16, 7, 3 * 2048), (BF, 8, 4 * 2048 + 8), (F32, 17, 5 * 1024 - 1), (BF, 3, 63 * 2048 + 77),
+              (F32, 2, 64 * 1024), (BF, 190, 13 * 2048 + 5), (BF, 260, 13 * 2048 + 5), (F32, 96, 31 * 1024 + 9), (BF, 768, 700), (BF, 1030, 700)]
+
+
+@pytest.mark.parametrize("dtype,B,V", ONE_LAUNCH)
+def test_one_launch_gives_what_two_give(svip, dtype, B, V):
+    """Bit for bit, over a chain of three steps whose stop flags are updated in place (some rows stopped before it, others on the
+    way), in a workspace that the same steps have used before."""
+    records = -(-V // (1024 if dtype == F32 else 2048))
+    rows = [_rows(dtype, B, V, seed=31 * V + j) for j in range(3)]
+    ws = svip.new_workspace(B, 3, V)
+    got = []
+    try:
+        for forced in (0, 0, records):
+            svip.bench_set_tuning(draft_slices=forced)
+            for greedy in (False, True):
+                o = {n: torch.full((B, 3), -7, dtype=t, device="cuda") for n, t in
+                     (("tok", torch.int32), ("ent", F32), ("q", F32), ("lse", torch.float64))}
+                stop, dlen = torch.zeros(B, dtype=torch.uint8, device="cuda"), torch.full((B,), -7, dtype=torch.int32, device="cuda")
+                stop[1::5] = 1
+                for j, (x, u) in enumerate(rows):
+                    svip.draft_step(x, temperature=0.9, h=1.3, step_j=j, k_max=4, greedy=greedy,
+                                    u_sample=None if greedy else u[:, None].expand(B, 3).contiguous()[:, j], stop_in=stop,
+                                    token_out=o["tok"][:, j], entropy_out=o["ent"][:, j], q_tok_out=o["q"][:, j],
+                                    lse_out=o["lse"][:, j], stop_out=stop, draft_len_out=dlen, workspace=ws)
+                torch.cuda.synchronize()
+                got.append(dict(o, stop=stop, dlen=dlen))
+    finally:
+        svip.bench_set_tuning()
+    for i in range(4):
+        for n, want in got[4 + i % 2].items():
+            assert torch.equal(got[i][n], want), (i, n)
+
+
+@pytest.mark.parametrize("dtype,B,V", [(BF, 5, 65 * 2048 - 9), (F16, 19, 70 * 2048), (BF, 2, 128 * 2048), (F32, 8, 100 * 1024 + 3)])
+def test_one_launch_two_records_per_lane(svip, dtype, B, V):
+    x, u = _rows(dtype, B, V, seed=V + B)
+    for greedy in (False, True):
+        _check(_step(svip, x, u, 0.8, greedy), x, u, 0.8, greedy)
