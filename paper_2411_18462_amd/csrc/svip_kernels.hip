@@ -840,9 +840,10 @@ svip_status svip_warp_logits(const void *logits_in, void *logits_out, int dtype,
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     bool ok = false;
     by_dtype(dtype, [&](auto tag) {
-        const bool nucleus = !(top_k > 0 && top_k < V) && a.top_p < 1.0;
-        ok = launch(nucleus ? k_warp<decltype(tag), true> : k_warp<decltype(tag), false>, (unsigned)((long long)B * k_max),
-                    WARP_WG, st, a);
+        using DT = decltype(tag);
+        const bool nucleus = !(top_k > 0 && top_k < V) && a.top_p < 1.0, shortcut = V >= NUCLEUS_MIN_V && !a.no_shortcut;
+        ok = launch(!nucleus ? k_warp<DT, GENERAL> : (shortcut ? k_warp<DT, NUCLEUS> : k_warp<DT, HISTOGRAMS>),
+                    (unsigned)((long long)B * k_max), WARP_WG, st, a);
     });
     return ok ? SVIP_OK : SVIP_ERR_HIP;
 }

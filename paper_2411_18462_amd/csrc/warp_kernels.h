@@ -16,6 +16,8 @@
 // from a sample, one sweep for the candidates above it (which also writes the output when that
 // is a different buffer), everything else on the list.  top_p alone does likewise with two sweeps.
 #pragma once
+#include <type_traits>
+
 #include "row_math.h"
 
 namespace svip {
@@ -148,18 +150,36 @@ __device__ __forceinline__ typename RawOf<DT>::type warp_load(const DT *row, int
     return load_raw_edge(row, vi, V);
 }
 
-// f(vector index, its N values) for every vector of the row, U loads in flight per thread.
-template <typename DT, int U = 4, typename F>
+// f(vector index, its N values) for every vector of the row, U loads in flight per thread.  LONG: no branch stands between the loads,
+// and no check while all U vectors are whole: 1 row of 128256 bf16 logits, two sweeps, 32.6 us so 27.6; but rows of 32000, one batch per
+// thread, are 4 to 8 % slower than with a check for each, and fp32 ones that end in the histograms up to 3 %.
+template <typename DT, bool LONG, int U = 4, typename F>
 __device__ __forceinline__ void for_each_vector(const DT *row, int V, F f)
 {
     constexpr int N = VecOf<DT>::N;
-    const int nvec = (V + N - 1) / N;
-    for (int v0 = threadIdx.x; v0 < nvec; v0 += U * WARP_WG) {
+    const int nvec = (V + N - 1) / N, whole = V / N;
+    int v0 = threadIdx.x;
+    for (; LONG && v0 + (U - 1) * WARP_WG < whole; v0 += U * WARP_WG) {
         typename RawOf<DT>::type r[U];
 #pragma unroll
+        for (int u = 0; u < U; ++u) r[u] = *(reinterpret_cast<const typename RawOf<DT>::type *>(row) + v0 + u * WARP_WG);
+#pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int v = v0 + u * WARP_WG;
-            r[u] = warp_load<DT>(row, v < nvec ? v : v0, V);
+            float z[N];
+            unpack<DT>(r[u], z);
+            f(v0 + u * WARP_WG, z);
+        }
+    }
+    for (; v0 < nvec; v0 += U * WARP_WG) {
+        typename RawOf<DT>::type r[U];
+        if (LONG) {
+            warp_load_batch<DT, U>(row, v0, V, r, false);
+        } else {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int v = v0 + u * WARP_WG;
+                r[u] = warp_load<DT>(row, v < nvec ? v : v0, V);
+            }
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -174,14 +194,14 @@ __device__ __forceinline__ void for_each_vector(const DT *row, int V, F f)
 }
 
 // Sources of candidate keys: the whole row, or the list of one first-digit bin.  f(key, value).
-template <typename DT>
+template <typename DT, bool LONG>
 struct RowSource {
     const DT *row;
     int V;
     template <typename F>
     __device__ __forceinline__ void for_each(F f) const
     {
-        for_each_vector<DT>(row, V, [&](int, const float(&z)[VecOf<DT>::N]) {
+        for_each_vector<DT, LONG>(row, V, [&](int, const float(&z)[VecOf<DT>::N]) {
 #pragma unroll
             for (int e = 0; e < VecOf<DT>::N; ++e) f(value_key(z[e]), z[e]);
         });
@@ -279,6 +299,35 @@ template <> struct Threshold<float> {
         unsigned m = (unsigned)(__builtin_elementwise_sub_sat(ordered((int)word), p) >> 31);
         asm("" : "+v"(m));
         return m;
+    }
+};
+// The same for 16-bit logits and a threshold whose sign the whole wave branches on, in two or three instructions per word instead of five:
+// among the logits of one sign the stored words have the order of the numbers or its reverse, and those of the other sign are all
+// above or all below.
+template <typename DT> struct SignedThreshold {
+    typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+    unsigned p;
+    bool negative;                                 // -0 or below; what counts as 0 is at or above -0
+    __device__ __forceinline__ explicit SignedThreshold(unsigned key)
+    {
+        static_assert(VecOf<DT>::N == 8, "16-bit storage");
+        const i16x2 o = Threshold<DT>(key).p;
+        negative = __builtin_amdgcn_readfirstlane(o[0] < 0);
+        p = (unsigned)__builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, o[0] < 0 ? ordered(o) : o));
+    }
+    __device__ __forceinline__ void below(const u32x4 &w, unsigned (&m)[4]) const
+    {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (negative) {
+                const u16x2 d = __builtin_elementwise_sub_sat(__builtin_bit_cast(u16x2, (unsigned)w[i]), __builtin_bit_cast(u16x2, p));
+                m[i] = __builtin_bit_cast(unsigned, (u16x2)(u16x2{0, 0} - __builtin_elementwise_min(d, u16x2{1, 1})));
+            } else {
+                m[i] = __builtin_bit_cast(unsigned, __builtin_elementwise_sub_sat(__builtin_bit_cast(i16x2, (unsigned)w[i]),
+                                                                                  __builtin_bit_cast(i16x2, p)) >> 15);
+            }
+            asm("" : "+v"(m[i]));                  // (or it becomes a comparison and a select per logit)
+        }
     }
 };
 template <typename DT> __device__ __forceinline__ u32x4 neg_inf_words() { return __builtin_bit_cast(u32x4, NegInfVec<DT>::value()); }
@@ -379,13 +428,16 @@ __device__ __forceinline__ Crossing crossing(const T *h, unsigned long long targ
 // src at or above floor_key that carry `prefix` in their top `done` bits (done = 0: all, three
 // digits; done = 11: inside first-digit bin `prefix`, two digits): the key v among them with
 //   measure(candidates > v) < target <= measure(candidates >= v).
-template <typename Src, typename Measure>
+// BITS: the most of a key that the logits' type fills, 32 or, a 16-bit number having at most 19, 22: its last digit need not be looked for,
+// and with the bits behind the others at zero a key still stands for its number, as no other number lies between the two.
+template <typename DT> constexpr int KEY_BITS = VecOf<DT>::N == 8 ? 22 : 32;
+template <int BITS, typename Src, typename Measure>
 __device__ __forceinline__ unsigned select_digits(const Src &src, unsigned floor_key, Measure measure, unsigned prefix, int done,
                                   unsigned long long target, WarpLds &L)
 {
     const int tid = threadIdx.x;
 #pragma unroll 1
-    while (done < 32) {
+    while (done < BITS) {
         const int bits = done < 22 ? 11 : 10;
         const int shift = 32 - done - bits;
         const unsigned mask = (1u << bits) - 1u;
@@ -403,13 +455,13 @@ __device__ __forceinline__ unsigned select_digits(const Src &src, unsigned floor
         target = c.rem;
         done += bits;
     }
-    return prefix;
+    return prefix << (32 - BITS);
 }
-template <typename Src, typename Measure>
+template <int BITS, typename Src, typename Measure>
 __device__ __forceinline__ unsigned refine(const Src &src, unsigned floor_key, Measure measure, unsigned d1,
                            unsigned long long target, WarpLds &L)
 {
-    return select_digits(src, floor_key, measure, d1, 11, target, L);
+    return select_digits<BITS>(src, floor_key, measure, d1, 11, target, L);
 }
 
 // Sum over the workgroup of one 64-bit value per thread (uniform result; uses L.acc).
@@ -437,35 +489,113 @@ __device__ __forceinline__ unsigned lds_add(unsigned *p, unsigned n)
 
 // One sweep over the row: the keys of the logits at or above the pivot into L.list (n_list counts them, also those that do
 // not fit), with `FUSED` their indices behind them (`cap` of each) and the output -- the logit itself at and above the pivot,
-// -inf below; with `MASS` the total mass of the row (per thread).
-// A row's chunk of 64 vectors holds some candidates more often than not, so what every logit pays for is kept apart from
-// what a candidate does: the comparison works on the stored words (11 cycles of issue per 16-bit logit), and the lanes
-// that have candidates go through them one at a time.
-// `stream` (MASS, which sweeps the row for the second and last time): for calls that move more than the last-level cache,
-// loads and stores go past the caches, so that they keep the rows whose second sweep is still to come.  us, through the
+// -inf below; and with MASS the total mass of the row (per thread).
+// What bounds it is vector-ALU issue: about 75 cycles per logit of 64 lanes with a mass, on one workgroup 17 of a row's 27 us.  A row's
+// chunk of 64 vectors holds some candidates more often than not, so what every logit pays for is kept apart from what a candidate
+// does: the comparison works on the stored words, and the lanes that have candidates go through them one at a time.  With a mass, whole
+// vectors go without a check, the comparison goes by the pivot's sign and constants stay in vector registers: top-p 0.9, 1 row
+// of 128256 bf16 logits 32.7 / 27.7 us, 64 rows 39.0 / 32.4, 1088 rows 178 / 165 (with the select below).
+// Tried and dropped: the row held in a workgroup's registers (one read; its phases no longer overlap another row's: 1088 rows 207 us), and
+// one sweep relative to a sample's maximum with an approximate total (155 us, but 3 to 9 % more for rows that it cannot decide).
+// `stream` (with a mass): for calls that move more than the last-level cache, loads and stores go past the caches, so that
+// they keep the rows whose second sweep is still to come.  us, through the
 // caches / past them, top_p 0.9 on inputs not used just before | the same input again and again: 1088 rows of 128256 bf16
 // logits 211 / 195 | 211 / 178, 685 rows of 151936 158 / 140 | 156 / 126, 256 rows of 151936 fp32 (311 MB in all) 114 / 87 |
 // 94 / 84, but 300 rows of 151936 bf16 (182 MB) 96 / 86 | 73 / 85: the line is drawn for inputs that are in the cache already.
 // A call that reads the output next finds none of it there: svip_verify behind 1088 rows takes 57 us instead of 47, and the two
 // together 280 / 254.  A single sweep gains nothing (top_k 50, 1088 rows 165 / 167); a plain copy does (1088 rows 114 / 110).
-// Without masses there is little to do between the loads: two at a time, each with its own check, beat four without branches.
-// top_k 50, us, four / two: 1 row of 32000 fp32 logits 17.8 / 17.4, 1 of 50257 fp16 19.7 / 19.1, 512 of 32000 bf16 31.7 / 30.4, 1088 of 151936
-// bf16 179.7 / 176.2; but 16 of 151936 fp32 34.4 / 35.1.
 template <typename DT, bool FUSED, bool MASS, int U>
 __device__ __forceinline__ unsigned long long candidate_sweep(const DT *row, DT *dst, int V, unsigned pivot, unsigned cap, const MassMeasure &mass,
-                                                              float fix_scale, bool stream, WarpLds &L)
+                                                    float fix_scale, bool stream, WarpLds &L)
 {
     constexpr int N = VecOf<DT>::N, PER = N / 4;                 // logits per word
-    const Threshold<DT> pv(pivot);
-    const u32x4 low = neg_inf_words<DT>();
-    const int nvec = (V + N - 1) / N;
+    constexpr bool SIGNED = MASS && N == 8;
+    const std::conditional_t<SIGNED, SignedThreshold<DT>, Threshold<DT>> pv(pivot);       // (without a mass the branch costs more than it saves)
+    u32x4 low = neg_inf_words<DT>();
+    if (MASS) asm("" : "+v"(low));                 // (or the masking takes two instructions per word)
+    const int nvec = (V + N - 1) / N, whole = V / N;
+    MassMeasure measure = mass;
+    measure.sc.c_hi = in_vgpr(mass.sc.c_hi);
+    measure.sc.c_lo = in_vgpr(mass.sc.c_lo);
     MassSum sum(fix_scale);
+    const auto note = [&](const typename RawOf<DT>::type &r, int vi, double &acc, u32x4 &o) {
+        if (MASS) {
+            float z[N];
+            unpack<DT>(r, z);
+#pragma unroll
+            for (int e = 0; e < N; ++e) MassSum::add(acc, measure.weight(z[e]));
+        }
+        const u32x4 w = __builtin_bit_cast(u32x4, r);
+        unsigned m[4];
+        if constexpr (SIGNED) {
+            pv.below(w, m);
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) m[i] = pv.below(w[i]);
+        }
+        if ((m[0] & m[1] & m[2] & m[3]) != 0xFFFFFFFFu) {
+            unsigned at = 0u;                                    // one bit per candidate
+#pragma unroll
+            for (int i = 0; i < 4; ++i) at |= (~m[i] & (PER == 2 ? 0x00010001u : 1u)) << (PER * i);
+            if (PER == 2) at = (at | (at >> 15)) & 0xFFu;
+            unsigned slot = lds_add(&L.n_list, (unsigned)__popc(at));
+            while (at) {
+                const int e = __ffs((int)at) - 1, i = e / PER;
+                at &= at - 1u;
+                const unsigned word = i & 2 ? (i & 1 ? w[3] : w[2]) : (i & 1 ? w[1] : w[0]);
+                float v;
+                if constexpr (PER == 1) v = __uint_as_float(word);
+                else v = widen(DT{(uint16_t)(e & 1 ? word >> 16 : word)});
+                if (slot < cap) {
+                    L.pairs[slot] = value_key(v);
+                    if (FUSED) L.pairs[cap + slot] = (unsigned)(vi * N + e);
+                }
+                ++slot;
+            }
+        }
+        if (FUSED) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) o[i] = (w[i] & ~m[i]) | (low[i] & m[i]);
+        }
+    };
+    const bool last_use = FUSED && stream && MASS;
     if (MASS) MassSum::begin();
-    for (int v0 = threadIdx.x; v0 < nvec; v0 += U * WARP_WG) {
+    int v0 = threadIdx.x;
+    for (; MASS && v0 + (U - 1) * WARP_WG < whole; v0 += U * WARP_WG) {       // whole vectors, without a check
+        typedef typename RawOf<DT>::type R;
+        R r[U];
+        double acc = sum.zero;
+        if (last_use) {
+            asm volatile("");                      // (else the compiler makes one of the two branches, and drops what differs)
+#pragma unroll
+            for (int u = 0; u < U; ++u) r[u] = load_raw<DT>(row, v0 + u * WARP_WG);
+            asm volatile("");
+        } else {
+#pragma unroll
+            for (int u = 0; u < U; ++u) r[u] = *(reinterpret_cast<const R *>(row) + v0 + u * WARP_WG);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            u32x4 o;
+            note(r[u], v0 + u * WARP_WG, acc, o);
+            if (FUSED) {
+                u32x4 *to = reinterpret_cast<u32x4 *>(dst) + v0 + u * WARP_WG;
+                if (last_use) {
+                    asm volatile("");
+                    __builtin_nontemporal_store(o, to);
+                    asm volatile("");
+                } else {
+                    *to = o;
+                }
+            }
+        }
+        if (MASS) sum.take(acc);
+    }
+    for (; v0 < nvec; v0 += U * WARP_WG) {
         typename RawOf<DT>::type r[U];
         double acc = sum.zero;
         if (MASS) {
-            warp_load_batch<DT, U>(row, v0, V, r, FUSED && stream);
+            warp_load_batch<DT, U>(row, v0, V, r, last_use);
         } else {
 #pragma unroll
             for (int u = 0; u < U; ++u) r[u] = warp_load<DT>(row, v0 + u * WARP_WG < nvec ? v0 + u * WARP_WG : v0, V);
@@ -474,46 +604,79 @@ __device__ __forceinline__ unsigned long long candidate_sweep(const DT *row, DT 
         for (int u = 0; u < U; ++u) {
             const int vi = v0 + u * WARP_WG;
             if (vi >= nvec) continue;
-            if (MASS) {
-                float z[N];
-                unpack<DT>(r[u], z);
-#pragma unroll
-                for (int e = 0; e < N; ++e) MassSum::add(acc, mass.weight(z[e]));
-            }
-            const u32x4 w = __builtin_bit_cast(u32x4, r[u]);
             u32x4 o;
-            unsigned m[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                m[i] = pv.below(w[i]);
-                o[i] = (w[i] & ~m[i]) | (low[i] & m[i]);
-            }
-            if ((m[0] & m[1] & m[2] & m[3]) != 0xFFFFFFFFu) {
-                unsigned at = 0u;                                // one bit per candidate
-#pragma unroll
-                for (int i = 0; i < 4; ++i) at |= (~m[i] & (PER == 2 ? 0x00010001u : 1u)) << (PER * i);
-                if (PER == 2) at = (at | (at >> 15)) & 0xFFu;
-                unsigned slot = lds_add(&L.n_list, (unsigned)__popc(at));
-                while (at) {
-                    const int e = __ffs((int)at) - 1, i = e / PER;
-                    at &= at - 1u;
-                    const unsigned word = i & 2 ? (i & 1 ? w[3] : w[2]) : (i & 1 ? w[1] : w[0]);
-                    float z;
-                    if constexpr (PER == 1) z = __uint_as_float(word);
-                    else z = widen(DT{(uint16_t)(e & 1 ? word >> 16 : word)});
-                    if (slot < cap) {
-                        L.pairs[slot] = value_key(z);
-                        if (FUSED) L.pairs[cap + slot] = (unsigned)(vi * N + e);
-                    }
-                    ++slot;
-                }
-            }
-            if (FUSED) store_words<DT>(dst, vi, V, o, MASS && stream);
+            note(r[u], vi, acc, o);
+            if (FUSED) store_words<DT>(dst, vi, V, o, last_use);
         }
         if (MASS) sum.take(acc);
     }
     if (MASS) MassSum::end();
     return sum.units;
+}
+
+// The largest value of the list (uniform; ends behind a barrier).
+__device__ __forceinline__ float list_max(const ListSource &ls, WarpLds &L)
+{
+    float m = neg_inf();
+    ls.for_each([&](unsigned, float z) { m = vmax(m, z); });
+    m = wave_max(m);
+    if ((threadIdx.x & 63) == 0) L.wave_max[threadIdx.x >> 6] = m;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < WARP_WAVES; ++w) m = vmax(m, L.wave_max[w]);
+    return m;
+}
+
+template <typename DT> constexpr int KEY_LOW = VecOf<DT>::N == 4 ? 0 : 13;       // low bits of a key that are the same in all numbers of one sign
+// The key v of the list with  measure(> v) < target <= measure(>= v), as select_digits, for keys between lo and hi: the first digit is as
+// fine as 2048 bins over that span are.  The upper digits of the keys themselves put a list into some ten bins, where the atomics of
+// as many lanes wait for one another; here 16-bit numbers come one to a bin, mostly, and one digit does.  us, top-k 50 and top-p 0.9 by
+// three such digits / so: 1 row of 128256 bf16 logits 29.0 / 22.3, 544 of 32000 51.1 / 35.8, 1088 of 128256 161 / 143; top-k alone 24.1 / 20.3,
+// 41.5 / 32.8, 148 / 138.  Keys of fp32 logits take three digits either way.  The low bits that all numbers share are zero in v.
+// *rem = target - measure(> v), 0 if the list falls short of the target.
+template <typename DT, typename Measure>
+__device__ __forceinline__ unsigned select_span(const ListSource &ls, unsigned lo, unsigned hi, Measure measure, unsigned long long target,
+                                                unsigned long long *rem, WarpLds &L)
+{
+    constexpr int LOW = KEY_LOW<DT>;
+    const int tid = threadIdx.x;
+    unsigned base = lo >> LOW << LOW;
+    int shift = 21 - __clz((int)((hi - base) | 1u));              // (hi - base) >> shift < 2048
+    if (shift < LOW) shift = LOW;
+    unsigned width = 0xFFFFFFFFu;                                 // keys of [base, base + width]
+#pragma unroll 1
+    for (;;) {
+        L.sub[tid] = 0ull;
+        L.sub[tid + WARP_WG] = 0ull;
+        __syncthreads();
+        ls.for_each([&](unsigned key, float z) {
+            if (key >= base && key - base <= width) atomicAdd(&L.sub[min((key - base) >> shift, WARP_BINS - 1u)], measure(z));      // (a NaN's is above hi)
+        });
+        __syncthreads();
+        const Crossing c = crossing(L.sub, target, -1.0, L);
+        base += c.digit << shift;
+        *rem = c.rem;
+        if (shift == LOW || c.rem == 0ull) return base;
+        width = (1u << shift) - 1u;
+        target = c.rem;
+        shift = shift - 11 > LOW ? shift - 11 : LOW;
+    }
+}
+
+// The output behind a sweep that has written it down to its pivot: the candidates below tau become -inf as well.  (The sweep's stores
+// are complete: every barrier since waited for them.)  Returns how many logits are kept.
+template <typename DT>
+__device__ __forceinline__ int drop_candidates(DT *dst, int V, unsigned tau, unsigned n, WarpLds &L)
+{
+    unsigned long long kept = 0ull;
+    for (unsigned i = threadIdx.x; i < n; i += WARP_WG) {
+        const unsigned idx = L.pairs[WARP_PAIRS + i];
+        if (idx < (unsigned)V) {
+            if (L.list[i] >= tau) kept += 1ull;
+            else store_one<DT>(dst + idx, neg_inf());
+        }
+    }
+    return (int)wg_sum_u64(kept, L);
 }
 
 // Shortcut for a small top_k: a pivot from a sample of the row (one vector per thread), aimed at
@@ -532,7 +695,7 @@ __device__ __forceinline__ int small_k_shortcut(const DT *row, DT *dst, int V, c
                                              unsigned *tau_out, int *kept_out, WarpLds &L)
 {
     constexpr int N = VecOf<DT>::N;
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int tid = threadIdx.x;
     const int nvec = (V + N - 1) / N;
     const int nsamp = nvec < WARP_WG ? nvec : WARP_WG;            // sampled vectors
     constexpr unsigned cap = fused ? WARP_PAIRS : WARP_CAP;
@@ -548,7 +711,7 @@ __device__ __forceinline__ int small_k_shortcut(const DT *row, DT *dst, int V, c
     }
     __syncthreads();
     const ListSource sample{L.list, (unsigned)(nsamp * N)};
-    const unsigned pivot = select_digits(sample, 0u, CountMeasure{}, 0u, 0, (unsigned long long)want, L);
+    const unsigned pivot = select_digits<KEY_BITS<DT>>(sample, 0u, CountMeasure{}, 0u, 0, (unsigned long long)want, L);
     if (tid == 0) L.n_list = 0u;
     __syncthreads();
     candidate_sweep<DT, fused, false, 2>(row, dst, V, pivot, cap, MassMeasure{}, a.fix_scale, a.stream, L);
@@ -557,16 +720,12 @@ __device__ __forceinline__ int small_k_shortcut(const DT *row, DT *dst, int V, c
     __syncthreads();
     if (n < (unsigned)a.top_k || n > cap) return 0;
     const ListSource ls{L.list, n};
-    unsigned tau = select_digits(ls, 0u, CountMeasure{}, 0u, 0, (unsigned long long)a.top_k, L);
+    // (fp32 keys take three digits either way)
+    const float m = N == 8 || P ? list_max(ls, L) : 0.f;
+    unsigned long long rem;
+    unsigned tau = N == 8 ? select_span<DT>(ls, pivot, value_key(m), CountMeasure{}, (unsigned long long)a.top_k, &rem, L)
+                          : select_digits<32>(ls, 0u, CountMeasure{}, 0u, 0, (unsigned long long)a.top_k, L);
     if (P) {
-        float m = neg_inf();
-        ls.for_each([&](unsigned, float z) { m = vmax(m, z); });
-        m = wave_max(m);
-        if (lane == 0) L.wave_max[wave] = m;
-        __syncthreads();
-        m = L.wave_max[0];
-#pragma unroll
-        for (int w = 1; w < WARP_WAVES; ++w) m = vmax(m, L.wave_max[w]);
         const MassMeasure mass{m, a.sc, a.fix_scale * (1.0f / 4294967296.0f)};
         unsigned long long mine = 0ull;
         ls.for_each([&](unsigned key, float z) { mine += key >= tau ? mass(z) : 0ull; });
@@ -574,22 +733,13 @@ __device__ __forceinline__ int small_k_shortcut(const DT *row, DT *dst, int V, c
         unsigned long long target = (unsigned long long)llrint(a.top_p * (double)Zk);
         target = target ? target : 1ull;
         if (Zk >= target) {
-            const unsigned tau_p = select_digits(ls, tau, mass, 0u, 0, target, L);
+            const unsigned tau_p = select_span<DT>(ls, tau, value_key(m), mass, target, &rem, L);
             tau = tau_p > tau ? tau_p : tau;
         }
     }
     *tau_out = tau;
     if (!fused) return 1;
-    // the sweep's stores are complete (every barrier since waited for them): drop the candidates below tau
-    unsigned long long kept = 0ull;
-    for (unsigned i = tid; i < n; i += WARP_WG) {
-        const unsigned idx = L.pairs[cap + i];
-        if (idx < (unsigned)V) {
-            if (L.list[i] >= tau) kept += 1ull;
-            else store_one<DT>(dst + idx, neg_inf());
-        }
-    }
-    *kept_out = (int)wg_sum_u64(kept, L);
+    *kept_out = drop_candidates(dst, V, tau, n, L);
     return 2;
 }
 
@@ -616,7 +766,7 @@ __device__ __forceinline__ int nucleus_shortcut(const DT *row, DT *dst, int V, c
     const int nvec = (V + N - 1) / N;
     constexpr unsigned cap = fused ? WARP_PAIRS : WARP_CAP;
     float mine_max = neg_inf();
-    for_each_vector<DT>(row, V, [&](int, const float(&z)[N]) { mine_max = vmax(mine_max, tree_max<N>(z)); });
+    for_each_vector<DT, N == 8>(row, V, [&](int, const float(&z)[N]) { mine_max = vmax(mine_max, tree_max<N>(z)); });
     const float pair = vmax(mine_max, __shfl_xor(mine_max, 1));
     const float group = vmax(pair, __shfl_xor(pair, 2));
     // the same runs of whole cache lines as in small_k_shortcut
@@ -676,25 +826,13 @@ __device__ __forceinline__ int nucleus_shortcut(const DT *row, DT *dst, int V, c
     const unsigned n = L.n_list;
     if (n > cap) return 0;
     const ListSource ls{L.list, n};
-    mine = 0ull;
-    ls.for_each([&](unsigned, float z) { mine += mass(z); });
-    const unsigned long long Zl = wg_sum_u64(mine, L);
-    unsigned long long target = (unsigned long long)llrint(a.top_p * (double)Z);
+    unsigned long long target = (unsigned long long)llrint(a.top_p * (double)Z), rem;
     target = target ? target : 1ull;
-    if (Zl < target) return 0;
-    const unsigned tau = select_digits(ls, 0u, mass, 0u, 0, target, L);
+    const unsigned tau = select_span<DT>(ls, value_key(pz), value_key(m), mass, target, &rem, L);
+    if (rem == 0ull) return 0;                                    // the list falls short of it
     *tau_out = tau;
     if (!fused) return 1;
-    // the sweep's stores are complete (every barrier since waited for them): drop the candidates below tau
-    unsigned long long kept = 0ull;
-    for (unsigned i = tid; i < n; i += WARP_WG) {
-        const unsigned idx = L.pairs[cap + i];
-        if (idx < (unsigned)V) {
-            if (L.list[i] >= tau) kept += 1ull;
-            else store_one<DT>(dst + idx, neg_inf());
-        }
-    }
-    *kept_out = (int)wg_sum_u64(kept, L);
+    *kept_out = drop_candidates(dst, V, tau, n, L);
     return 2;
 }
 
@@ -755,8 +893,8 @@ __device__ __forceinline__ void plain_copy(const DT *row, DT *dst, int V, bool s
 }
 
 // The keys of first-digit bin d1 into L.list (the caller has checked that they fit).
-template <typename DT>
-__device__ __forceinline__ void collect(const RowSource<DT> &rs, unsigned d1, WarpLds &L)
+template <typename Row>
+__device__ __forceinline__ void collect(const Row &rs, unsigned d1, WarpLds &L)
 {
     if (threadIdx.x == 0) L.n_list = 0u;
     __syncthreads();
@@ -769,9 +907,10 @@ __device__ __forceinline__ void collect(const RowSource<DT> &rs, unsigned d1, Wa
     __syncthreads();
 }
 
-// grid (rows), WARP_WG threads.  NUCLEUS: top_p alone (an instance of its own: either shortcut's code costs the other
-// one registers).
-template <typename DT, bool NUCLEUS>
+// grid (rows), WARP_WG threads.  Instances of their own, because the shortcuts' code costs the other paths registers: NUCLEUS for
+// top_p alone over rows that have a shortcut, HISTOGRAMS for top_p alone without one (rows of 65536 bf16 logits 4 % slower otherwise).
+enum WarpKind { GENERAL, NUCLEUS, HISTOGRAMS };
+template <typename DT, WarpKind KIND>
 __global__ __launch_bounds__(WARP_WG, 8) void k_warp(WarpArgs a)
 {
     constexpr int N = VecOf<DT>::N;
@@ -783,7 +922,7 @@ __global__ __launch_bounds__(WARP_WG, 8) void k_warp(WarpArgs a)
     DT *dst = static_cast<DT *>(a.out) + off;
     const int V = a.V;
 
-    const bool K = !NUCLEUS && a.top_k > 0 && a.top_k < V, P = NUCLEUS || a.top_p < 1.0;
+    const bool K = KIND == GENERAL && a.top_k > 0 && a.top_k < V, P = KIND != GENERAL || a.top_p < 1.0;
     if (!K && !P) {
         plain_copy<DT>(row, dst, V, a.stream);
         if (tid == 0) {
@@ -792,7 +931,8 @@ __global__ __launch_bounds__(WARP_WG, 8) void k_warp(WarpArgs a)
         }
         return;
     }
-    const RowSource<DT> rs{row, V};
+    constexpr bool LONG = KIND == NUCLEUS && N == 8;
+    const RowSource<DT, LONG> rs{row, V};
     unsigned tau = 0u;                      // keep keys >= tau
     int kept = 0;
     int decided = 0;
@@ -801,8 +941,8 @@ __global__ __launch_bounds__(WARP_WG, 8) void k_warp(WarpArgs a)
                       ? small_k_shortcut<DT, true>(row, dst, V, a, P, &tau, &kept, L)
                       : small_k_shortcut<DT, false>(row, dst, V, a, P, &tau, &kept, L);
     float m = neg_inf();
-    const bool m_known = NUCLEUS && !a.no_shortcut && V >= NUCLEUS_MIN_V;
-    if (m_known)
+    const bool m_known = KIND == NUCLEUS;
+    if constexpr (KIND == NUCLEUS)
         decided = a.in != a.out ? nucleus_shortcut<DT, true>(row, dst, V, a, &tau, &kept, &m, L)
                                 : nucleus_shortcut<DT, false>(row, dst, V, a, &tau, &kept, &m, L);
     if (a.routes && tid == 0) a.routes[y] = decided;
@@ -815,7 +955,7 @@ __global__ __launch_bounds__(WARP_WG, 8) void k_warp(WarpArgs a)
             L.cnt[tid + WARP_WG] = 0u;
             __syncthreads();
         }
-        if (!m_known) for_each_vector<DT>(row, V, [&](int, const float(&z)[N]) {
+        if (!m_known) for_each_vector<DT, LONG>(row, V, [&](int, const float(&z)[N]) {
             if (P) m = vmax(m, tree_max<N>(z));
             if (K) {
 #pragma unroll
@@ -859,7 +999,7 @@ __global__ __launch_bounds__(WARP_WG, 8) void k_warp(WarpArgs a)
         }
         __syncthreads();
         const ListSource ls{L.list, listA ? L.n_list : 0u};
-        if (K) tau = listA ? refine(ls, 0u, CountMeasure{}, d_k, k_rem, L) : refine(rs, 0u, CountMeasure{}, d_k, k_rem, L);
+        if (K) tau = listA ? refine<KEY_BITS<DT>>(ls, 0u, CountMeasure{}, d_k, k_rem, L) : refine<KEY_BITS<DT>>(rs, 0u, CountMeasure{}, d_k, k_rem, L);
         if (P) {
             if (K) {
                 // bin d_k counts only with its keys >= tau
@@ -881,16 +1021,16 @@ __global__ __launch_bounds__(WARP_WG, 8) void k_warp(WarpArgs a)
             unsigned tau_p = 0u;
             if (c.rem != 0ull) {
                 if (K && c.digit == d_k) {
-                    tau_p = listA ? refine(ls, tau, mass, d_k, c.rem, L) : refine(rs, tau, mass, d_k, c.rem, L);
+                    tau_p = listA ? refine<KEY_BITS<DT>>(ls, tau, mass, d_k, c.rem, L) : refine<KEY_BITS<DT>>(rs, tau, mass, d_k, c.rem, L);
                 } else {
                     // sweep 3; a bin too crowded for the list is refined by sweeps over the row instead
                     const bool fits = !K || L.cnt[c.digit] <= (unsigned)WARP_CAP;
-                    if (fits) collect<DT>(rs, c.digit, L);
+                    if (fits) collect(rs, c.digit, L);
                     if (fits && L.n_list <= (unsigned)WARP_CAP) {
                         const ListSource lp{L.list, L.n_list};
-                        tau_p = refine(lp, tau, mass, c.digit, c.rem, L);
+                        tau_p = refine<KEY_BITS<DT>>(lp, tau, mass, c.digit, c.rem, L);
                     } else {
-                        tau_p = refine(rs, tau, mass, c.digit, c.rem, L);
+                        tau_p = refine<KEY_BITS<DT>>(rs, tau, mass, c.digit, c.rem, L);
                     }
                 }
             }
