@@ -1,0 +1,48 @@
+"""Verification, diagnostics and greedy verification of rows of 7 to 32 tiles, which are cut into up to four slices where there are few of
+them: against the same calls with one slice per row.  Comparisons are exact; probabilities and divergences differ by the order of fp32 and
+fp64 partial sums, logsumexps by 2^-22 of themselves at most, which is 1e-5 of a probability at most for logsumexps below 40."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+BF, F16, F32 = torch.bfloat16, torch.float16, torch.float32
+CASES = [(BF, 3, 5, 7 * 2048 - 3), (BF, 3, 5, 8 * 2048), (F16, 2, 7, 15 * 2048 + 1), (F32, 5, 4, 16 * 1024 - 5), (BF, 9, 6, 31 * 2048 + 9),
+         (F32, 2, 3, 32 * 1024), (BF, 40, 5, 11 * 2048), (BF, 90, 5, 11 * 2048)]
+
+
+@pytest.mark.parametrize("dtype,B,k,V", CASES)
+@pytest.mark.parametrize("lse", [True, False])
+def test_slices_of_short_rows(svip, dtype, B, k, V, lse):
+    g = torch.Generator(device="cuda").manual_seed(V + B)
+    per16 = 4 if dtype == F32 else 8
+    stride = -(-V // per16) * per16
+    draft = torch.empty(B, k, stride, dtype=dtype, device="cuda")[:, :, :V]
+    target = torch.empty(B, k + 1, stride, dtype=dtype, device="cuda")[:, :, :V]
+    z = torch.randn(B, k + 1, V, device="cuda", generator=g) * 4
+    draft.copy_(z[:, :k])
+    target.copy_(z + torch.randn(z.shape, device="cuda", generator=g))
+    tokens = draft.float().argmax(-1).int()
+    draft_len = torch.randint(0, k + 1, (B,), device="cuda", generator=g, dtype=torch.int32)
+    draft_lse = torch.logsumexp(draft.double(), -1) if lse else None
+    ua, ur = torch.rand(B, k, device="cuda", generator=g), torch.rand(B, device="cuda", generator=g)
+    got = []
+    try:
+        for slices in (1, 0):
+            svip.bench_set_tuning(stats_slices=slices, pair_slices=slices)
+            ws = svip.new_workspace(B, k, V)
+            o = {n: torch.full((B,), -7, dtype=torch.int32, device="cuda") for n in ("nacc", "next", "gacc", "gnext")}
+            prob, stats = torch.zeros(B, k, device="cuda"), torch.zeros(B, k, svip.PAIR_NSTAT, device="cuda")
+            svip.verify(target, draft, temperature=1.0, draft_tokens=tokens, draft_len=draft_len, draft_lse=draft_lse, u_accept=ua,
+                        u_resample=ur, n_accepted_out=o["nacc"], next_token_out=o["next"], accept_prob_out=prob, workspace=ws)
+            svip.verify_greedy(target, draft_tokens=tokens, draft_len=draft_len, n_accepted_out=o["gacc"], next_token_out=o["gnext"],
+                               workspace=ws)
+            svip.pair_stats(target, draft, temperature=1.0, draft_len=draft_len, c=0.18, stats_out=stats, workspace=ws, draft_lse=draft_lse)
+            torch.cuda.synchronize()
+            got.append((o, prob, stats[:, :, :4].nan_to_num(-1.0)))
+    finally:
+        svip.bench_set_tuning()
+    for n in got[0][0]:
+        assert torch.equal(got[0][0][n], got[1][0][n]), n
+    assert (got[0][1] - got[1][1]).abs().max() <= 1e-5
+    assert ((got[0][2] - got[1][2]).abs() <= 1e-5 * got[0][2].abs().clamp_min(1.0)).all()
