@@ -90,7 +90,8 @@ size_t svip_workspace_bytes(int B, int k_max, int V);
 
 /* Bytes of workspace one particular call uses for these sizes (pure host function; 0 on bad
  * arguments).  svip_workspace_bytes(B, k_max, V) is never smaller than any of them; the calls
- * themselves check against these figures. */
+ * themselves check against these figures.  Verification and diagnostics of few short rows cut them finer where the workspace
+ * holds more than that, as one of svip_workspace_bytes does; their sums are then added in another order. */
 typedef enum {
     SVIP_CALL_DRAFT_STEP = 0,            /* svip_draft_step, svip_draft_step_greedy */
     SVIP_CALL_VERIFY = 1,                /* svip_verify with draft_lse given */

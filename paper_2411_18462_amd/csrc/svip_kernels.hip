@@ -111,7 +111,7 @@ static int *g_warp_routes = nullptr;             // svip_bench_warp_routes
 // Slices per row of the passes that give a slice to a workgroup: enough workgroups to fill 256 CUs several
 // times over, at most MAX_SLICES; want_one_batch (the residual pass): slices of min_tiles tiles, which the
 // sampler scans as one batch and whose tiles each get a mass of their own.
-static Geo make_geo(int V, int vec, long long rows, bool want_one_batch, int forced_ns, int min_tiles = 4, bool draft_rows = false)
+static Geo make_geo(int V, int vec, long long rows, bool want_one_batch, int forced_ns, int min_tiles = 4, long long fine = 0)
 {
     Geo g;
     g.V = V;
@@ -130,8 +130,7 @@ static Geo make_geo(int V, int vec, long long rows, bool want_one_batch, int for
         if (rows >= 512 && g.ntiles >= 14) ns = (g.ntiles + 6) / 7;
     } else {
         // streaming passes: about 8192 workgroups of at least 8 tiles each; rows of fewer than 32 tiles up to four slices (as many as
-        // the acceptance test requests together) of at least 4 while that makes few workgroups, or twice as many where a sequence's draft
-        // rows are read as well.  us, 8 tiles / so: svip_verify of 64 sequences of 4 positions of 20000 bf16 logits (10 tiles, 640 workgroups)
+        // the acceptance test requests together) of at least 4 while that makes at most `fine` workgroups.  us, 8 tiles / so: svip_verify of 64 sequences of 4 positions of 20000 bf16 logits (10 tiles, 640 workgroups)
         // 16.6 / 15.45, svip_pair_stats 21.25 / 18.6, svip_verify_greedy 9.1 / 7.65; 8 of 30 of 40000 (20 tiles, 992) 17.1 / 16.4, 23.95 / 21.3,
         // 9.1 / 8.6; but greedy 32 of 8 of 50257 (25 tiles, 1152) 10.3 / 10.6, and of 100 of 4 of 32000 (2000) 10.5 / 10.7; with logsumexps
         // recomputed svip_verify of 32 of 8 of 50257 (2176) 23.4 / 22.8, svip_pair_stats 29.65 / 28.97.
@@ -139,7 +138,7 @@ static Geo make_geo(int V, int vec, long long rows, bool want_one_batch, int for
         long long most = g.ntiles / 8;
         if (g.ntiles < 32) {
             const long long finer = g.ntiles >= 16 ? 4 : g.ntiles / 4;
-            if (rows * finer <= (draft_rows ? 2304 : 1000)) most = finer;
+            if (rows * finer <= fine) most = finer;
         }
         if (ns > most) ns = most;
     }
@@ -271,10 +270,12 @@ static Geo geo_draft(int B, int V, int vec, int forced)
     g.ns = (g.ntiles + g.tps - 1) / g.tps;
     return g;
 }
-static Geo geo_stats(long long stat_rows, int V, int vec, int forced, bool draft_rows = false)
+// A call needs a workspace for slices of at least 8 tiles (fine = 0), and takes finer ones where what it was given holds them.
+static Geo geo_stats(long long stat_rows, int V, int vec, int forced, long long fine = 0)
 {
-    return make_geo(V, vec, stat_rows, false, forced, 4, draft_rows);
+    return make_geo(V, vec, stat_rows, false, forced, 4, fine);
 }
+constexpr long long FINE = 1000, FINE_DRAFT_ROWS = 2304;          // (the latter where a sequence's draft rows are read as well)
 // the residual pass: slices of four tiles like the draft step (at 64 sequences of 128K logits, 16 slices of
 // 4 tiles take 13 us, 32 slices of 2 tiles 16 us, 8 slices 20 us, one tile per slice 26 us)
 static Geo geo_resid(int B, int V, int vec, int forced) { return make_geo(V, vec, B, true, forced, 4); }
@@ -547,6 +548,8 @@ static svip_status verify_greedy_call(const VerifyCall &c)
     GreedyArgs a;
     a.geo = geo_stats(rows, c.V, vec, g_tune.stats_slices);
     if (!workspace_ok(c.workspace, c.workspace_bytes, need_verify_greedy(c.B, c.k_max, a.geo))) return SVIP_ERR_WORKSPACE;
+    const Geo finer = geo_stats(rows, c.V, vec, g_tune.stats_slices, FINE);
+    if (workspace_ok(c.workspace, c.workspace_bytes, need_verify_greedy(c.B, c.k_max, finer))) a.geo = finer;
     const Workspace w = carve(c.workspace, c.workspace_bytes, c.B, 0);
     a.target = c.target;
     a.seq_t = c.seq_stride_t;
@@ -614,10 +617,12 @@ svip_status verify_call(const VerifyCall &c)
     if (!(c.temperature > 0.f) || !isfinite(c.temperature)) return SVIP_ERR_PARAM;
 
     VerifyArgs a;
-    a.geo = geo_stats(stat_rows, c.V, vec, g_tune.stats_slices, kd != 0);
+    a.geo = geo_stats(stat_rows, c.V, vec, g_tune.stats_slices);
     a.geo_s = geo_resid(c.B, c.V, vec, g_tune.resid_slices);
     if (!workspace_ok(c.workspace, c.workspace_bytes, need_verify(c.B, c.k_max, kd != 0, a.geo, a.geo_s)))
         return SVIP_ERR_WORKSPACE;
+    const Geo finer = geo_stats(stat_rows, c.V, vec, g_tune.stats_slices, kd ? FINE_DRAFT_ROWS : FINE);
+    if (workspace_ok(c.workspace, c.workspace_bytes, need_verify(c.B, c.k_max, kd != 0, finer, a.geo_s))) a.geo = finer;
     a.target = c.target;
     a.draft = c.draft;
     a.seq_t = c.seq_stride_t;
@@ -708,13 +713,13 @@ size_t svip_workspace_needed(int call, int dtype, int B, int k_max, int V)
         case SVIP_CALL_DRAFT_STEP: return need_draft(B, geo_draft(B, V, vec, 0), false);      // greedy records are no larger
         case SVIP_CALL_VERIFY: return need_verify(B, k_max, false, geo_stats(rows_t, V, vec, 0), geo_resid(B, V, vec, 0));
         case SVIP_CALL_VERIFY_RECOMPUTE:
-            return need_verify(B, k_max, true, geo_stats(rows_all, V, vec, 0, true), geo_resid(B, V, vec, 0));
+            return need_verify(B, k_max, true, geo_stats(rows_all, V, vec, 0), geo_resid(B, V, vec, 0));
         case SVIP_CALL_VERIFY_GREEDY: return need_verify_greedy(B, k_max, geo_stats(rows_t, V, vec, 0));
         case SVIP_CALL_PAIR_STATS:
             return need_pair(B, k_max, false, geo_stats(rows_t, V, vec, 0), geo_stats((long long)B * k_max, V, vec, 0),
                              nullptr, nullptr);
         case SVIP_CALL_PAIR_STATS_RECOMPUTE:
-            return need_pair(B, k_max, true, geo_stats(rows_all, V, vec, 0, true), geo_stats((long long)B * k_max, V, vec, 0),
+            return need_pair(B, k_max, true, geo_stats(rows_all, V, vec, 0), geo_stats((long long)B * k_max, V, vec, 0),
                              nullptr, nullptr);
         default: return 0;
     }
@@ -883,12 +888,19 @@ svip_status svip_pair_stats(const void *target_logits, const void *draft_logits,
     if (!(temperature > 0.f) || !isfinite(temperature) || !(c >= 0.f) || !isfinite(c)) return SVIP_ERR_PARAM;
 
     PairArgs a;
-    a.v.geo = geo_stats(stat_rows, V, vec, g_tune.stats_slices, kd != 0);
-    a.v.geo_s = a.v.geo;
+    a.v.geo = geo_stats(stat_rows, V, vec, g_tune.stats_slices);
     a.geo2 = geo_stats(pos, V, vec, g_tune.pair_slices);
     size_t part_bytes, L_bytes;
     const size_t need = need_pair(B, k_max, kd != 0, a.v.geo, a.geo2, &part_bytes, &L_bytes);
     if (!workspace_ok(workspace, workspace_bytes, need)) return SVIP_ERR_WORKSPACE;
+    const Geo finer = geo_stats(stat_rows, V, vec, g_tune.stats_slices, kd ? FINE_DRAFT_ROWS : FINE);
+    const Geo finer2 = geo_stats(pos, V, vec, g_tune.pair_slices, FINE);
+    if (workspace_ok(workspace, workspace_bytes, need_pair(B, k_max, kd != 0, finer, finer2, nullptr, nullptr))) {
+        a.v.geo = finer;
+        a.geo2 = finer2;
+        need_pair(B, k_max, kd != 0, a.v.geo, a.geo2, &part_bytes, &L_bytes);
+    }
+    a.v.geo_s = a.v.geo;
     a.v.target = target_logits;
     a.v.draft = draft_logits;
     a.v.seq_t = seq_stride_t;

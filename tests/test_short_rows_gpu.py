@@ -28,9 +28,10 @@ def test_slices_of_short_rows(svip, dtype, B, k, V, lse):
     ua, ur = torch.rand(B, k, device="cuda", generator=g), torch.rand(B, device="cuda", generator=g)
     got = []
     try:
-        for slices in (1, 0):
+        for slices, exact in ((1, False), (0, False), (0, True)):          # exact: a workspace with no room for finer slices
             svip.bench_set_tuning(stats_slices=slices, pair_slices=slices)
-            ws = svip.new_workspace(B, k, V)
+            need = max(svip.workspace_needed(call, dtype, B, k, V) for call in ((1, 3, 4) if lse else (2, 3, 5)))
+            ws = torch.zeros(need, dtype=torch.uint8, device="cuda") if exact else svip.new_workspace(B, k, V)
             o = {n: torch.full((B,), -7, dtype=torch.int32, device="cuda") for n in ("nacc", "next", "gacc", "gnext")}
             prob, stats = torch.zeros(B, k, device="cuda"), torch.zeros(B, k, svip.PAIR_NSTAT, device="cuda")
             svip.verify(target, draft, temperature=1.0, draft_tokens=tokens, draft_len=draft_len, draft_lse=draft_lse, u_accept=ua,
@@ -42,7 +43,8 @@ def test_slices_of_short_rows(svip, dtype, B, k, V, lse):
             got.append((o, prob, stats[:, :, :4].nan_to_num(-1.0)))
     finally:
         svip.bench_set_tuning()
-    for n in got[0][0]:
-        assert torch.equal(got[0][0][n], got[1][0][n]), n
-    assert (got[0][1] - got[1][1]).abs().max() <= 1e-5
-    assert ((got[0][2] - got[1][2]).abs() <= 1e-5 * got[0][2].abs().clamp_min(1.0)).all()
+    for other in got[1:]:
+        for n in got[0][0]:
+            assert torch.equal(got[0][0][n], other[0][n]), n
+        assert (got[0][1] - other[1]).abs().max() <= 1e-5
+        assert ((got[0][2] - other[2]).abs() <= 1e-5 * got[0][2].abs().clamp_min(1.0)).all()
