@@ -3,6 +3,7 @@
 #include "exchange.h"
 #include "kernel_args.h"
 #include "sample_weights.h"
+#include "trace_rows.h"
 
 namespace svip {
 
@@ -11,6 +12,13 @@ namespace svip {
 __device__ __forceinline__ long long draft_row_offset(const DraftArgs &a, int b, int j)
 {
     return (long long)b * a.row_stride + (a.pos ? (long long)(__builtin_amdgcn_readfirstlane(a.pos[b]) + j) * a.pos_stride : 0ll);
+}
+// The row that a step's statistics request before the stop flag is looked at (behind it the row is that of step_j).
+__device__ __forceinline__ long long step_row_offset(const DraftArgs &a, int b)
+{
+    long long row = 0;
+    if (a.pos) row = __builtin_amdgcn_readfirstlane(a.pos[b]) + step_row(a.step_j, __builtin_amdgcn_readfirstlane(a.cap[b]));
+    return (long long)b * a.row_stride + row * a.pos_stride;
 }
 __device__ __forceinline__ bool at_cap(const DraftArgs &a, int b)
 {
@@ -380,7 +388,7 @@ __global__ __launch_bounds__(WG, TPS == 1 ? 8 : 6) void k_draft_stats(DraftArgs 
         b = (int)(a.div == 1u ? gw : __umulhi(gw, a.div_magic));
         r = (int)(gw - (unsigned)b * (unsigned)nrec);
     }
-    const DT *row = static_cast<const DT *>(a.logits) + draft_row_offset(a, b, a.step_j);
+    const DT *row = static_cast<const DT *>(a.logits) + step_row_offset(a, b);
     const int tps = TPS ? TPS : a.geo.tps;
     const int tb = r * tps, te = min(tb + tps, a.geo.ntiles);
     const int fe = min(te, a.geo.V / (WG * N));           // end of the tiles wholly inside the row
@@ -746,7 +754,7 @@ __global__ __launch_bounds__(WG, 4) void k_draft_step(DraftArgs a)
     const int b = (int)(q * 8u + xcd), r = (int)s * NWAVE + wave;
     if (b >= a.B) return;
     const long long o = (long long)b * a.io_stride;
-    const DT *row = static_cast<const DT *>(a.logits) + draft_row_offset(a, b, a.step_j);
+    const DT *row = static_cast<const DT *>(a.logits) + step_row_offset(a, b);
     const unsigned flag = request_stop_flag(a, b);
     const float u = KIND == QUARTERS ? a.u[o] : 0.f;
     const size_t first = (size_t)b * nrec;

@@ -83,7 +83,7 @@ struct DraftArgs {
     long long row_stride;   // between the rows of consecutive sequences
     const int *pos;         // optional [B]: sequence b reads trace row pos[b] + step_j of its own trace
     long long pos_stride;   // elements between consecutive trace rows (used with pos)
-    const int *cap;         // optional [B]: per-sequence limit on the draft length (at most k_max)
+    const int *cap;         // optional [B], given with pos: per-sequence limit on the draft length (at most k_max)
     int B;
     Geo geo;
     Scale sc;

@@ -16,7 +16,7 @@ struct DraftCall {
     long long row_stride;        // elements between the rows (or traces) of consecutive sequences
     const int *pos;              // device [B] or nullptr: sequence b reads trace row pos[b] + step_j
     long long pos_stride;        // elements between consecutive trace rows
-    const int *cap;              // device [B] or nullptr: per-sequence draft-length limit (<= k_max)
+    const int *cap;              // device [B] or nullptr, given with pos: per-sequence draft-length limit (<= k_max)
     float temperature, h;
     int step_j, k_max;
     const float *u_sample;

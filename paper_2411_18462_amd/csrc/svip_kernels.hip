@@ -290,6 +290,7 @@ static bool workspace_ok(const void *ws, size_t have, size_t need)
 static svip_status check_draft(const DraftCall &c)
 {
     if (!c.logits || (!c.greedy && !c.u_sample) || !c.token_out || !c.lse_out || !c.stop_out) return SVIP_ERR_NULL;
+    if (c.pos && !c.cap) return SVIP_ERR_NULL;
     if (!dtype_ok(c.dtype)) return SVIP_ERR_DTYPE;
     if (c.B <= 0 || c.B > MAX_BATCH || c.V <= 0 || c.k_max < 1 || c.k_max > SVIP_MAX_K || c.step_j < 0 ||
         c.step_j >= c.k_max || c.io_stride < 1 || c.row_stride < c.V || (c.pos && c.pos_stride < c.V))
