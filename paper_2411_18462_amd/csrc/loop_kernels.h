@@ -18,7 +18,7 @@ struct GroupArgs {
     const void *target;        // traces laid out as the draft's
     unsigned long long *keys;  // [(group + 1) * lane_rows][ns] first-maximum keys of the target rows
     unsigned *flags;           // sticky device-data flags
-    int ahead;                 // rows to read past the last token's, see stream_rows
+    int ahead;                 // rows to read past the last token's, see trace_rows.h
     int last_round;            // a sequence pauses where its next round would be this one
     Mail active, running, rounds;      // counter[1], counter[0], counter[2] as the launch finds them
     LoopArgs l;
@@ -109,18 +109,12 @@ __global__ __launch_bounds__(GROUP_FINISH_WAVES * 64) void k_group_finish(GroupA
 // MB (5.3 TB/s) and k_stream_advance 19 us for 101 rows and 33 rounds (records 8, logarithms 1, rounds 6), the whole generation
 // 144 us with what the host does before and after; a pair of launches per round, all of them latency, 482.
 
-// Draft rows that a launch reads of a sequence whose round began at `pos` and of which `drafted` are known: up to where all
-// tokens are there, and `ahead` more for the round that gets there last; behind that the unfinished draft, as many rows again as
-// are known of it.  At least 1, and no further than the last row that a round of the sequence can reach.
-__device__ __forceinline__ int stream_rows(const GroupArgs &a, int pos, int drafted, int cap, int start)
+// Draft rows that a launch reads of a sequence, see trace_rows.h.
+__device__ __forceinline__ int rows_to_read(const GroupArgs &a, int pos, int drafted, int cap, int start)
 {
-    const int known = drafted > 0 ? drafted : 0;                                         // relative to pos, as all below
-    const int goal = (int)min((long long)start + a.l.max_new, (long long)a.l.L + a.l.gamma_max) - pos;
-    int n = goal + a.ahead - known;
-    if (known >= goal) n = min(max(a.ahead, known), cap - known);
-    n = min(n, min(a.l.L - pos, goal + a.l.gamma_max) - 1 - known);
-    return min(n, a.group);
+    return stream_rows(pos, drafted, cap, start, a.l.L, a.l.gamma_max, a.l.max_new, a.ahead, a.group);
 }
+
 // First-maximum key (argmax_key) of one tile of a row by one wave.
 template <typename DT>
 __device__ __forceinline__ unsigned long long tile_argmax(const DT *row, int V, int tile)
@@ -167,7 +161,7 @@ __global__ __launch_bounds__(WG, 8) void k_stream_rows(GroupArgs a)
     const int cap = min(a.d.cap[b], a.d.k_max), stopped = a.d.stop_in[b], drafted = rb.drafted[b], pos = a.d.pos[b];
     const int start = a.l.state[(size_t)b * SVIP_LOOP_NSTATE + 7];
     if (stopped) return;
-    const int n = stream_rows(a, pos, drafted, cap, start);
+    const int n = rows_to_read(a, pos, drafted, cap, start);
     const bool of_target = jj >= a.group;
     const int i = of_target ? jj - a.group : jj;
     // (the target row behind the rows of the launch before is known)
@@ -210,7 +204,7 @@ __global__ __launch_bounds__(GROUP_FINISH_WAVES * 64) void k_stream_advance(Grou
     const int pos0 = __builtin_amdgcn_readfirstlane(rb.pos[b]), start = __builtin_amdgcn_readfirstlane(st[7]);
     int cap = __builtin_amdgcn_readfirstlane(min(a.d.cap[b], a.d.k_max));
     const int drafted = __builtin_amdgcn_readfirstlane(rb.drafted[b]), known = drafted > 0 ? drafted : 0;
-    const int n = stream_rows(a, pos0, drafted, cap, start);
+    const int n = rows_to_read(a, pos0, drafted, cap, start);
     int *tokens = rb.tokens + (size_t)b * a.l.gamma_max, *am = rb.argmax + (size_t)b * (a.d.k_max + 1);
     for (int i0 = wave; i0 <= n; i0 += GROUP * nwaves) {
         unsigned long long k[GROUP][RPL];

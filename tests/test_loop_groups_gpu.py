@@ -225,3 +225,27 @@ def test_greedy_rows_read_ahead(svip, B, k, V, L, max_new, h, policy, workspace)
         for x, y in zip(results[0][:3], got[:3]):
             assert torch.equal(x, y)
         assert got[3] == results[0][3]
+
+
+@pytest.mark.parametrize("later", [0, 3, 17])
+def test_a_later_call_asks_for_fewer_tokens(svip, later):
+    """Sequences that have all the tokens a call asks for, but were not finished by the calls before it, go through one more round."""
+    B, k, V, max_new, L = 5, 6, 700, 40, 60
+    draft, target = _trace(B, L, V, torch.bfloat16, 21, False)
+    results = []
+    for one_by_one in (True, False):
+        try:
+            if one_by_one:
+                svip.bench_set_tuning(draft_slices=64)
+            loop = svip.Loop(target, draft, temperature=1.0, h=1.5, gamma0=k, gamma_max=k, max_new=max_new, rounds=max_new, greedy=True)
+            ran = [loop.run(8)]
+            before = loop.state.clone()
+            loop.config.max_new = later
+            ran += [loop.run(1), loop.run()]
+        finally:
+            svip.bench_set_tuning()
+        assert ran[0][0] == 8 and ran[2][1] == 0 and (before[:, 6] > later + (0 if later == 17 else k)).any() and (before[:, 2] == 0).all()
+        results.append((ran, loop.state.cpu(), loop.out_tokens.cpu(), loop.round_log.cpu()[:int(loop.state[:, 3].max())]))
+    assert results[0][0] == results[1][0]
+    for x, y in zip(results[0][1:], results[1][1:]):
+        assert torch.equal(x, y)

@@ -51,3 +51,35 @@ def test_the_statistics_kernels_take_their_row_from_the_rule():
         body = text[text.index(kernel):]
         body = body[:body.index("request_stop_flag(a, b)")]
         assert "step_row_offset(a, b)" in body and "draft_row_offset(a, b, a.step_j)" not in body, kernel
+
+
+def test_rows_of_the_greedy_stream(tmp_path):
+    """Of every running sequence a launch reads at least one further row (or the loop would launch for ever), none outside the trace, and
+    none past what a round of it can reach -- also where a call asks for fewer tokens than one before it did, so that the sequence has
+    them already."""
+    _run(tmp_path, """
+int main()
+{
+    long seen = 0;
+    for (int gamma_max = 1; gamma_max <= 5; ++gamma_max)
+    for (int L = gamma_max + 1; L <= 14; ++L)
+    for (int start = 0; start < L; ++start)
+    for (int max_new : {0, 1, 2, 5, 9, 30, 2147483647})
+    for (int cap = 1; cap <= gamma_max; ++cap)
+    for (int pos = start; pos + cap + 1 <= L; ++pos)
+    for (int drafted = -1; drafted < cap; ++drafted)
+    for (int ahead : {1, 2, 7})
+    for (int group : {1, 3, 128}) {
+        const int n = stream_rows(pos, drafted, cap, start, L, gamma_max, max_new, ahead, group);
+        const int known = drafted > 0 ? drafted : 0;
+        const long long tokens = (long long)start + max_new, last = std::max(tokens - 1 + gamma_max, (long long)pos + cap);   // target row
+        ++seen;
+        if (n < 1 || n > group || pos + known + n > L - 1 || pos + known + n > last) {
+            std::printf("gamma_max %d L %d start %d max_new %d cap %d pos %d drafted %d ahead %d group %d: %d\\n", gamma_max, L, start,
+                        max_new, cap, pos, drafted, ahead, group, n);
+            return 1;
+        }
+    }
+    std::printf("%ld\\n", seen);
+}
+""")
