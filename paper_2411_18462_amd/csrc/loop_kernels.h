@@ -202,7 +202,7 @@ __global__ __launch_bounds__(GROUP_FINISH_WAVES * 64) void k_stream_advance(Grou
     if (a.d.stop_in[b]) return;                           // (the flag is only stored behind the last barrier)
     int *st = a.l.state + (size_t)b * SVIP_LOOP_NSTATE;
     const int pos0 = __builtin_amdgcn_readfirstlane(rb.pos[b]), start = __builtin_amdgcn_readfirstlane(st[7]);
-    int cap = __builtin_amdgcn_readfirstlane(min(a.d.cap[b], a.d.k_max));
+    int limit = __builtin_amdgcn_readfirstlane(a.d.cap[b]), cap = min(limit, a.d.k_max);   // (apart where the state says more than gamma_max)
     const int drafted = __builtin_amdgcn_readfirstlane(rb.drafted[b]), known = drafted > 0 ? drafted : 0;
     const int n = rows_to_read(a, pos0, drafted, cap, start);
     int *tokens = rb.tokens + (size_t)b * a.l.gamma_max, *am = rb.argmax + (size_t)b * (a.d.k_max + 1);
@@ -280,8 +280,8 @@ __global__ __launch_bounds__(GROUP_FINISH_WAVES * 64) void k_stream_advance(Grou
             const int seen = p + min(g, (na / 64 + 1) * 64);
             bad_token = bad_token || next_in(sets[2], p, rows) < seen;
         }
-        if (lane == 0) log_round(a.l, b, round, pos0 + p, cap, g, na);
-        cap = next_cap(a.l, cap, na == g);
+        if (lane == 0) log_round(a.l, b, round, pos0 + p, limit, g, na);
+        limit = cap = next_cap(a.l, limit, na == g);
         p += na + 1;
         ++round;
         all_drafted += g;

@@ -249,3 +249,34 @@ def test_a_later_call_asks_for_fewer_tokens(svip, later):
     assert results[0][0] == results[1][0]
     for x, y in zip(results[0][1:], results[1][1:]):
         assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("greedy", [True, False])
+def test_limits_set_between_calls(svip, greedy):
+    """A caller with a rule of its own stores the next round's limits into the state; one above gamma_max drafts gamma_max positions, is
+    logged as it stands and counted down from."""
+    B, k, V, max_new = 6, 5, 900, 24
+    draft, target = _trace(B, 60, V, torch.float16, 33, False)
+    g = torch.Generator(device="cuda").manual_seed(4)
+    u = {} if greedy else dict(u_sample=torch.rand(max_new, B, k, device="cuda", generator=g),
+                               u_accept=torch.rand(max_new, B, k, device="cuda", generator=g),
+                               u_resample=torch.rand(max_new, B, device="cuda", generator=g))
+    limits = torch.tensor([[1, 2, 3, 5, 7, 9], [9, 6, 4, 3, 2, 1]], dtype=torch.int32, device="cuda")
+    results = []
+    for one_by_one in (True, False):
+        try:
+            if one_by_one:
+                svip.bench_set_tuning(draft_slices=64)
+            loop = svip.Loop(target, draft, temperature=1.0, h=math.inf, gamma0=k, gamma_max=k, gamma_inc=2, gamma_dec=1, max_new=max_new,
+                             rounds=max_new, greedy=greedy, **u)
+            for n in (1, 2):
+                loop.run(n)
+                loop.state[:, 1] = limits[n - 1]
+            loop.run()
+        finally:
+            svip.bench_set_tuning()
+        rounds = int(loop.state[:, 3].max())
+        assert (loop.state[:, 2] == 1).all() and (loop.round_log[:rounds, :, 1] > k).any()
+        results.append((loop.state.cpu(), loop.out_tokens.cpu(), loop.round_log.cpu()[:rounds]))
+    for x, y in zip(*results):
+        assert torch.equal(x, y)
