@@ -46,7 +46,8 @@
  *     partial results it holds, at its end, the counters with which the workgroups of svip_verify's
  *     residual pass and of a small draft step hand a row's draw to whichever of them finishes last;
  *     every call leaves them at zero again.  Pass the same `workspace_bytes` with a workspace on every
- *     call; one that serves calls of several batch sizes has svip_workspace_bytes of the largest.  Calls
+ *     call; one that serves calls of several sizes has svip_workspace_bytes of the largest B, k_max and V
+ *     among them, or a call may overwrite counters of a larger batch (see svip_workspace_needed).  Calls
  *     that run concurrently must use different workspaces.
  *   - Same inputs give bit-identical outputs (no floating-point atomics, fixed combine order).
  */
@@ -90,7 +91,9 @@ size_t svip_workspace_bytes(int B, int k_max, int V);
 
 /* Bytes of workspace one particular call uses for these sizes (pure host function; 0 on bad
  * arguments).  svip_workspace_bytes(B, k_max, V) is never smaller than any of them; the calls
- * themselves check against these figures.  Verification and diagnostics of few short rows cut them finer where the workspace
+ * themselves check against these figures.  A workspace of such a size is for calls of one batch size: svip_verify's counters
+ * of the last sequences may be overwritten by a call of fewer sequences that fills it (draft steps use no counters there: in less than
+ * svip_workspace_bytes of their sizes they take two launches).  Verification and diagnostics of few short rows cut them finer where the workspace
  * holds more than that, as one of svip_workspace_bytes does; their sums are then added in another order. */
 typedef enum {
     SVIP_CALL_DRAFT_STEP = 0,            /* svip_draft_step, svip_draft_step_greedy */

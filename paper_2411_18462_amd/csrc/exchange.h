@@ -16,8 +16,9 @@
 //   take_ticket  device-scope relaxed atomic add on the counter, executed at memory
 //   fetch_*      device-scope relaxed atomic loads (global_load ... sc1): served by memory, not by an
 //                L2 line that may be stale
-// Only the thread that published may take the ticket (program order + stores_done is what orders the
-// two), and only data written through publish_* may be read by the last workgroup.  Nothing waits or
+// A ticket stands for everything its workgroup has published: every wave that published waits for its own stores (stores_done)
+// before the ticket is taken, by the same wave or, as in k_draft_step, by another one behind a barrier.  Only data written
+// through publish_* may be read by the last workgroup.  Nothing waits or
 // spins: every workgroup runs to its end whatever the others do.  The last workgroup puts the counter
 // back to zero, so counters only have to be cleared once, when the workspace is created.
 #pragma once

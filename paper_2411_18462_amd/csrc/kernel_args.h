@@ -19,7 +19,7 @@ struct Workspace {
     unsigned *tickets;   // END of the ticket counters (see ticket()): they grow downwards from here
     SeqRec *rec;         // [B]
     double *mass;        // [B][slices of the residual pass] masses of half tiles, verification only
-    void *part;          // slice statistics (LsePart, sized for sizeof(Partial) each), keys or records of the call
+    void *part;          // slice statistics (LsePart, though sizes count sizeof(Partial) each), keys or records of the call
 };
 
 constexpr int MAX_BATCH = 1 << 20;               // sequences per call (grids are one-dimensional)
@@ -36,10 +36,12 @@ static size_t ws_ticket_bytes(int B) { return align256((size_t)B * TICKETS_PER_R
 
 // Layout: flag word | records | slice masses | slice statistics ...            ... ticket counters.
 // The counters sit at the END of the workspace (the given size rounded down to 256 bytes) and counter
-// t of row b lies TICKETS_PER_ROW * b + t + 1 words below that end, whatever the batch size of the call: regions at the
-// front never reach them (every call checks front + counters <= size), so they keep the zeros that
-// svip_workspace_reset wrote and that every kernel restores, also when calls of different batch sizes
-// share a workspace.
+// t of row b lies TICKETS_PER_ROW * b + t + 1 words below that end, whatever the batch size of the call.  Every call checks
+// front + its own counters <= size, so its regions at the front leave the counters of as many rows alone as it has itself, and they
+// keep the zeros that svip_workspace_reset wrote and that every kernel restores.  The counters of a larger batch a call may overwrite
+// where the workspace holds little more than what that call needs.  With svip_workspace_bytes of the largest batch, draft and
+// vocabulary among the calls that share it none does; a draft step uses counters only where the workspace has svip_workspace_bytes
+// of its own sizes, and where the others have as much none of them reaches those either.
 static Workspace carve(void *ws, size_t bytes, int B, int mass_slices)
 {
     char *p = static_cast<char *>(ws);
@@ -55,6 +57,7 @@ static Workspace carve(void *ws, size_t bytes, int B, int mass_slices)
     return w;
 }
 enum { TICKET_RESID = 0, TICKET_DRAFT = 1 };        // (the draft step has two)
+static_assert(TICKETS_PER_ROW >= TICKET_DRAFT + 2, "a row's counters lie side by side");
 __device__ __forceinline__ unsigned *ticket(unsigned *tickets_end, int b, int t)
 {
     return tickets_end - ((size_t)b * TICKETS_PER_ROW + t + 1);

@@ -239,11 +239,10 @@ static size_t need_pair(int B, int k, bool recompute_lse, const Geo &g, const Ge
                         size_t *L_bytes)
 {
     const size_t stat_rows = (size_t)B * ((recompute_lse ? k : 0) + k + 1), pos = (size_t)B * k;
-    const size_t pb = align256(stat_rows * g.ns * sizeof(Partial));
     const size_t lb = align256(pos * 2 * sizeof(double));
-    if (part_bytes) *part_bytes = pb;
+    if (part_bytes) *part_bytes = align256(stat_rows * g.ns * sizeof(LsePart));      // (less than counted: the front ends earlier)
     if (L_bytes) *L_bytes = lb;
-    return ws_fixed_bytes(B, 0) + pb + lb + align256(pos * g2.ns * 3 * sizeof(double));
+    return ws_fixed_bytes(B, 0) + align256(stat_rows * g.ns * sizeof(Partial)) + lb + align256(pos * g2.ns * 3 * sizeof(double));
 }
 
 // The slicing each pass uses (forced = an experiment's override, 0 = the library's choice).
@@ -345,11 +344,13 @@ static DraftArgs draft_args(const DraftCall &c, const Geo &geo, void *records)
 //   greedy            1 row of 32000 fp32 4.50 / 4.38, 8 of 128256 bf16 6.25 / 5.71, 64 (1024) 8.96 / 8.43, 112 (1792) 11.02 / 10.98;
 //                     32 of 128256 fp32 (1024) 8.08 / 8.03, 40 8.65 / 8.93, 56 of 151936 bf16 (1064) 9.41 / 9.14, 4096 of 2000 11.6 / 12.9
 // Sampling's line stands below 1024 workgroups, where the gain is down to 2 % and a step's two kernels are still reported apart by
-// the benchmark.  A forced shape (an experiment's override) takes two.
+// the benchmark.  A forced shape (an experiment's override) takes two, and so does a workspace of less than svip_workspace_bytes: two
+// launches need no counters, and in one that only holds what some call needs, calls of other sizes may have overwritten them.
 static unsigned row_workgroups(const Geo &g) { return ((unsigned)g.ns + NWAVE - 1) / NWAVE; }
 static bool one_launch_step(const DraftCall &c, const Geo &g)
 {
     if (g.tps != 1 || g_tune.draft_slices) return false;
+    if ((c.workspace_bytes & ~(size_t)255) < svip_workspace_bytes(c.B, c.k_max, c.V)) return false;
     const long long workgroups = ((long long)c.B + 7) / 8 * 8 * row_workgroups(g);
     if (c.greedy) return workgroups <= 1024;
     if (!quarter_records(c.B, g)) return false;
