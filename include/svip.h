@@ -164,7 +164,7 @@ svip_status svip_draft_step(
  *   - All calls on one GPU share the array: calls that overlap on one GPU (different streams, or
  *     threads) race and must be serialised by the caller.  Device-data flags are not reported.
  *   - The first call on a GPU asks the runtime for the array's address on that GPU (no allocation,
- *     nothing enqueued); nothing in the array has to be cleared (its counters start at zero).
+ *     nothing enqueued); nothing in the array has to be cleared.
  */
 #define SVIP_STATIC_SCRATCH_BYTES (1 << 21)
 svip_status svip_draft_step_static(

@@ -31,6 +31,7 @@ struct DraftCall {
     void *workspace;
     size_t workspace_bytes;
     void *stream;
+    bool counters;               // the workspace has hand-over counters that svip_workspace_reset clears
 };
 
 // A message to the host: the word of its mailbox and the ticket that shows it has arrived.

@@ -345,12 +345,13 @@ static DraftArgs draft_args(const DraftCall &c, const Geo &geo, void *records)
 //                     32 of 128256 fp32 (1024) 8.08 / 8.03, 40 8.65 / 8.93, 56 of 151936 bf16 (1064) 9.41 / 9.14, 4096 of 2000 11.6 / 12.9
 // Sampling's line stands below 1024 workgroups, where the gain is down to 2 % and a step's two kernels are still reported apart by
 // the benchmark.  A forced shape (an experiment's override) takes two, and so does a workspace of less than svip_workspace_bytes: two
-// launches need no counters, and in one that only holds what some call needs, calls of other sizes may have overwritten them.
+// launches need no counters, and in one that only holds what some call needs, calls of other sizes may have overwritten them.  So does the fixed
+// scratch: calls that overlap there leave nothing behind that a later call would read, and nothing could clear it.
 static unsigned row_workgroups(const Geo &g) { return ((unsigned)g.ns + NWAVE - 1) / NWAVE; }
 static bool one_launch_step(const DraftCall &c, const Geo &g)
 {
     if (g.tps != 1 || g_tune.draft_slices) return false;
-    if ((c.workspace_bytes & ~(size_t)255) < svip_workspace_bytes(c.B, c.k_max, c.V)) return false;
+    if (!c.counters || (c.workspace_bytes & ~(size_t)255) < svip_workspace_bytes(c.B, c.k_max, c.V)) return false;
     const long long workgroups = ((long long)c.B + 7) / 8 * 8 * row_workgroups(g);
     if (c.greedy) return workgroups <= 1024;
     if (!quarter_records(c.B, g)) return false;
@@ -520,8 +521,7 @@ svip_status greedy_stream_call(const DraftCall &c, const void *target, int group
 
 // Device address of `scratch` on the current device, or nullptr.  The first call on a device looks the
 // symbol up (hipGetSymbolAddress with that device current); every GPU holds its own copy of the array at
-// its own address.  Its counters start at zero, as the array does, and every step leaves them there; records are written before
-// they are read.
+// its own address.  Nothing in it has to start at zero: a draft step in two launches writes every record before it reads it.
 static void *static_scratch()
 {
     constexpr int MAX_DEVICES = 64;
@@ -763,7 +763,7 @@ svip_status svip_draft_step(const void *draft_logits, int dtype, int B, int V, l
 {
     const DraftCall c{false, draft_logits, dtype, B, V, row_stride, nullptr, 0, nullptr, temperature, h, step_j,
                       k_max, u_sample, stop_in, token_out, entropy_out, q_tok_out, lse_out, stop_out,
-                      draft_len_out, io_stride, workspace, workspace_bytes, hip_stream};
+                      draft_len_out, io_stride, workspace, workspace_bytes, hip_stream, true};
     return draft_step_call(c);
 }
 
@@ -782,7 +782,7 @@ svip_status svip_draft_step_static(const void *draft_logits, int dtype, int B, i
     if (!ws) return SVIP_ERR_HIP;
     const DraftCall c{false, draft_logits, dtype, B, V, row_stride, nullptr, 0, nullptr, temperature, h, step_j,
                       k_max, u_sample, stop_in, token_out, entropy_out, q_tok_out, lse_out, stop_out,
-                      draft_len_out, io_stride, ws, (size_t)SVIP_STATIC_SCRATCH_BYTES, hip_stream};
+                      draft_len_out, io_stride, ws, (size_t)SVIP_STATIC_SCRATCH_BYTES, hip_stream, false};
     return draft_step_call(c);
 }
 
@@ -795,7 +795,7 @@ svip_status svip_draft_step_greedy(const void *draft_logits, int dtype, int B, i
 {
     const DraftCall c{true, draft_logits, dtype, B, V, row_stride, nullptr, 0, nullptr, temperature, h, step_j,
                       k_max, nullptr, stop_in, token_out, entropy_out, q_tok_out, lse_out, stop_out,
-                      draft_len_out, io_stride, workspace, workspace_bytes, hip_stream};
+                      draft_len_out, io_stride, workspace, workspace_bytes, hip_stream, true};
     return draft_step_call(c);
 }
 

@@ -354,6 +354,7 @@ static DraftCall draft_call(const svip_loop_config *c, const RoundBuffers &rb, s
     d.workspace = c->workspace;
     d.workspace_bytes = base;
     d.stream = c->hip_stream;
+    d.counters = true;
     return d;
 }
 

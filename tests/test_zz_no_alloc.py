@@ -52,3 +52,22 @@ def test_static_scratch_entry_point_matches_the_workspace_one(svip):
                                     None, z.data_ptr(), z.data_ptr(), None, 1, None)
     assert rc == 5 and b"WORKSPACE" in lib.svip_status_string(rc)
     torch.cuda.synchronize()
+
+
+def test_static_steps_depend_on_nothing_that_earlier_calls_left(svip):
+    """A step of few rows is one launch whose workgroups count themselves, in the workspace; in the fixed array, which nothing could clear
+    after calls that overlapped, it is two that do not."""
+    B, k, V = 3, 2, 32000
+    x = torch.randn(B, k, V, device="cuda")
+    u = torch.rand(B, k, device="cuda")
+    for ws, finish_launches in ((svip.new_workspace(B, k, V), 0), (None, k)):
+        events = [[torch.cuda.Event(enable_timing=True) for _ in range(k)] for _ in range(2)]
+        for e in events[0] + events[1]:
+            e.record()                            # creates it
+        keep = svip.bench_time_kernels(4, *[[e.cuda_event for e in es] for es in events])      # the second launch of a draft step
+        try:
+            _chain(svip, x, u, 1.0, 9.0, ws)
+            assert svip.bench_events_used(4) == finish_launches
+        finally:
+            svip.bench_time_kernels(4, [], [])
+        del keep
