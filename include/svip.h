@@ -49,7 +49,9 @@
  *     call; one that serves calls of several sizes has svip_workspace_bytes of the largest B, k_max and V
  *     among them, or a call may overwrite counters of a larger batch (see svip_workspace_needed).  Calls
  *     that run concurrently must use different workspaces.
- *   - Same inputs give bit-identical outputs (no floating-point atomics, fixed combine order).
+ *   - Same inputs give bit-identical outputs (no floating-point atomics, fixed combine order), in every workspace of
+ *     svip_workspace_bytes or more; a smaller one (svip_workspace_needed) may give other last bits of the sums, and a decision within
+ *     rounding of its threshold may then fall on the other side.
  */
 #ifndef SVIP_H
 #define SVIP_H
@@ -92,9 +94,9 @@ size_t svip_workspace_bytes(int B, int k_max, int V);
 /* Bytes of workspace one particular call uses for these sizes (pure host function; 0 on bad
  * arguments).  svip_workspace_bytes(B, k_max, V) is never smaller than any of them; the calls
  * themselves check against these figures.  A workspace of such a size is for calls of one batch size: svip_verify's counters
- * of the last sequences may be overwritten by a call of fewer sequences that fills it (draft steps use no counters there: in less than
- * svip_workspace_bytes of their sizes they take two launches).  Verification and diagnostics of few short rows cut them finer where the workspace
- * holds more than that, as one of svip_workspace_bytes does; their sums are then added in another order. */
+ * of the last sequences may be overwritten by a call of fewer sequences that fills it.  (Draft steps use no counters there: in
+ * less than svip_workspace_bytes of their sizes they take two launches.)  Nor do verification and diagnostics of few short rows cut
+ * them as finely there as in svip_workspace_bytes and more; their partial sums are added in another order then. */
 typedef enum {
     SVIP_CALL_DRAFT_STEP = 0,            /* svip_draft_step, svip_draft_step_greedy */
     SVIP_CALL_VERIFY = 1,                /* svip_verify with draft_lse given */

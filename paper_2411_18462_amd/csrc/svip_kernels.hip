@@ -111,7 +111,7 @@ static int *g_warp_routes = nullptr;             // svip_bench_warp_routes
 // Slices per row of the passes that give a slice to a workgroup: enough workgroups to fill 256 CUs several
 // times over, at most MAX_SLICES; want_one_batch (the residual pass): slices of min_tiles tiles, which the
 // sampler scans as one batch and whose tiles each get a mass of their own.
-static Geo make_geo(int V, int vec, long long rows, bool want_one_batch, int forced_ns, int min_tiles = 4, long long fine = 0)
+static Geo make_geo(int V, int vec, long long rows, bool want_one_batch, int forced_ns, int min_tiles = 4, bool fine = false)
 {
     Geo g;
     g.V = V;
@@ -129,16 +129,25 @@ static Geo make_geo(int V, int vec, long long rows, bool want_one_batch, int for
         // tiles (7) stream better than one-batch slices of 4, at the price of a two-batch search
         if (rows >= 512 && g.ntiles >= 14) ns = (g.ntiles + 6) / 7;
     } else {
-        // streaming passes: about 8192 workgroups of at least 8 tiles each; rows of fewer than 32 tiles up to four slices (as many as
-        // the acceptance test requests together) of at least 4 while that makes at most `fine` workgroups.  us, 8 tiles / so: svip_verify of 64 sequences of 4 positions of 20000 bf16 logits (10 tiles, 640 workgroups)
-        // 16.6 / 15.45, svip_pair_stats 21.25 / 18.6, svip_verify_greedy 9.1 / 7.65; 8 of 30 of 40000 (20 tiles, 992) 17.1 / 16.4, 23.95 / 21.3,
-        // 9.1 / 8.6; but greedy 32 of 8 of 50257 (25 tiles, 1152) 10.3 / 10.6, and of 100 of 4 of 32000 (2000) 10.5 / 10.7; with logsumexps
-        // recomputed svip_verify of 32 of 8 of 50257 (2176) 23.4 / 22.8, svip_pair_stats 29.65 / 28.97.
+        // streaming passes: about 8192 workgroups of at least 8 tiles each.  fine: rows of fewer than 32 tiles up to four slices (as many
+        // as the acceptance test requests together) of at least 4 tiles, while that makes few workgroups.  Two to four slices in place of one
+        // or two, rows of 8 to 23 tiles: us, coarse / finer, of svip_verify, svip_verify_greedy, svip_pair_stats and, the logsumexps
+        // recomputed, svip_verify:
+        //   workgroups  10 tiles                           14 tiles                          20 tiles                          23 tiles
+        //     160..300  13.4 12.6,  6.6 5.7, 17.3 14.5     13.8 11.9, 7.2 5.6, 17.5 13.6     17.1 15.6, 7.5 6.3, 19.9 16.1     15.8 14.8, 7.9 6.7, 18.8 15.4
+        //     650..700  14.8 13.8,  8.1 6.7, 20.6 17.9     15.6 14.2, 8.1 7.1, 19.2 16.8     16.7 15.4, 7.8 7.1, 18.9 16.7     15.3 14.6, 7.8 7.5, 19.7 18.3
+        //   1050..1250  20.6 20.0,  9.1 8.3, 25.3 23.4     15.7 14.9, 8.6 7.6, 23.4 21.0     19.1 18.6, 8.5 7.9, 24.5 23.4     21.3 21.2, 9.1 9.0, 27.8 25.9
+        //    ... recomp. 17.2 16.1                         16.7 15.5                         17.0 15.9                         21.1 20.2
+        //   1970..2020  18.1 18.2 (recomputed)             17.9 17.8                         22.0 21.9                         22.9 23.6, 24.1 24.6
+        //   2800                                                                             24.9 26.0                         28.0 29.0, 26.7 28.1
+        // Four in place of three, 24 to 31 tiles: up to 400 workgroups 0 to 9 % less, at 650 to 720 from 4 % less to 5 % more (30 tiles
+        // of bf16, 648: 14.9 15.8, 8.5 8.3, 22.0 23.3), beyond up to 6 % more.  Errors against 64 bits are smaller with finer
+        // slices (rms of acceptance probabilities 5.5e-8 / 5.1e-8, of divergences 1.8e-7 / 1.7e-7 relative).
         ns = (8192 + rows - 1) / rows;
         long long most = g.ntiles / 8;
-        if (g.ntiles < 32) {
+        if (fine && g.ntiles < 32) {
             const long long finer = g.ntiles >= 16 ? 4 : g.ntiles / 4;
-            if (rows * finer <= fine) most = finer;
+            if (rows * finer <= (g.ntiles < 24 ? 1250 : 400)) most = finer;
         }
         if (ns > most) ns = most;
     }
@@ -269,12 +278,13 @@ static Geo geo_draft(int B, int V, int vec, int forced)
     g.ns = (g.ntiles + g.tps - 1) / g.tps;
     return g;
 }
-// A call needs a workspace for slices of at least 8 tiles (fine = 0), and takes finer ones where what it was given holds them.
-static Geo geo_stats(long long stat_rows, int V, int vec, int forced, long long fine = 0)
+static Geo geo_stats(long long stat_rows, int V, int vec, int forced, bool fine = false)
 {
     return make_geo(V, vec, stat_rows, false, forced, 4, fine);
 }
-constexpr long long FINE = 1000, FINE_DRAFT_ROWS = 2304;          // (the latter where a sequence's draft rows are read as well)
+// A call needs a workspace for slices of at least 8 tiles.  It takes finer ones in every workspace of at least svip_workspace_bytes, and in
+// no smaller one: its results are the same bits in all of the former, and in all of the latter.
+static bool room_for_finer(size_t have, int B, int k, int V) { return (have & ~(size_t)255) >= svip_workspace_bytes(B, k, V); }
 // the residual pass: slices of four tiles like the draft step (at 64 sequences of 128K logits, 16 slices of
 // 4 tiles take 13 us, 32 slices of 2 tiles 16 us, 8 slices 20 us, one tile per slice 26 us)
 static Geo geo_resid(int B, int V, int vec, int forced) { return make_geo(V, vec, B, true, forced, 4); }
@@ -550,8 +560,7 @@ static svip_status verify_greedy_call(const VerifyCall &c)
     GreedyArgs a;
     a.geo = geo_stats(rows, c.V, vec, g_tune.stats_slices);
     if (!workspace_ok(c.workspace, c.workspace_bytes, need_verify_greedy(c.B, c.k_max, a.geo))) return SVIP_ERR_WORKSPACE;
-    const Geo finer = geo_stats(rows, c.V, vec, g_tune.stats_slices, FINE);
-    if (workspace_ok(c.workspace, c.workspace_bytes, need_verify_greedy(c.B, c.k_max, finer))) a.geo = finer;
+    a.geo = geo_stats(rows, c.V, vec, g_tune.stats_slices, room_for_finer(c.workspace_bytes, c.B, c.k_max, c.V));
     const Workspace w = carve(c.workspace, c.workspace_bytes, c.B, 0);
     a.target = c.target;
     a.seq_t = c.seq_stride_t;
@@ -623,8 +632,7 @@ svip_status verify_call(const VerifyCall &c)
     a.geo_s = geo_resid(c.B, c.V, vec, g_tune.resid_slices);
     if (!workspace_ok(c.workspace, c.workspace_bytes, need_verify(c.B, c.k_max, kd != 0, a.geo, a.geo_s)))
         return SVIP_ERR_WORKSPACE;
-    const Geo finer = geo_stats(stat_rows, c.V, vec, g_tune.stats_slices, kd ? FINE_DRAFT_ROWS : FINE);
-    if (workspace_ok(c.workspace, c.workspace_bytes, need_verify(c.B, c.k_max, kd != 0, finer, a.geo_s))) a.geo = finer;
+    a.geo = geo_stats(stat_rows, c.V, vec, g_tune.stats_slices, room_for_finer(c.workspace_bytes, c.B, c.k_max, c.V));
     a.target = c.target;
     a.draft = c.draft;
     a.seq_t = c.seq_stride_t;
@@ -892,16 +900,13 @@ svip_status svip_pair_stats(const void *target_logits, const void *draft_logits,
     PairArgs a;
     a.v.geo = geo_stats(stat_rows, V, vec, g_tune.stats_slices);
     a.geo2 = geo_stats(pos, V, vec, g_tune.pair_slices);
+    if (!workspace_ok(workspace, workspace_bytes, need_pair(B, k_max, kd != 0, a.v.geo, a.geo2, nullptr, nullptr)))
+        return SVIP_ERR_WORKSPACE;
+    const bool fine = room_for_finer(workspace_bytes, B, k_max, V);
+    a.v.geo = geo_stats(stat_rows, V, vec, g_tune.stats_slices, fine);
+    a.geo2 = geo_stats(pos, V, vec, g_tune.pair_slices, fine);
     size_t part_bytes, L_bytes;
-    const size_t need = need_pair(B, k_max, kd != 0, a.v.geo, a.geo2, &part_bytes, &L_bytes);
-    if (!workspace_ok(workspace, workspace_bytes, need)) return SVIP_ERR_WORKSPACE;
-    const Geo finer = geo_stats(stat_rows, V, vec, g_tune.stats_slices, kd ? FINE_DRAFT_ROWS : FINE);
-    const Geo finer2 = geo_stats(pos, V, vec, g_tune.pair_slices, FINE);
-    if (workspace_ok(workspace, workspace_bytes, need_pair(B, k_max, kd != 0, finer, finer2, nullptr, nullptr))) {
-        a.v.geo = finer;
-        a.geo2 = finer2;
-        need_pair(B, k_max, kd != 0, a.v.geo, a.geo2, &part_bytes, &L_bytes);
-    }
+    need_pair(B, k_max, kd != 0, a.v.geo, a.geo2, &part_bytes, &L_bytes);
     a.v.geo_s = a.v.geo;
     a.v.target = target_logits;
     a.v.draft = draft_logits;
