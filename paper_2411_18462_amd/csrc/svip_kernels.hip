@@ -346,17 +346,19 @@ static DraftArgs draft_args(const DraftCall &c, const Geo &geo, void *records)
 // Whether a step is one launch (k_draft_step) or two.  One saves a launch (1.8 us in a graph, 2.5 us of the caller's time) and
 // pays with an exchange through memory, which takes longer the more rows are at it: their records are stored past the L2 and
 // fetched from behind it, sampling twice as many words as greedy, by two waves.  us per step in a graph, two launches / one:
-//   sampling, 16-bit  1 row of 128256 5.88 / 5.79, 8 6.80 / 6.45, 32 8.15 / 7.72, 64 (1024 workgroups) 9.68 / 9.43, 72 10.35 / 10.09,
-//                     112 11.88 / 12.32; 256 of 32000 (1024) 9.78 / 9.50, 288 10.44 / 10.28, 512 of 2000 7.87 / 6.86, 4096 14.0 / 16.8
+//   sampling, 16-bit  1 row of 128256 5.88 / 5.79, 8 6.56 / 6.17, 32 (512 workgroups) 8.13 / 7.53, 48 (768) 8.88 / 8.38, 64 (1024)
+//                     9.70 / 9.31, 80 (1280) 10.53 / 10.39, 88 (1408) 10.91 / 11.10, 104 (1664) 11.68 / 12.11; 192 of 32000 (768) 8.92 / 8.41,
+//                     256 (1024) 9.72 / 9.44, 320 (1280) 10.58 / 10.43; 768 of 2000 8.15 / 7.03, 1536 10.13 / 8.56, 2048 10.30 / 10.87
 //     over 64 records 16 rows of 151936 (304) 7.92 / 7.48, 32 (608) 8.98 / 9.07, 56 10.43 / 11.21
-//   sampling, fp32    1 row of 32000 4.91 / 4.73, 16 6.15 / 5.86, 64 (512) 7.23 / 7.04, 144 (1152) 9.21 / 9.54
+//   sampling, fp32    1 row of 32000 4.83 / 4.60, 16 6.15 / 5.89, 64 (512) 7.26 / 7.00, 88 (704) 7.74 / 7.54, 96 (768) 7.88 / 7.77,
+//                     112 (896) 8.43 / 8.37, 128 (1024) 8.50 / 8.64; 48 of 65536 (768) 7.93 / 8.03, 64 (1024) 8.62 / 8.86
 //     over 64 records 8 rows of 128256 (256) 6.73 / 7.39
-//   greedy            1 row of 32000 fp32 4.50 / 4.38, 8 of 128256 bf16 6.25 / 5.71, 64 (1024) 8.96 / 8.43, 112 (1792) 11.02 / 10.98;
+//   greedy            1 row of 32000 fp32 4.50 / 4.38, 8 of 128256 bf16 6.05 / 5.49, 64 (1024) 8.98 / 8.40, 112 (1792) 11.02 / 10.98;
 //                     32 of 128256 fp32 (1024) 8.08 / 8.03, 40 8.65 / 8.93, 56 of 151936 bf16 (1064) 9.41 / 9.14, 4096 of 2000 11.6 / 12.9
-// Sampling's line stands below 1024 workgroups, where the gain is down to 2 % and a step's two kernels are still reported apart by
-// the benchmark.  A forced shape (an experiment's override) takes two, and so does a workspace of less than svip_workspace_bytes: two
-// launches need no counters, and in one that only holds what some call needs, calls of other sizes may have overwritten them.  So does the fixed
-// scratch: calls that overlap there leave nothing behind that a later call would read, and nothing could clear it.
+// Sampling has one line for all types, where fp32 rows cross over.  16-bit rows would gain 1 to 4 % more on a line of their own at 1280
+// workgroups.  A forced shape (an experiment's override) takes two, and so does a workspace of less than svip_workspace_bytes: two
+// launches need no counters, and in one that only holds what some call needs, calls of other sizes may have overwritten them.  So does the
+// fixed scratch: calls that overlap there leave nothing behind that a later call would read, and nothing could clear it.
 static unsigned row_workgroups(const Geo &g) { return ((unsigned)g.ns + NWAVE - 1) / NWAVE; }
 static bool one_launch_step(const DraftCall &c, const Geo &g)
 {
