@@ -182,12 +182,26 @@ def test_rows_of_several_records_per_lane(svip, B, V, dtype, greedy):
         assert st["rounds"] >= 2 * min(B, 3) and (not greedy or st["free_checked"] == min(B, 3))
 
 
+def _least_workspace(svip, B, k, V):
+    """The least that rows are read ahead with (plan_groups and plan_bytes in svip_loop.hip): the records of the sampling loop's largest
+    group, which a greedy launch shares its rows and keys into, and the same of a small greedy launch."""
+    up = lambda n: (n + 255) // 256 * 256
+    lanes, most = B if B < 8 else (B + 7) // 8 * 8, 0
+    for vec in (4, 8):
+        tiles = -(-V // (256 * vec))
+        first, small = (min(k, max(2, n // (B * tiles))) for n in (4800, min(2400, 64 * B * tiles)))
+        largest = max(first, min(k, 32768 // (tiles * ((B + 7) // 8 * 8))))
+        most = max(most, up(lanes * largest * tiles * 64), up(lanes * small * tiles * 32) + up(lanes * (small + 1) * tiles * 8))
+    serial = up(svip.workspace_bytes(B, k, V)) + up(4 * B * k) + up(8 * B * k) + 2 * up(B) + 6 * up(4 * B) + 256
+    return serial + 2 * up(4 * B) + up(4 * B * (k + 1)) + most
+
+
 @pytest.mark.parametrize("B,k,V,L,max_new,h,policy,workspace", [
     (2, 200, 600, 420, 210, math.inf, (200, 0, 0), "full"),      # drafts longer than a launch's rows; all but a few rows accepted
     (3, 300, 72, 700, 390, 4.0, (300, 0, 0), "full"),            # stops here and there, drafts of up to 300
-    (2, 130, 500, 300, 250, math.inf, (3, 7, 2), "least"),       # growing limits, small launches only
+    (64, 30, 65536, 64, 40, math.inf, (3, 7, 2), "least"),       # growing limits, drafts of several launches of 12 rows
     (5, 64, 400, 150, 200, math.inf, (64, 0, 0), "full"),        # the trace ends before max_new
-    (9, 1, 2500, 40, 38, 1.0, (1, 0, 0), "least"),               # drafts of one token
+    (9, 1, 2500, 40, 38, 1.0, (1, 0, 0), "least"),               # drafts of one token, one row per launch
     (4, 20, 300, 60, 30, 9.0, (20, 0, 0), "unfinished"),         # rows without any maximum: tokens of -1 are flagged and accepted
 ])
 def test_greedy_rows_read_ahead(svip, B, k, V, L, max_new, h, policy, workspace):
@@ -208,10 +222,9 @@ def test_greedy_rows_read_ahead(svip, B, k, V, L, max_new, h, policy, workspace)
                 svip.bench_set_tuning(draft_slices=64)
             loop = svip.Loop(target, draft, temperature=1.0, h=h, gamma0=policy[0], gamma_max=k, gamma_inc=policy[1], gamma_dec=policy[2],
                              max_new=max_new, rounds=max_new, greedy=True)
-            if workspace == "least" and not one_by_one:                    # what groups are taken with at all
-                up = lambda n: (n + 255) // 256 * 256
-                serial = up(svip.workspace_bytes(B, k, V)) + up(4 * B * k) + up(8 * B * k) + 2 * up(B) + 6 * up(4 * B) + 256
-                loop.config.workspace_bytes = min(loop.workspace.numel(), serial + 2 * up(4 * B) + up(4 * B * (k + 1)) + 64 * 8 * k * 16)
+            if workspace == "least" and not one_by_one:
+                loop.config.workspace_bytes = _least_workspace(svip, B, k, V)
+                assert loop.config.workspace_bytes < loop.workspace.numel()
             ran, running = 0, 1
             while running and loop.next_round < max_new:
                 n, running = loop.run(chunk)
@@ -221,10 +234,37 @@ def test_greedy_rows_read_ahead(svip, B, k, V, L, max_new, h, policy, workspace)
         assert running == 0 and ran == int(loop.state[:, 3].max())
         results.append((loop.state.cpu(), loop.out_tokens.cpu(), loop.round_log.cpu()[:ran], loop.flags()))
     assert (results[0][3] != 0) == (workspace == "unfinished")
+    if workspace == "least":
+        _launches_of_the_least_workspace(svip, draft, target, B, k, V, max_new, h, policy)
     for got in results[1:]:
         for x, y in zip(results[0][:3], got[:3]):
             assert torch.equal(x, y)
         assert got[3] == results[0][3]
+
+
+def _launches_of_the_least_workspace(svip, draft, target, B, k, V, max_new, h, policy):
+    """Pairs of launches of a whole run: with the least workspace more than with all of it, and with a byte less the loop goes position
+    by position."""
+    least, used = _least_workspace(svip, B, k, V), []
+    for size in (None, least, least - 256):
+        loop = svip.Loop(target, draft, temperature=1.0, h=h, gamma0=policy[0], gamma_max=k, gamma_inc=policy[1], gamma_dec=policy[2],
+                         max_new=max_new, rounds=max_new, greedy=True)
+        loop.config.workspace_bytes = size or loop.config.workspace_bytes
+        events = [[torch.cuda.Event(enable_timing=True) for _ in range(2000)] for _ in range(2)]
+        for e in events[0] + events[1]:
+            e.record()                            # creates it
+        keep = svip.bench_time_kernels(0, *[[e.cuda_event for e in es] for es in events])      # k_stream_rows; else the steps' statistics
+        try:
+            loop.run()
+            used.append(svip.bench_events_used(0))
+        finally:
+            svip.bench_time_kernels(0, [], [])
+        del keep
+    rounds = int(loop.state[:, 3].max())
+    print("  launches", used, "rounds", rounds, flush=True)
+    assert used[0] < used[1] <= used[2] and used[2] >= rounds
+    if k > 1:
+        assert used[1] < used[2] and used[1] >= -(-max_new // 12)
 
 
 @pytest.mark.parametrize("later", [0, 3, 17])
