@@ -230,7 +230,8 @@ def kernel_durations(svip, sets, h, steps):
     """The same rounds launched eagerly with HIP events attached to every launch of the library's
     kernels (hipExtLaunchKernel), so each pair takes that kernel's own begin and end on the stream;
     the host's launch rate does not enter.  {kernel: [us, ...]} of the kernels that were launched: the acceptance test of
-    svip_verify is part of k_resid in smaller calls and a launch of its own (k_accept) in larger ones."""
+    svip_verify is part of k_resid in smaller calls and a launch of its own (k_accept) in larger ones, and a small draft step is
+    one launch (k_draft_step, timed in the statistics' class) instead of two."""
     import torch
     k = sets[0].k
     clock = KernelClock(svip, {"k_draft_stats": steps * k, "k_draft_finish": steps * k, "k_verify_stats": steps, "k_accept": steps,
@@ -240,7 +241,10 @@ def kernel_durations(svip, sets, h, steps):
         s.draft_round(h)
         s.verify()
     torch.cuda.synchronize()
-    return {name: us for name, us in clock.finish().items() if len(us)}
+    taken = {name: us for name, us in clock.finish().items() if len(us)}
+    if "k_draft_finish" not in taken and "k_draft_stats" in taken:
+        taken["k_draft_step"] = taken.pop("k_draft_stats")
+    return taken
 
 
 def stream_read_peak(svip, dev, nbytes=1 << 30, reps=20):
@@ -394,7 +398,7 @@ def loop_policies(svip, si, dev, max_new=96, gamma_max=PAPER["max_draft_length"]
 SWEEP_B, SWEEP_V, SWEEP_K, SWEEP_T = (1, 8, 64, 256), (32000, 128256, 151936), (4, 16, 64), (0.7, 1.0)
 SWEEP_POOL_BYTES = 1 << 30       # inputs rotate through at least this much, or the cell is labelled cache-warm
 SWEEP_MAX_SETS = 8
-SWEEP_KERNELS = ("k_draft_stats", "k_draft_finish", "k_verify_stats", "k_accept", "k_resid")
+SWEEP_KERNELS = ("k_draft_step", "k_draft_stats", "k_draft_finish", "k_verify_stats", "k_accept", "k_resid")
 
 
 def sweep_cells():
@@ -469,7 +473,7 @@ def sweep(svip, dev, cells, counter_pass):
                 s.draft_round(H_FULL)
                 s.verify()
             torch.cuda.synchronize()
-            cell["launches"] = {"k_draft_stats": 2 * k, "k_draft_finish": 2 * k, "k_verify_stats": 2, "k_resid": 2}
+            cell["rounds"] = 2
             out.append(cell)
             print(json.dumps({"sweep_cell": cell}), file=sys.stderr, flush=True)
             del sets
@@ -491,13 +495,14 @@ def sweep(svip, dev, cells, counter_pass):
         assert int(sets[0].draft_len.min()) == k
         verify_bytes = B * (k + 1) * row_bytes + nrej * row_bytes
         med = {name: float(np.median(v)) for name, v in kd.items()}
+        reader = "k_draft_step" if "k_draft_step" in med else "k_draft_stats"       # what reads the draft rows
         o_rate, o_rows = sweep_oracle(np, oracle, sets[0].draft, sets[0].target, sets[0].us, sets[0].ua, sets[0].ur, T)
         cell.update({
             "draft_step_us": 1e6 * t_draft / k, "draft_step_GBps": B * row_bytes / (t_draft / k) / 1e9,
             "verify_us": 1e6 * t_verify, "verify_GBps": verify_bytes / t_verify / 1e9,
             "round_rows_per_s": B * (2 * k + 1) / (t_draft + t_verify),
-            "k_draft_stats_us": med["k_draft_stats"], "k_draft_stats_GBps": B * row_bytes / (med["k_draft_stats"] * 1e-6) / 1e9,
-            "k_draft_finish_us": med["k_draft_finish"],
+            f"{reader}_us": med[reader], f"{reader}_GBps": B * row_bytes / (med[reader] * 1e-6) / 1e9,
+            "k_draft_finish_us": med.get("k_draft_finish"),
             "k_verify_stats_us": med["k_verify_stats"],
             "k_verify_stats_GBps": B * (k + 1) * row_bytes / (med["k_verify_stats"] * 1e-6) / 1e9,
             "k_accept_us": med.get("k_accept"), "k_resid_us": med["k_resid"], "rejecting": nrej,
@@ -531,7 +536,7 @@ def merge_counters(cells, directory):
         return rows
 
     def classify(name):
-        for kn in ("k_draft_stats", "k_draft_finish", "k_verify_stats", "k_accept", "k_resid"):
+        for kn in SWEEP_KERNELS:
             if re.search(rf"svip::{kn}(_quarters|_total)?<", name):
                 return kn
         return None
@@ -556,14 +561,14 @@ def merge_counters(cells, directory):
                 rounds_done += 1
         assert rounds_done == 2 * len(cells), f"{rounds_done} rounds in the {sub} run, {2 * len(cells)} expected"
         for i, c in enumerate(cells):
-            for kn in ("k_draft_stats", "k_draft_finish", "k_verify_stats", "k_accept", "k_resid"):
+            for kn in SWEEP_KERNELS:
                 if (i, kn) in acc:
                     tot, n = acc[(i, kn)]
                     c[f"{kn}_{sub}_MB"] = tot / n / factors[counter] * 1024 / 1e6
                     c[f"{kn}_launches_counted"] = n
     for c in cells:
         B, V, k = c["B"], c["V"], c["k"]
-        c["k_draft_stats_alg_MB"] = B * V * 2 / 1e6
+        c["k_draft_step_alg_MB" if "k_draft_step_us" in c else "k_draft_stats_alg_MB"] = B * V * 2 / 1e6
         c["k_verify_stats_alg_MB"] = B * (k + 1) * V * 2 / 1e6
     return cells, factors
 
@@ -676,7 +681,7 @@ def main():
     # the kernels' own durations: the same rounds, eager, events attached to every launch
     k_steps = min(a.steps, 200)
     kd = kernel_durations(svip, sets, H_FULL, k_steps)
-    per_launch_bytes = {"k_draft_stats": B * row_bytes, "k_draft_finish": 0, "k_verify_stats": stats_bytes, "k_accept": 0,
+    per_launch_bytes = {"k_draft_step": B * row_bytes, "k_draft_stats": B * row_bytes, "k_draft_finish": 0, "k_verify_stats": stats_bytes, "k_accept": 0,
                         "k_resid": resid_bytes}
     kernels = {}
     for name, v in kd.items():

@@ -76,3 +76,19 @@ def test_bench_prints_one_json_line_with_the_required_objects():
     assert c["kind"] == "oracle" and c["unit"] == "rows/s" and c["cores"] >= 1 and c["value"] > 0 and c["sample"]
     assert c["one_thread_rows_per_s"] > 0 and c["os_cpu_count"] >= 1
     assert d["value"] > 100 * c["value"]
+
+
+@pytest.mark.gpu
+def test_sweep_reports_small_and_large_draft_steps():
+    """A cell whose draft steps are one launch each and one whose steps are two."""
+    sys.path.insert(0, ROOT)
+    import bench
+    cells = [bench.sweep_cells().index((B, 32000, 4, 1.0)) for B in (1, 256)]
+    p = subprocess.run([sys.executable, os.path.join(ROOT, "bench.py"), "--sweep", "--sweep-cells", ",".join(map(str, cells))],
+                       capture_output=True, text=True, timeout=600)
+    assert p.returncode == 0, p.stderr[-2000:]
+    small, large = json.loads(p.stdout.strip().splitlines()[-1])["sweep"]
+    assert small["k_draft_step_us"] > 0 and small["k_draft_finish_us"] is None and "k_draft_stats_us" not in small
+    assert large["k_draft_stats_us"] > 0 and large["k_draft_finish_us"] > 0 and "k_draft_step_us" not in large
+    for c in (small, large):
+        assert c["draft_step_us"] > 0 and c["verify_us"] > 0 and c["oracle_rows_per_s_1thread"] > 0
