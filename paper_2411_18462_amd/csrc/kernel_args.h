@@ -118,6 +118,7 @@ struct VerifyArgs {
     int kd;        // draft rows per sequence in the statistics pass: k if the draft logsumexps are recomputed, else 0
     int bonus;     // 1: the statistics pass also covers target row draft_len (verification), 0: rows j < draft_len only
     Geo geo;       // slicing of the statistics pass
+    int first_half;   // > 0: slices 2 i and 2 i + 1 are the first `first_half` tiles and the rest of the i-th geo.tps tiles
     long long stat_items;   // statistics rows * slices: the work items of the statistics pass
     Geo geo_s;     // slicing of the sampling pass (slices of at most LOCATE_UNROLL tiles when possible)
     Scale sc;

@@ -17,10 +17,10 @@ struct PairArgs {
 };
 
 // Logsumexps of position y's two rows from their slice statistics.  Both rows' slices travel together, CH at a time.
-template <int CH>
+template <int CH, bool HALVES>
 __device__ __forceinline__ void pair_logsumexps(const PairArgs &a, long long y, int b, int j)
 {
-    RowStats<CH> target, draft;
+    RowStats<CH, HALVES> target, draft;
     double lse = 0.0;
     target.request(a.v, b, a.v.kd + j);
     if (a.v.draft_lse) lse = a.v.draft_lse[y];
@@ -43,8 +43,9 @@ __global__ __launch_bounds__(64) void k_pair_L(PairArgs a)
     const int g = clamp_len(graw, a.v.k);
     if (graw != g && j == 0) atomicOr(a.v.ws.flags, (unsigned)SVIP_FLAG_BAD_DRAFT_LEN);
     if (j >= g) return;
-    if (a.v.geo.ns == 1) pair_logsumexps<1>(a, y, b, j);
-    else pair_logsumexps<4>(a, y, b, j);
+    if (a.v.geo.ns == 1) pair_logsumexps<1, false>(a, y, b, j);
+    else if (a.v.first_half) pair_logsumexps<4, true>(a, y, b, j);
+    else pair_logsumexps<4, false>(a, y, b, j);
 }
 
 // One batch of NU vector pairs per thread: with p = exp2(xp), q = exp2(xq) the normalised

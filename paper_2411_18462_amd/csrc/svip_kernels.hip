@@ -129,25 +129,24 @@ static Geo make_geo(int V, int vec, long long rows, bool want_one_batch, int for
         // tiles (7) stream better than one-batch slices of 4, at the price of a two-batch search
         if (rows >= 512 && g.ntiles >= 14) ns = (g.ntiles + 6) / 7;
     } else {
-        // streaming passes: about 8192 workgroups of at least 8 tiles each.  fine: rows of fewer than 32 tiles up to four slices (as many
-        // as the acceptance test requests together) of at least 4 tiles, while that makes few workgroups.  Two to four slices in place of one
-        // or two, rows of 8 to 23 tiles: us, coarse / finer, of svip_verify, svip_verify_greedy, svip_pair_stats and, the logsumexps
-        // recomputed, svip_verify:
+        // streaming passes: about 8192 workgroups of at least 8 tiles each.  fine: rows of 8 to 23 tiles, of one or two such slices, two to
+        // four (as many as the acceptance test requests together) of at least 4 tiles, while that makes few workgroups: us, coarse / finer,
+        // of svip_verify (see finer_stats), svip_verify_greedy, svip_pair_stats and, the logsumexps recomputed, svip_verify:
         //   workgroups  10 tiles                           14 tiles                          20 tiles                          23 tiles
-        //     160..300  13.4 12.6,  6.6 5.7, 17.3 14.5     13.8 11.9, 7.2 5.6, 17.5 13.6     17.1 15.6, 7.5 6.3, 19.9 16.1     15.8 14.8, 7.9 6.7, 18.8 15.4
-        //     650..700  14.8 13.8,  8.1 6.7, 20.6 17.9     15.6 14.2, 8.1 7.1, 19.2 16.8     16.7 15.4, 7.8 7.1, 18.9 16.7     15.3 14.6, 7.8 7.5, 19.7 18.3
-        //   1050..1250  20.6 20.0,  9.1 8.3, 25.3 23.4     15.7 14.9, 8.6 7.6, 23.4 21.0     19.1 18.6, 8.5 7.9, 24.5 23.4     21.3 21.2, 9.1 9.0, 27.8 25.9
-        //    ... recomp. 17.2 16.1                         16.7 15.5                         17.0 15.9                         21.1 20.2
+        //     160..300  14.0 13.0,  7.2 6.2, 17.3 14.5     14.9 13.1, 7.4 6.1, 17.5 13.6     18.0 16.5, 7.6 6.4, 19.9 16.1     14.3 13.2, 7.5 6.7, 18.8 15.4
+        //     640..700  15.2 14.7,  8.3 7.1, 20.6 17.9     15.8 14.4, 8.0 7.0, 19.2 16.8     16.1 15.2, 7.7 6.9, 18.9 16.7     17.8 17.8, 8.4 7.7, 19.7 18.3
+        //   1160..1250  19.6 18.9,  9.0 8.3, 25.3 23.4     19.1 17.7, 9.4 8.2, 23.4 21.0     18.9 17.4, 8.5 7.5, 24.5 23.4     20.2 19.7, 9.3 9.0, 27.8 25.9
+        //    ... recomp. 17.7 16.7                         16.7 15.3                         17.5 16.6                         21.4 21.0
         //   1970..2020  18.1 18.2 (recomputed)             17.9 17.8                         22.0 21.9                         22.9 23.6, 24.1 24.6
         //   2800                                                                             24.9 26.0                         28.0 29.0, 26.7 28.1
         // Four in place of three, 24 to 31 tiles: up to 400 workgroups 0 to 9 % less, at 650 to 720 from 4 % less to 5 % more (30 tiles
-        // of bf16, 648: 14.9 15.8, 8.5 8.3, 22.0 23.3), beyond up to 6 % more.  Errors against 64 bits are smaller with finer
+        // of bf16, 648: 14.9 15.8, 8.5 8.3, 22.0 23.3), beyond up to 6 % more: not taken.  Errors against 64 bits are smaller with finer
         // slices (rms of acceptance probabilities 5.5e-8 / 5.1e-8, of divergences 1.8e-7 / 1.7e-7 relative).
         ns = (8192 + rows - 1) / rows;
         long long most = g.ntiles / 8;
-        if (fine && g.ntiles < 32) {
+        if (fine && g.ntiles < 24) {
             const long long finer = g.ntiles >= 16 ? 4 : g.ntiles / 4;
-            if (rows * finer <= (g.ntiles < 24 ? 1250 : 400)) most = finer;
+            if (rows * finer <= 1250) most = finer;
         }
         if (ns > most) ns = most;
     }
@@ -285,6 +284,14 @@ static Geo geo_stats(long long stat_rows, int V, int vec, int forced, bool fine 
 // A call needs a workspace for slices of at least 8 tiles.  It takes finer ones in every workspace of at least svip_workspace_bytes, and in
 // no smaller one: its results are the same bits in all of the former, and in all of the latter.
 static bool room_for_finer(size_t have, int B, int k, int V) { return (have & ~(size_t)255) >= svip_workspace_bytes(B, k, V); }
+// The same for logsumexps, whose slices of a.geo are there already: each is halved, so that a logit of +inf or NaN costs a row the same
+// tiles as before (see RowStats).
+static void finer_stats(VerifyArgs &a, long long stat_rows, int vec, int forced, bool fine)
+{
+    const bool halves = geo_stats(stat_rows, a.geo.V, vec, forced, fine).ns > a.geo.ns;
+    a.first_half = halves ? (a.geo.tps + 1) / 2 : 0;
+    if (halves) a.geo.ns *= 2;
+}
 // the residual pass: slices of four tiles like the draft step (at 64 sequences of 128K logits, 16 slices of
 // 4 tiles take 13 us, 32 slices of 2 tiles 16 us, 8 slices 20 us, one tile per slice 26 us)
 static Geo geo_resid(int B, int V, int vec, int forced) { return make_geo(V, vec, B, true, forced, 4); }
@@ -634,7 +641,9 @@ svip_status verify_call(const VerifyCall &c)
     a.geo_s = geo_resid(c.B, c.V, vec, g_tune.resid_slices);
     if (!workspace_ok(c.workspace, c.workspace_bytes, need_verify(c.B, c.k_max, kd != 0, a.geo, a.geo_s)))
         return SVIP_ERR_WORKSPACE;
-    a.geo = geo_stats(stat_rows, c.V, vec, g_tune.stats_slices, room_for_finer(c.workspace_bytes, c.B, c.k_max, c.V));
+    // (rows this short have short slices in the residual pass too, unless an experiment forces others)
+    finer_stats(a, stat_rows, vec, g_tune.stats_slices,
+                a.geo_s.tps <= TILE_MASSES && room_for_finer(c.workspace_bytes, c.B, c.k_max, c.V));
     a.target = c.target;
     a.draft = c.draft;
     a.seq_t = c.seq_stride_t;
@@ -665,11 +674,15 @@ svip_status verify_call(const VerifyCall &c)
     bool ok = false;
     by_dtype(c.dtype, [&](auto tag) {
         using DT = decltype(tag);
+        const auto finish = [&](auto of) {
+            constexpr bool H = decltype(of)::value;
+            return (test || launch(k_accept<DT, H>, (unsigned)c.B, 64, st, a, SVIP_BENCH_K_ACCEPT)) &&
+                   launch(a.geo_s.tps <= TILE_MASSES ? (test ? k_resid<DT, true, true, H> : k_resid<DT, true, false, false>)
+                                                     : (test ? k_resid<DT, false, true, false> : k_resid<DT, false, false, false>),
+                          g_resid, WG, st, a, SVIP_BENCH_K_RESID);
+        };
         ok = launch(k_verify_stats<DT>, g_stats, WG, st, a, SVIP_BENCH_K_VERIFY_STATS) &&
-             (test || launch(k_accept<DT>, (unsigned)c.B, 64, st, a, SVIP_BENCH_K_ACCEPT)) &&
-             launch(a.geo_s.tps <= TILE_MASSES ? (test ? k_resid<DT, true, true> : k_resid<DT, true, false>)
-                                               : (test ? k_resid<DT, false, true> : k_resid<DT, false, false>),
-                    g_resid, WG, st, a, SVIP_BENCH_K_RESID);
+             (a.first_half ? finish(std::true_type{}) : finish(std::false_type{}));
     });
     return ok ? SVIP_OK : SVIP_ERR_HIP;
 }
@@ -905,7 +918,7 @@ svip_status svip_pair_stats(const void *target_logits, const void *draft_logits,
     if (!workspace_ok(workspace, workspace_bytes, need_pair(B, k_max, kd != 0, a.v.geo, a.geo2, nullptr, nullptr)))
         return SVIP_ERR_WORKSPACE;
     const bool fine = room_for_finer(workspace_bytes, B, k_max, V);
-    a.v.geo = geo_stats(stat_rows, V, vec, g_tune.stats_slices, fine);
+    finer_stats(a.v, stat_rows, vec, g_tune.stats_slices, fine);
     a.geo2 = geo_stats(pos, V, vec, g_tune.pair_slices, fine);
     size_t part_bytes, L_bytes;
     need_pair(B, k_max, kd != 0, a.v.geo, a.geo2, &part_bytes, &L_bytes);

@@ -91,3 +91,40 @@ def test_results_by_workspace_and_against_64_bits(svip, dtype, B, k, V, lse):
     for size in (least, enough):
         assert (got[size][2] - ratio).abs().max() <= 1e-5
         assert ((got[size][3][:, :, :4] - want).abs() <= 1e-5 * want.abs().clamp_min(1.0)).all()
+
+
+@pytest.mark.parametrize("dtype", [BF, F16, F32])
+@pytest.mark.parametrize("tiles", [7, 8, 15, 16, 23, 31])
+@pytest.mark.parametrize("lse", [True, False])
+def test_rows_without_a_distribution_have_no_token(svip, dtype, tiles, lse):
+    """A logit of +inf in any slice of a row that is cut finer: the same as with the longer slices, and where those are one per row no
+    correction or bonus token (-1) and no rejection at that position; its neighbours are unaffected."""
+    per16 = 4 if dtype == F32 else 8
+    B, k, V = 6, 2, tiles * 256 * per16 - 3
+    g = torch.Generator(device="cuda").manual_seed(tiles)
+    stride = -(-V // per16) * per16
+    draft = torch.empty(B, k, stride, dtype=dtype, device="cuda")[:, :, :V]
+    target = torch.empty(B, k + 1, stride, dtype=dtype, device="cuda")[:, :, :V]
+    z = torch.randn(B, k + 1, V, device="cuda", generator=g) * 4
+    draft.copy_(z[:, :k])
+    target.copy_(z + torch.randn(z.shape, device="cuda", generator=g))
+    for b, at in enumerate((0, V // 4, V // 2, V - 1)):                    # sequences 4 and 5 have none
+        target[b, 0, at] = float("inf")
+    tokens = draft.float().argmax(-1).int()
+    draft_len = torch.tensor([0, 0, 0, 0, 0, 2], dtype=torch.int32, device="cuda")
+    for first in (0, 1):                       # the row is the bonus row, then the first position's target row
+        draft_len[:5] = first
+        results = []
+        for size in (svip.workspace_bytes(B, k, V), max(svip.workspace_needed(c, dtype, B, k, V) for c in (1, 2))):
+            ws = torch.zeros(size, dtype=torch.uint8, device="cuda")
+            nacc, nxt = (torch.full((B,), -7, dtype=torch.int32, device="cuda") for _ in range(2))
+            svip.verify(target, draft, temperature=1.0, draft_tokens=tokens, draft_len=draft_len,
+                        draft_lse=torch.logsumexp(draft.double(), -1) if lse else None, u_accept=torch.full((B, k), 0.999, device="cuda"),
+                        u_resample=torch.full((B,), 0.4, device="cuda"), n_accepted_out=nacc, next_token_out=nxt, accept_prob_out=None,
+                        workspace=ws)
+            torch.cuda.synchronize()
+            results.append((nacc, nxt))
+        for a, b in zip(*results):
+            assert torch.equal(a, b) and (a[4:] >= 0).all()
+        if tiles < 16:
+            assert (results[0][0][:4] == first).all() and (first == 1 or (results[0][1][:4] == -1).all())
