@@ -14,6 +14,7 @@
 // from biasing every term of a row in the same direction.  Per-element work is fp32 (v_exp_f32);
 // everything that combines partial sums is fp64.
 #pragma once
+#include <float.h>
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -48,6 +49,7 @@ struct Geo {
 struct Scale {
     float c_hi, c_lo;   // log2(e) / T as nearest float + remainder
     float c_dn, c_up;   // the same constant as a float strictly below it + a positive remainder
+    float m0;           // logits at or below it have c_dn times themselves beyond fp32 (-inf: none has)
     double c;
     double inv_T;
 };
@@ -400,7 +402,9 @@ struct CombineLds {
 // two rounded operations per logit, no subtraction, and no floor -- because c_up > 0, a logit
 // of -inf gives x = -inf and weight 0 without passing through inf - inf.  The exact value of
 // ref does not matter (it cancels in ref + log2 S); it only has to sit next to m c so that the
-// largest weight is about 1.
+// largest weight is about 1, and to be finite.  So a thread begins with the lowest finite reference, and with m = Scale::m0, below
+// which m c would be beyond fp32: masks of the type's lowest number then weigh nothing, as next to any other logit, whatever part of
+// the row a thread sees (a reference of -inf would give them an infinite weight), and no sum needs to be asked whether it has begun.
 template <int N, int NU>
 __device__ __forceinline__ void accumulate_lse(const float (&z)[NU][N], float &m, float &ref, float &S,
                                                const Scale &sc)
@@ -410,11 +414,11 @@ __device__ __forceinline__ void accumulate_lse(const float (&z)[NU][N], float &m
     for (int u = 1; u < NU; ++u) mb = vmax(mb, tree_max<N>(z[u]));
     if (mb > m) {
         const float nref = mb * sc.c_dn;
-        if (m != neg_inf()) S *= exp2_raw(ref - nref);
+        S *= exp2_raw(ref - nref);
         m = mb;
         ref = nref;
     }
-    const float nr = (m == neg_inf()) ? 0.f : -ref;
+    const float nr = -ref;
     const float c_up = in_vgpr(sc.c_up), c_dn = in_vgpr(sc.c_dn);
     float Sb = 0.f;
 #pragma unroll
@@ -441,7 +445,7 @@ __device__ __forceinline__ void lse_batch(const DT *row, int t0, float &m, float
 }
 
 // (ref, S) of tiles [tb, te) of one row with S = sum exp2(z c - ref): m holds ref (log2
-// units); m = -inf marks a slice without finite logits.  Batches hold 32
+// units); S = 0 marks a slice without any logit of weight.  Batches hold 32
 // logits per thread (4 bf16 vectors or 8 fp32 vectors): small enough for 8 waves per SIMD.
 // Result valid in thread 0.
 struct alignas(16) LsePart {
@@ -455,7 +459,7 @@ __device__ __forceinline__ LsePart slice_lse(const DT *row, int V, int tb, int t
 {
     constexpr int N = VecOf<DT>::N, NB = 32 / N;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    float m = neg_inf(), ref = neg_inf(), S = 0.f;
+    float m = sc.m0, ref = -FLT_MAX, S = 0.f;
     const int fe = min(te, V / (WG * N));
     int t0 = tb;
     for (; t0 + NB <= fe; t0 += NB) lse_batch<DT, NB>(row, t0, m, ref, S, sc);
@@ -475,7 +479,7 @@ __device__ __forceinline__ LsePart slice_lse(const DT *row, int V, int tb, int t
     float rg = lds.m[0];
 #pragma unroll
     for (int w = 1; w < NWAVE; ++w) rg = vmax(rg, lds.m[w]);
-    double Sd = (m != neg_inf()) ? (double)S * (double)exp2_raw(ref - rg) : 0.0;
+    double Sd = (m != sc.m0) ? (double)S * (double)exp2_raw(ref - rg) : 0.0;
     Sd = wave_sum(Sd);
     if (lane == 0) lds.S[wave] = Sd;
     __syncthreads();

@@ -172,6 +172,11 @@ static Scale make_scale(float temperature)
     s.c_dn = s.c_hi;
     while ((double)s.c_dn >= s.c) s.c_dn = nextafterf(s.c_dn, 0.f);      // strictly below c: the remainder is > 0
     s.c_up = (float)(s.c - (double)s.c_dn);
+    s.m0 = -INFINITY;
+    if (s.c_dn > 1.f) {
+        s.m0 = (float)(-(double)FLT_MAX / (double)s.c_dn);
+        while (!isinf(s.m0 * s.c_dn)) s.m0 = nextafterf(s.m0, -INFINITY);       // the highest whose product is -inf
+    }
     return s;
 }
 
