@@ -122,6 +122,7 @@ struct VerifyArgs {
     long long stat_items;   // statistics rows * slices: the work items of the statistics pass
     Geo geo_s;     // slicing of the sampling pass (slices of at most LOCATE_UNROLL tiles when possible)
     Scale sc;
+    float m0;      // logits at or below it have sc.c_dn times themselves beyond fp32 (-inf: none has), see accumulate_lse
     const int *tokens;
     const int *draft_len;
     const double *draft_lse;

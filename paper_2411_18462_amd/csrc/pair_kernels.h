@@ -17,10 +17,10 @@ struct PairArgs {
 };
 
 // Logsumexps of position y's two rows from their slice statistics.  Both rows' slices travel together, CH at a time.
-template <int CH, bool HALVES>
+template <int CH, int PARTS>
 __device__ __forceinline__ void pair_logsumexps(const PairArgs &a, long long y, int b, int j)
 {
-    RowStats<CH, HALVES> target, draft;
+    RowStats<CH, PARTS> target, draft;
     double lse = 0.0;
     target.request(a.v, b, a.v.kd + j);
     if (a.v.draft_lse) lse = a.v.draft_lse[y];
@@ -34,6 +34,7 @@ __device__ __forceinline__ void pair_logsumexps(const PairArgs &a, long long y, 
 // One thread per position (b, j < draft_len): logsumexps of its two rows.  Four slices at a time (a call of 63 positions of 32000
 // fp32 logits 15.8 us, with eight at a time 16.2, one by one 16.1; 20 positions of 151936 22.7, 22.4, 25.8), but rows of one
 // slice have no more to request: 1 position of 18658 bf16 logits 14.7 / 14.1, with logsumexps recomputed 15.4 / 14.5.
+template <int PARTS>
 __global__ __launch_bounds__(64) void k_pair_L(PairArgs a)
 {
     const long long y = (long long)blockIdx.x * 64 + threadIdx.x;
@@ -43,9 +44,8 @@ __global__ __launch_bounds__(64) void k_pair_L(PairArgs a)
     const int g = clamp_len(graw, a.v.k);
     if (graw != g && j == 0) atomicOr(a.v.ws.flags, (unsigned)SVIP_FLAG_BAD_DRAFT_LEN);
     if (j >= g) return;
-    if (a.v.geo.ns == 1) pair_logsumexps<1, false>(a, y, b, j);
-    else if (a.v.first_half) pair_logsumexps<4, true>(a, y, b, j);
-    else pair_logsumexps<4, false>(a, y, b, j);
+    if (PARTS == 1 && a.v.geo.ns == 1) pair_logsumexps<1, 1>(a, y, b, j);
+    else pair_logsumexps<4, PARTS>(a, y, b, j);
 }
 
 // One batch of NU vector pairs per thread: with p = exp2(xp), q = exp2(xq) the normalised

@@ -49,7 +49,6 @@ struct Geo {
 struct Scale {
     float c_hi, c_lo;   // log2(e) / T as nearest float + remainder
     float c_dn, c_up;   // the same constant as a float strictly below it + a positive remainder
-    float m0;           // logits at or below it have c_dn times themselves beyond fp32 (-inf: none has)
     double c;
     double inv_T;
 };
@@ -402,7 +401,7 @@ struct CombineLds {
 // two rounded operations per logit, no subtraction, and no floor -- because c_up > 0, a logit
 // of -inf gives x = -inf and weight 0 without passing through inf - inf.  The exact value of
 // ref does not matter (it cancels in ref + log2 S); it only has to sit next to m c so that the
-// largest weight is about 1, and to be finite.  So a thread begins with the lowest finite reference, and with m = Scale::m0, below
+// largest weight is about 1, and to be finite.  So a thread begins with the lowest finite reference, and with a maximum m0 (VerifyArgs), below
 // which m c would be beyond fp32: masks of the type's lowest number then weigh nothing, as next to any other logit, whatever part of
 // the row a thread sees (a reference of -inf would give them an infinite weight), and no sum needs to be asked whether it has begun.
 template <int N, int NU>
@@ -454,12 +453,12 @@ struct alignas(16) LsePart {
     float pad;
 };
 template <typename DT>
-__device__ __forceinline__ LsePart slice_lse(const DT *row, int V, int tb, int te, const Scale &sc,
+__device__ __forceinline__ LsePart slice_lse(const DT *row, int V, int tb, int te, const Scale &sc, float m0,
                                              CombineLds &lds)
 {
     constexpr int N = VecOf<DT>::N, NB = 32 / N;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    float m = sc.m0, ref = -FLT_MAX, S = 0.f;
+    float m = m0, ref = -FLT_MAX, S = 0.f;
     const int fe = min(te, V / (WG * N));
     int t0 = tb;
     for (; t0 + NB <= fe; t0 += NB) lse_batch<DT, NB>(row, t0, m, ref, S, sc);
@@ -479,7 +478,7 @@ __device__ __forceinline__ LsePart slice_lse(const DT *row, int V, int tb, int t
     float rg = lds.m[0];
 #pragma unroll
     for (int w = 1; w < NWAVE; ++w) rg = vmax(rg, lds.m[w]);
-    double Sd = (m != sc.m0) ? (double)S * (double)exp2_raw(ref - rg) : 0.0;
+    double Sd = (m != m0) ? (double)S * (double)exp2_raw(ref - rg) : 0.0;
     Sd = wave_sum(Sd);
     if (lane == 0) lds.S[wave] = Sd;
     __syncthreads();

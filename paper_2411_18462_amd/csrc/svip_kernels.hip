@@ -133,10 +133,10 @@ static Geo make_geo(int V, int vec, long long rows, bool want_one_batch, int for
         // four (as many as the acceptance test requests together) of at least 4 tiles, while that makes few workgroups: us, coarse / finer,
         // of svip_verify (see finer_stats), svip_verify_greedy, svip_pair_stats and, the logsumexps recomputed, svip_verify:
         //   workgroups  10 tiles                           14 tiles                          20 tiles                          23 tiles
-        //     160..300  14.0 13.0,  7.2 6.2, 17.3 14.5     14.9 13.1, 7.4 6.1, 17.5 13.6     18.0 16.5, 7.6 6.4, 19.9 16.1     14.3 13.2, 7.5 6.7, 18.8 15.4
-        //     640..700  15.2 14.7,  8.3 7.1, 20.6 17.9     15.8 14.4, 8.0 7.0, 19.2 16.8     16.1 15.2, 7.7 6.9, 18.9 16.7     17.8 17.8, 8.4 7.7, 19.7 18.3
-        //   1160..1250  19.6 18.9,  9.0 8.3, 25.3 23.4     19.1 17.7, 9.4 8.2, 23.4 21.0     18.9 17.4, 8.5 7.5, 24.5 23.4     20.2 19.7, 9.3 9.0, 27.8 25.9
-        //    ... recomp. 17.7 16.7                         16.7 15.3                         17.5 16.6                         21.4 21.0
+        //     160..300  13.4 12.6,  7.2 6.2, 17.3 14.5     13.8 11.9, 7.2 5.6, 17.5 13.6     18.0 16.5, 7.6 6.4, 19.9 16.1     14.3 13.2, 7.5 6.7, 18.8 15.4
+        //     640..700  14.8 13.8,  8.3 7.1, 20.6 17.9     15.6 14.2, 8.1 7.1, 19.2 16.8     16.1 15.2, 7.7 6.9, 18.9 16.7     17.8 17.8, 8.4 7.7, 19.7 18.3
+        //   1050..1250  20.6 20.0,  9.0 8.3, 25.3 23.4     15.7 14.9, 8.6 7.6, 23.4 21.0     18.9 17.4, 8.5 7.5, 24.5 23.4     20.2 19.7, 9.3 9.0, 27.8 25.9
+        //    ... recomp. 17.2 16.1                         16.7 15.5                         17.5 16.6                         21.4 21.0
         //   1970..2020  18.1 18.2 (recomputed)             17.9 17.8                         22.0 21.9                         22.9 23.6, 24.1 24.6
         //   2800                                                                             24.9 26.0                         28.0 29.0, 26.7 28.1
         // Four in place of three, 24 to 31 tiles: up to 400 workgroups 0 to 9 % less, at 650 to 720 from 4 % less to 5 % more (30 tiles
@@ -172,12 +172,16 @@ static Scale make_scale(float temperature)
     s.c_dn = s.c_hi;
     while ((double)s.c_dn >= s.c) s.c_dn = nextafterf(s.c_dn, 0.f);      // strictly below c: the remainder is > 0
     s.c_up = (float)(s.c - (double)s.c_dn);
-    s.m0 = -INFINITY;
-    if (s.c_dn > 1.f) {
-        s.m0 = (float)(-(double)FLT_MAX / (double)s.c_dn);
-        while (!isinf(s.m0 * s.c_dn)) s.m0 = nextafterf(s.m0, -INFINITY);       // the highest whose product is -inf
-    }
     return s;
+}
+
+// The highest logit whose product with the scale's c_dn is below fp32's range; -inf if there is none.
+static float beyond_range(const Scale &s)
+{
+    if (!(s.c_dn > 1.f)) return -INFINITY;
+    float m = (float)(-(double)FLT_MAX / (double)s.c_dn);
+    while (!isinf(m * s.c_dn)) m = nextafterf(m, -INFINITY);
+    return m;
 }
 
 static bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -289,13 +293,28 @@ static Geo geo_stats(long long stat_rows, int V, int vec, int forced, bool fine 
 // A call needs a workspace for slices of at least 8 tiles.  It takes finer ones in every workspace of at least svip_workspace_bytes, and in
 // no smaller one: its results are the same bits in all of the former, and in all of the latter.
 static bool room_for_finer(size_t have, int B, int k, int V) { return (have & ~(size_t)255) >= svip_workspace_bytes(B, k, V); }
-// The same for logsumexps, whose slices of a.geo are there already: each is halved, so that a logit of +inf or NaN costs a row the same
-// tiles as before (see RowStats).
-static void finer_stats(VerifyArgs &a, long long stat_rows, int vec, int forced, bool fine)
+// The same for logsumexps, whose slices of a.geo are there already.  A logit of +inf or NaN has to cost a row the same tiles as before: a
+// row of one slice all of them, and two slices are halved.  Returns how many slices stand for one (see RowStats).
+static int finer_stats(VerifyArgs &a, long long stat_rows, int vec, int forced, bool fine)
 {
-    const bool halves = geo_stats(stat_rows, a.geo.V, vec, forced, fine).ns > a.geo.ns;
-    a.first_half = halves ? (a.geo.tps + 1) / 2 : 0;
-    if (halves) a.geo.ns *= 2;
+    const Geo g = geo_stats(stat_rows, a.geo.V, vec, forced, fine);
+    a.first_half = 0;
+    if (g.ns <= a.geo.ns) return 1;
+    if (a.geo.ns == 1) {
+        a.geo = g;
+        return 4;
+    }
+    a.first_half = (a.geo.tps + 1) / 2;
+    a.geo.ns *= 2;
+    return 2;
+}
+// f with that number as a constant.
+template <typename F>
+static bool by_parts(int parts, F f)
+{
+    if (parts == 4) return f(std::integral_constant<int, 4>{});
+    if (parts == 2) return f(std::integral_constant<int, 2>{});
+    return f(std::integral_constant<int, 1>{});
 }
 // the residual pass: slices of four tiles like the draft step (at 64 sequences of 128K logits, 16 slices of
 // 4 tiles take 13 us, 32 slices of 2 tiles 16 us, 8 slices 20 us, one tile per slice 26 us)
@@ -647,8 +666,8 @@ svip_status verify_call(const VerifyCall &c)
     if (!workspace_ok(c.workspace, c.workspace_bytes, need_verify(c.B, c.k_max, kd != 0, a.geo, a.geo_s)))
         return SVIP_ERR_WORKSPACE;
     // (rows this short have short slices in the residual pass too, unless an experiment forces others)
-    finer_stats(a, stat_rows, vec, g_tune.stats_slices,
-                a.geo_s.tps <= TILE_MASSES && room_for_finer(c.workspace_bytes, c.B, c.k_max, c.V));
+    const int parts = finer_stats(a, stat_rows, vec, g_tune.stats_slices,
+                                  a.geo_s.tps <= TILE_MASSES && room_for_finer(c.workspace_bytes, c.B, c.k_max, c.V));
     a.target = c.target;
     a.draft = c.draft;
     a.seq_t = c.seq_stride_t;
@@ -661,6 +680,7 @@ svip_status verify_call(const VerifyCall &c)
     a.kd = kd;
     a.bonus = 1;
     a.sc = make_scale(c.temperature);
+    a.m0 = beyond_range(a.sc);
     a.tokens = c.draft_tokens;
     a.draft_len = c.draft_len;
     a.draft_lse = c.draft_lse;
@@ -679,15 +699,13 @@ svip_status verify_call(const VerifyCall &c)
     bool ok = false;
     by_dtype(c.dtype, [&](auto tag) {
         using DT = decltype(tag);
-        const auto finish = [&](auto of) {
-            constexpr bool H = decltype(of)::value;
-            return (test || launch(k_accept<DT, H>, (unsigned)c.B, 64, st, a, SVIP_BENCH_K_ACCEPT)) &&
-                   launch(a.geo_s.tps <= TILE_MASSES ? (test ? k_resid<DT, true, true, H> : k_resid<DT, true, false, false>)
-                                                     : (test ? k_resid<DT, false, true, false> : k_resid<DT, false, false, false>),
-                          g_resid, WG, st, a, SVIP_BENCH_K_RESID);
-        };
-        ok = launch(k_verify_stats<DT>, g_stats, WG, st, a, SVIP_BENCH_K_VERIFY_STATS) &&
-             (a.first_half ? finish(std::true_type{}) : finish(std::false_type{}));
+        ok = launch(k_verify_stats<DT>, g_stats, WG, st, a, SVIP_BENCH_K_VERIFY_STATS) && by_parts(parts, [&](auto of) {
+                 constexpr int P = decltype(of)::value;
+                 return (test || launch(k_accept<DT, P>, (unsigned)c.B, 64, st, a, SVIP_BENCH_K_ACCEPT)) &&
+                        launch(a.geo_s.tps <= TILE_MASSES ? (test ? k_resid<DT, true, true, P> : k_resid<DT, true, false, 1>)
+                                                          : (test ? k_resid<DT, false, true, 1> : k_resid<DT, false, false, 1>),
+                               g_resid, WG, st, a, SVIP_BENCH_K_RESID);
+             });
     });
     return ok ? SVIP_OK : SVIP_ERR_HIP;
 }
@@ -923,7 +941,7 @@ svip_status svip_pair_stats(const void *target_logits, const void *draft_logits,
     if (!workspace_ok(workspace, workspace_bytes, need_pair(B, k_max, kd != 0, a.v.geo, a.geo2, nullptr, nullptr)))
         return SVIP_ERR_WORKSPACE;
     const bool fine = room_for_finer(workspace_bytes, B, k_max, V);
-    finer_stats(a.v, stat_rows, vec, g_tune.stats_slices, fine);
+    const int parts = finer_stats(a.v, stat_rows, vec, g_tune.stats_slices, fine);
     a.geo2 = geo_stats(pos, V, vec, g_tune.pair_slices, fine);
     size_t part_bytes, L_bytes;
     need_pair(B, k_max, kd != 0, a.v.geo, a.geo2, &part_bytes, &L_bytes);
@@ -940,6 +958,7 @@ svip_status svip_pair_stats(const void *target_logits, const void *draft_logits,
     a.v.kd = kd;
     a.v.bonus = 0;
     a.v.sc = make_scale(temperature);
+    a.v.m0 = beyond_range(a.v.sc);
     a.v.tokens = nullptr;
     a.v.draft_len = draft_len;
     a.v.draft_lse = draft_lse;
@@ -960,7 +979,7 @@ svip_status svip_pair_stats(const void *target_logits, const void *draft_logits,
                    g_sums = (unsigned)(pos * a.geo2.ns);
     bool ok = false;
     by_dtype(dtype, [&](auto tag) { ok = launch(k_verify_stats<decltype(tag)>, g_stats, WG, st, a.v); });
-    ok = ok && launch(k_pair_L, g_pos, 64, st, a);
+    ok = ok && by_parts(parts, [&](auto of) { return launch(k_pair_L<decltype(of)::value>, g_pos, 64, st, a); });
     if (ok) by_dtype(dtype, [&](auto tag) { ok = launch(k_pair_sums<decltype(tag)>, g_sums, WG, st, a); });
     ok = ok && launch(k_pair_finish, g_pos, 64, st, a);
     return ok ? SVIP_OK : SVIP_ERR_HIP;

@@ -53,7 +53,7 @@ __global__ __launch_bounds__(WG, 8) void k_verify_stats(VerifyArgs a)
         const int te = min(tb + n, a.geo.ntiles);
         // the LDS block can be reused at once: every wave has read the maxima before the second barrier of
         // slice_lse, and thread 0 has read the sums before its wave reaches the next item's first barrier
-        const LsePart p = slice_lse<DT>(row, a.geo.V, tb, te, a.sc, lds);
+        const LsePart p = slice_lse<DT>(row, a.geo.V, tb, te, a.sc, a.m0, lds);
         if (threadIdx.x == 0) static_cast<LsePart *>(a.ws.part)[stat_at(a, b, jj, s)] = p;
     }
 }
@@ -63,9 +63,10 @@ __global__ __launch_bounds__(WG, 8) void k_verify_stats(VerifyArgs a)
 // The logsumexp of statistics row jj of sequence b from its slices: the sums are brought to the largest
 // reference with single-precision exp2 of the (small, exactly formed) reference differences and added in fp64.  CH slices
 // are requested together, the first of them (request) before the caller's other loads are waited for.  A slice with a logit of +inf or
-// NaN has no sum and does not count; HALVES: slices 2 i and 2 i + 1 are halves of one (VerifyArgs::first_half), and such a logit takes the
-// other half with it.  (An instance of its own: the test costs the other calls 0.1 to 0.2 us.)
-template <int CH, bool HALVES>
+// NaN has no sum and does not count.  PARTS: where a row of its length has longer slices (finer_stats in svip_kernels.hip), consecutive
+// slices that such a logit takes with it: 2, or 4 for all of a row of at most four.  (Instances of their own: the tests cost
+// other calls 0.1 to 0.2 us.)
+template <int CH, int PARTS>
 struct RowStats {
     float r = neg_inf();
     double S = 0.0;
@@ -78,10 +79,14 @@ struct RowStats {
     }
     __device__ __forceinline__ void add(int n)
     {
-        if (HALVES) {
+        if (PARTS == 2) {
 #pragma unroll
             for (int u = 0; u + 1 < CH; u += 2)
                 if (!(p[u].S + p[u + 1].S > 0.0)) p[u].S = p[u + 1].S = 0.0;         // (either may be no number)
+        }
+        if constexpr (PARTS == 4) {
+            static_assert(CH == 4, "all of the row");
+            if (!((p[0].S + p[1].S) + (p[2].S + p[3].S) > 0.0)) p[0].S = p[1].S = p[2].S = p[3].S = 0.0;
         }
 #pragma unroll
         for (int u = 0; u < CH; ++u)            // after all of the loads (else each is waited for in turn)
@@ -132,7 +137,7 @@ constexpr int LANE_POSITIONS = 64;
 // statistics of target row j; lanes j < draft_len run the acceptance test; a ballot finds the first rejection.
 // PASSES: drafts of any length; goes on behind the pass of the first rejection only if the accept probabilities are wanted, and
 // writes them.  Otherwise (k <= LANE_POSITIONS) nothing is written.
-template <typename DT, bool PASSES, bool HALVES>
+template <typename DT, bool PASSES, int PARTS>
 __device__ __forceinline__ Accepted accept_sequence(const VerifyArgs &a, int b, int lane)
 {
     // One wave, a chain of trips to memory: the draft length, then tokens / uniforms / logsumexps / slice
@@ -179,7 +184,7 @@ __device__ __forceinline__ Accepted accept_sequence(const VerifyArgs &a, int b, 
                 zp_stored = (tgt + (long long)j * a.row_stride)[x];
                 zq_stored = (drf + (long long)j * a.row_stride)[x];
             }
-            RowStats<ACCEPT_SLICES, HALVES> target, draft;
+            RowStats<ACCEPT_SLICES, PARTS> target, draft;
             target.request(a, b, a.kd + j);
             if (a.kd && j < g) draft.request(a, b, j);
             target.merge(a, b, a.kd + j);
@@ -220,12 +225,12 @@ __device__ __forceinline__ Accepted accept_sequence(const VerifyArgs &a, int b, 
 }
 
 // grid (sequences), one wave: the acceptance test in a launch of its own (see accept_in_resid in svip_kernels.hip).
-template <typename DT, bool HALVES>
+template <typename DT, int PARTS>
 __global__ __launch_bounds__(64) void k_accept(VerifyArgs a)
 {
     const int b = blockIdx.x, lane = threadIdx.x;
     if (a.skip && a.skip[b]) return;
-    const Accepted acc = accept_sequence<DT, true, HALVES>(a, b, lane);
+    const Accepted acc = accept_sequence<DT, true, PARTS>(a, b, lane);
     if (acc.flags) atomicOr(a.ws.flags, acc.flags);
     if (lane == 0) {
         SeqRec rec;
@@ -357,7 +362,7 @@ constexpr int resid_waves(bool tiles, bool test) { return tiles && (test || !std
 // 128256 bf16 logits 61.0 / 58.9 (this kernel alone 13.3 + 4.7 / 14.6), 8 of 64 and 151936 28.7 / 27.3, 32 of 8 and 50257 fp16
 // 26.5 / 24.6.  With every wave testing for itself instead of one for its workgroup: 60.5, 27.3, 25.8 -- the loads of the
 // statistics are many and small.  TILES: slices have at most TILE_MASSES tiles; otherwise the search walks the chosen slice.
-template <typename DT, bool TILES, bool TEST, bool HALVES>
+template <typename DT, bool TILES, bool TEST, int PARTS>
 __global__ __launch_bounds__(WG, resid_waves<DT>(TILES, TEST)) void k_resid(VerifyArgs a)
 {
     constexpr int N = VecOf<DT>::N;
@@ -375,7 +380,7 @@ __global__ __launch_bounds__(WG, resid_waves<DT>(TILES, TEST)) void k_resid(Veri
     if constexpr (TEST) {
         __shared__ Accepted shared_acc;
         if (wave == 0) {
-            acc = accept_sequence<DT, false, HALVES>(a, b, lane);
+            acc = accept_sequence<DT, false, PARTS>(a, b, lane);
             if (lane == 0) shared_acc = acc;
         }
         __syncthreads();
