@@ -364,8 +364,8 @@ __global__ __launch_bounds__(WG, TPS == 1 ? 8 : 6) void k_draft_stats(DraftArgs 
     const int nrec = a.geo.ns;
     // All arguments are requested at once: left to itself the compiler loads those behind the first branch only there,
     // a second trip to the scalar cache before the first load of a logit.
-    asm volatile("" : : "s"(a.logits), "s"(a.row_stride), "s"(a.pos), "s"(a.stop_in), "s"(a.geo.V), "s"(a.part), "s"(a.sc.c_dn),
-                 "s"(a.sc.c_up), "s"(a.sc.c), "s"(a.common_range), "s"(a.step_j));
+    asm volatile("" : : "s"(a.logits), "s"(a.row_stride), "s"(a.pos), "s"(a.cap), "s"(a.stop_in), "s"(a.geo.V), "s"(a.part),
+                 "s"(a.sc.c_dn), "s"(a.sc.c_up), "s"(a.sc.c), "s"(a.common_range), "s"(a.step_j));
     // Which record this wave takes is the same in all its lanes: worked out in scalar registers, with the one
     // division done by a multiplication the host prepared, so that none of it takes vector-ALU slots.  (This and the
     // reading of the tiles are written out here: shared with the loop's kernels as functions they compile to 8 vector
@@ -746,8 +746,8 @@ template <typename DT, RecordKind KIND, int RPL>
 __global__ __launch_bounds__(WG, 4) void k_draft_step(DraftArgs a)
 {
     static_assert(KIND != TOTAL, "records of one tile");
-    asm volatile("" : : "s"(a.logits), "s"(a.row_stride), "s"(a.pos), "s"(a.stop_in), "s"(a.geo.V), "s"(a.part), "s"(a.sc.c_dn),
-                 "s"(a.sc.c_up), "s"(a.sc.c), "s"(a.common_range), "s"(a.step_j));
+    asm volatile("" : : "s"(a.logits), "s"(a.row_stride), "s"(a.pos), "s"(a.cap), "s"(a.stop_in), "s"(a.geo.V), "s"(a.part),
+                 "s"(a.sc.c_dn), "s"(a.sc.c_up), "s"(a.sc.c), "s"(a.common_range), "s"(a.step_j));
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, nrec = a.geo.ns;
     const unsigned xcd = blockIdx.x & 7u, slot = blockIdx.x >> 3;           // div = workgroups per row
     const unsigned q = a.div == 1u ? slot : __umulhi(slot, a.div_magic), s = slot - q * a.div;

@@ -490,7 +490,8 @@ __device__ __forceinline__ unsigned lds_add(unsigned *p, unsigned n)
 // One sweep over the row: the keys of the logits at or above the pivot into L.list (n_list counts them, also those that do
 // not fit), with `FUSED` their indices behind them (`cap` of each) and the output -- the logit itself at and above the pivot,
 // -inf below; and with MASS the total mass of the row (per thread).
-// What bounds it is vector-ALU issue: about 75 cycles per logit of 64 lanes with a mass, on one workgroup 17 of a row's 27 us.  A row's
+// What bounds it is vector-ALU issue: a wave of the nucleus path is active for 103 cycles per logit of its 64 lanes, by counters, in both
+// sweeps and the select together (1088 rows of 128256 bf16 logits); with a mass it is 17 of one row's 27 us.  A row's
 // chunk of 64 vectors holds some candidates more often than not, so what every logit pays for is kept apart from what a candidate
 // does: the comparison works on the stored words, and the lanes that have candidates go through them one at a time.  With a mass, whole
 // vectors go without a check, the comparison goes by the pivot's sign and constants stay in vector registers: top-p 0.9, 1 row
