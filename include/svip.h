@@ -289,11 +289,15 @@ svip_status svip_pair_stats(
  * at absolute position n (independent of the tokens chosen before).  A sequence starts a new round
  * while it has produced fewer than max_new tokens and its trace holds limit + 1 more rows; a round
  * produces the accepted draft tokens followed by the correction or bonus token.  The rows of several
- * draft positions are read at once where one position of the batch would not fill the GPU, so rows
- * behind the position that ends a draft may be read too (never past the sequence's limit).
+ * draft positions are read at once where one position of the batch would not fill the GPU, so rows that no
+ * round uses may be read too: sampling, rows behind the position that ends a draft, never past the sequence's
+ * limit; greedy, rows of rounds to come as well, of draft and target trace, below position
+ * min(L, n0 + max_new + gamma_max) (or the end of the round at hand, where a call asks for fewer tokens than a
+ * sequence has already).
  * Everything per round stays on the device; the host learns one counter per round (and, if
  * check_every > 0, one more about every check_every draft positions, to end the drafting phase early
- * where several launches of it are left).  The counters come as
+ * where several launches of it are left), greedy: one set of counters per pair of launches, which may cover many
+ * rounds.  The counters come as
  * messages the counting kernels store into pinned host memory -- no copy is enqueued and the stream
  * is not synchronised between rounds -- and the host launches one round ahead of the counter it
  * waits for: a round launched after the last sequence finished changes nothing (its sequences are

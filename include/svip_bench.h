@@ -16,11 +16,11 @@ extern "C" {
 
 /* Kernel classes whose launches can carry timing events. */
 enum {
-    SVIP_BENCH_K_DRAFT_STATS = 0,   /* statistics launch of svip_draft_step / svip_draft_step_greedy */
+    SVIP_BENCH_K_DRAFT_STATS = 0,   /* statistics launch of svip_draft_step / svip_draft_step_greedy; the only one of small steps */
     SVIP_BENCH_K_VERIFY_STATS = 1,  /* statistics pass of svip_verify (argmax pass of svip_verify_greedy) */
     SVIP_BENCH_K_RESID = 2,         /* residual / bonus pass of svip_verify, with the acceptance tests of smaller calls */
     SVIP_BENCH_K_ACCEPT = 3,        /* acceptance tests and first-rejection scan in a launch of their own */
-    SVIP_BENCH_K_DRAFT_FINISH = 4,  /* second launch of a draft step: the rows' merge, stop test and token */
+    SVIP_BENCH_K_DRAFT_FINISH = 4,  /* second launch of a draft step that has one: the rows' merge, stop test and token */
     SVIP_BENCH_KERNEL_CLASSES = 5
 };
 
