@@ -141,7 +141,7 @@ static Geo make_geo(int V, int vec, long long rows, bool want_one_batch, int for
         //   2800                                                                             24.9 26.0                         28.0 29.0, 26.7 28.1
         // Four in place of three, 24 to 31 tiles: up to 400 workgroups 0 to 9 % less, at 650 to 720 from 4 % less to 5 % more (30 tiles
         // of bf16, 648: 14.9 15.8, 8.5 8.3, 22.0 23.3), beyond up to 6 % more: not taken.  Errors against 64 bits are smaller with finer
-        // slices (rms of acceptance probabilities 5.5e-8 / 5.1e-8, of divergences 1.8e-7 / 1.7e-7 relative).
+        // slices (rms of acceptance probabilities 5.6e-8 / 5.0e-8, of the four divergences 0.94 to 0.99 times what it is).
         ns = (8192 + rows - 1) / rows;
         long long most = g.ntiles / 8;
         if (fine && g.ntiles < 24) {
